@@ -505,7 +505,7 @@ def measure_mfma_ceiling(dev, real_codes):
         ms = time_launches(run, 4, warm=2)
         out[name] = ops[0] / (ms * 1e-3) / 1e12
     out["unit"] = "TOP/s"
-    out["what"] = "256 workgroups x 8 wavefronts x %d x 16 v_mfma_i32_32x32x32_i8 on 4 KB of operand bytes, no memory traffic" % iters
+    out["what"] = "256 workgroups x 8 wavefronts x %d x 32 v_mfma_i32_16x16x64_i8 on 4 KB of operand bytes, no memory traffic" % iters
     return out
 
 

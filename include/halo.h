@@ -172,16 +172,16 @@ halo_status halo_gemm_i8(const int8_t* A, int64_t lda, const int8_t* B, int64_t 
                          const float* col_scale, void* C, halo_dtype c_dt, int64_t ldc,
                          int32_t* acc_out, int64_t ld_acc, void* stream);
 
-/* Tile configurations of the INT8 GEMM: macro tile M x N x K-step (bytes), wavefronts per workgroup.  They differ in
- * speed only, the results are identical.  HALO_GEMM_AUTO lets the library choose by shape.  A configuration whose
- * K step does not divide K is refused with HALO_ESHAPE (the staged one takes any K that is a multiple of 16). */
+/* Tile configurations of the INT8 GEMM: macro tile M x N x K granularity (bytes).  They differ in speed only, the results
+ * are identical.  HALO_GEMM_AUTO lets the library choose by shape and takes any K that is a multiple of 16.  A named
+ * configuration whose K granularity does not divide K is refused with HALO_ESHAPE (the last one takes any such K). */
 typedef enum {
     HALO_GEMM_AUTO = -1,
-    HALO_GEMM_256x256x64 = 0,        /* 8 wavefronts, four-stage global->LDS ring                  */
-    HALO_GEMM_256x256x128 = 1,       /* 8 wavefronts, two-stage ring                               */
-    HALO_GEMM_256x128x128 = 2,       /* 8 wavefronts, three-stage ring                             */
-    HALO_GEMM_128x128x64 = 3,        /* 4 wavefronts, four-stage ring                              */
-    HALO_GEMM_STAGED_128x128x64 = 4  /* 4 wavefronts, register-staged, zero-fills a ragged K       */
+    HALO_GEMM_256x256x64 = 0,        /* 256 x 256 tiles                                            */
+    HALO_GEMM_256x256x128 = 1,       /* the same; K a multiple of 128                              */
+    HALO_GEMM_256x128x128 = 2,       /* 256 x 128 tiles                                            */
+    HALO_GEMM_128x128x64 = 3,        /* 128 x 128 tiles                                            */
+    HALO_GEMM_STAGED_128x128x64 = 4  /* 128 x 128 tiles, any K                                     */
 } halo_gemm_config;
 
 /* One product described by a struct: every field means what the argument of the same name means in halo_gemm_i8;
@@ -203,13 +203,13 @@ halo_status halo_gemm_i8_desc(const halo_gemm_desc* g, void* stream);
 /* Two independent products in one launch: same semantics and bit-identical results as two halo_gemm_i8_desc calls (in
  * either order).  halo_linear_bwd uses it for E_X = E W and G = E^T X, where the tail and the epilogue of one product
  * overlap the main loop of the other and the smaller one cannot leave compute units idle.  Products with a
- * K-contiguous B, a K that is not a multiple of 64, different configurations, a configuration other than AUTO,
+ * K-contiguous B, different configurations, a configuration other than AUTO,
  * 256x256x64 or 128x128x64, or an empty shape are simply run one after the other. */
 halo_status halo_gemm_i8_pair(const halo_gemm_desc* g1, const halo_gemm_desc* g2, void* stream);
 
 /* Measurement aid: the INT8 MFMA rate this machine sustains on given operand bytes.  256 workgroups of 8 wavefronts
- * each issue iters x 16 v_mfma_i32_32x32x32_i8 on the 4096 operand bytes at `operands` (device, 16-byte aligned) with
- * nothing else in the loop: 256 * 8 * iters * 16 * 65536 integer operations.  The rate depends on the operand data
+ * each issue iters x 32 v_mfma_i32_16x16x64_i8 on the 4096 operand bytes at `operands` (device, 16-byte aligned) with
+ * nothing else in the loop: 256 * 8 * iters * 32 * 32768 integer operations.  The rate depends on the operand data
  * (the clock drops as more multiplier bits toggle), which is why the throughput of halo_gemm_i8 is reported against
  * this figure next to the published peak (Section 4, "Speedup Analysis", measures against an ideal layer likewise).
  * `sink` is an optional int32 the kernel may write (it keeps the loop from being optimised away). */

@@ -24,6 +24,25 @@ SHAPES = [
 ]
 
 
+# K around the 128-byte units of the main loop (a partial one, one, one and a bit, odd and even counts), M and N around the
+# tile edges, every tile size: what lies beyond the matrix must enter as zeros and must not be stored.
+@pytest.mark.parametrize("K", [16, 112, 128, 144, 384, 656])
+@pytest.mark.parametrize("M,N,config", [(127, 112, 4), (129, 144, 4), (255, 128, 2), (272, 96, 2), (257, 272, 0), (240, 250, 0)])
+@pytest.mark.parametrize("trans_b", [True, False])
+def test_units_and_tile_edges(M, N, K, config, trans_b):
+    step = {0: 64, 2: 128, 4: 16}[config]
+    K = (K + step - 1) // step * step
+    rng = np.random.default_rng(M + N + K)
+    a = rand_codes(rng, (M, K)); b = rand_codes(rng, (N, K) if trans_b else (K, N))
+    bd = torch.zeros((b.shape[0], (b.shape[1] + 15) // 16 * 16), dtype=torch.int8, device=gu.DEV)
+    bd[:, :b.shape[1]] = gu.to_dev(b)
+    acc = torch.full((M + 1, (N + 3) // 4 * 4 + 16), -7, dtype=torch.int32, device=gu.DEV)
+    binding.halo_gemm_i8_desc(binding.gemm_desc(gu.to_dev(a), bd[:, :b.shape[1]], trans_b=trans_b, acc_out=acc[:M, :N],
+                                                config=config))
+    gu.assert_codes_equal(acc[:M, :N], orc.gemm_codes(a, b.T if trans_b else b), "accumulators")
+    assert bool((acc[M:] == -7).all()) and bool((acc[:, N:] == -7).all())
+
+
 # Every tile configuration on shapes its K step divides (ragged M and N, several trips through the ring), through
 # halo_gemm_i8_desc: the configurations differ in speed only.
 @pytest.mark.parametrize("name", sorted(binding.HALO_GEMM_CONFIGS))
