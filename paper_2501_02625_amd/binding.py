@@ -1,12 +1,14 @@
-"""Thin ctypes binding of libhalo's C ABI (include/halo.h).
+"""Thin binding of libhalo's C ABI (include/halo.h).
 
 Argument marshalling only: every step of the HALO linear layer runs in the HIP kernels of libhalo.so.
-torch is used for device memory and the current stream, nothing else.  There is no CPU fallback: if the
-shared library is missing, importing a function from here raises.
+torch is used for device memory and the current stream, nothing else.  The entry points of a layer's step go through
+_halo_native.so (csrc/native_binding.cpp), the others through ctypes.  There is no CPU fallback: if a shared library is
+missing, calling a function from here raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional, Tuple
@@ -126,6 +128,24 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     return lib
 
 
+_native_module = None
+
+
+def _native():
+    """_halo_native.so (built in-tree by _build.build(), linked to libhalo.so).  Raises if it is not there."""
+    global _native_module
+    if _native_module is None:
+        load_library()
+        if not os.path.exists(_build.NATIVE_PATH):
+            raise RuntimeError("_halo_native.so is not built (%s). Run `python -c 'import __graft_entry__ as g; g.build()'`; "
+                               "there is no fallback path." % _build.NATIVE_PATH)
+        spec = importlib.util.spec_from_file_location("_halo_native", _build.NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _native_module = module
+    return _native_module
+
+
 def status_string(status: int) -> str:
     return load_library().halo_status_string(int(status)).decode()
 
@@ -144,6 +164,10 @@ def _dt(dtype: torch.dtype) -> int:
     if dtype == torch.float32:
         return HALO_F32
     raise TypeError("HALO tensors are bf16 or fp32, got %s" % dtype)
+
+
+def _failed(status: int, where: str):
+    raise HaloError(status, where)
 
 
 def _check(status: int, where: str):
@@ -170,27 +194,8 @@ def halo_hadamard_quant(x: torch.Tensor, *, axis: int = HALO_QUANT_ROWS, had_blo
                         out_q: Optional[torch.Tensor] = None, out_scale: Optional[torch.Tensor] = None,
                         workspace: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor]:
     """rotate -> fold -> absmax -> INT8.  Returns (codes int8, scales fp32)."""
-    lib = load_library()
-    _need_cuda(x, fold, out_q, out_scale, workspace)
-    assert x.dim() == 2 and x.stride(1) == 1
-    rows, cols = x.shape
-    if axis == HALO_QUANT_ROWS:
-        qshape, nscale = (rows, cols), rows
-    else:
-        qshape, nscale = (cols, rows), cols
-    if out_q is None:
-        out_q = _empty_padded(qshape[0], qshape[1], torch.int8, x.device)
-    if out_scale is None:
-        out_scale = torch.empty((nscale,), dtype=torch.float32, device=x.device)
-    need = lib.halo_hadamard_quant_workspace_bytes(rows, cols, axis, had_block_left)
-    if workspace is None and need:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=x.device)
-    st = lib.halo_hadamard_quant(_ptr(x), _dt(x.dtype), rows, cols, x.stride(0) if rows else cols, axis,
-                                 had_block, had_block_left, _ptr(fold), _ptr(out_q),
-                                 out_q.stride(0) if out_q.numel() else qshape[1], _ptr(out_scale), _ptr(workspace),
-                                 workspace.numel() if workspace is not None else 0, _stream())
-    _check(st, "halo_hadamard_quant")
-    return out_q, out_scale
+    r = _native().hadamard_quant(x, axis, had_block, had_block_left, fold, out_q, out_scale, workspace)
+    return r if type(r) is tuple else _failed(r, "halo_hadamard_quant")
 
 
 def halo_hadamard_quant_tensor(x: torch.Tensor, *, axis: int = HALO_QUANT_ROWS, had_block: int = 0,
@@ -264,23 +269,9 @@ def halo_gemm_i8(a: torch.Tensor, b: torch.Tensor, *, trans_b: bool, row_scale: 
                  want_acc: bool = False, out: Optional[torch.Tensor] = None,
                  acc_out: Optional[torch.Tensor] = None):
     """C = diag(row_scale) (A op(B)) diag(col_scale); returns (C or None, acc or None)."""
-    lib = load_library()
-    _need_cuda(a, b, row_scale, col_scale, out, acc_out)
-    assert a.dtype == torch.int8 and b.dtype == torch.int8 and a.dim() == 2 and b.dim() == 2
-    M, K = a.shape
-    N = b.shape[0] if trans_b else b.shape[1]
-    assert (b.shape[1] if trans_b else b.shape[0]) == K
-    if out is None and out_dtype is not None:
-        out = _empty_padded(M, N, out_dtype, a.device)
-    if acc_out is None and want_acc:
-        acc_out = _empty_padded(M, N, torch.int32, a.device)
-    st = lib.halo_gemm_i8(_ptr(a), a.stride(0) if M else K, _ptr(b), b.stride(0) if b.shape[0] else b.shape[1],
-                          1 if trans_b else 0, M, N, K, _ptr(row_scale), _ptr(col_scale), _ptr(out),
-                          _dt(out.dtype) if out is not None else HALO_F32,
-                          (out.stride(0) if M else N) if out is not None else 0, _ptr(acc_out),
-                          (acc_out.stride(0) if M else N) if acc_out is not None else 0, _stream())
-    _check(st, "halo_gemm_i8")
-    return out, acc_out
+    r = _native().gemm_i8(a, b, trans_b, row_scale, col_scale, -1 if out_dtype is None else _dt(out_dtype), want_acc, out,
+                          acc_out)
+    return r if type(r) is tuple else _failed(r, "halo_gemm_i8")
 
 
 def gemm_desc(a: torch.Tensor, b: torch.Tensor, *, trans_b: bool, row_scale: Optional[torch.Tensor] = None,
@@ -321,33 +312,15 @@ def halo_mx6_quant(x: torch.Tensor, *, had_block: int = 0, out_codes: Optional[t
                    out_scales: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor]:
     """rotate -> E8M0 scale per 32 elements -> packed FP6 E3M2.  Returns (codes uint8 [rows, cols/32*24],
     scales uint8 [rows, cols/32])."""
-    _need_cuda(x, out_codes, out_scales)
-    assert x.dim() == 2 and x.stride(1) == 1 and x.dtype == torch.bfloat16
-    rows, cols = x.shape
-    if out_codes is None:
-        out_codes = torch.empty((rows, cols // 32 * 24), dtype=torch.uint8, device=x.device)
-    if out_scales is None:
-        out_scales = torch.empty((rows, cols // 32), dtype=torch.uint8, device=x.device)
-    st = load_library().halo_mx6_quant(_ptr(x), rows, cols, x.stride(0) if rows else cols, had_block, _ptr(out_codes),
-                                       out_codes.stride(0) if rows else 24, _ptr(out_scales),
-                                       out_scales.stride(0) if rows else 1, _stream())
-    _check(st, "halo_mx6_quant")
-    return out_codes, out_scales
+    r = _native().mx6_quant(x, had_block, out_codes, out_scales)
+    return r if type(r) is tuple else _failed(r, "halo_mx6_quant")
 
 
 def halo_gemm_mx6(a: torch.Tensor, sa: torch.Tensor, b: torch.Tensor, sb: torch.Tensor, *,
                   out_dtype: torch.dtype = torch.float32, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """C = A B^T on packed MXFP6 operands (codes [rows, K/32*24] uint8, scales [rows, K/32] uint8)."""
-    _need_cuda(a, sa, b, sb, out)
-    M, N, K = a.shape[0], b.shape[0], sa.shape[1] * 32
-    assert a.shape[1] == K // 32 * 24 and b.shape[1] == K // 32 * 24 and sb.shape[1] * 32 == K
-    if out is None:
-        out = _empty_padded(M, N, out_dtype, a.device)
-    st = load_library().halo_gemm_mx6(_ptr(a), a.stride(0) if M else 24, _ptr(sa), sa.stride(0) if M else 4, _ptr(b),
-                                      b.stride(0) if N else 24, _ptr(sb), sb.stride(0) if N else 4, M, N, K, _ptr(out),
-                                      _dt(out.dtype), out.stride(0) if M else N, _stream())
-    _check(st, "halo_gemm_mx6")
-    return out
+    r = _native().gemm_mx6(a, sa, b, sb, _dt(out_dtype), out)
+    return r if type(r) is not int else _failed(r, "halo_gemm_mx6")
 
 
 def halo_dequant_unrotate(acc: torch.Tensor, row_scale: Optional[torch.Tensor], *, had_block: int = 0,
@@ -393,48 +366,23 @@ def halo_linear_fwd(desc: LinearDesc, X: Optional[torch.Tensor], W: Optional[tor
                     workspace: Optional[torch.Tensor] = None):
     """Forward product; returns (Y, LinearState).  Pass X=None / W=None with a `state` that already holds
     the corresponding codes to reuse them."""
-    lib = load_library()
-    dev = (X if X is not None else state.Xq).device
-    odt = torch.bfloat16 if desc.out_dt == HALO_BF16 else torch.float32
     if state is None:
-        state = LinearState(torch.empty((desc.b, desc.m), dtype=torch.int8, device=dev),
-                            torch.empty((desc.b,), dtype=torch.float32, device=dev),
-                            torch.empty((desc.n, desc.m), dtype=torch.int8, device=dev),
-                            torch.empty((desc.n,), dtype=torch.float32, device=dev))
-    if Y is None:
-        Y = torch.empty((desc.b, desc.n), dtype=odt, device=dev)
-    _need_cuda(X, W, Y, state.Xq, state.Wq)
-    for t in (X, W):
-        assert t is None or (t.dtype == torch.bfloat16 and t.is_contiguous())
-    if workspace is None and desc.scale_mode == HALO_SCALE_PER_TENSOR:
-        workspace = torch.empty((max(halo_linear_workspace_bytes(desc), 16),), dtype=torch.uint8, device=dev)
-    st = lib.halo_linear_fwd(ctypes.byref(desc), _ptr(X), _ptr(W), _ptr(Y), _ptr(state.Xq), _ptr(state.s_x),
-                             _ptr(state.Wq), _ptr(state.s_w), _ptr(workspace),
-                             workspace.numel() if workspace is not None else 0, _stream())
-    _check(st, "halo_linear_fwd")
-    return Y, state
+        r = _native().linear_fwd(desc, X, W, None, None, None, None, Y, workspace)
+        if type(r) is tuple:
+            return r[0], LinearState(r[1], r[2], r[3], r[4])
+    else:
+        r = _native().linear_fwd(desc, X, W, state.Xq, state.s_x, state.Wq, state.s_w, Y, workspace)
+        if type(r) is tuple:
+            return r[0], state
+    return _failed(r, "halo_linear_fwd")
 
 
 def halo_linear_bwd(desc: LinearDesc, E: torch.Tensor, state: LinearState, *, want_ex: bool = True,
                     want_g: bool = True, workspace: Optional[torch.Tensor] = None,
                     EX: Optional[torch.Tensor] = None, G: Optional[torch.Tensor] = None):
     """Both backward products; returns (E_X or None, G or None)."""
-    lib = load_library()
-    _need_cuda(E, workspace, EX, G)
-    assert E.dtype == torch.bfloat16 and E.is_contiguous()
-    odt = torch.bfloat16 if desc.out_dt == HALO_BF16 else torch.float32
-    if want_ex and EX is None:
-        EX = torch.empty((desc.b, desc.m), dtype=odt, device=E.device)
-    if want_g and G is None:
-        G = torch.empty((desc.n, desc.m), dtype=odt, device=E.device)
-    need = halo_linear_workspace_bytes(desc)
-    if workspace is None:
-        workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=E.device)
-    st = lib.halo_linear_bwd(ctypes.byref(desc), _ptr(E), _ptr(state.Xq), _ptr(state.s_x), _ptr(state.Wq),
-                             _ptr(state.s_w), _ptr(EX) if want_ex else None, _ptr(G) if want_g else None,
-                             _ptr(workspace), workspace.numel(), _stream())
-    _check(st, "halo_linear_bwd")
-    return (EX if want_ex else None), (G if want_g else None)
+    r = _native().linear_bwd(desc, E, state.Xq, state.s_x, state.Wq, state.s_w, bool(want_ex), bool(want_g), workspace, EX, G)
+    return r if type(r) is tuple else _failed(r, "halo_linear_bwd")
 
 
 def halo_peft_workspace_bytes(desc: LinearDesc, rank: int) -> int:
@@ -445,23 +393,8 @@ def halo_peft_fwd(desc: LinearDesc, X: torch.Tensor, Wq: torch.Tensor, s_w: torc
                   V: torch.Tensor, *, workspace: Optional[torch.Tensor] = None, Y: Optional[torch.Tensor] = None,
                   T: Optional[torch.Tensor] = None):
     """Forward pass of the LoRA-style module on a frozen quantised weight; returns (Y, T = X U^T in fp32)."""
-    lib = load_library()
-    _need_cuda(X, Wq, s_w, U, V, workspace, Y, T)
-    rank = U.shape[0]
-    assert X.dtype == torch.bfloat16 and U.dtype == torch.bfloat16 and V.dtype == torch.bfloat16
-    assert X.is_contiguous() and U.is_contiguous() and V.is_contiguous() and Wq.is_contiguous()
-    assert tuple(V.shape) == (desc.n, rank) and tuple(U.shape) == (rank, desc.m)
-    odt = torch.bfloat16 if desc.out_dt == HALO_BF16 else torch.float32
-    if Y is None:
-        Y = torch.empty((desc.b, desc.n), dtype=odt, device=X.device)
-    if T is None:
-        T = torch.empty((desc.b, rank), dtype=torch.float32, device=X.device)
-    if workspace is None:
-        workspace = torch.empty((max(halo_peft_workspace_bytes(desc, rank), 1),), dtype=torch.uint8, device=X.device)
-    st = lib.halo_peft_fwd(ctypes.byref(desc), rank, _ptr(X), _ptr(Wq), _ptr(s_w), _ptr(U), _ptr(V), _ptr(Y), _ptr(T),
-                           _ptr(workspace), workspace.numel(), _stream())
-    _check(st, "halo_peft_fwd")
-    return Y, T
+    r = _native().peft_fwd(desc, X, Wq, s_w, U, V, workspace, Y, T)
+    return r if type(r) is tuple else _failed(r, "halo_peft_fwd")
 
 
 def halo_peft_bwd(desc: LinearDesc, E: torch.Tensor, X: torch.Tensor, T: torch.Tensor, Wq: torch.Tensor,
@@ -469,21 +402,5 @@ def halo_peft_bwd(desc: LinearDesc, E: torch.Tensor, X: torch.Tensor, T: torch.T
                   want_gv: bool = True, workspace: Optional[torch.Tensor] = None, EX: Optional[torch.Tensor] = None,
                   GU: Optional[torch.Tensor] = None, GV: Optional[torch.Tensor] = None):
     """Backward pass of the module; returns (E_X, G_U [rank x m] fp32, G_V [n x rank] fp32), None where not wanted."""
-    lib = load_library()
-    _need_cuda(E, X, T, Wq, s_w, U, V, workspace, EX, GU, GV)
-    rank = U.shape[0]
-    assert E.dtype == torch.bfloat16 and E.is_contiguous()
-    odt = torch.bfloat16 if desc.out_dt == HALO_BF16 else torch.float32
-    if want_ex and EX is None:
-        EX = torch.empty((desc.b, desc.m), dtype=odt, device=E.device)
-    if want_gu and GU is None:
-        GU = torch.empty((rank, desc.m), dtype=torch.float32, device=E.device)
-    if want_gv and GV is None:
-        GV = torch.empty((desc.n, rank), dtype=torch.float32, device=E.device)
-    if workspace is None:
-        workspace = torch.empty((max(halo_peft_workspace_bytes(desc, rank), 1),), dtype=torch.uint8, device=E.device)
-    st = lib.halo_peft_bwd(ctypes.byref(desc), rank, _ptr(E), _ptr(X), _ptr(T), _ptr(Wq), _ptr(s_w), _ptr(U), _ptr(V),
-                           _ptr(EX) if want_ex else None, _ptr(GU) if want_gu else None, _ptr(GV) if want_gv else None,
-                           _ptr(workspace), workspace.numel(), _stream())
-    _check(st, "halo_peft_bwd")
-    return (EX if want_ex else None), (GU if want_gu else None), (GV if want_gv else None)
+    r = _native().peft_bwd(desc, E, X, T, Wq, s_w, U, V, bool(want_ex), bool(want_gu), bool(want_gv), workspace, EX, GU, GV)
+    return r if type(r) is tuple else _failed(r, "halo_peft_bwd")
