@@ -39,6 +39,7 @@
 // it lies in memory (K-major rows of BN bytes) and transposed by the LDS read itself, ds_read_b64_tr_b8: a group of 16 lanes
 // reads an 8(k) x 16(n) byte block, lane i supplying the address of row i/2, half i%2, and receiving column i; the two
 // groups of a half-wavefront read rows 0-7 and 16-23, which the swizzle (kmajor_swizzle) spreads over all banks.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -830,6 +831,220 @@ gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, 
     epilogue<Cfg, LR, RAGGED>(a, at, lane);
 }
 
+// ------------------------------------------------------------------------------------------------ small products
+// Products with too few 128 x 128 tiles to fill the chip: what bounds them is latency (of the first loads, of every unit of
+// K, of the launch), not the matrix pipes.  A workgroup computes a 16 TM x 64 tile and its four wavefronts SPLIT K: wavefront
+// w takes the units w, w + 4, ...  Each has an LDS ring of its own (three stages of A and B, filled and laid out as in the
+// main kernel), so there is no barrier in the loop and three units are in flight per wavefront from the start.  The four
+// partial sums meet in LDS at the end, where every thread also picks up consecutive columns for the store.
+// TM = 1 is for at most 16 rows (decode).  choose_config has the figures.
+template <int TM, bool TRANSB>
+struct SmallCfg {
+    static constexpr int BM = 16 * TM, BN = 64, TN = 4, BK = 128, NS = TM == 4 ? 2 : 3, SPLIT = 4;
+    static constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = A_BYTES + B_BYTES;
+    static constexpr int LA = A_BYTES / 1024, LB = B_BYTES / 1024, L = LA + LB;  // DMA instructions per stage
+    static constexpr int PITCH = BN + 4;                         // dwords per row of a partial sum
+    static constexpr int RING_BYTES = SPLIT * NS * STAGE, SUM_BYTES = SPLIT * BM * PITCH * 4;
+    static constexpr int LDS_BYTES = RING_BYTES > SUM_BYTES ? RING_BYTES : SUM_BYTES;
+};
+// Chunk swizzle of a K-major row of 64 bytes (see kmajor_swizzle).
+__device__ __forceinline__ int kmajor_swizzle64(int row) { return ((row >> 2) & 1) | (((row >> 4) & 1) << 1); }
+
+template <int TM, bool TRANSB>
+__global__ void __launch_bounds__(256)
+gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigned blocks1) {
+    using Cfg = SmallCfg<TM, TRANSB>;
+    constexpr int TN = Cfg::TN, BK = Cfg::BK, LA = Cfg::LA, LB = Cfg::LB, NS = Cfg::NS;
+    unsigned bid = blockIdx.x;
+    if (bid >= blocks1) {                  // the second product of a paired launch
+        bid -= blocks1;
+        a = a2;
+        tiles_n = tiles_n2;
+    }
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, g4 = lane >> 4;
+    const int64_t m0 = (int64_t)(bid / tiles_n) * Cfg::BM, n0 = (int64_t)(bid % tiles_n) * Cfg::BN;
+    const uint32_t ring = (uint32_t)(uintptr_t)HALO_LDS_PTR(smem) + wave * NS * Cfg::STAGE;
+
+    // ---- source offsets, as in main_loop, but every wavefront fetches the whole tile at its own K
+    const int64_t rows_a = a.M - m0, rows_b = a.N - n0, pitch_b = a.ldb - n0;
+    const int r8 = lane >> 3, k0 = 16 * ((lane & 7) ^ (r8 >> 1));
+    const int kc[2] = {k0, k0 ^ 64};
+    const int krow = lane >> 2;                                  // K-strided B: 16 rows of 64 bytes per request
+    uint32_t avo[LA], bvo[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i)
+        avo[i] = r8 + 8 * i < rows_a ? (uint32_t)(r8 + 8 * i) * (uint32_t)a.lda + kc[i & 1] : kOutside;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        if constexpr (TRANSB) {
+            bvo[i] = r8 + 8 * i < rows_b ? (uint32_t)(r8 + 8 * i) * (uint32_t)a.ldb + kc[i & 1] : kOutside;
+        } else {
+            const int c = 16 * ((lane & 3) ^ kmajor_swizzle64(krow) ^ kmajor_swizzle64(16 * i));
+            bvo[i] = c < pitch_b ? (uint32_t)(krow + 16 * i) * (uint32_t)a.ldb + c : kOutside;
+        }
+    }
+    const int64_t b_unit = TRANSB ? (int64_t)BK : (int64_t)BK * a.ldb;
+    v4u abuf = make_buffer(a.A + m0 * a.lda + wave * BK);
+    v4u bbuf = make_buffer((TRANSB ? a.B + n0 * a.ldb : a.B + n0) + wave * b_unit);
+    int64_t left = a.K - wave * BK;
+    auto trim = [&]() {
+        if (left >= BK) return;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) avo[i] = kc[i & 1] < left ? avo[i] : kOutside;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) bvo[i] = (TRANSB ? kc[i & 1] : krow + 16 * i) < left ? bvo[i] : kOutside;
+    };
+    auto request = [&](int slot) {
+        trim();
+        const uint32_t base = ring + slot * Cfg::STAGE;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) dma16(bvo[i], bbuf, base + Cfg::A_BYTES + i * 1024);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) dma16(avo[i], abuf, base + i * 1024);
+        advance(abuf, Cfg::SPLIT * BK);
+        advance(bbuf, Cfg::SPLIT * b_unit);
+        left -= Cfg::SPLIT * BK;
+    };
+    const int units = (int)((a.K + Cfg::SPLIT * BK - 1) / (Cfg::SPLIT * BK));
+#pragma unroll
+    for (int i = 0; i + 1 < NS; ++i) request(i);
+
+    v4i acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = (v4i){0, 0, 0, 0};
+    uint32_t a_addr[2], b_addr[TRANSB ? 2 : TN];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) a_addr[k] = ring + l16 * BK + 16 * ((4 * k + g4) ^ (l16 >> 1));
+    if constexpr (TRANSB) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) b_addr[k] = a_addr[k] + Cfg::A_BYTES;
+    } else {
+        const int row = 16 * g4 + (l16 >> 1);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            b_addr[j] = ring + Cfg::A_BYTES + row * Cfg::BN + 16 * (j ^ kmajor_swizzle64(row)) + 8 * (l16 & 1);
+    }
+    int slot = 0;
+    for (int u = 0; u < units; ++u) {
+        const int ahead = slot == 0 ? NS - 1 : slot - 1;         // (slot + NS - 1) % NS: read in the previous round
+        request(ahead);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * Cfg::L) : "memory");
+        const uint32_t st = slot * Cfg::STAGE;
+        v4i fa[2][TM], fb[2][TN];
+        v2i ft[2][TN][2];
+        StaticFor<0, 2>::run([&](auto kk) {
+            constexpr int k = decltype(kk)::value;
+            auto& ra = fa;
+            auto& rb = fb;
+            auto& rt = ft;
+            StaticFor<0, TM>::run([&](auto ii) {
+                constexpr int i = decltype(ii)::value;
+                lds_read16<i * 16 * BK>(ra[k][i], a_addr[k] + st);
+            });
+            StaticFor<0, TN>::run([&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                if constexpr (TRANSB) {
+                    lds_read16<j * 16 * BK>(rb[k][j], b_addr[k] + st);
+                } else {
+                    lds_read8_tr<k * 64 * Cfg::BN>(rt[k][j][0], b_addr[j] + st);
+                    lds_read8_tr<k * 64 * Cfg::BN + 8 * Cfg::BN>(rt[k][j][1], b_addr[j] + st);
+                }
+            });
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(fa[k][i]));
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (TRANSB) {
+                    asm volatile("" : "+v"(fb[k][j]));
+                } else {
+                    asm volatile("" : "+v"(ft[k][j][0]), "+v"(ft[k][j][1]));
+                    fb[k][j] = (v4i){ft[k][j][0][0], ft[k][j][0][1], ft[k][j][1][0], ft[k][j][1][1]};
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[k][j], fa[k][i], acc[i][j], 0, 0, 0);
+        slot = slot == NS - 1 ? 0 : slot + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the requests past the end have landed
+    __syncthreads();
+    int32_t* sums = reinterpret_cast<int32_t*>(smem);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            *reinterpret_cast<v4i*>(sums + (wave * Cfg::BM + 16 * i + l16) * Cfg::PITCH + 16 * j + 4 * g4) = acc[i][j];
+    __syncthreads();
+    // ---- every thread: EPT consecutive columns of one row
+    constexpr int EPT = 4 * TM, TPR = Cfg::BN / EPT;
+    const int row_l = threadIdx.x / TPR, col_l = threadIdx.x % TPR * EPT;
+    v4i v[TM];
+#pragma unroll
+    for (int q = 0; q < TM; ++q) {
+        v[q] = (v4i){0, 0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < Cfg::SPLIT; ++w)
+            v[q] += *reinterpret_cast<const v4i*>(sums + (w * Cfg::BM + row_l) * Cfg::PITCH + col_l + 4 * q);
+    }
+    const int64_t row = m0 + row_l, col = n0 + col_l;
+    if (row >= a.M || col >= a.N) return;
+    const bool whole = col + EPT <= a.N;
+    auto store = [&](int32_t* dst, const v4i(&x)[TM]) {
+#pragma unroll
+        for (int q = 0; q < TM; ++q) {
+            if (whole) {
+                *reinterpret_cast<v4i*>(dst + 4 * q) = x[q];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + 4 * q + e < a.N) dst[4 * q + e] = x[q][e];
+            }
+        }
+    };
+    if (a.acc_out) store(a.acc_out + row * a.ld_acc + col, v);
+    if (!a.C) return;
+    const float rs = a.row_scale ? a.row_scale[row] : 1.0f;
+    v4i f[TM];
+#pragma unroll
+    for (int q = 0; q < TM; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t c = col + 4 * q + e;
+            const float cs = a.col_scale ? a.col_scale[c < a.N ? c : a.N - 1] : 1.0f;
+            f[q][e] = __float_as_int(((float)v[q][e] * rs) * cs);
+        }
+    if (a.c_is_f32) {
+        store(reinterpret_cast<int32_t*>(a.C) + row * a.ldc + col, f);
+        return;
+    }
+    uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + row * a.ldc + col;
+#pragma unroll
+    for (int q = 0; q < TM; ++q) {
+        const v2u w = {pack_bf16x2(__int_as_float(f[q][0]), __int_as_float(f[q][1])),
+                       pack_bf16x2(__int_as_float(f[q][2]), __int_as_float(f[q][3]))};
+        if (whole) {
+            *reinterpret_cast<v2u*>(dst + 4 * q) = w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + 4 * q + e < a.N) dst[4 * q + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        }
+    }
+}
+
 // One thread per output, for what the tiles do not take: K = 0 (zeros), and row pitches so large that the rows of a tile do
 // not fit one buffer's 4 GiB.
 __global__ void __launch_bounds__(256) gemm_i8_plain_kernel(GemmArgs a) {
@@ -933,6 +1148,24 @@ hipError_t launch_tiles(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = n
     return hipGetLastError();
 }
 
+template <int TM, bool TRANSB>
+hipError_t launch_small(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = nullptr) {
+    using Cfg = SmallCfg<TM, TRANSB>;
+    if (a.left_stages != 0 || a.lr_rank != 0 || (a2 && (a2->left_stages != 0 || a2->lr_rank != 0))) return hipErrorInvalidValue;
+    static std::once_flag once;
+    static hipError_t attr_result = hipSuccess;
+    auto kern = gemm_i8_small_kernel<TM, TRANSB>;
+    hipError_t e = raise_lds_limit(kern, Cfg::LDS_BYTES, &once, &attr_result);
+    if (e != hipSuccess) return e;
+    auto tiles = [](int64_t n, int t) { return (n + t - 1) / t; };
+    const int64_t b1 = tiles(a.M, Cfg::BM) * tiles(a.N, Cfg::BN);
+    const int64_t b2 = a2 ? tiles(a2->M, Cfg::BM) * tiles(a2->N, Cfg::BN) : 0;
+    if (b1 + b2 > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(b1 + b2)), dim3(256), Cfg::LDS_BYTES, s, a, (int)tiles(a.N, Cfg::BN), a2 ? *a2 : a,
+                       (int)(a2 ? tiles(a2->N, Cfg::BN) : 1), (unsigned)b1);
+    return hipGetLastError();
+}
+
 inline bool tiles_can_run(const GemmArgs& a) {
     const int64_t most = ((int64_t(1) << 32) - 1024) / 256;       // 256 rows of a tile within one buffer
     return a.K > 0 && a.lda <= most && a.ldb <= most;
@@ -949,22 +1182,79 @@ hipError_t launch_plain(const GemmArgs& a, hipStream_t s) {
 // K granularity of the tile configurations 0..3 that the ABI promises to refuse a K for (halo_gemm_config in halo.h).
 constexpr int kStepOfConfig[4] = {64, 128, 128, 64};
 
-// Tile configurations (halo_gemm_config in halo.h): 0, 1: 256 x 256; 2: 256 x 128; 3, 4: 128 x 128.
+// Tile configurations (halo_gemm_config in halo.h): 0, 1: 256 x 256; 2: 256 x 128; 3, 4: 128 x 128.  Two more are chosen by
+// shape only: 64 x 64 and 32 x 64 (16 x 64) tiles with K split over the wavefronts (gemm_i8_small_kernel).
+enum { kTiles256 = 0, kTiles256x128 = 2, kTiles128 = 3, kSmall64 = 5, kSmall32 = 6 };
+
+inline int64_t tiles_of(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
+inline double units_of(const GemmArgs& a) { return (double)((a.K + 127) / 128); }
+
+// Estimated microseconds of the tile configurations, fitted to measurements on products from 1024 x 1024 x 1024 to
+// 8192 x 4096 x 4096 (within 15 %): so much per tile for the launch of its workgroup, the first loads and the store, so
+// much per unit of K.  256 compute units; two 128 x 128 workgroups share one, which smooths its last round.
+// 256 x 256: 2048 x 4096 x 4096 45 us, 4096 x 4096 x 4096 51, 3072 x 4096 x 4096 50;  256 x 128: 28 (128 tiles), 35 (256), 58
+// (384);  128 x 128: 21 (256 tiles), 38 (512), 53 (768).
+inline double tile_cost(const GemmArgs& a, int config) {
+    const double u = units_of(a), wide = (a.acc_out || a.c_is_f32) ? 4.0 : 0.0;
+    if (config == kTiles256) return 8.0 + wide + 1.2 * u;
+    if (config == kTiles256x128) return 3.4 + 0.5 * wide + (a.transB ? 0.85 : 0.95) * u;
+    return 2.5 + 0.48 * u;
+}
+double product_cost(const GemmArgs& a, int config) {
+    const double t = tile_cost(a, config);
+    if (config == kTiles128) return 3.0 + std::max(1.0, tiles_of(a, 128, 128) / 256.0) * t;
+    const int64_t tiles = config == kTiles256 ? tiles_of(a, 256, 256) : tiles_of(a, 256, 128);
+    return 4.0 + (double)((tiles + 255) / 256) * t;
+}
+// Two products in one launch.  256 x 256 tiles are dispatched in order, the first product's first: the time at which the
+// last of the second product's tiles is done, when each compute unit takes the next tile as it gets free.
+double pair_cost(const GemmArgs& a1, const GemmArgs& a2, int config) {
+    const double t1 = tile_cost(a1, config), t2 = tile_cost(a2, config);
+    if (config == kTiles128) {
+        const int64_t n1 = tiles_of(a1, 128, 128), n2 = tiles_of(a2, 128, 128);
+        return 3.0 + std::max(std::max(t1, t2), (n1 * t1 + n2 * t2) / 256.0);
+    }
+    const int64_t n1 = tiles_of(a1, 256, 256), n2 = tiles_of(a2, 256, 256);
+    const double f = (double)(n1 / 256) * t1;                     // when the first compute units are free of the first product
+    const int64_t late = n1 % 256;                                // compute units that take one more of its tiles
+    auto done = [&](double x) {
+        const double e = (x - f) / t2 + 1e-6, l = (x - f - t1) / t2 + 1e-6;
+        return (256 - late) * (int64_t)(e > 0 ? e : 0) + late * (int64_t)(l > 0 ? l : 0);
+    };
+    const int64_t rounds = n2 / 256;                              // lower bound of the rounds of the second product
+    double best = 1e30;
+    for (int64_t k = rounds; k <= rounds + 3 + (int64_t)(t1 / t2); ++k)
+        for (const double x : {f + k * t2, f + t1 + k * t2})
+            if (x < best && done(x) >= n2) best = x;
+    return 4.0 + std::max(best, f + (late ? t1 : 0.0));
+}
+
+// The configuration of one product, or of a pair (a2).  A product whose 32 x 64 (64 x 64) tiles fit the compute units once
+// goes to the small kernel: 16 x 4096 x 4096 7.2 us (128 x 128 tiles: 18), 256 x 1024 x 512 4.4 (5.8), 256 x 4096 x 4096 11.5
+// (18.8), 1024 x 1024 x 1024 6.9 (8.2); at twice as many tiles it is level with the 128 x 128 tiles or behind.
+int choose_config(const GemmArgs& a, const GemmArgs* a2) {
+    const bool special = a.left_stages || a.lr_rank || (a2 && (a2->left_stages || a2->lr_rank));
+    if (!special) {
+        if (tiles_of(a, 32, 64) + (a2 ? tiles_of(*a2, 32, 64) : 0) <= 256) return kSmall32;
+        if (tiles_of(a, 64, 64) + (a2 ? tiles_of(*a2, 64, 64) : 0) <= 256) return kSmall64;
+    }
+    if (a2) return pair_cost(a, *a2, kTiles128) < 0.85 * pair_cost(a, *a2, kTiles256) ? kTiles128 : kTiles256;
+    int best = kTiles256;
+    for (const int c : {kTiles256x128, kTiles128})
+        if (product_cost(a, c) < product_cost(a, best)) best = c;
+    return best;
+}
+
 template <bool TRANSB>
 hipError_t launch_by_shape(const GemmArgs& a, hipStream_t s) {
-    auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    int cfg = a.config;
-    if (cfg < 0) {
-        // Enough 256x256 tiles to fill the 256 CUs: largest tile.  Otherwise halve the tile in N; small problems take
-        // 128x128 tiles.
-        cfg = tiles(256, 256) >= 200 ? 0 : (tiles(256, 128) >= 200 ? 2 : 3);
-    }
-    switch (cfg) {
+    switch (a.config < 0 ? choose_config(a, nullptr) : a.config) {
         case 0:
         case 1: return launch_tiles<8, 8, TRANSB>(a, s);
         case 2: return launch_tiles<8, 4, TRANSB>(a, s);
         case 3:
         case 4: return launch_tiles<4, 4, TRANSB>(a, s);
+        case kSmall64: return launch_small<4, TRANSB>(a, s);
+        case kSmall32: return a.M <= 16 ? launch_small<1, TRANSB>(a, s) : launch_small<2, TRANSB>(a, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -985,9 +1275,19 @@ hipError_t launch_gemm_i8_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream
         hipError_t e = launch_gemm_i8(a1, s);
         return e != hipSuccess ? e : launch_gemm_i8(a2, s);
     }
-    // 256x256 tiles: the E product alone would leave half the CUs idle at 2048 tokens, the pair fills them.
-    if (a1.config == 3) return launch_tiles<4, 4, false>(a1, s, &a2);
-    return launch_tiles<8, 8, false>(a1, s, &a2);
+    switch (a1.config < 0 ? choose_config(a1, &a2) : a1.config) {
+        case kSmall32: return launch_small<2, false>(a1, s, &a2);
+        case kSmall64: return launch_small<4, false>(a1, s, &a2);
+        case kTiles128: return launch_tiles<4, 4, false>(a1, s, &a2);
+        default: return launch_tiles<8, 8, false>(a1, s, &a2);
+    }
+}
+
+double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
+    const int c = a.config < 0 ? choose_config(a, a2) : a.config;
+    if (c == kSmall32 || c == kSmall64) return 3.5 + 0.8 * units_of(a) / 4 + (a2 ? 0.8 * units_of(*a2) / 4 : 0.0);
+    const double left = a.left_stages || (a2 && a2->left_stages) ? 8.0 : 0.0;   // what the left-hand epilogue adds to a tile
+    return left + (a2 ? pair_cost(a, *a2, c) : product_cost(a, c));
 }
 
 hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t s) {

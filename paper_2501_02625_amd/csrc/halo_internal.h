@@ -167,6 +167,8 @@ struct GemmArgs {
 constexpr int kMaxLowRank = 64;
 hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_i8_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t s);
+// Estimated microseconds of launch_gemm_i8(a) / launch_gemm_i8_pair(a, *a2), for choices between ways to split the work.
+double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2);
 // True if `cfg` names a tile configuration that can run a product with reduction length K.
 bool gemm_config_valid(int cfg, int64_t K);
 // 256 workgroups x 8 wavefronts x iters x 16 MFMAs on the 4 KB of operand bytes at `operands`.

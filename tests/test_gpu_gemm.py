@@ -43,6 +43,42 @@ def test_units_and_tile_edges(M, N, K, config, trans_b):
     assert bool((acc[M:] == -7).all()) and bool((acc[:, N:] == -7).all())
 
 
+# The split-K kernel for small products (16, 32 or 64 rows of a tile by 64 columns, K dealt to four wavefronts in units of
+# 128): fewer units than wavefronts, partial units, several trips, ragged rows and columns; sums, scaled outputs and the pair.
+@pytest.mark.parametrize("M,N", [(1, 64), (16, 16), (17, 72), (31, 250), (48, 4100), (200, 4096 + 40)])
+@pytest.mark.parametrize("K", [16, 128, 400, 512, 1040, 2064])
+@pytest.mark.parametrize("trans_b", [True, False])
+def test_small_products(M, N, K, trans_b):
+    rng = np.random.default_rng(M + N + K)
+    a = rand_codes(rng, (M, K)); b = rand_codes(rng, (N, K) if trans_b else (K, N))
+    bd = torch.full((b.shape[0], (b.shape[1] + 15) // 16 * 16), 77, dtype=torch.int8, device=gu.DEV)
+    bd[:, :b.shape[1]] = gu.to_dev(b)
+    ad, bd = gu.to_dev(a), bd[:, :b.shape[1]]
+    rs = rng.uniform(1e-3, 1e-2, M).astype(np.float32); cs = rng.uniform(1e-3, 1e-2, N).astype(np.float32)
+    want = orc.gemm_codes(a, b.T if trans_b else b)
+    pitch = (N + 3) // 4 * 4 + 16
+    acc = torch.full((M + 1, pitch), -7, dtype=torch.int32, device=gu.DEV)
+    binding.halo_gemm_i8_desc(binding.gemm_desc(ad, bd, trans_b=trans_b, acc_out=acc[:M, :N]))
+    gu.assert_codes_equal(acc[:M, :N], want, "accumulators")
+    assert bool((acc[M:] == -7).all()) and bool((acc[:, N:] == -7).all())
+    out = torch.zeros((M, (N + 7) // 8 * 8), dtype=torch.float32, device=gu.DEV)
+    y, _ = binding.halo_gemm_i8(ad, bd, trans_b=trans_b, row_scale=gu.to_dev(rs), col_scale=gu.to_dev(cs), out=out[:, :N])
+    gu.assert_f32_identical(y, orc.dequantize(want, rs, cs), "scaled output")
+    y, _ = binding.halo_gemm_i8(ad, bd, trans_b=trans_b, row_scale=gu.to_dev(rs), col_scale=gu.to_dev(cs),
+                                out=out.bfloat16()[:, :N])
+    gu.assert_bf16_within_one_ulp(y, orc.dequantize(want, rs, cs), "scaled bf16 output")
+    if not trans_b:                                   # a pair of unequal products, as in the layer's backward pass
+        g = rand_codes(rng, (N, 48)); gd = gu.to_dev(g)
+        acc2 = torch.full((K, 48), -7, dtype=torch.int32, device=gu.DEV)
+        left = torch.zeros((K, (N + 15) // 16 * 16), dtype=torch.int8, device=gu.DEV)
+        left[:, :N] = gu.to_dev(b)
+        acc.fill_(-7)
+        binding.halo_gemm_i8_pair(binding.gemm_desc(ad, bd, trans_b=False, acc_out=acc[:M, :N]),
+                                  binding.gemm_desc(left[:, :N // 16 * 16], gd[:N // 16 * 16], trans_b=False, acc_out=acc2))
+        gu.assert_codes_equal(acc[:M, :N], want, "accumulators, first of a pair")
+        gu.assert_codes_equal(acc2, orc.gemm_codes(b[:, :N // 16 * 16], g[:N // 16 * 16]), "accumulators, second of a pair")
+
+
 # Every tile configuration on shapes its K step divides (ragged M and N, several trips through the ring), through
 # halo_gemm_i8_desc: the configurations differ in speed only.
 @pytest.mark.parametrize("name", sorted(binding.HALO_GEMM_CONFIGS))
