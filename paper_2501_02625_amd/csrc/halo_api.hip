@@ -108,8 +108,21 @@ BwdWorkspace bwd_layout(const halo_linear_desc* d) {
 }
 
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
-// left block covers whole 256-row tiles and the product can take the 256 x 256 configuration (K = n in 64-byte steps).
-inline bool left_in_epilogue(int64_t b, int64_t n, int32_t hb) { return hb >= 256 && b % 256 == 0 && n % 64 == 0; }
+// left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
+// tiles, followed by strided passes over its accumulators (256 tokens, 1024 x 512: 24 us for the four 256 x 256 tiles of
+// the E product against 5 + 2 x 3).  gx, gg: the plain forms of the products (gg null: only E_X is wanted).
+bool left_in_epilogue(const GemmArgs& gx, const GemmArgs* gg, int32_t hb, int32_t hm) {
+    const int64_t b = gx.M, m = gx.N;
+    if (hb < 256 || b % 256) return false;
+    const double pass = 3.0 + 8.0 * (double)b * (double)m / 4.5e6;         // a strided pass: fp32 read and written
+    GemmArgs l = gx, g2 = gg ? *gg : gx;
+    l.left_stages = 8; l.config = HALO_GEMM_256x256x64; g2.config = HALO_GEMM_256x256x64;
+    const int top = ilog2_exact(hb) - 8, stages = ilog2_exact(hb);
+    const bool one_kernel = is_pow2(hm) && row_left_top_ok(b, m, ilog2_exact(hm), top);
+    const double fused = gemm_i8_cost(l, gg ? &g2 : nullptr) + (top == 0 || one_kernel ? 0.0 : pass);
+    const double plain = gemm_i8_cost(gx, gg) + (stages + 5) / 6 * pass;
+    return fused <= plain;
+}
 
 // The rest of that un-rotation: t [b x m] fp32 holds the product after the eight low left-hand strides.  Either one
 // kernel (top strides across the wavefronts of a workgroup, then each row's right-hand un-rotation), or the remaining
@@ -667,14 +680,14 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
             }
             st = halo_hadamard_quant_tensor(src, src_dt, b, n, n, HALO_QUANT_ROWS, 0, 0, Eq, n, s_e, tq, tq_bytes, stream);
             if (st != HALO_OK) return st;
-            if (level >= 2 && left_in_epilogue(b, n, hb)) {
-                GemmArgs gx{Eq, n, Wq, m, 0, b, m, n, s_e, nullptr, acc, 1, m, nullptr, 0, HALO_GEMM_256x256x64};
+            GemmArgs gx{Eq, n, Wq, m, 0, b, m, n, nullptr, nullptr, nullptr, 0, m, acc, m, HALO_GEMM_AUTO};
+            if (level >= 2 && left_in_epilogue(gx, nullptr, hb, hm)) {
+                gx = GemmArgs{Eq, n, Wq, m, 0, b, m, n, s_e, nullptr, acc, 1, m, nullptr, 0, HALO_GEMM_256x256x64};
                 gx.left_stages = 8; gx.post_scale = s_w;
                 if (launch_gemm_i8(gx, hs) != hipSuccess) return HALO_EHIP;
                 if (finish_left_unrotation(reinterpret_cast<float*>(acc), b, m, hb, hm, EX, odt, hs) != hipSuccess)
                     return HALO_EHIP;
             } else {
-                GemmArgs gx{Eq, n, Wq, m, 0, b, m, n, nullptr, nullptr, nullptr, 0, m, acc, m, HALO_GEMM_AUTO};
                 if (launch_gemm_i8(gx, hs) != hipSuccess) return HALO_EHIP;
                 st = halo_dequant_unrotate(acc, m, b, m, s_e, s_w, level >= 1 ? hm : 0, level >= 2 ? hb : 0, EX, odt, m, f32,
                                            level >= 2 ? round256((size_t)b * m * 4) : 0, stream);
@@ -734,7 +747,7 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
                 odt == HALO_F32 ? 1 : 0, m, level == 0 ? nullptr : acc_g, m, HALO_GEMM_AUTO};
     // Level 2: the E product scales its accumulators and runs the low strides of the left-hand un-rotation in its
     // epilogue, and leaves fp32 where the int32 accumulators would go (same size).
-    const bool left_fused = EX && level >= 2 && left_in_epilogue(b, n, hb);
+    const bool left_fused = EX && level >= 2 && left_in_epilogue(gx, both ? &gg : nullptr, hb, hm);
     if (left_fused) {
         gx.row_scale = s_e; gx.C = acc; gx.c_is_f32 = 1; gx.ldc = m; gx.acc_out = nullptr; gx.left_stages = 8;
         gx.config = HALO_GEMM_256x256x64;
@@ -860,10 +873,10 @@ halo_status halo_peft_bwd(const halo_linear_desc* desc, int32_t rank, const void
     st = halo_hadamard_quant(E, HALO_BF16, b, n, n, HALO_QUANT_ROWS, 0, level >= 2 ? hb : 0, s_w, Eq, n, s_e, f32,
                              level >= 2 ? round256((size_t)b * n * 4) : 0, stream);
     if (st != HALO_OK) return st;
-    const bool left_fused = level >= 2 && left_in_epilogue(b, n, hb);
     GemmArgs gx{Eq, n, Wq, m, 0, b, m, n, s_e, nullptr, level == 0 ? EX : (void*)c32,
                 (level > 0 || odt == HALO_F32) ? 1 : 0, m, nullptr, 0, HALO_GEMM_AUTO};
     gx.lr_rank = rank; gx.lr_a = lr_a; gx.lr_b = Up;                 // (U H)^T, [m x rank]
+    const bool left_fused = level >= 2 && left_in_epilogue(gx, nullptr, hb, hm);
     if (left_fused) { gx.left_stages = 8; gx.config = HALO_GEMM_256x256x64; }
     if (launch_gemm_i8(gx, hs) != hipSuccess) return HALO_EHIP;
     if (level == 0) return HALO_OK;
