@@ -367,11 +367,11 @@ def halo_linear_fwd(desc: LinearDesc, X: Optional[torch.Tensor], W: Optional[tor
     """Forward product; returns (Y, LinearState).  Pass X=None / W=None with a `state` that already holds
     the corresponding codes to reuse them."""
     if state is None:
-        r = _native().linear_fwd(desc, X, W, None, None, None, None, Y, workspace)
+        r = _native().linear_fwd(desc, X, W, None, None, None, None, Y, workspace, True)
         if type(r) is tuple:
             return r[0], LinearState(r[1], r[2], r[3], r[4])
     else:
-        r = _native().linear_fwd(desc, X, W, state.Xq, state.s_x, state.Wq, state.s_w, Y, workspace)
+        r = _native().linear_fwd(desc, X, W, state.Xq, state.s_x, state.Wq, state.s_w, Y, workspace, False)
         if type(r) is tuple:
             return r[0], state
     return _failed(r, "halo_linear_fwd")

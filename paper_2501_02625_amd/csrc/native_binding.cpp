@@ -133,18 +133,20 @@ halo_status without_gil(const F& f) {
     return st;
 }
 
-// desc, X, W, Xq, s_x, Wq, s_w, Y, workspace
+// desc, X, W, Xq, s_x, Wq, s_w, Y, workspace, new_state.  new_state: the caller has no state, the codes and scales are made
+// here; otherwise a missing member of its state goes to the C ABI as the null pointer that it is, and is refused there.
 PyObject* linear_fwd(PyObject* const* a) {
     const Desc desc(a[0]);
     const halo_linear_desc& d = *desc.d;
     const at::Tensor *X = tensor(a[1]), *W = tensor(a[2]), *xq = tensor(a[3]), *sx = tensor(a[4]), *wq = tensor(a[5]),
                      *sw = tensor(a[6]), *y = tensor(a[7]), *ws = tensor(a[8]);
+    const bool make = a[9] == Py_True;
     const at::Tensor* like = X ? X : xq;
     require(like != nullptr, "X or a state is needed");
     require((!X || (bf16(X) && X->is_contiguous())) && (!W || (bf16(W) && W->is_contiguous())), "X and W are contiguous bf16");
     const Context c;
-    const at::Tensor Xq = output(xq, true, {d.b, d.m}, at::kChar, *like, c), s_x = output(sx, true, {d.b}, at::kFloat, *like, c),
-                     Wq = output(wq, true, {d.n, d.m}, at::kChar, *like, c), s_w = output(sw, true, {d.n}, at::kFloat, *like, c),
+    const at::Tensor Xq = output(xq, make, {d.b, d.m}, at::kChar, *like, c), s_x = output(sx, make, {d.b}, at::kFloat, *like, c),
+                     Wq = output(wq, make, {d.n, d.m}, at::kChar, *like, c), s_w = output(sw, make, {d.n}, at::kFloat, *like, c),
                      Y = output(y, true, {d.b, d.n}, desc.out_type(), *like, c);
     at::Tensor scratch;
     if (!ws && d.scale_mode == HALO_SCALE_PER_TENSOR) {
@@ -354,7 +356,7 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t count) {
 }
 
 #define HALO_ENTRY(F, N) {#F, (PyCFunction)(void (*)(void))entry<F, N>, METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {HALO_ENTRY(linear_fwd, 9), HALO_ENTRY(linear_bwd, 11), HALO_ENTRY(peft_fwd, 9), HALO_ENTRY(peft_bwd, 15),
+PyMethodDef methods[] = {HALO_ENTRY(linear_fwd, 10), HALO_ENTRY(linear_bwd, 11), HALO_ENTRY(peft_fwd, 9), HALO_ENTRY(peft_bwd, 15),
                          HALO_ENTRY(mx6_quant, 4),  HALO_ENTRY(gemm_mx6, 6),    HALO_ENTRY(hadamard_quant, 8),
                          HALO_ENTRY(gemm_i8, 9),    {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_halo_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -1,0 +1,32 @@
+"""GPU tests of what the native half of the binding decides by itself: which tensors it makes and what it refuses."""
+import pytest
+import torch
+
+from paper_2501_02625_amd import binding, inputs
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+B, M, N = 64, 128, 96
+
+
+def layer(level=1):
+    desc = binding.make_desc(B, M, N, level, torch.float32)
+    return desc, gu.bits_to_dev(inputs.make_activations(B, M, 0.01, 1)), gu.bits_to_dev(inputs.make_weights(N, M, 1))
+
+
+@pytest.mark.parametrize("missing", ["Xq", "s_x", "Wq", "s_w"])
+def test_a_state_with_a_missing_member_is_refused(missing):
+    """Nothing stands in for a saved tensor that is not there, whether the call would read it or write it."""
+    desc, X, W = layer()
+    Y, st = binding.halo_linear_fwd(desc, X, W)
+    full = dict(Xq=st.Xq, s_x=st.s_x, Wq=st.Wq, s_w=st.s_w)
+    st = binding.LinearState(**dict(full, **{missing: None}))
+    for x, w in ((X, W), (X, None), (None, W), (None, None)):
+        if missing == "Xq" and x is None:
+            continue                          # neither X nor its codes: no tensor that names the device
+        with pytest.raises(binding.HaloError) as e:
+            binding.halo_linear_fwd(desc, x, w, state=st)
+        assert e.value.status == binding.HALO_EINVAL
+    again, _ = binding.halo_linear_fwd(desc, None, None, state=binding.LinearState(**full))
+    assert torch.equal(again, Y)
