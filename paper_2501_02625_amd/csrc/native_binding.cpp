@@ -124,13 +124,16 @@ void* data(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 
 bool bf16(const at::Tensor* t) { return t->scalar_type() == at::kBFloat16; }
 
-template <class F>
-halo_status without_gil(const F& f) {
-    halo_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return st;
+// f(args...) with the interpreter lock released.  The pointers are arguments, so they are taken before the release: a tensor
+// without storage (inside a functorch transform) makes data_ptr() throw, and the handler in entry() needs the lock.
+struct ReleaseGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~ReleaseGil() { PyEval_RestoreThread(state); }
+};
+template <class... P, class... A>
+halo_status without_gil(halo_status (*f)(P...), A... args) {
+    const ReleaseGil released;
+    return f(args...);
 }
 
 // desc, X, W, Xq, s_x, Wq, s_w, Y, workspace, new_state.  new_state: the caller has no state, the codes and scales are made
@@ -154,10 +157,9 @@ PyObject* linear_fwd(PyObject* const* a) {
         scratch = new_tensor({(int64_t)(need > 16 ? need : 16)}, at::kByte, *like, c.device);
         ws = &scratch;
     }
-    const halo_status st = without_gil([&] {
-        return halo_linear_fwd(&d, data(X), data(W), data(Y), (int8_t*)data(Xq), (float*)data(s_x), (int8_t*)data(Wq),
-                               (float*)data(s_w), data(ws), bytes(ws), c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_linear_fwd, &d, data(X), data(W), data(Y), (int8_t*)data(Xq), (float*)data(s_x), (int8_t*)data(Wq),
+        (float*)data(s_w), data(ws), bytes(ws), c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NNNNN)", wrap(Y), wrap(Xq), wrap(s_x), wrap(Wq), wrap(s_w));
 }
@@ -179,10 +181,9 @@ PyObject* linear_bwd(PyObject* const* a) {
         scratch = new_tensor({(int64_t)(need > 1 ? need : 1)}, at::kByte, *E, c.device);
         ws = &scratch;
     }
-    const halo_status st = without_gil([&] {
-        return halo_linear_bwd(&d, data(E), (int8_t*)data(Xq), (float*)data(s_x), (int8_t*)data(Wq), (float*)data(s_w),
-                               want_ex ? data(EX) : nullptr, want_g ? data(G) : nullptr, data(ws), bytes(ws), c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_linear_bwd, &d, data(E), (int8_t*)data(Xq), (float*)data(s_x), (int8_t*)data(Wq), (float*)data(s_w),
+        want_ex ? data(EX) : nullptr, want_g ? data(G) : nullptr, data(ws), bytes(ws), c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NN)", wrap_or_none(want_ex, EX), wrap_or_none(want_g, G));
 }
@@ -206,10 +207,9 @@ PyObject* peft_fwd(PyObject* const* a) {
         scratch = new_tensor({(int64_t)(need > 1 ? need : 1)}, at::kByte, *X, c.device);
         ws = &scratch;
     }
-    const halo_status st = without_gil([&] {
-        return halo_peft_fwd(&d, (int32_t)rank, data(X), (int8_t*)data(Wq), (float*)data(s_w), data(U), data(V), data(Y),
-                             (float*)data(T), data(ws), bytes(ws), c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_peft_fwd, &d, (int32_t)rank, data(X), (int8_t*)data(Wq), (float*)data(s_w), data(U), data(V), data(Y),
+        (float*)data(T), data(ws), bytes(ws), c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NN)", wrap(Y), wrap(T));
 }
@@ -234,11 +234,10 @@ PyObject* peft_bwd(PyObject* const* a) {
         scratch = new_tensor({(int64_t)(need > 1 ? need : 1)}, at::kByte, *E, c.device);
         ws = &scratch;
     }
-    const halo_status st = without_gil([&] {
-        return halo_peft_bwd(&d, (int32_t)rank, data(E), data(X), (float*)data(T), (int8_t*)data(Wq), (float*)data(s_w), data(U),
-                             data(V), want_ex ? data(EX) : nullptr, want_gu ? (float*)data(GU) : nullptr,
-                             want_gv ? (float*)data(GV) : nullptr, data(ws), bytes(ws), c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_peft_bwd, &d, (int32_t)rank, data(E), data(X), (float*)data(T), (int8_t*)data(Wq), (float*)data(s_w), data(U),
+        data(V), want_ex ? data(EX) : nullptr, want_gu ? (float*)data(GU) : nullptr, want_gv ? (float*)data(GV) : nullptr,
+        data(ws), bytes(ws), c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NNN)", wrap_or_none(want_ex, EX), wrap_or_none(want_gu, GU), wrap_or_none(want_gv, GV));
 }
@@ -252,10 +251,9 @@ PyObject* mx6_quant(PyObject* const* a) {
     const Context c;
     const at::Tensor q = output(codes, true, {rows, cols / 32 * 24}, at::kByte, *x, c),
                      s = output(scales, true, {rows, cols / 32}, at::kByte, *x, c);
-    const halo_status st = without_gil([&] {
-        return halo_mx6_quant(data(x), rows, cols, rows ? x->stride(0) : cols, block, (uint8_t*)data(q), rows ? q.stride(0) : 24,
-                              (uint8_t*)data(s), rows ? s.stride(0) : 1, c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_mx6_quant, data(x), rows, cols, rows ? x->stride(0) : cols, block, (uint8_t*)data(q), rows ? q.stride(0) : 24,
+        (uint8_t*)data(s), rows ? s.stride(0) : 1, c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NN)", wrap(q), wrap(s));
 }
@@ -278,11 +276,9 @@ PyObject* gemm_mx6(PyObject* const* a) {
     const Context c;
     const at::Tensor C = out ? *out : new_padded(M, N, out_dtype(code), *A, c.device);
     const halo_dtype dt = dtype_code(C);
-    const halo_status st = without_gil([&] {
-        return halo_gemm_mx6((uint8_t*)data(A), M ? A->stride(0) : 24, (uint8_t*)data(sa), M ? sa->stride(0) : 4,
-                             (uint8_t*)data(B), N ? B->stride(0) : 24, (uint8_t*)data(sb), N ? sb->stride(0) : 4, M, N, K,
-                             data(C), dt, M ? C.stride(0) : N, c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_gemm_mx6, (uint8_t*)data(A), M ? A->stride(0) : 24, (uint8_t*)data(sa), M ? sa->stride(0) : 4, (uint8_t*)data(B),
+        N ? B->stride(0) : 24, (uint8_t*)data(sb), N ? sb->stride(0) : 4, M, N, K, data(C), dt, M ? C.stride(0) : N, c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return wrap(C);
 }
@@ -304,10 +300,9 @@ PyObject* hadamard_quant(PyObject* const* a) {
         scratch = new_tensor({(int64_t)need}, at::kByte, *x, c.device);
         ws = &scratch;
     }
-    const halo_status st = without_gil([&] {
-        return halo_hadamard_quant(data(x), dt, rows, cols, rows ? x->stride(0) : cols, axis, block, left, (float*)data(fold),
-                                   (int8_t*)data(q), q.numel() ? q.stride(0) : qc, (float*)data(s), data(ws), bytes(ws), c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_hadamard_quant, data(x), dt, rows, cols, rows ? x->stride(0) : cols, axis, block, left, (float*)data(fold),
+        (int8_t*)data(q), q.numel() ? q.stride(0) : qc, (float*)data(s), data(ws), bytes(ws), c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NN)", wrap(q), wrap(s));
 }
@@ -326,12 +321,10 @@ PyObject* gemm_i8(PyObject* const* a) {
     at::Tensor C = out ? *out : (code >= 0 ? new_padded(M, N, out_dtype(code), *A, c.device) : at::Tensor());
     at::Tensor S = acc ? *acc : (want_acc ? new_padded(M, N, at::kInt, *A, c.device) : at::Tensor());
     const halo_dtype dt = C.defined() ? dtype_code(C) : HALO_F32;
-    const halo_status st = without_gil([&] {
-        return halo_gemm_i8((int8_t*)data(A), M ? A->stride(0) : K, (int8_t*)data(B), B->size(0) ? B->stride(0) : B->size(1),
-                            trans ? 1 : 0, M, N, K, (float*)data(rs), (float*)data(cs), data(C), dt,
-                            C.defined() ? (M ? C.stride(0) : N) : 0, (int32_t*)data(S), S.defined() ? (M ? S.stride(0) : N) : 0,
-                            c.stream);
-    });
+    const halo_status st = without_gil(
+        halo_gemm_i8, (int8_t*)data(A), M ? A->stride(0) : K, (int8_t*)data(B), B->size(0) ? B->stride(0) : B->size(1),
+        trans ? 1 : 0, M, N, K, (float*)data(rs), (float*)data(cs), data(C), dt, C.defined() ? (M ? C.stride(0) : N) : 0,
+        (int32_t*)data(S), S.defined() ? (M ? S.stride(0) : N) : 0, c.stream);
     if (st != HALO_OK) return PyLong_FromLong(st);
     return Py_BuildValue("(NN)", wrap_or_none(C.defined(), C), wrap_or_none(S.defined(), S));
 }
