@@ -13,6 +13,7 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/core/Allocator.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/VirtualGuardImpl.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -56,14 +57,21 @@ long integer(PyObject* o) {
 void* data(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
 size_t bytes(const at::Tensor* t) { return t ? (size_t)t->numel() : 0; }      // workspaces are uint8
 
+// True if at::empty would do nothing but allocate: no dispatch mode, functorch transform or tracer sees tensors being made.
+bool plain_creation() {
+    const c10::DispatchKeySet on = c10::impl::tls_local_dispatch_key_set().included_;
+    return (on - c10::default_included_set - c10::autocast_dispatch_keyset).empty();
+}
+
 at::Tensor new_tensor(at::IntArrayRef size, at::ScalarType dtype, const at::Tensor& like, int current_device) {
+    if (!plain_creation() || like.device().index() != current_device)
+        return at::empty(size, at::TensorOptions().dtype(dtype).device(like.device()));
     // the allocator that torch.empty uses for device memory, taken from a tensor that it made
     static c10::Allocator* const allocator =
         at::empty({1}, at::TensorOptions().dtype(at::kByte).device(like.device())).storage().allocator();
-    if (allocator && like.device().index() == current_device)
-        return at::Tensor(at::detail::empty_generic(size, allocator, c10::DispatchKeySet(c10::DispatchKey::CUDA), dtype,
-                                                    std::nullopt));
-    return at::empty(size, at::TensorOptions().dtype(dtype).device(like.device()));
+    if (!allocator) return at::empty(size, at::TensorOptions().dtype(dtype).device(like.device()));
+    return at::Tensor(at::detail::empty_generic(size, allocator, c10::DispatchKeySet(c10::DispatchKey::CUDA), dtype,
+                                                std::nullopt));
 }
 
 // [rows, cols] whose row pitch is a multiple of 16 bytes (the ABI's alignment rule).

@@ -48,3 +48,21 @@ with FakeTensorMode():
             print("refused" if "storage" in str(e) else repr(e))
 """)
     assert out.split() == ["refused", "refused"]
+
+
+def test_an_allocator_is_never_taken_from_a_fake_tensor():
+    """A first call under a mode that fakes tensors must not leave its allocator behind: the next call asks for device
+    memory (which fails without a device) instead of handing null pointers to the library."""
+    out = run("""
+with FakeTensorMode():
+    X, W = new(16, 64), new(32, 64)
+    try:
+        binding.halo_linear_fwd(desc, X, W)
+    except binding.HaloError as e:
+        print(e.status == binding.HALO_EINVAL)      # fake outputs: null pointers
+try:
+    binding.halo_linear_fwd(desc, X, W)
+except Exception as e:
+    print(not isinstance(e, binding.HaloError))
+""")
+    assert out.split() == ["True", "True"]
