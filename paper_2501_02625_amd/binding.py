@@ -269,8 +269,8 @@ def halo_gemm_i8(a: torch.Tensor, b: torch.Tensor, *, trans_b: bool, row_scale: 
                  want_acc: bool = False, out: Optional[torch.Tensor] = None,
                  acc_out: Optional[torch.Tensor] = None):
     """C = diag(row_scale) (A op(B)) diag(col_scale); returns (C or None, acc or None)."""
-    r = _native().gemm_i8(a, b, trans_b, row_scale, col_scale, -1 if out_dtype is None else _dt(out_dtype), want_acc, out,
-                          acc_out)
+    r = _native().gemm_i8(a, b, trans_b, row_scale, col_scale, -1 if out is not None or out_dtype is None else _dt(out_dtype),
+                          want_acc, out, acc_out)
     return r if type(r) is tuple else _failed(r, "halo_gemm_i8")
 
 
@@ -319,7 +319,7 @@ def halo_mx6_quant(x: torch.Tensor, *, had_block: int = 0, out_codes: Optional[t
 def halo_gemm_mx6(a: torch.Tensor, sa: torch.Tensor, b: torch.Tensor, sb: torch.Tensor, *,
                   out_dtype: torch.dtype = torch.float32, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """C = A B^T on packed MXFP6 operands (codes [rows, K/32*24] uint8, scales [rows, K/32] uint8)."""
-    r = _native().gemm_mx6(a, sa, b, sb, _dt(out_dtype), out)
+    r = _native().gemm_mx6(a, sa, b, sb, HALO_F32 if out is not None else _dt(out_dtype), out)
     return r if type(r) is not int else _failed(r, "halo_gemm_mx6")
 
 

@@ -30,3 +30,17 @@ def test_a_state_with_a_missing_member_is_refused(missing):
         assert e.value.status == binding.HALO_EINVAL
     again, _ = binding.halo_linear_fwd(desc, None, None, state=binding.LinearState(**full))
     assert torch.equal(again, Y)
+
+
+def test_the_type_of_an_output_that_is_given_is_the_output_s_own():
+    """out_dtype is for an output that the call makes; next to `out` any value of it is accepted, as it always was."""
+    a = torch.ones((16, 64), dtype=torch.int8, device=gu.DEV)
+    out = torch.empty((16, 16), dtype=torch.bfloat16, device=gu.DEV)
+    y, _ = binding.halo_gemm_i8(a, a, trans_b=True, out_dtype=torch.float16, out=out)
+    assert y is out and bool((y == 64).all())
+    with pytest.raises(TypeError):
+        binding.halo_gemm_i8(a, a, trans_b=True, out_dtype=torch.float16)
+    x = torch.ones((16, 128), dtype=torch.bfloat16, device=gu.DEV)
+    q, s = binding.halo_mx6_quant(x)
+    y = binding.halo_gemm_mx6(q, s, q, s, out_dtype=torch.float16, out=out)
+    assert y is out and bool((y == 128).all())
