@@ -43,6 +43,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "gemm_offsets.h"
 #include "halo_internal.h"
 
 namespace halo {
@@ -107,19 +108,12 @@ struct GemmCfg {
     static constexpr int LDS_BYTES = NSA * A_BYTES + NSB * B_BYTES;
     static constexpr int ROW = 2 * TN;                           // matrix instructions per row of tiles
     static constexpr int READS_B = TRANSB ? 2 * TN : 4 * TN;     // LDS read instructions for B's fragments of one unit
-    static constexpr int CHB = BN / 16;                          // 16-byte chunks per K-major row of B
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
 };
 
-// Chunk swizzle of a K-major row: distinct for the rows 0-7 and 16-23 (+ 8, + 32 ...) that one half-wavefront reads, where
-// rows of 128 bytes already alternate between the two halves of the banks.
-template <int BN>
-__device__ __forceinline__ int kmajor_swizzle(int row) {
-    return BN == 256 ? (2 * (row & 7)) | ((row >> 4) & 1) : ((row >> 1) & 3) | (((row >> 4) & 1) << 2);
-}
-
 // 16 bytes per lane, buffer offset voff -> LDS (lds + 16 * lane).  Offsets past the buffer's end deliver zeros.
-constexpr uint32_t kBufferBytes = 0xFFFFFF00u, kOutside = 0xFFFFFFF0u;
+constexpr uint32_t kBufferBytes = 0xFFFFFF00u;
+static_assert(kOutside >= kBufferBytes, "kOutside is past the end");
 __device__ __forceinline__ void dma16(uint32_t voff, const v4u& buffer, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(buffer), "s"(lds)
                  : "memory");
@@ -227,7 +221,8 @@ struct Frags {
 template <class Cfg, bool TRANSB, bool SWAP>
 __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t n0, int wave, int lane, unsigned char* smem) {
     constexpr int TM = Cfg::TM, TN = Cfg::TN, BK = Cfg::BK, BN = Cfg::BN, LA = Cfg::LA, LB = Cfg::LB;
-    constexpr int RPI = 64 / Cfg::CHB;                            // K-major rows per DMA instruction
+    using KMajor = KMajorRequests<BN>;
+    constexpr int RPI = KMajor::ROWS;
     const int wave_m = wave >> 1, wave_n = wave & 1;
     const int l16 = lane & 15, g4 = lane >> 4, lrow = row_of_lane(l16);
     const int units = (int)((a.K + BK - 1) / BK);
@@ -235,14 +230,14 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
     const uint32_t lds_b = lds_a + Cfg::NSA * Cfg::A_BYTES;
 
     // ---- source offsets of this lane's DMA requests, relative to the tile's first row / column at the stage's first K.
-    // Rows beyond the matrix, and columns beyond B's row pitch, come as zeros.
+    // Rows and columns beyond the matrix (columns in whole chunks) come as zeros.
     // K-contiguous operand: request i covers rows 8 i .. of this wavefront's share; their swizzle differs by bit 2 of the
     // chunk between even and odd i.  ka[i & 1]: K offset of the lane's chunk.
     uint32_t avo[LA], bvo[LB];
     const int r8 = lane >> 3;
     const int k0 = 16 * ((lane & 7) ^ (r8 >> 1));
     const int kc[2] = {k0, k0 ^ 64};
-    const int64_t rows_a = a.M - m0, rows_b = a.N - n0, pitch_b = a.ldb - n0;
+    const int64_t rows_a = a.M - m0, rows_b = a.N - n0, cols_b = KMajor::columns(a.N, n0);
     {
         const int row = wave * LA * 8 + r8;
         const uint32_t off = (uint32_t)row * (uint32_t)a.lda;
@@ -250,7 +245,7 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
         for (int i = 0; i < LA; ++i)
             avo[i] = row + 8 * i < rows_a ? off + (uint32_t)(8 * i) * (uint32_t)a.lda + kc[i & 1] : kOutside;
     }
-    const int krow = TRANSB ? 0 : wave * LB * RPI + lane / Cfg::CHB;   // K-strided B: this lane's first K-major row
+    const int krow = TRANSB ? 0 : KMajor::first_row(wave, lane, LB);   // K-strided B: this lane's first K-major row
     if constexpr (TRANSB) {
         const int row = wave * LB * 8 + r8;
         const uint32_t off = (uint32_t)row * (uint32_t)a.ldb;
@@ -258,14 +253,8 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
         for (int i = 0; i < LB; ++i)
             bvo[i] = row + 8 * i < rows_b ? off + (uint32_t)(8 * i) * (uint32_t)a.ldb + kc[i & 1] : kOutside;
     } else {
-        // the swizzle is linear in the bits of the row, and a lane's rows differ in bits of their own
-        const int c0 = 16 * ((lane % Cfg::CHB) ^ kmajor_swizzle<BN>(lane / Cfg::CHB));
-        const uint32_t off = (uint32_t)krow * (uint32_t)a.ldb;
 #pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int c = c0 ^ (16 * kmajor_swizzle<BN>(i * RPI));
-            bvo[i] = c < pitch_b ? off + (uint32_t)(i * RPI) * (uint32_t)a.ldb + c : kOutside;
-        }
+        for (int i = 0; i < LB; ++i) bvo[i] = KMajor::offset(krow + i * RPI, KMajor::column(lane, i), a.ldb, cols_b);
     }
     v4u abuf = make_buffer(a.A + m0 * a.lda), bbuf = make_buffer(TRANSB ? a.B + n0 * a.ldb : a.B + n0);
     const int64_t b_step = TRANSB ? (int64_t)BK : (int64_t)BK * a.ldb;
@@ -847,8 +836,6 @@ struct SmallCfg {
     static constexpr int RING_BYTES = SPLIT * NS * STAGE, SUM_BYTES = SPLIT * BM * PITCH * 4;
     static constexpr int LDS_BYTES = RING_BYTES > SUM_BYTES ? RING_BYTES : SUM_BYTES;
 };
-// Chunk swizzle of a K-major row of 64 bytes (see kmajor_swizzle).
-__device__ __forceinline__ int kmajor_swizzle64(int row) { return ((row >> 2) & 1) | (((row >> 4) & 1) << 1); }
 
 template <int TM, bool TRANSB>
 __global__ void __launch_bounds__(256)
@@ -868,10 +855,11 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
     const uint32_t ring = (uint32_t)(uintptr_t)HALO_LDS_PTR(smem) + wave * NS * Cfg::STAGE;
 
     // ---- source offsets, as in main_loop, but every wavefront fetches the whole tile at its own K
-    const int64_t rows_a = a.M - m0, rows_b = a.N - n0, pitch_b = a.ldb - n0;
+    using KMajor = KMajorRequests<Cfg::BN>;
+    const int64_t rows_a = a.M - m0, rows_b = a.N - n0, cols_b = KMajor::columns(a.N, n0);
     const int r8 = lane >> 3, k0 = 16 * ((lane & 7) ^ (r8 >> 1));
     const int kc[2] = {k0, k0 ^ 64};
-    const int krow = lane >> 2;                                  // K-strided B: 16 rows of 64 bytes per request
+    const int krow = KMajor::first_row(0, lane, LB);             // K-strided B: 16 rows of 64 bytes per request
     uint32_t avo[LA], bvo[LB];
 #pragma unroll
     for (int i = 0; i < LA; ++i)
@@ -881,8 +869,7 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
         if constexpr (TRANSB) {
             bvo[i] = r8 + 8 * i < rows_b ? (uint32_t)(r8 + 8 * i) * (uint32_t)a.ldb + kc[i & 1] : kOutside;
         } else {
-            const int c = 16 * ((lane & 3) ^ kmajor_swizzle64(krow) ^ kmajor_swizzle64(16 * i));
-            bvo[i] = c < pitch_b ? (uint32_t)(krow + 16 * i) * (uint32_t)a.ldb + c : kOutside;
+            bvo[i] = KMajor::offset(krow + 16 * i, KMajor::column(lane, i), a.ldb, cols_b);
         }
     }
     const int64_t b_unit = TRANSB ? (int64_t)BK : (int64_t)BK * a.ldb;
@@ -926,7 +913,7 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
         const int row = 16 * g4 + (l16 >> 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-            b_addr[j] = ring + Cfg::A_BYTES + row * Cfg::BN + 16 * (j ^ kmajor_swizzle64(row)) + 8 * (l16 & 1);
+            b_addr[j] = ring + Cfg::A_BYTES + row * Cfg::BN + 16 * (j ^ kmajor_swizzle<Cfg::BN>(row)) + 8 * (l16 & 1);
     }
     int slot = 0;
     for (int u = 0; u < units; ++u) {

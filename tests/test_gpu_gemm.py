@@ -43,6 +43,20 @@ def test_units_and_tile_edges(M, N, K, config, trans_b):
     assert bool((acc[M:] == -7).all()) and bool((acc[:, N:] == -7).all())
 
 
+# B as a column slice that ends with its allocation (K-strided: the last row's pitch reaches past the end): the tiled kernels
+# and the split-K kernel, N below, at and beyond a tile.
+@pytest.mark.parametrize("M,config", [(48, -1), (130, 4), (130, 2), (130, 0)])
+@pytest.mark.parametrize("N", [40, 64, 200, 272])
+def test_b_is_a_column_slice(M, N, config):
+    K, c0 = 384, 64
+    rng = np.random.default_rng(M + N)
+    a = rand_codes(rng, (M, K)); wide = rand_codes(rng, (K, c0 + (N + 15) // 16 * 16))
+    acc = torch.empty((M, (N + 3) // 4 * 4), dtype=torch.int32, device=gu.DEV)
+    binding.halo_gemm_i8_desc(binding.gemm_desc(gu.to_dev(a), gu.to_dev(wide)[:, c0:c0 + N], trans_b=False, acc_out=acc[:, :N],
+                                                config=config))
+    gu.assert_codes_equal(acc[:, :N], orc.gemm_codes(a, wide[:, c0:c0 + N]), "accumulators")
+
+
 # The split-K kernel for small products (16, 32 or 64 rows of a tile by 64 columns, K dealt to four wavefronts in units of
 # 128): fewer units than wavefronts, partial units, several trips, ragged rows and columns; sums, scaled outputs and the pair.
 @pytest.mark.parametrize("M,N", [(1, 64), (16, 16), (17, 72), (31, 250), (48, 4100), (200, 4096 + 40)])
