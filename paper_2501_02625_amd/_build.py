@@ -2,9 +2,11 @@
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sysconfig
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -34,13 +36,60 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found: libhalo needs the ROCm toolchain to build")
 
 
-def _run(cmd):
-    proc = subprocess.run(cmd, capture_output=True, text=True)
+def _run(cmd, cwd=None):
+    proc = subprocess.run(cmd, capture_output=True, text=True, cwd=cwd)
     err = "\n".join(l for l in proc.stderr.splitlines()
                     if "packed-fp32-ops" not in l and "is not a recognized feature" not in l)
     if proc.returncode != 0:
         raise RuntimeError("build step failed: %s\n%s\n%s" % (" ".join(cmd), proc.stdout, err))
     return err
+
+
+# Kernels whose accumulators are accumulation registers named in the text of inline assembly (csrc/gemm_i8.hip).
+ACCUMULATOR_KERNELS = "gemm_i8_kernel"
+
+
+def accumulator_faults(asm: str, kernel: str = ACCUMULATOR_KERNELS):
+    """What the generated code of the kernels named `kernel` does to registers that the compiler does not know to be taken: uses
+    of an accumulation register or of m0 outside inline assembly, and scratch memory (a spill could go to an accumulation
+    register as well).  Returns (number of kernels looked at, list of faults)."""
+    name = inline = None
+    seen, faults = set(), []
+    for line in asm.splitlines():
+        label = re.match(r"(\w+):", line)
+        if label and kernel in label.group(1):
+            name, inline = label.group(1), False
+            seen.add(name)
+        elif name is None:
+            continue
+        elif line.startswith(".Lfunc_end"):
+            name = None
+        elif "#ASMSTART" in line:
+            inline = True
+        elif "#ASMEND" in line:
+            inline = False
+        elif not inline:
+            code = line.split(";")[0]
+            if re.match(r"\s*scratch_", code) or \
+                    re.search(r"\ba(\d+|\[\d+(:\d+)?\])(?=[\s,]|$)|accvgpr|\bm0\b", code):
+                faults.append("%s: %s" % (name, code.strip()))
+            elif re.match(r"\s*\.amdhsa_private_segment_fixed_size\s+[1-9]", code):
+                faults.append("%s: %s" % (name, code.strip()))
+    return len(seen), faults
+
+
+def _compile(src: str, obj: str) -> str:
+    cmd = [_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    if src != "gemm_i8.hip":
+        return _run(cmd)
+    with tempfile.TemporaryDirectory() as tmp:
+        log = _run(cmd + ["-save-temps"], cwd=tmp)
+        with open(os.path.join(tmp, "gemm_i8-hip-amdgcn-amd-amdhsa-gfx950.s")) as f:
+            count, faults = accumulator_faults(f.read())
+    if not count or faults:
+        raise RuntimeError("%s: the compiler uses registers or scratch memory of %d kernels that hold their accumulators in "
+                           "registers it does not know of:\n%s" % (src, count, "\n".join(faults[:20])))
+    return log
 
 
 def _build_native() -> str:
@@ -63,12 +112,8 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     objs = [os.path.join(BUILD_DIR, s.replace(".hip", ".o")) for s in SOURCES]
 
-    def compile_one(pair):
-        src, obj = pair
-        return _run([hipcc, *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
-
     with ThreadPoolExecutor(max_workers=min(7, len(SOURCES))) as pool:
-        logs = list(pool.map(compile_one, zip(SOURCES, objs)))
+        logs = list(pool.map(_compile, SOURCES, objs))
     logs.append(_run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH]))
     logs.append(_build_native())
     if verbose:

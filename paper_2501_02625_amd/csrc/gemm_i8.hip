@@ -112,6 +112,7 @@ struct GemmCfg {
 };
 
 // 16 bytes per lane, buffer offset voff -> LDS (lds + 16 * lane).  Offsets past the buffer's end deliver zeros.
+// m0 is a reserved register and cannot be declared as overwritten; the build fails if the compiler uses it in these kernels.
 constexpr uint32_t kBufferBytes = 0xFFFFFF00u;
 static_assert(kOutside >= kBufferBytes, "kOutside is past the end");
 __device__ __forceinline__ void dma16(uint32_t voff, const v4u& buffer, uint32_t lds) {
@@ -137,8 +138,10 @@ __device__ __forceinline__ void lds_read8_tr(v2i& d, uint32_t addr) {
 }
 // The accumulators are NOT variables: register tile t of a wavefront is the accumulation registers a[4 t .. 4 t + 3], named
 // in the text of the assembly below.  (As variables they fill the whole accumulation half of the register file, and every
-// branch or epilogue made the compiler copy or spill them.)  hold_accumulators() tells the compiler that they are taken: it
-// is part of every wait, so nothing the compiler keeps can live in them.
+// branch or epilogue made the compiler copy or spill them.)  hold_accumulators() tells the compiler that they are taken:
+// nothing that the compiler keeps can live in them across one, and one stands at every wait and before every row or column
+// of tiles of the epilogues.  Between two holds the compiler could still put a short-lived value there: the build reads the
+// generated code and fails if these kernels touch an accumulation register outside this assembly, or use scratch memory.
 #define HALO_A8(n) "a" #n "0", "a" #n "1", "a" #n "2", "a" #n "3", "a" #n "4", "a" #n "5", "a" #n "6", "a" #n "7", "a" #n "8", "a" #n "9"
 #define HALO_ACCUMULATORS                                                                                               \
     "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", HALO_A8(1), HALO_A8(2), HALO_A8(3), HALO_A8(4), HALO_A8(5), \
@@ -443,6 +446,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const Place<Cfg>& at
             StaticFor<0, TM>::run([&](auto ii) {
                 constexpr int i = decltype(ii)::value;
                 __builtin_amdgcn_sched_barrier(0);                // one row of tiles at a time
+                hold_accumulators<TM * TN>();
                 if (at.row0 + 16 * i < a.M) {
                     int32_t* row = a.acc_out + (at.row0 + 16 * i) * a.ld_acc;
                     StaticFor<0, TN>::run([&](auto jj) {
@@ -493,6 +497,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const Place<Cfg>& at
         StaticFor<0, TM>::run([&](auto ii) {
             constexpr int i = decltype(ii)::value;
             __builtin_amdgcn_sched_barrier(0);                    // one row of tiles at a time
+            hold_accumulators<TM * TN>();
             if (at.row0 + 16 * i < a.M) {
                 int32_t* row = reinterpret_cast<int32_t*>(a.C) + (at.row0 + 16 * i) * a.ldc;
                 StaticFor<0, TN>::run([&](auto jj) {
@@ -509,6 +514,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const Place<Cfg>& at
     StaticFor<0, TM>::run([&](auto ii) {
         constexpr int i = decltype(ii)::value;
         __builtin_amdgcn_sched_barrier(0);                        // one row of tiles at a time
+        hold_accumulators<TM * TN>();
         const bool row_ok = at.row0 + 16 * i < a.M;
         uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (at.row0 + 16 * i) * a.ldc + shift;
         StaticFor<0, TN / 2>::run([&](auto hh) {
@@ -599,6 +605,7 @@ __device__ __forceinline__ void epilogue_left8(const GemmArgs& a, const Place<Cf
     auto stages = [&](auto jj, float (&f)[TM][4]) {
         constexpr int j = decltype(jj)::value;
         __builtin_amdgcn_sched_barrier(0);                        // one column tile at a time
+        hold_accumulators<TM * TN>();
         StaticFor<0, TM>::run([&](auto ii) {
             constexpr int i = decltype(ii)::value;
             const v4i x = read_acc<i * TN + j>();
@@ -729,6 +736,7 @@ __device__ __forceinline__ void lowrank_prepare(const GemmArgs& a, const Place<C
             write_acc<t>(x);
         });
         __builtin_amdgcn_sched_barrier(0);
+        hold_accumulators<TM * TN>();
     });
     auto hi16 = [](uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); };
     auto split8 = [&](const v4f& x0, const v4f& x1, bool in, v8bf& h, v8bf& m, v8bf& l) {
