@@ -1177,69 +1177,6 @@ hipError_t launch_plain(const GemmArgs& a, hipStream_t s) {
 // K granularity of the tile configurations 0..3 that the ABI promises to refuse a K for (halo_gemm_config in halo.h).
 constexpr int kStepOfConfig[4] = {64, 128, 128, 64};
 
-// Tile configurations (halo_gemm_config in halo.h): 0, 1: 256 x 256; 2: 256 x 128; 3, 4: 128 x 128.  Two more are chosen by
-// shape only: 64 x 64 and 32 x 64 (16 x 64) tiles with K split over the wavefronts (gemm_i8_small_kernel).
-enum { kTiles256 = 0, kTiles256x128 = 2, kTiles128 = 3, kSmall64 = 5, kSmall32 = 6 };
-
-inline int64_t tiles_of(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
-inline double units_of(const GemmArgs& a) { return (double)((a.K + 127) / 128); }
-
-// Estimated microseconds of the tile configurations, fitted to measurements on products from 1024 x 1024 x 1024 to
-// 8192 x 4096 x 4096 (within 15 %): so much per tile for the launch of its workgroup, the first loads and the store, so
-// much per unit of K.  256 compute units; two 128 x 128 workgroups share one, which smooths its last round.
-// 256 x 256: 2048 x 4096 x 4096 45 us, 4096 x 4096 x 4096 51, 3072 x 4096 x 4096 50;  256 x 128: 28 (128 tiles), 35 (256), 58
-// (384);  128 x 128: 21 (256 tiles), 38 (512), 53 (768).
-inline double tile_cost(const GemmArgs& a, int config) {
-    const double u = units_of(a), wide = (a.acc_out || a.c_is_f32) ? 4.0 : 0.0;
-    if (config == kTiles256) return 8.0 + wide + 1.2 * u;
-    if (config == kTiles256x128) return 3.4 + 0.5 * wide + (a.transB ? 0.85 : 0.95) * u;
-    return 2.5 + 0.48 * u;
-}
-double product_cost(const GemmArgs& a, int config) {
-    const double t = tile_cost(a, config);
-    if (config == kTiles128) return 3.0 + std::max(1.0, tiles_of(a, 128, 128) / 256.0) * t;
-    const int64_t tiles = config == kTiles256 ? tiles_of(a, 256, 256) : tiles_of(a, 256, 128);
-    return 4.0 + (double)((tiles + 255) / 256) * t;
-}
-// Two products in one launch.  256 x 256 tiles are dispatched in order, the first product's first: the time at which the
-// last of the second product's tiles is done, when each compute unit takes the next tile as it gets free.
-double pair_cost(const GemmArgs& a1, const GemmArgs& a2, int config) {
-    const double t1 = tile_cost(a1, config), t2 = tile_cost(a2, config);
-    if (config == kTiles128) {
-        const int64_t n1 = tiles_of(a1, 128, 128), n2 = tiles_of(a2, 128, 128);
-        return 3.0 + std::max(std::max(t1, t2), (n1 * t1 + n2 * t2) / 256.0);
-    }
-    const int64_t n1 = tiles_of(a1, 256, 256), n2 = tiles_of(a2, 256, 256);
-    const double f = (double)(n1 / 256) * t1;                     // when the first compute units are free of the first product
-    const int64_t late = n1 % 256;                                // compute units that take one more of its tiles
-    auto done = [&](double x) {
-        const double e = (x - f) / t2 + 1e-6, l = (x - f - t1) / t2 + 1e-6;
-        return (256 - late) * (int64_t)(e > 0 ? e : 0) + late * (int64_t)(l > 0 ? l : 0);
-    };
-    const int64_t rounds = n2 / 256;                              // lower bound of the rounds of the second product
-    double best = 1e30;
-    for (int64_t k = rounds; k <= rounds + 3 + (int64_t)(t1 / t2); ++k)
-        for (const double x : {f + k * t2, f + t1 + k * t2})
-            if (x < best && done(x) >= n2) best = x;
-    return 4.0 + std::max(best, f + (late ? t1 : 0.0));
-}
-
-// The configuration of one product, or of a pair (a2).  A product whose 32 x 64 (64 x 64) tiles fit the compute units once
-// goes to the small kernel: 16 x 4096 x 4096 7.2 us (128 x 128 tiles: 18), 256 x 1024 x 512 4.4 (5.8), 256 x 4096 x 4096 11.5
-// (18.8), 1024 x 1024 x 1024 6.9 (8.2); at twice as many tiles it is level with the 128 x 128 tiles or behind.
-int choose_config(const GemmArgs& a, const GemmArgs* a2) {
-    const bool special = a.left_stages || a.lr_rank || (a2 && (a2->left_stages || a2->lr_rank));
-    if (!special) {
-        if (tiles_of(a, 32, 64) + (a2 ? tiles_of(*a2, 32, 64) : 0) <= 256) return kSmall32;
-        if (tiles_of(a, 64, 64) + (a2 ? tiles_of(*a2, 64, 64) : 0) <= 256) return kSmall64;
-    }
-    if (a2) return pair_cost(a, *a2, kTiles128) < 0.85 * pair_cost(a, *a2, kTiles256) ? kTiles128 : kTiles256;
-    int best = kTiles256;
-    for (const int c : {kTiles256x128, kTiles128})
-        if (product_cost(a, c) < product_cost(a, best)) best = c;
-    return best;
-}
-
 template <bool TRANSB>
 hipError_t launch_by_shape(const GemmArgs& a, hipStream_t s) {
     switch (a.config < 0 ? choose_config(a, nullptr) : a.config) {
@@ -1276,13 +1213,6 @@ hipError_t launch_gemm_i8_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream
         case kTiles128: return launch_tiles<4, 4, false>(a1, s, &a2);
         default: return launch_tiles<8, 8, false>(a1, s, &a2);
     }
-}
-
-double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
-    const int c = a.config < 0 ? choose_config(a, a2) : a.config;
-    if (c == kSmall32 || c == kSmall64) return 3.5 + 0.8 * units_of(a) / 4 + (a2 ? 0.8 * units_of(*a2) / 4 : 0.0);
-    const double left = a.left_stages || (a2 && a2->left_stages) ? 8.0 : 0.0;   // what the left-hand epilogue adds to a tile
-    return left + (a2 ? pair_cost(a, *a2, c) : product_cost(a, c));
 }
 
 hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t s) {

@@ -1,0 +1,148 @@
+// One INT8 product as its launcher takes it, and the rules that choose between ways to run it: plain host functions, for the
+// launchers and for a host program that asks which way a shape goes.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+#include "halo.h"
+
+namespace halo {
+
+struct GemmArgs {
+    const int8_t* A;
+    int64_t lda;
+    const int8_t* B;
+    int64_t ldb;
+    int transB;
+    int64_t M, N, K;
+    const float* row_scale;
+    const float* col_scale;
+    void* C;
+    int c_is_f32;
+    int64_t ldc;
+    int32_t* acc_out;
+    int64_t ld_acc;
+    int config;              // halo_gemm_config: -1 = chosen by shape
+    // left_stages == 8 (256-row tiles only, C fp32, M a multiple of 256): the epilogue scales the accumulators,
+    // (float(acc) * row_scale[row]) * post_scale[0], and then runs the eight lowest strides (1 .. 128 rows) of a left-hand
+    // Walsh-Hadamard rotation down each column of the tile, unnormalised, before it stores C.
+    int left_stages;
+    const float* post_scale;
+    // lr_rank > 0 (C required, no acc_out; K-step configurations only): the epilogue adds a low-rank product to the
+    // scaled accumulators before anything else happens to them,
+    //   value(row, col) = ((float(acc) * row_scale[row]) * col_scale[col]) * post_scale + sum_k lr_a[row, k] * lr_b[k, col]
+    // with lr_a fp32 [M x lr_rank] and lr_b [N x lr_rank] (fp32, or bf16 with lr_b_bf16), both dense, 16-byte aligned,
+    // lr_rank a multiple of 8; the sum is accumulated in fp32.
+    int lr_rank;
+    const float* lr_a;
+    const void* lr_b;
+    int lr_b_bf16;
+};
+
+inline int ilog2_exact(int64_t v) {
+    int l = 0;
+    while ((int64_t(1) << l) < v) ++l;
+    return l;
+}
+inline bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
+
+// The shapes that launch_row_left_top takes: log_block 9..12 dividing cols, left_top 1..4, or 5 with log_block <= 11, rows a
+// multiple of the left block.
+inline bool row_left_top_ok(int64_t rows, int64_t cols, int log_block, int left_top) {
+    if (log_block < 9 || log_block > 12 || left_top < 1 || left_top > 5) return false;
+    if (left_top == 5 && log_block > 11) return false;      // 32 rows of 4096 columns do not fit a compute unit
+    if (rows <= 0 || cols <= 0 || cols % (int64_t(1) << log_block) != 0) return false;
+    return rows % (int64_t(256) << left_top) == 0;
+}
+
+constexpr int64_t kComputeUnits = 256;                            // of a GPU
+
+// Tile configurations (halo_gemm_config in halo.h): 0, 1: 256 x 256; 2: 256 x 128; 3, 4: 128 x 128.  Two more are chosen by
+// shape only: 64 x 64 and 32 x 64 (16 x 64) tiles with K split over the wavefronts (gemm_i8_small_kernel).
+enum { kTiles256 = 0, kTiles256x128 = 2, kTiles128 = 3, kSmall64 = 5, kSmall32 = 6 };
+
+inline int64_t tiles_of(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
+inline double units_of(const GemmArgs& a) { return (double)((a.K + 127) / 128); }
+
+// Estimated microseconds of the tile configurations, fitted to measurements on products from 1024 x 1024 x 1024 to
+// 8192 x 4096 x 4096 (within 15 %): so much per tile for the launch of its workgroup, the first loads and the store, so
+// much per unit of K.  256 compute units; two 128 x 128 workgroups share one, which smooths its last round.
+// 256 x 256: 2048 x 4096 x 4096 45 us, 4096 x 4096 x 4096 51, 3072 x 4096 x 4096 50;  256 x 128: 28 (128 tiles), 35 (256), 58
+// (384);  128 x 128: 21 (256 tiles), 38 (512), 53 (768).
+inline double tile_cost(const GemmArgs& a, int config) {
+    const double u = units_of(a), wide = (a.acc_out || a.c_is_f32) ? 4.0 : 0.0;
+    if (config == kTiles256) return 8.0 + wide + 1.2 * u;
+    if (config == kTiles256x128) return 3.4 + 0.5 * wide + (a.transB ? 0.85 : 0.95) * u;
+    return 2.5 + 0.48 * u;
+}
+inline double product_cost(const GemmArgs& a, int config) {
+    const double t = tile_cost(a, config);
+    if (config == kTiles128) return 3.0 + std::max(1.0, tiles_of(a, 128, 128) / (double)kComputeUnits) * t;
+    const int64_t tiles = config == kTiles256 ? tiles_of(a, 256, 256) : tiles_of(a, 256, 128);
+    return 4.0 + (double)((tiles + kComputeUnits - 1) / kComputeUnits) * t;
+}
+// Two products in one launch.  256 x 256 tiles are dispatched in order, the first product's first: the time at which the
+// last of the second product's tiles is done, when each compute unit takes the next tile as it gets free.
+inline double pair_cost(const GemmArgs& a1, const GemmArgs& a2, int config) {
+    const double t1 = tile_cost(a1, config), t2 = tile_cost(a2, config);
+    if (config == kTiles128) {
+        const int64_t n1 = tiles_of(a1, 128, 128), n2 = tiles_of(a2, 128, 128);
+        return 3.0 + std::max(std::max(t1, t2), (n1 * t1 + n2 * t2) / kComputeUnits);
+    }
+    const int64_t n1 = tiles_of(a1, 256, 256), n2 = tiles_of(a2, 256, 256);
+    const double f = (double)(n1 / kComputeUnits) * t1;           // when the first compute units are free of the first product
+    const int64_t late = n1 % kComputeUnits;                      // compute units that take one more of its tiles
+    auto done = [&](double x) {
+        const double e = (x - f) / t2 + 1e-6, l = (x - f - t1) / t2 + 1e-6;
+        return (kComputeUnits - late) * (int64_t)(e > 0 ? e : 0) + late * (int64_t)(l > 0 ? l : 0);
+    };
+    const int64_t rounds = n2 / kComputeUnits;                    // lower bound of the rounds of the second product
+    double best = 1e30;
+    for (int64_t k = rounds; k <= rounds + 3 + (int64_t)(t1 / t2); ++k)
+        for (const double x : {f + k * t2, f + t1 + k * t2})
+            if (x < best && done(x) >= n2) best = x;
+    return 4.0 + std::max(best, f + (late ? t1 : 0.0));
+}
+
+// The configuration of one product, or of a pair (a2).  A product whose 32 x 64 (64 x 64) tiles fit the compute units once
+// goes to the small kernel: 16 x 4096 x 4096 7.2 us (128 x 128 tiles: 18), 256 x 1024 x 512 4.4 (5.8), 256 x 4096 x 4096 11.5
+// (18.8), 1024 x 1024 x 1024 6.9 (8.2); at twice as many tiles it is level with the 128 x 128 tiles or behind.
+inline int choose_config(const GemmArgs& a, const GemmArgs* a2) {
+    const bool special = a.left_stages || a.lr_rank || (a2 && (a2->left_stages || a2->lr_rank));
+    if (!special) {
+        if (tiles_of(a, 32, 64) + (a2 ? tiles_of(*a2, 32, 64) : 0) <= kComputeUnits) return kSmall32;
+        if (tiles_of(a, 64, 64) + (a2 ? tiles_of(*a2, 64, 64) : 0) <= kComputeUnits) return kSmall64;
+    }
+    if (a2) return pair_cost(a, *a2, kTiles128) < 0.85 * pair_cost(a, *a2, kTiles256) ? kTiles128 : kTiles256;
+    int best = kTiles256;
+    for (const int c : {kTiles256x128, kTiles128})
+        if (product_cost(a, c) < product_cost(a, best)) best = c;
+    return best;
+}
+
+// Estimated microseconds of launch_gemm_i8(a) / launch_gemm_i8_pair(a, *a2), for choices between ways to split the work.
+inline double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
+    const int c = a.config < 0 ? choose_config(a, a2) : a.config;
+    if (c == kSmall32 || c == kSmall64) return 3.5 + 0.8 * units_of(a) / 4 + (a2 ? 0.8 * units_of(*a2) / 4 : 0.0);
+    const double left = a.left_stages || (a2 && a2->left_stages) ? 8.0 : 0.0;   // what the left-hand epilogue adds to a tile
+    return left + (a2 ? pair_cost(a, *a2, c) : product_cost(a, c));
+}
+
+// Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
+// left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
+// tiles, followed by strided passes over its accumulators (256 tokens, 1024 x 512: 24 us for the four 256 x 256 tiles of
+// the E product against 5 + 2 x 3).  gx, gg: the plain forms of the products (gg null: only E_X is wanted).
+inline bool left_in_epilogue(const GemmArgs& gx, const GemmArgs* gg, int32_t hb, int32_t hm) {
+    const int64_t b = gx.M, m = gx.N;
+    if (hb < 256 || b % 256) return false;
+    const double pass = 3.0 + 8.0 * (double)b * (double)m / 4.5e6;         // a strided pass: fp32 read and written
+    GemmArgs l = gx, g2 = gg ? *gg : gx;
+    l.left_stages = 8; l.config = HALO_GEMM_256x256x64; g2.config = HALO_GEMM_256x256x64;
+    const int top = ilog2_exact(hb) - 8, stages = ilog2_exact(hb);
+    const bool one_kernel = is_pow2(hm) && row_left_top_ok(b, m, ilog2_exact(hm), top);
+    const double fused = gemm_i8_cost(l, gg ? &g2 : nullptr) + (top == 0 || one_kernel ? 0.0 : pass);
+    const double plain = gemm_i8_cost(gx, gg) + (stages + 5) / 6 * pass;
+    return fused <= plain;
+}
+
+}  // namespace halo

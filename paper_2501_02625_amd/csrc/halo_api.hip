@@ -107,23 +107,6 @@ BwdWorkspace bwd_layout(const halo_linear_desc* d) {
     return w;
 }
 
-// Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
-// left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
-// tiles, followed by strided passes over its accumulators (256 tokens, 1024 x 512: 24 us for the four 256 x 256 tiles of
-// the E product against 5 + 2 x 3).  gx, gg: the plain forms of the products (gg null: only E_X is wanted).
-bool left_in_epilogue(const GemmArgs& gx, const GemmArgs* gg, int32_t hb, int32_t hm) {
-    const int64_t b = gx.M, m = gx.N;
-    if (hb < 256 || b % 256) return false;
-    const double pass = 3.0 + 8.0 * (double)b * (double)m / 4.5e6;         // a strided pass: fp32 read and written
-    GemmArgs l = gx, g2 = gg ? *gg : gx;
-    l.left_stages = 8; l.config = HALO_GEMM_256x256x64; g2.config = HALO_GEMM_256x256x64;
-    const int top = ilog2_exact(hb) - 8, stages = ilog2_exact(hb);
-    const bool one_kernel = is_pow2(hm) && row_left_top_ok(b, m, ilog2_exact(hm), top);
-    const double fused = gemm_i8_cost(l, gg ? &g2 : nullptr) + (top == 0 || one_kernel ? 0.0 : pass);
-    const double plain = gemm_i8_cost(gx, gg) + (stages + 5) / 6 * pass;
-    return fused <= plain;
-}
-
 // The rest of that un-rotation: t [b x m] fp32 holds the product after the eight low left-hand strides.  Either one
 // kernel (top strides across the wavefronts of a workgroup, then each row's right-hand un-rotation), or the remaining
 // strides in place and then the row kernel (1/sqrt(left block), right-hand un-rotation, conversion).

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_plan.h"
 #include "halo.h"
 
 namespace halo {
@@ -54,9 +55,7 @@ hipError_t launch_row_transform(const RowArgs& a, InKind in, OutKind out, hipStr
 // The end of a left+right un-rotation in one kernel.  `in` is fp32 [rows x cols] on which all strides of a left-hand
 // rotation of block 256 << left_top have run except the top left_top ones; the kernel runs those (the 2^left_top rows
 // they mix sit in the wavefronts of one workgroup and meet in LDS), multiplies by in_mul, un-rotates each row in blocks
-// of 2^log_block and stores bf16 / fp32.  row_left_top_ok: the shapes it takes (log_block 9..12 dividing cols,
-// left_top 1..4, or 5 with log_block <= 11, rows a multiple of the left block).
-bool row_left_top_ok(int64_t rows, int64_t cols, int log_block, int left_top);
+// of 2^log_block and stores bf16 / fp32.  row_left_top_ok: the shapes it takes.
 hipError_t launch_row_left_top(const RowArgs& a, OutKind out, hipStream_t s);
 bool row_kron_shape_ok(int64_t cols, int64_t block);
 hipError_t launch_row_kron(const RowArgs& a, InKind in, OutKind out, hipStream_t s);
@@ -134,41 +133,9 @@ constexpr size_t kStaticScratchBytes = size_t(8) << 20;
 hipError_t launch_dual_quant_static(DualQuantArgs a, hipStream_t s);
 
 // ---- INT8 GEMM ----
-struct GemmArgs {
-    const int8_t* A;
-    int64_t lda;
-    const int8_t* B;
-    int64_t ldb;
-    int transB;
-    int64_t M, N, K;
-    const float* row_scale;
-    const float* col_scale;
-    void* C;
-    int c_is_f32;
-    int64_t ldc;
-    int32_t* acc_out;
-    int64_t ld_acc;
-    int config;              // halo_gemm_config: -1 = chosen by shape
-    // left_stages == 8 (256-row tiles only, C fp32, M a multiple of 256): the epilogue scales the accumulators,
-    // (float(acc) * row_scale[row]) * post_scale[0], and then runs the eight lowest strides (1 .. 128 rows) of a left-hand
-    // Walsh-Hadamard rotation down each column of the tile, unnormalised, before it stores C.
-    int left_stages;
-    const float* post_scale;
-    // lr_rank > 0 (C required, no acc_out; K-step configurations only): the epilogue adds a low-rank product to the
-    // scaled accumulators before anything else happens to them,
-    //   value(row, col) = ((float(acc) * row_scale[row]) * col_scale[col]) * post_scale + sum_k lr_a[row, k] * lr_b[k, col]
-    // with lr_a fp32 [M x lr_rank] and lr_b [N x lr_rank] (fp32, or bf16 with lr_b_bf16), both dense, 16-byte aligned,
-    // lr_rank a multiple of 8; the sum is accumulated in fp32.
-    int lr_rank;
-    const float* lr_a;
-    const void* lr_b;
-    int lr_b_bf16;
-};
 constexpr int kMaxLowRank = 64;
 hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_i8_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t s);
-// Estimated microseconds of launch_gemm_i8(a) / launch_gemm_i8_pair(a, *a2), for choices between ways to split the work.
-double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2);
 // True if `cfg` names a tile configuration that can run a product with reduction length K.
 bool gemm_config_valid(int cfg, int64_t K);
 // 256 workgroups x 8 wavefronts x iters x 16 MFMAs on the 4 KB of operand bytes at `operands`.
@@ -228,12 +195,5 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, halo_bf16x2));
 }
 __device__ __forceinline__ uint16_t bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-
-inline int ilog2_exact(int64_t v) {
-    int l = 0;
-    while ((int64_t(1) << l) < v) ++l;
-    return l;
-}
-inline bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
 }  // namespace halo

@@ -679,13 +679,6 @@ hipError_t launch_left_top_by_seg(const RowArgs& a, hipStream_t s) {
 
 }  // namespace
 
-bool row_left_top_ok(int64_t rows, int64_t cols, int log_block, int left_top) {
-    if (log_block < 9 || log_block > 12 || left_top < 1 || left_top > 5) return false;
-    if (left_top == 5 && log_block > 11) return false;      // 32 rows of 4096 columns do not fit a compute unit
-    if (rows <= 0 || cols <= 0 || cols % (int64_t(1) << log_block) != 0) return false;
-    return rows % (int64_t(256) << left_top) == 0;
-}
-
 hipError_t launch_row_left_top(const RowArgs& a, OutKind out, hipStream_t s) {
     if (a.kron_m != 0 || a.fold || a.rows2 != 0 || !row_left_top_ok(a.rows, a.cols, a.log_block, a.left_top))
         return hipErrorInvalidValue;

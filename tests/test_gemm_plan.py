@@ -1,0 +1,83 @@
+"""CPU test of which way the rules in csrc/gemm_plan.h send the shapes of the GPU tests: a test that is there for one kernel
+keeps reaching it when a rule changes, or fails here."""
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2501_02625_amd import _build
+from tests import test_gpu_gemm, test_gpu_linear, test_gpu_peft, test_gpu_per_tensor
+
+PROGRAM = r"""
+#include <cstdio>
+#include "gemm_plan.h"
+using namespace halo;
+
+int32_t somewhere;
+GemmArgs product(long M, long N, long K) {
+    GemmArgs g{};
+    g.M = M; g.N = N; g.K = K; g.config = HALO_GEMM_AUTO; g.acc_out = &somewhere;
+    return g;
+}
+
+// each line: `one M N K`, `pair M N K M N K` or `left tokens in out right-block left-block both-products rank`
+int main() {
+    char what[8];
+    while (std::scanf("%7s", what) == 1) {
+        long v[7];
+        const int count = what[0] == 'o' ? 3 : what[0] == 'p' ? 6 : 7;
+        for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
+        if (what[0] == 'l') {
+            GemmArgs gx = product(v[0], v[1], v[2]);
+            const GemmArgs gg = product(v[2], v[1], v[0]);
+            if (v[6]) { gx.lr_rank = (int)v[6]; gx.acc_out = nullptr; gx.C = &somewhere; gx.c_is_f32 = 1; }
+            std::printf("%d\n", (int)left_in_epilogue(gx, v[5] ? &gg : nullptr, (int32_t)v[4], (int32_t)v[3]));
+            continue;
+        }
+        const GemmArgs a = product(v[0], v[1], v[2]), a2 = product(v[3], v[4], v[5]);
+        const int c = choose_config(a, what[0] == 'p' ? &a2 : nullptr);
+        std::puts(c == kTiles256 ? "256x256" : c == kTiles256x128 ? "256x128" : c == kTiles128 ? "128x128" : c == kSmall64 ? "64x64"
+                  : what[0] == 'o' && a.M <= 16 ? "16x64" : "32x64");
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(PROGRAM)
+    subprocess.run([shutil.which("g++") or "g++", "-std=c++17", "-O1", "-I" + _build.CSRC, "-I" + _build.INCLUDE,
+                    str(d / "plan.cpp"), "-o", str(d / "plan")], check=True)
+
+    def answers(lines):
+        text = "\n".join(" ".join(map(str, l)) for l in lines)
+        return subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True).stdout.split()
+
+    return answers
+
+
+def test_shapes_of_the_small_product_tests(ask):
+    shapes, longest = sorted(test_gpu_gemm.SMALL_SHAPES), max(test_gpu_gemm.SMALL_K)
+    single = ask(("one", M, N, K) for M, N in shapes for K in test_gpu_gemm.SMALL_K)
+    per = len(test_gpu_gemm.SMALL_K)
+    for i, s in enumerate(shapes):
+        assert set(single[i * per:(i + 1) * per]) == {test_gpu_gemm.SMALL_SHAPES[s][0]}, s
+    pairs = ask(("pair", M, N, longest, longest, 48, N // 16 * 16) for M, N in shapes)
+    assert dict(zip(shapes, pairs)) == {s: test_gpu_gemm.SMALL_SHAPES[s][1] for s in shapes}
+
+
+def left(b, m, n, hm, hb, both, rank=0):
+    return "left", b, m, n, hm, hb, int(both), rank
+
+
+def test_shapes_of_the_left_epilogue_tests(ask):
+    lines = [left(*s, both=True) for s in test_gpu_linear.LEFT_IN_EPILOGUE]
+    lines += [left(b, m, n, min(m & -m, 4096), b & -b, both=False) for b, m, n in test_gpu_per_tensor.LEFT_IN_EPILOGUE]
+    lines += [left(b, m, n, hm, hb, both=False, rank=rank) for b, m, n, rank, level, hm, hb in test_gpu_peft.LEFT_IN_EPILOGUE]
+    for line, said in zip(lines, ask(lines)):
+        assert said == "1", line
+    # one top stride to five, and none, each on every right block that one kernel finishes or that needs a pass of its own
+    tops = {hb.bit_length() - 9 for b, m, n, hm, hb in test_gpu_linear.LEFT_IN_EPILOGUE}
+    blocks = {hm for b, m, n, hm, hb in test_gpu_linear.LEFT_IN_EPILOGUE}
+    assert tops == {0, 1, 2, 3, 4, 5} and blocks == {512, 1024, 2048, 4096, 14336}

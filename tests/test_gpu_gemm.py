@@ -10,18 +10,26 @@ from tests import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 
-# M, N, K -- chosen to hit each macro-tile configuration, ragged edges and a K tail
+# M, N, K: the configuration is the library's choice, ragged edges and a K tail.  test_gemm_plan.py holds the choice; a test
+# that means a tile size names it (test_units_and_tile_edges, test_every_tile_configuration_gives_the_same_accumulators).
 SHAPES = [
-    (128, 512, 512),       # config c1 forward
+    (128, 512, 512),       # config c1 forward: 32x64 tiles
     (32, 32, 16),
     (1, 1, 64),
-    (300, 200, 272),       # ragged M, N; K not a multiple of the K step
+    (300, 200, 272),       # ragged M, N; K not a multiple of the 128-byte unit
     (257, 129, 1040),
-    (2048, 4096, 256),     # 256x128 tiles
-    (4096, 4096, 128),     # 256x256 tiles
-    (4100, 3900, 80),      # 256x256 tiles with ragged edges
+    (2048, 4096, 256),     # 128x128 tiles, two rounds
+    (4096, 4096, 128),     # 128x128 tiles, four rounds
+    (4100, 3900, 80),      # 128x128 tiles with ragged edges
     (512, 14336, 64),
 ]
+# M, N of test_small_products: the tile that one product takes, and that the pair takes at the longest K of the test
+SMALL_SHAPES = {
+    (1, 64): ("16x64", "32x64"), (16, 16): ("16x64", "32x64"), (17, 72): ("32x64", "32x64"), (31, 250): ("32x64", "32x64"),
+    (48, 4100): ("32x64", "32x64"), (100, 4056): ("32x64", "64x64"), (200, 4056): ("64x64", "128x128"),
+    (200, 4096 + 40): ("128x128", "128x128"),
+}
+SMALL_K = [16, 128, 400, 512, 1040, 2064]
 
 
 # K around the 128-byte units of the main loop (a partial one, one, one and a bit, odd and even counts), M and N around the
@@ -58,9 +66,10 @@ def test_b_is_a_column_slice(M, N, config):
 
 
 # The split-K kernel for small products (16, 32 or 64 rows of a tile by 64 columns, K dealt to four wavefronts in units of
-# 128): fewer units than wavefronts, partial units, several trips, ragged rows and columns; sums, scaled outputs and the pair.
-@pytest.mark.parametrize("M,N", [(1, 64), (16, 16), (17, 72), (31, 250), (48, 4100), (200, 4096 + 40)])
-@pytest.mark.parametrize("K", [16, 128, 400, 512, 1040, 2064])
+# 128) and the first shape beyond it: fewer units than wavefronts, partial units, several trips, ragged rows and columns;
+# sums, scaled outputs and the pair.
+@pytest.mark.parametrize("M,N", sorted(SMALL_SHAPES))
+@pytest.mark.parametrize("K", SMALL_K)
 @pytest.mark.parametrize("trans_b", [True, False])
 def test_small_products(M, N, K, trans_b):
     rng = np.random.default_rng(M + N + K)

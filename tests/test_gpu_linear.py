@@ -101,23 +101,47 @@ def test_small_layers_all_levels(b, m, n, level):
 
 
 @pytest.mark.parametrize("b,m,n,hm,hb,odt", [
-    (1024, 1024, 256, 0, 0, torch.float32),        # left block 1024: two top strides after the epilogue's eight; right block 1024
-    (2048, 2048, 128, 0, 0, torch.bfloat16),       # three top strides, right block 2048
-    (4096, 512, 64, 0, 0, torch.float32),          # four top strides, right block 512
-    (1024, 1536, 192, 512, 512, torch.float32),    # two left blocks of 512 (one top stride), three right blocks of 512
-    (8192, 512, 64, 0, 0, torch.float32),          # left block 8192: five strides left, two rows per wavefront
-    (8192, 2048, 64, 0, 0, torch.bfloat16),        # the same with the widest segment that fits (2048)
+    (1024, 1024, 256, 0, 0, torch.float32),        # left block 1024, right block 1024
+    (2048, 2048, 128, 0, 0, torch.bfloat16),       # right block 2048
+    (4096, 512, 64, 0, 0, torch.float32),          # right block 512
+    (1024, 1536, 192, 512, 512, torch.float32),    # two left blocks of 512, three right blocks of 512
+    (8192, 512, 64, 0, 0, torch.float32),          # left block 8192
+    (8192, 2048, 64, 0, 0, torch.bfloat16),        # the same, five strides in one kernel with the widest segment that fits (2048)
     (16384, 1024, 64, 0, 8192, torch.float32),     # two left blocks of 8192
     (8192, 4096, 64, 0, 0, torch.float32),         # five strides and a 4096 block: the strided pass takes them
-    (768, 1024, 128, 0, 0, torch.float32),         # b = 3 * 256: left block 256, nothing left after the epilogue
-    (512, 4096, 64, 0, 0, torch.float32),          # one top stride, right block 4096 (64 values per lane)
+    (768, 1024, 128, 0, 0, torch.float32),         # b = 3 * 256: left block 256
+    (512, 4096, 64, 0, 0, torch.float32),          # right block 4096 (64 values per lane)
     (4096, 4096, 128, 0, 0, torch.bfloat16),       # four top strides, right block 4096
     (2048, 8192, 64, 4096, 1024, torch.float32),   # two left blocks of 1024, two right blocks of 4096
 ])
 def test_level2_output_side_variants(b, m, n, hm, hb, odt):
-    """Level 2 with the low left-hand strides in the product's epilogue: every way the rest of the un-rotation can go."""
+    """Level 2: left and right blocks of every size, whichever way the rule sends their un-rotation."""
     Xb = inputs.make_activations(b, m, 0.01, b + m); Wb = inputs.make_weights(n, m, b + m); Eb = inputs.make_errors(b, n, b + m)
     run_and_check(b, m, n, 2, Xb, Wb, Eb, odt=odt, hm=hm, hb=hb)
+
+
+# tokens, in- and out-features, right and left block: the low left-hand strides run in the product's epilogue
+# (test_gemm_plan.py asserts that the rule says so), and every way the rest of the un-rotation can go is there.
+LEFT_IN_EPILOGUE = [
+    (768, 9216, 16, 1024, 256),       # left block 256: nothing left after the epilogue
+    (512, 9216, 144, 512, 512),       # one top stride
+    (1536, 4096, 144, 4096, 512),
+    (1024, 5120, 80, 1024, 1024),     # two
+    (2048, 3584, 16, 512, 2048),      # three
+    (2048, 4096, 272, 2048, 2048),
+    (4096, 3072, 16, 1024, 4096),     # four
+    (4096, 4096, 32, 4096, 4096),
+    (8192, 1536, 16, 512, 8192),      # five
+    (8192, 2048, 32, 2048, 8192),
+    (8192, 4096, 16, 4096, 8192),     # five, with a right block that leaves them to a strided pass
+    (512, 14336, 144, 14336, 512),    # a Kronecker block: a strided pass, then its own kernel
+]
+
+
+@pytest.mark.parametrize("b,m,n,hm,hb", LEFT_IN_EPILOGUE)
+def test_level2_low_left_strides_in_the_epilogue(b, m, n, hm, hb):
+    Xb = inputs.make_activations(b, m, 0.01, b + m); Wb = inputs.make_weights(n, m, b + m); Eb = inputs.make_errors(b, n, b + m)
+    run_and_check(b, m, n, 2, Xb, Wb, Eb, odt=torch.bfloat16 if n == 32 else torch.float32, hm=hm, hb=hb)
 
 
 def test_bf16_outputs_and_explicit_blocks():

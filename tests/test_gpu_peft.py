@@ -110,20 +110,27 @@ def run_peft(b, m, n, rank, level, seed, odt=torch.float32, hm=0, hb=0, zero_v=F
 # (tokens, in-features, out-features, rank, level, right block, left block)
 SHAPES = [
     (128, 512, 512, 16, 2, 0, 0),          # 128x128 tiles; left block 128: plain epilogue, all left strides afterwards
-    (512, 1024, 768, 8, 2, 0, 0),          # rank 8; left block 512: low strides in the epilogue
-    (768, 512, 1024, 16, 2, 512, 256),     # left block 256 = the tile: nothing left for the strided passes
+    (512, 1024, 768, 8, 2, 0, 0),          # rank 8; left block 512
+    (768, 512, 1024, 16, 2, 512, 256),     # left block 256
     (272, 640, 448, 32, 1, 128, 0),        # ragged row tile, rank 32, block-diagonal rotation
     (304, 576, 320, 64, 0, 0, 0),          # level 0 (no rotation), rank 64, product stored straight from the epilogue
     (96, 192, 64, 24, 2, 64, 32),          # rank 24 (a masked half tile), small blocks
     (256, 1792, 256, 16, 2, 1792, 256),    # Kronecker rotation H_64 (x) H_28
-    (2048, 4096, 4096, 16, 2, 0, 0),       # 256x128 forward tiles, 256x256 backward tiles, four top left strides
+    (2048, 4096, 4096, 16, 2, 0, 0),       # 256x128 forward tiles, 256x256 backward tiles, three top left strides
     (32768, 64, 64, 8, 2, 64, 32768),      # left block too long for the small rotation kernel: strided passes for H S
     (512, 14336, 128, 16, 2, 14336, 512),  # one Kronecker block H_512 (x) H_28 over 14336
     (1024, 2048, 192, 64, 2, 2048, 1024),  # rank 64 (four rank tiles), right block 2048
 ]
+# the low left-hand strides and the low-rank product share the epilogue (test_gemm_plan.py asserts that the rule says so)
+LEFT_IN_EPILOGUE = [
+    (1536, 2560, 192, 8, 2, 512, 512),     # rank 8: most of a 32-deep matrix instruction is masked
+    (2048, 2048, 128, 64, 2, 1024, 2048),  # rank 64: two trips of 32
+    (1024, 4096, 64, 24, 2, 2048, 1024),   # rank 24
+    (768, 5120, 64, 32, 2, 512, 256),      # left block 256: nothing left after the epilogue
+]
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + LEFT_IN_EPILOGUE, ids=lambda s: "x".join(map(str, s)))
 def test_peft_module_fp32_outputs(shape):
     b, m, n, rank, level, hm, hb = shape
     run_peft(b, m, n, rank, level, seed=b + rank, hm=hm, hb=hb)
@@ -136,7 +143,7 @@ def test_peft_module_bf16_outputs(shape):
 
 
 @pytest.mark.parametrize("shape,odt", [(SHAPES[1], torch.float32), (SHAPES[2], torch.bfloat16), (SHAPES[3], torch.float32),
-                                       (SHAPES[4], torch.float32)], ids=lambda s: str(s).replace(" ", ""))
+                                       (SHAPES[4], torch.float32), (LEFT_IN_EPILOGUE[1], torch.float32)], ids=lambda s: str(s).replace(" ", ""))
 def test_zero_adapter_is_the_plain_layer(shape, odt):
     b, m, n, rank, level, hm, hb = shape
     run_peft(b, m, n, rank, level, seed=3 * b, odt=odt, hm=hm, hb=hb, zero_v=True)

@@ -60,11 +60,21 @@ def test_per_tensor_layers_all_levels(b, m, n, level):
 
 def test_config_c7_full_size_per_tensor():
     """Config c7: the shape of c2 (tokens 2048, 4096 x 4096, HALO-1) with one scale per tensor, compared in full; and a
-    level-2 layer large enough for the product's epilogue to run the low left-hand strides with the tensor scale."""
+    level-2 layer."""
     cfg = inputs.CONFIGS["c7"]
     assert cfg.per_tensor
     run_per_tensor(cfg.tokens, 4096, 4096, cfg.level, cfg.seed * 1000)
     run_per_tensor(1024, 2048, 512, 2, 11)
+
+
+# tokens, in- and out-features: at level 2 the product's epilogue runs the low left-hand strides with the tensor scale
+# (test_gemm_plan.py asserts that the rule says so)
+LEFT_IN_EPILOGUE = [(768, 5120, 16), (512, 8192, 144), (1024, 4096, 272), (4096, 1024, 80)]
+
+
+@pytest.mark.parametrize("b,m,n", LEFT_IN_EPILOGUE)
+def test_per_tensor_low_left_strides_in_the_epilogue(b, m, n):
+    run_per_tensor(b, m, n, 2, b + n)
 
 
 def test_per_tensor_bf16_and_quantisation_error_of_both_modes_on_config_c1():
