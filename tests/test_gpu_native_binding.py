@@ -44,3 +44,30 @@ def test_the_type_of_an_output_that_is_given_is_the_output_s_own():
     q, s = binding.halo_mx6_quant(x)
     y = binding.halo_gemm_mx6(q, s, q, s, out_dtype=torch.float16, out=out)
     assert y is out and bool((y == 128).all())
+
+
+def test_calls_run_on_the_current_stream():
+    """Operands written on a side stream, behind other work there: a launch on any other stream would read them too early."""
+    desc, X, W = layer(2)
+    E = gu.bits_to_dev(inputs.make_errors(B, N, 1))
+    Y, st = binding.halo_linear_fwd(desc, X, W)
+    EX, G = binding.halo_linear_bwd(desc, E, st)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        x, e = torch.zeros_like(X), torch.zeros_like(E)
+        torch.cuda._sleep(20_000_000)
+        x.copy_(X); e.copy_(E)
+        y, s = binding.halo_linear_fwd(desc, x, W)
+        ex, g = binding.halo_linear_bwd(desc, e, s)
+    side.synchronize()
+    assert torch.equal(y, Y) and torch.equal(ex, EX) and torch.equal(g, G)
+
+
+def test_an_output_that_does_not_fit_the_device_raises_out_of_memory():
+    desc, X, W = layer()
+    Y, _ = binding.halo_linear_fwd(desc, X, W)
+    with pytest.raises(torch.OutOfMemoryError):
+        binding.halo_hadamard_quant(X[:1, :16].expand(1 << 44, 16))       # 256 TiB of codes
+    again, _ = binding.halo_linear_fwd(desc, X, W)
+    assert torch.equal(again, Y)
