@@ -28,8 +28,8 @@ struct GemmArgs {
     // Walsh-Hadamard rotation down each column of the tile, unnormalised, before it stores C.
     int left_stages;
     const float* post_scale;
-    // lr_rank > 0 (C required, no acc_out; K-step configurations only): the epilogue adds a low-rank product to the
-    // scaled accumulators before anything else happens to them,
+    // lr_rank > 0 (C required, no acc_out, N a multiple of 16, not in the small kernel): the epilogue adds a low-rank product
+    // to the scaled accumulators before anything else happens to them,
     //   value(row, col) = ((float(acc) * row_scale[row]) * col_scale[col]) * post_scale + sum_k lr_a[row, k] * lr_b[k, col]
     // with lr_a fp32 [M x lr_rank] and lr_b [N x lr_rank] (fp32, or bf16 with lr_b_bf16), both dense, 16-byte aligned,
     // lr_rank a multiple of 8; the sum is accumulated in fp32.
@@ -64,11 +64,14 @@ enum { kTiles256 = 0, kTiles256x128 = 2, kTiles128 = 3, kSmall64 = 5, kSmall32 =
 inline int64_t tiles_of(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
 inline double units_of(const GemmArgs& a) { return (double)((a.K + 127) / 128); }
 
-// Estimated microseconds of the tile configurations, fitted to measurements on products from 1024 x 1024 x 1024 to
-// 8192 x 4096 x 4096 (within 15 %): so much per tile for the launch of its workgroup, the first loads and the store, so
-// much per unit of K.  256 compute units; two 128 x 128 workgroups share one, which smooths its last round.
-// 256 x 256: 2048 x 4096 x 4096 45 us, 4096 x 4096 x 4096 51, 3072 x 4096 x 4096 50;  256 x 128: 28 (128 tiles), 35 (256), 58
-// (384);  128 x 128: 21 (256 tiles), 38 (512), 53 (768).
+// Estimated microseconds of the tile configurations: so much per tile for the launch of its workgroup, the first loads and the
+// store, so much per unit of K.  Two 128 x 128 workgroups share a compute unit, which smooths its last round.
+// Coarse: against a kernel trace with warm operands, 28 products from 1024 x 2048 x 512 to 8192 x 4096 x 4096 in each of the
+// three tiles, the estimates lie between 27 % below and 47 % above, most of them above and most of all where a round leaves
+// compute units idle (256 x 128 tiles at K = 4096: 128 tiles 27.5 us, 256 tiles 31.4, both 34.6 here).  That goes for all three
+// tiles alike: the choice is the fastest tile in 26 of the 28 and within 3 % of it in the other two (3072 x 4096 x 4096 with
+// sums out: 256 x 256 53.7 us, 128 x 128 52.4).  In tiles of 256 x 256 / 256 x 128 / 128 x 128, bf16 out, 2048 x 4096 x 4096 takes
+// 45.3 / 31.4 / 32.9 us, 4096 x 4096 x 4096 52.0 / 60.0 / 62.0, 2048 x 2048 x 2048 25.5 / 16.9 / 12.1.
 inline double tile_cost(const GemmArgs& a, int config) {
     const double u = units_of(a), wide = (a.acc_out || a.c_is_f32) ? 4.0 : 0.0;
     if (config == kTiles256) return 8.0 + wide + 1.2 * u;
@@ -105,8 +108,12 @@ inline double pair_cost(const GemmArgs& a1, const GemmArgs& a2, int config) {
 }
 
 // The configuration of one product, or of a pair (a2).  A product whose 32 x 64 (64 x 64) tiles fit the compute units once
-// goes to the small kernel: 16 x 4096 x 4096 7.2 us (128 x 128 tiles: 18), 256 x 1024 x 512 4.4 (5.8), 256 x 4096 x 4096 11.5
-// (18.8), 1024 x 1024 x 1024 6.9 (8.2); at twice as many tiles it is level with the 128 x 128 tiles or behind.
+// goes to the small kernel: 16 x 4096 x 4096 5.5 us warm, 7.2 cold (128 x 128 tiles: 15.7, 18), 256 x 1024 x 512 4.3 (6.3),
+// 256 x 4096 x 4096 10.3 (16.3), 1024 x 1024 x 1024 6.4 (7.8); at twice as many tiles it is level with the 128 x 128 tiles or
+// behind.  A pair takes 128 x 128 tiles where their estimate is 15 % lower: the estimate of a full chip of 128 x 128 tiles is
+// too high by about as much as that of a part-filled one of 256 x 256 (measured, 256 x 256 against 128 x 128: two of 4096 x 4096
+// x 4096 117 us against 126, 2048 x 4096 x 4096 with its G product 68.9 / 71.6, 3072 x 4096 x 2048 with its G product 71.2 /
+// 56.0, 1024 x 4096 x 4096 with its G product 51.7 / 42.6); the faster one on all 14 pairs of that trace.
 inline int choose_config(const GemmArgs& a, const GemmArgs* a2) {
     const bool special = a.left_stages || a.lr_rank || (a2 && (a2->left_stages || a2->lr_rank));
     if (!special) {
@@ -123,25 +130,36 @@ inline int choose_config(const GemmArgs& a, const GemmArgs* a2) {
 // Estimated microseconds of launch_gemm_i8(a) / launch_gemm_i8_pair(a, *a2), for choices between ways to split the work.
 inline double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
     const int c = a.config < 0 ? choose_config(a, a2) : a.config;
+    // 16 x 512 x 512 3.9 us, 256 x 1024 x 2048 5.5, 256 x 4096 x 4096 10.3 and 13.8 with a K-strided B
     if (c == kSmall32 || c == kSmall64) return 3.5 + 0.8 * units_of(a) / 4 + (a2 ? 0.8 * units_of(*a2) / 4 : 0.0);
-    const double left = a.left_stages || (a2 && a2->left_stages) ? 8.0 : 0.0;   // what the left-hand epilogue adds to a tile
-    return left + (a2 ? pair_cost(a, *a2, c) : product_cost(a, c));
+    const double t = a2 ? pair_cost(a, *a2, c) : product_cost(a, c);
+    if (!a.left_stages && !(a2 && a2->left_stages)) return t;
+    // what the left-hand epilogue adds (5 to 6 us with 128 and 384 tiles in the launch, 17 with 512), over an estimate that is
+    // high where the chip is not full
+    const double fill = (double)(tiles_of(a, 256, 256) + (a2 ? tiles_of(*a2, 256, 256) : 0)) / kComputeUnits;
+    return t + 3.0 + 4.0 * std::min(1.0, fill);
 }
 
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
 // left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
-// tiles, followed by strided passes over its accumulators (256 tokens, 1024 x 512: 24 us for the four 256 x 256 tiles of
-// the E product against 5 + 2 x 3).  gx, gg: the plain forms of the products (gg null: only E_X is wanted).
+// tiles, followed by strided passes over its accumulators.  gx, gg: the plain forms of the products (gg null: only E_X is
+// wanted).  A pass of six strides costs 3.5 us and 1.5 us per million elements (kernel trace: 2.7 us at 256 x 1024, 7.7 at
+// 1024 x 4096, 14 at 4096 x 2048); the first one, where it starts from the int32 accumulators, 8 and 2 (10, 13 and 16).
+// The backward pass timed both ways on 171 shapes, 256 .. 8192 tokens, 512 .. 14336 by 256 .. 4096, each with both products,
+// with E_X alone and with rank-16 adapters: the rule takes the faster way or one within 3 % of it in 491 of 513, 12 % behind
+// at worst.  Both products, in the epilogue against passes: 256 x 1024 x 1024 53.5 us against 48.2, 256 x 8192 x 4096 152 against
+// 126, 1536 x 3072 x 1024 64.7 against 73.8, 4096 x 2048 x 1024 103 against 116.
 inline bool left_in_epilogue(const GemmArgs& gx, const GemmArgs* gg, int32_t hb, int32_t hm) {
     const int64_t b = gx.M, m = gx.N;
     if (hb < 256 || b % 256) return false;
-    const double pass = 3.0 + 8.0 * (double)b * (double)m / 4.5e6;         // a strided pass: fp32 read and written
+    const double melems = (double)b * (double)m / 1e6, pass = 3.5 + 1.5 * melems;
+    const double first = gx.lr_rank ? pass : 8.0 + 2.0 * melems;           // adapters: the product is stored as fp32
     GemmArgs l = gx, g2 = gg ? *gg : gx;
     l.left_stages = 8; l.config = HALO_GEMM_256x256x64; g2.config = HALO_GEMM_256x256x64;
     const int top = ilog2_exact(hb) - 8, stages = ilog2_exact(hb);
     const bool one_kernel = is_pow2(hm) && row_left_top_ok(b, m, ilog2_exact(hm), top);
     const double fused = gemm_i8_cost(l, gg ? &g2 : nullptr) + (top == 0 || one_kernel ? 0.0 : pass);
-    const double plain = gemm_i8_cost(gx, gg) + (stages + 5) / 6 * pass;
+    const double plain = gemm_i8_cost(gx, gg) + first + ((stages + 5) / 6 - 1) * pass;
     return fused <= plain;
 }
 

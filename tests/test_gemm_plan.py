@@ -81,3 +81,14 @@ def test_shapes_of_the_left_epilogue_tests(ask):
     tops = {hb.bit_length() - 9 for b, m, n, hm, hb in test_gpu_linear.LEFT_IN_EPILOGUE}
     blocks = {hm for b, m, n, hm, hb in test_gpu_linear.LEFT_IN_EPILOGUE}
     assert tops == {0, 1, 2, 3, 4, 5} and blocks == {512, 1024, 2048, 4096, 14336}
+
+
+# tokens, in- and out-features, and whether the backward pass of both products is faster with the strides in the epilogue:
+# shapes where the two ways, timed on an MI355X, lie 10 % or more apart
+MEASURED = [(4096, 2048, 1024, True), (1536, 3072, 1024, True), (512, 5632, 256, True), (768, 5632, 256, True),
+            (1024, 3072, 256, True), (2048, 3072, 256, True), (256, 1024, 1024, False), (256, 8192, 4096, False)]
+
+
+def test_the_faster_way_of_the_left_hand_un_rotation(ask):
+    lines = [left(b, m, n, min(m & -m, 4096), b & -b, both=True) for b, m, n, faster in MEASURED]
+    assert ask(lines) == [str(int(faster)) for b, m, n, faster in MEASURED]
