@@ -17,15 +17,16 @@
 // pipe's rate) and the clock settles at 1.7 GHz on such operands.
 //
 // Main loop.  Workgroup = 2 x 2 wavefronts, each a grid of TM x TN tiles of 16 x 16; one UNIT = 128 bytes of K.  A sits in
-// a ring of three LDS stages, B in a ring of two, filled by global_load_lds_dwordx4 (global memory -> LDS without passing
+// a ring of three LDS stages, B in a ring of two, filled by buffer_load_dwordx4 ... lds (global memory -> LDS without passing
 // through registers): in unit u the A stage of unit u+3 and the B stage of unit u+2 are requested.  Fragments: all of B's
 // of the next unit are read during this one (two register sets), A's are read in place as soon as the last matrix
 // instruction of their row is issued.  One barrier per unit, after its first row of tiles: by then the wavefront holds all
 // fragments of this unit (so its stages may be overwritten) and has waited for its share of the next unit's stages.  All of
 // it is inline assembly in program order: the compiler would order every LDS read after every outstanding global->LDS
 // transfer, and the order of the instructions is the schedule.  Other instructions go between accumulator pairs only.
-// A K that is not a multiple of 128: the requests of the last stage that lie beyond K go to the stage's first chunk / row
-// instead, and the A fragments of the last unit are zeroed beyond K.
+// What lies beyond the matrix, in rows, columns or K: those lanes of a request get an offset past the end of the buffer
+// descriptor (kOutside), for which the hardware writes zeros to LDS and touches no memory.  Rows and columns are decided once
+// per tile, K when the last stage is reached (trim_a, trim_b).
 // A launch may carry two independent products (halo_gemm_i8_pair): workgroups past the first product's tile count take the
 // second argument block.
 //
@@ -686,7 +687,9 @@ __device__ __forceinline__ void epilogue_left8(const GemmArgs& a, const Place<Cf
 // into three bf16 pieces (8 + 8 + 8 mantissa bits, x = hi + mid + lo); every product of two pieces is exact and is
 // accumulated in fp32.  The products kept are those down to 2^-16 of the full one (all of them when one operand is bf16
 // already): what is dropped is below 2^-23 of |a b|, an fp32 rounding.  Smallest terms first.  Every address is clamped into
-// its matrix, so that all loads are unconditional and in flight together; what lies outside is zeroed afterwards.
+// its matrix, so that all loads are unconditional; what lies outside is zeroed afterwards.
+// What bounds it: the latency of its loads, then its vector instructions.  All of them are requested before the first is used
+// (the barriers keep the compiler from moving a load to its use) and land while the accumulators are scaled.
 // The s_nop: two wait states between a vector write and a matrix instruction that reads it.
 template <int T>
 __device__ __forceinline__ void lowrank_mfma(const v8bf& bh, const v8bf& ah, const v8bf& am, const v8bf& al) {
@@ -713,31 +716,62 @@ template <class Cfg, bool B_BF16>
 __device__ __forceinline__ void lowrank_prepare(const GemmArgs& a, const Place<Cfg>& at, int lane) {
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
     const int l16 = lane & 15, g4 = lane >> 4;
-    const float post = a.post_scale ? *a.post_scale : 1.0f;                          // x * 1.0f is x
+    // ---- requests: scales and the first 32 ranks
     float rs[TM];
+    v4f cs[TN], pa[TM][2];
+    v4u pb[TN][B_BF16 ? 1 : 2];                                   // eight bf16 or fp32 values of lr_b
+    auto request = [&](int c0) {
+        const int kb = c0 + 8 * g4 < a.lr_rank ? c0 + 8 * g4 : 0; // the rank is a multiple of 8
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int64_t row = at.row0 + 16 * i;
+            const v4f* p = reinterpret_cast<const v4f*>(a.lr_a + (row < a.M ? row : a.M - 1) * a.lr_rank + kb);
+            pa[i][0] = p[0];
+            pa[i][1] = p[1];
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t col = at.col(j) - 4 * g4 + l16, at_b = (col < a.N ? col : a.N - 1) * a.lr_rank + kb;
+            if constexpr (B_BF16) {
+                pb[j][0] = *reinterpret_cast<const v4u*>(reinterpret_cast<const uint16_t*>(a.lr_b) + at_b);
+            } else {
+                const v4u* p = reinterpret_cast<const v4u*>(reinterpret_cast<const float*>(a.lr_b) + at_b);
+                pb[j][0] = p[0];
+                pb[j][1] = p[1];
+            }
+        }
+    };
+    const float post = a.post_scale ? *a.post_scale : 1.0f;                          // x * 1.0f is x
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int64_t row = at.row0 + 16 * i;
         rs[i] = a.row_scale ? a.row_scale[row < a.M ? row : a.M - 1] : 1.0f;
     }
-    StaticFor<0, TN>::run([&](auto jj) {
-        constexpr int j = decltype(jj)::value;
-        v4f cs = {1.0f, 1.0f, 1.0f, 1.0f};
-        if (a.col_scale) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) cs[j] = (v4f){1.0f, 1.0f, 1.0f, 1.0f};
+    if (a.col_scale) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
             const float* p = a.col_scale + (at.col(j) < a.N ? at.col(j) : 0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) cs[e] = p[e];
+            for (int e = 0; e < 4; ++e) cs[j][e] = p[e];
         }
+    }
+    request(0);
+    // ---- the scaled accumulators
+    StaticFor<0, TN>::run([&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        hold_accumulators<TM * TN>();
         StaticFor<0, TM>::run([&](auto ii) {
             constexpr int t = decltype(ii)::value * TN + j;
             v4i x = read_acc<t>();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = __float_as_int((((float)x[r] * rs[decltype(ii)::value]) * cs[r]) * post);
+            for (int r = 0; r < 4; ++r) x[r] = __float_as_int((((float)x[r] * rs[decltype(ii)::value]) * cs[j][r]) * post);
             write_acc<t>(x);
         });
-        __builtin_amdgcn_sched_barrier(0);
-        hold_accumulators<TM * TN>();
     });
+    // ---- the low-rank sum
     auto hi16 = [](uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); };
     auto split8 = [&](const v4f& x0, const v4f& x1, bool in, v8bf& h, v8bf& m, v8bf& l) {
         uint32_t ph[8], pm[8], pl[8];
@@ -753,23 +787,18 @@ __device__ __forceinline__ void lowrank_prepare(const GemmArgs& a, const Place<C
         m = __builtin_bit_cast(v8bf, (v4u){hi16(pm[0], pm[1]), hi16(pm[2], pm[3]), hi16(pm[4], pm[5]), hi16(pm[6], pm[7])});
         l = __builtin_bit_cast(v8bf, (v4u){hi16(pl[0], pl[1]), hi16(pl[2], pl[3]), hi16(pl[4], pl[5]), hi16(pl[6], pl[7])});
     };
-    for (int c0 = 0; c0 < a.lr_rank; c0 += 32) {
-        const bool k_ok = c0 + 8 * g4 < a.lr_rank;              // the rank is a multiple of 8
-        const int kb = k_ok ? c0 + 8 * g4 : 0;
+    for (int c0 = 0;;) {
+        const bool k_ok = c0 + 8 * g4 < a.lr_rank;
         v8bf ah[TM], am[TM], al[TM];
+        __builtin_amdgcn_sched_barrier(0);
+        hold_accumulators<TM * TN>();
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int64_t row = at.row0 + 16 * i;
-            const v4f* p = reinterpret_cast<const v4f*>(a.lr_a + (row < a.M ? row : a.M - 1) * a.lr_rank + kb);
-            split8(p[0], p[1], k_ok && row < a.M, ah[i], am[i], al[i]);
-        }
+        for (int i = 0; i < TM; ++i) split8(pa[i][0], pa[i][1], k_ok && at.row0 + 16 * i < a.M, ah[i], am[i], al[i]);
         StaticFor<0, TN>::run([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            const int64_t col = at.col(j) - 4 * g4 + l16;
-            const int64_t colc = col < a.N ? col : a.N - 1;
-            const bool in = k_ok && col < a.N;
+            const bool in = k_ok && at.col(j) - 4 * g4 + l16 < a.N;
             if constexpr (B_BF16) {
-                v4u raw = *reinterpret_cast<const v4u*>(reinterpret_cast<const uint16_t*>(a.lr_b) + colc * a.lr_rank + kb);
+                v4u raw = pb[j][0];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) raw[e] = in ? raw[e] : 0u;
                 const v8bf bh = __builtin_bit_cast(v8bf, raw);
@@ -778,9 +807,8 @@ __device__ __forceinline__ void lowrank_prepare(const GemmArgs& a, const Place<C
                     lowrank_mfma<i * TN + j>(bh, ah[i], am[i], al[i]);
                 });
             } else {
-                const v4f* p = reinterpret_cast<const v4f*>(reinterpret_cast<const float*>(a.lr_b) + colc * a.lr_rank + kb);
                 v8bf bh, bm, bl;
-                split8(p[0], p[1], in, bh, bm, bl);
+                split8(__builtin_bit_cast(v4f, pb[j][0]), __builtin_bit_cast(v4f, pb[j][1]), in, bh, bm, bl);
                 StaticFor<0, TM>::run([&](auto ii) {
                     constexpr int i = decltype(ii)::value;
                     lowrank_mfma<i * TN + j>(bh, bm, bl, ah[i], am[i], al[i]);
@@ -788,6 +816,9 @@ __device__ __forceinline__ void lowrank_prepare(const GemmArgs& a, const Place<C
             }
         });
         hold_accumulators<TM * TN>();
+        c0 += 32;
+        if (c0 >= a.lr_rank) break;
+        request(c0);
     }
     asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");             // as after the main loop
 }
