@@ -138,7 +138,7 @@ hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_i8_pair(const GemmArgs& a1, const GemmArgs& a2, hipStream_t s);
 // True if `cfg` names a tile configuration that can run a product with reduction length K.
 bool gemm_config_valid(int cfg, int64_t K);
-// 256 workgroups x 8 wavefronts x iters x 16 MFMAs on the 4 KB of operand bytes at `operands`.
+// 256 workgroups x 8 wavefronts x iters x 32 MFMAs on the 4 KB of operand bytes at `operands`.
 hipError_t launch_mfma_i8_probe(const int8_t* operands, int iters, int32_t* sink, hipStream_t s);
 
 // ---- low-rank side branch (LoRA adapters next to the quantised products) ----
