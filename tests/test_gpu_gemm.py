@@ -51,6 +51,24 @@ def test_units_and_tile_edges(M, N, K, config, trans_b):
     assert bool((acc[M:] == -7).all()) and bool((acc[:, N:] == -7).all())
 
 
+# Scaled outputs of the tiled kernels, stored in pieces of 64 bytes that two column tiles (fp32) or two pairs of them (bf16)
+# share: column counts that end inside such a piece, rows that end inside the eight of a request, pitches off the line.
+@pytest.mark.parametrize("M,N", [(120, 16), (137, 48), (249, 80), (264, 112), (130, 208), (260, 272)])
+@pytest.mark.parametrize("config", [0, 2, 4])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_scaled_outputs_at_tile_edges(M, N, config, dtype):
+    K = 256
+    rng = np.random.default_rng(M + N + config)
+    a = rand_codes(rng, (M, K)); b = rand_codes(rng, (N, K))
+    rs = rng.uniform(1e-3, 1e-2, M).astype(np.float32); cs = rng.uniform(1e-3, 1e-2, N).astype(np.float32)
+    out = torch.full((M + 1, N + 24), -7.0, dtype=dtype, device=gu.DEV)
+    binding.halo_gemm_i8_desc(binding.gemm_desc(gu.to_dev(a), gu.to_dev(b), trans_b=True, row_scale=gu.to_dev(rs),
+                                                col_scale=gu.to_dev(cs), out=out[:M, :N], config=config))
+    want = orc.dequantize(orc.gemm_codes(a, b.T), rs, cs)
+    (gu.assert_f32_identical if dtype == torch.float32 else gu.assert_bf16_within_one_ulp)(out[:M, :N], want, "scaled output")
+    assert bool((out[M:] == -7).all()) and bool((out[:, N:] == -7).all())
+
+
 # B as a column slice that ends with its allocation (K-strided: the last row's pitch reaches past the end): the tiled kernels
 # and the split-K kernel, N below, at and beyond a tile.
 @pytest.mark.parametrize("M,config", [(48, -1), (130, 4), (130, 2), (130, 0)])
