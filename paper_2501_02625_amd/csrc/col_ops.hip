@@ -6,6 +6,7 @@
 //   * the dual quantiser: row-wise codes (E_Y)_Q and transposed column-wise codes (E_Y^T)_Q from one tiling of E.
 #pragma clang fp contract(off)
 
+#include <algorithm>
 #include <mutex>
 
 #include "halo_internal.h"
@@ -21,14 +22,10 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 // ------------------------------------------------------------------------------------------------
 // One pass of the left-hand FWHT: stages with row strides 2^p .. 2^(p+LOGR-1), ascending.
 // A wavefront owns 64*CPL consecutive columns and the 2^LOGR rows  base + t*2^p.
-// SIDE (bf16 input, first pass only): the pass also accumulates, per column, the absolute maximum of in[r, k] * side_fold[r]
-// over all rows into side_amax (bit patterns of non-negative floats, atomic integer max; zeroed by the caller): what the
-// column quantiser of the same matrix needs, taken from the one read of it.
-template <int LOGR, int CPL, int IN, int OUT, bool SIDE = false>
+template <int LOGR, int CPL, int IN>
 __global__ void __launch_bounds__(256)
 col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows, int64_t cols,
-                int p, float c_final, int64_t col_tiles, const float* row_scale, const float* post_scale,
-                const float* side_fold = nullptr, uint32_t* side_amax = nullptr) {
+                int p, float c_final, int64_t col_tiles, const float* row_scale, const float* post_scale) {
     constexpr int R = 1 << LOGR;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -45,9 +42,6 @@ col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_
     float my_scale = 1.0f;
     if constexpr (IN == IN_I32) {
         if (row_scale && lane < R) my_scale = row_scale[base + (int64_t)lane * stride];
-    }
-    if constexpr (SIDE) {
-        if (side_fold && lane < R) my_scale = side_fold[base + (int64_t)lane * stride];
     }
     if (col >= cols) return;
     const bool pair_ok = (CPL == 1) || (col + 1 < cols);
@@ -90,21 +84,6 @@ col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_
                 v[t][0] = src[0];
             }
         }
-    }
-
-    if constexpr (SIDE) {
-        float mx[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) mx[c] = 0.0f;
-#pragma unroll
-        for (int t = 0; t < R; ++t) {
-            const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_scale), t));
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) mx[c] = fmaxf(mx[c], fabsf(v[t][c] * f));
-        }
-#pragma unroll
-        for (int c = 0; c < CPL; ++c)
-            if (col + c < cols && mx[c] > 0.0f) atomicMax(side_amax + col + c, __float_as_uint(mx[c]));
     }
 
     if constexpr (IN == IN_I32) {
@@ -157,65 +136,278 @@ col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_
             for (int c = 0; c < CPL; ++c) v[t][c] *= c_final;
     }
 
-    if constexpr (OUT == OUT_F32) {
-        float* dst0 = reinterpret_cast<float*>(out) + base * ld_out + col;
-        if (CPL == 2 && pair_ok) {
+    float* dst0 = reinterpret_cast<float*>(out) + base * ld_out + col;
+    if (CPL == 2 && pair_ok) {
 #pragma unroll
-            for (int t = 0; t < R; ++t)
-                *reinterpret_cast<float2*>(dst0 + (int64_t)t * stride * ld_out) = make_float2(v[t][0], v[t][CPL - 1]);
-        } else {
-#pragma unroll
-            for (int t = 0; t < R; ++t) dst0[(int64_t)t * stride * ld_out] = v[t][0];
-        }
+        for (int t = 0; t < R; ++t)
+            *reinterpret_cast<float2*>(dst0 + (int64_t)t * stride * ld_out) = make_float2(v[t][0], v[t][CPL - 1]);
     } else {
-        uint16_t* dst0 = reinterpret_cast<uint16_t*>(out) + base * ld_out + col;
-        if (CPL == 2 && pair_ok) {
 #pragma unroll
-            for (int t = 0; t < R; ++t)
-                *reinterpret_cast<uint32_t*>(dst0 + (int64_t)t * stride * ld_out) = pack_bf16x2(v[t][0], v[t][CPL - 1]);
-        } else {
-#pragma unroll
-            for (int t = 0; t < R; ++t) dst0[(int64_t)t * stride * ld_out] = bf16_bits(v[t][0]);
-        }
+        for (int t = 0; t < R; ++t) dst0[(int64_t)t * stride * ld_out] = v[t][0];
     }
 }
 
-template <int LOGR, int CPL, int IN, int OUT>
+// ------------------------------------------------------------------------------------------------
+// The lowest LOGR stages (strides 1 .. 2^(LOGR-1)) of the left-hand FWHT in one pass over memory: a workgroup keeps 2^LOGR
+// consecutive rows of 32 columns (64 for LOGR 6) in registers, 32 rows x 2 columns per thread, and the rows change hands once,
+// through LDS.  First the thread holds 32 consecutive rows (five stages in registers), then, after the exchange, 32 rows that
+// lie 32 apart (the stages from stride 32 on).  LOGR 11 has one stage more than that: the halves of the 2048 rows then sit in
+// the two halves of the wavefront and v_permlane32_swap_b32 brings a pair together in one lane (one instruction for two values;
+// both results stay where they are, only the row that a register stands for changes).
+// A strided pass takes six stages (col_fwht_kernel), so blocks of 128 to 2048 rows save a round trip of the fp32 intermediate.
+// What bounds it: memory, 2 + 4 bytes an element.  64 values per thread and a 64 KB exchange buffer (one of the two columns at
+// a time), so that two workgroups of 1024 rows share a compute unit: one loads or stores while the other exchanges.
+// Neighbouring column tiles, which share cache lines of a bf16 row, run on the same XCD at the same time.
+// SIDE (bf16 input): the pass also writes, per column, the largest |in[r, k] * row_scale[r]| of its rows to
+// side_part[row block][cols]: what the column quantiser of the same matrix needs, taken from the one read of it.
+struct ColBlockArgs {
+    const void* in;
+    int64_t ld_in;
+    float* out;
+    int64_t ld_out;
+    int64_t cols;
+    int col_tiles, tiles;                // column tiles, all tiles
+    float c_final;                       // 1.0f: no multiply
+    const float* row_scale;              // IN_I32: multiplied in; SIDE: for the side output only.  May be null
+    const float* post_scale;             // IN_I32: device scalar, may be null
+    float* side_part;
+};
+template <int LOGR>
+struct ColBlockCfg {
+    static constexpr int R = 1 << LOGR, LOGCP = LOGR == 6 ? 5 : 4, CP = 1 << LOGCP;    // rows, column pairs of a workgroup
+    static constexpr int G = R / 32, T = G * CP;                                        // groups of 32 rows, threads
+    static constexpr int S = LOGR - 5 < 5 ? LOGR - 5 : 5;                               // stages of the second part in registers
+    // exchange buffer: rows of CP floats, one row of padding after every 32, so that the groups of a wavefront (or, on the way
+    // back, its consecutive rows) fall in different banks
+    static constexpr int XCH = G * 33 * CP, RED = 2 * CP * ((T + 63) / 64);
+    static constexpr int LDS_BYTES = 4 * (XCH + R + RED);
+};
+template <int LOGR, int IN, bool SIDE>
+__global__ void __launch_bounds__(ColBlockCfg<LOGR>::T, 4)
+col_block_kernel(ColBlockArgs a) {
+    using Cfg = ColBlockCfg<LOGR>;
+    constexpr int R = Cfg::R, CP = Cfg::CP, T = Cfg::T, S = Cfg::S, K = 1 << (5 - S);
+    extern __shared__ __align__(16) float smem[];
+    float* const s_scale = smem + Cfg::XCH;
+    float* const s_red = s_scale + R;
+    int tile = blockIdx.x;
+    if ((tile | 15) < a.tiles) tile = (tile & ~15) | ((tile & 7) << 1) | ((tile >> 3) & 1);    // b and b + 8: one XCD
+    const int ct = tile % a.col_tiles, rb = tile / a.col_tiles;
+    const int tid = threadIdx.x, cp = tid & (CP - 1), g = tid >> Cfg::LOGCP;
+    const int64_t r0 = (int64_t)rb << LOGR;
+    const int64_t c0 = (int64_t)ct * (2 * CP);
+    const bool whole = c0 + 2 * CP <= a.cols;                     // uniform; the number of columns is even
+    const bool col_ok = c0 + 2 * cp < a.cols;
+
+    constexpr bool SCALED = IN == IN_I32 || SIDE;
+    float sc[SCALED ? R / T : 1];
+    if constexpr (SCALED) {
+#pragma unroll
+        for (int i = 0; i < R / T; ++i) sc[i] = a.row_scale ? a.row_scale[r0 + tid + i * T] : 1.0f;
+    }
+    // ---- 32 consecutive rows, two columns; every load before the first use
+    constexpr int ESZ = IN == IN_BF16 ? 2 : 4;
+    const char* const src = reinterpret_cast<const char*>(a.in) + (r0 * a.ld_in + c0) * ESZ;    // uniform
+    const uint32_t pitch = (uint32_t)a.ld_in * ESZ;
+    const uint32_t first = (uint32_t)(32 * g) * pitch + (col_ok ? 2 * cp * ESZ : 0);            // columns outside: any valid address
+    float v[32][2];
+    if constexpr (IN == IN_BF16) {
+        uint32_t w[32];
+#pragma unroll
+        for (int t = 0; t < 32; ++t) w[t] = *reinterpret_cast<const uint32_t*>(src + (first + (uint32_t)t * pitch));
+        if constexpr (SCALED) {
+#pragma unroll
+            for (int i = 0; i < R / T; ++i) s_scale[tid + i * T] = sc[i];
+            __syncthreads();
+        }
+#pragma unroll
+        for (int t = 0; t < 32; ++t) {
+            v[t][0] = __uint_as_float(w[t] << 16);
+            v[t][1] = __uint_as_float(w[t] & 0xFFFF0000u);
+        }
+    } else if constexpr (IN == IN_F32) {
+#pragma unroll
+        for (int t = 0; t < 32; ++t) {
+            const float2 w = *reinterpret_cast<const float2*>(src + (first + (uint32_t)t * pitch));
+            v[t][0] = w.x;
+            v[t][1] = w.y;
+        }
+    } else {
+        int2 w[32];
+#pragma unroll
+        for (int t = 0; t < 32; ++t) w[t] = *reinterpret_cast<const int2*>(src + (first + (uint32_t)t * pitch));
+#pragma unroll
+        for (int i = 0; i < R / T; ++i) s_scale[tid + i * T] = sc[i];
+        __syncthreads();
+        const float post = a.post_scale ? *a.post_scale : 1.0f;   // x * 1.0f is x
+#pragma unroll
+        for (int t = 0; t < 32; ++t) {
+            const float rs = s_scale[32 * g + t];
+            v[t][0] = ((float)w[t].x * rs) * post;
+            v[t][1] = ((float)w[t].y * rs) * post;
+        }
+    }
+    if constexpr (SIDE) {
+        float m0 = 0.0f, m1 = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 32; ++t) {
+            const float f = s_scale[32 * g + t];
+            m0 = fmaxf(m0, fabsf(v[t][0] * f));
+            m1 = fmaxf(m1, fabsf(v[t][1] * f));
+        }
+#pragma unroll
+        for (int x = CP; x < 64; x <<= 1) {
+            m0 = fmaxf(m0, __shfl_xor(m0, x));
+            m1 = fmaxf(m1, __shfl_xor(m1, x));
+        }
+        if ((tid & 63) < CP) {
+            s_red[(tid >> 6) * 2 * CP + 2 * cp] = m0;
+            s_red[(tid >> 6) * 2 * CP + 2 * cp + 1] = m1;
+        }
+    }
+    // ---- strides 1 .. 16
+#pragma unroll
+    for (int h = 1; h < 32; h <<= 1)
+#pragma unroll
+        for (int t = 0; t < 32; ++t)
+            if ((t & h) == 0) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float x = v[t][c], y = v[t | h][c];
+                    v[t][c] = x + y;
+                    v[t | h][c] = x - y;
+                }
+            }
+    // ---- the rows change hands.  Afterwards register u = k * 2^S + t holds row r + k * 2^S + 32 t of the block (r < 2^S), for
+    // LOGR 11 row r + 32 t + 1024 * half.
+    const int lane = tid & 63;
+    const int half = LOGR == 11 ? lane >> 5 : 0;
+    const int r = LOGR == 11 ? 2 * (tid >> 6) + ((lane >> 4) & 1) : g;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        if (c > 0) __syncthreads();                               // everyone has read the first column
+#pragma unroll
+        for (int t = 0; t < 32; ++t) smem[(g * 33 + t) * CP + cp] = v[t][c];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int t = 0; t < (1 << S); ++t)
+                v[(k << S) + t][c] = smem[((t + 32 * half) * 33 + r + (k << S)) * CP + cp];
+    }
+    if constexpr (SIDE) {
+        if (tid < 2 * CP && c0 + tid < a.cols) {
+            float m = s_red[tid];
+#pragma unroll
+            for (int w = 1; w < (T + 63) / 64; ++w) m = fmaxf(m, s_red[w * 2 * CP + tid]);
+            a.side_part[rb * a.cols + c0 + tid] = m;
+        }
+    }
+    // ---- strides 32 ..
+#pragma unroll
+    for (int h = 1; h < (1 << S); h <<= 1)
+#pragma unroll
+        for (int t = 0; t < 32; ++t)
+            if ((t & h) == 0) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float x = v[t][c], y = v[t | h][c];
+                    v[t][c] = x + y;
+                    v[t | h][c] = x - y;
+                }
+            }
+    // LOGR 11, stride 1024: registers t and t + 1 trade, the upper half lanes of the one against the lower half lanes of the
+    // other; then t holds the sum and t + 1 the difference of row r + 32 t (lower half lanes) or r + 32 (t + 1) (upper).
+    if constexpr (LOGR == 11) {
+#pragma unroll
+        for (int t = 0; t < 32; t += 2)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+                const u2 s = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v[t][c]), __float_as_uint(v[t + 1][c]), false, false));
+                const float x = __uint_as_float(s[0]), y = __uint_as_float(s[1]);
+                v[t][c] = x + y;
+                v[t + 1][c] = x - y;
+            }
+    }
+    if (a.c_final != 1.0f) {
+#pragma unroll
+        for (int t = 0; t < 32; ++t) {
+            v[t][0] *= a.c_final;
+            v[t][1] *= a.c_final;
+        }
+    }
+    if (!whole && !col_ok) return;
+    char* const dst = reinterpret_cast<char*>(a.out + r0 * a.ld_out + c0);
+    const uint32_t opitch = (uint32_t)a.ld_out * 4;
+    const uint32_t ofirst = (uint32_t)(r + (LOGR == 11 ? 32 * half : 0)) * opitch + 8 * cp;
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+        const int k = u >> S, t = u & ((1 << S) - 1);
+        const uint32_t row = LOGR == 11 ? 32 * (t & ~1) + 1024 * (t & 1) : (k << S) + 32 * t;
+        *reinterpret_cast<float2*>(dst + (ofirst + row * opitch)) = make_float2(v[u][0], v[u][1]);
+    }
+}
+
+template <int LOGR, int IN, bool SIDE>
+hipError_t launch_col_block(const ColBlockArgs& a, hipStream_t s) {
+    using Cfg = ColBlockCfg<LOGR>;
+    static std::once_flag once;
+    static hipError_t attr_result = hipSuccess;
+    auto kern = col_block_kernel<LOGR, IN, SIDE>;
+    std::call_once(once, [&] {
+        if (Cfg::LDS_BYTES > 64 * 1024)
+            attr_result = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              Cfg::LDS_BYTES);
+    });
+    if (attr_result != hipSuccess) return attr_result;
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.tiles), dim3(Cfg::T), Cfg::LDS_BYTES, s, a);
+    return hipGetLastError();
+}
+
+template <int IN, bool SIDE>
+hipError_t launch_col_block_by_rows(int logr, const void* in, int64_t ld_in, float* out, int64_t ld_out, int64_t rows, int64_t cols,
+                                    float c_final, hipStream_t s, const float* row_scale, const float* post_scale,
+                                    float* side_part) {
+    const int64_t wide = logr == 6 ? 64 : 32, col_tiles = (cols + wide - 1) / wide, tiles = col_tiles * (rows >> logr);
+    if (tiles <= 0 || tiles > 0x7FFFFFF0) return hipErrorInvalidValue;
+    const ColBlockArgs a{in, ld_in, out, ld_out, cols, (int)col_tiles, (int)tiles, c_final, row_scale, post_scale, side_part};
+    switch (logr) {
+        case 6: return launch_col_block<6, IN, SIDE>(a, s);
+        case 7: return launch_col_block<7, IN, SIDE>(a, s);
+        case 8: return launch_col_block<8, IN, SIDE>(a, s);
+        case 9: return launch_col_block<9, IN, SIDE>(a, s);
+        case 10: return launch_col_block<10, IN, SIDE>(a, s);
+        case 11: return launch_col_block<11, IN, SIDE>(a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+template <int LOGR, int CPL, int IN>
 hipError_t launch_pass(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows, int64_t cols,
                        int p, float c_final, hipStream_t s, const float* row_scale, const float* post_scale) {
     const int64_t col_tiles = (cols + 256 * CPL - 1) / (256 * CPL);
     const int64_t groups = rows >> LOGR;
     const int64_t blocks = col_tiles * groups;
     if (blocks <= 0 || blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((col_fwht_kernel<LOGR, CPL, IN, OUT>), dim3((unsigned)blocks), dim3(256), 0, s, in, ld_in,
+    hipLaunchKernelGGL((col_fwht_kernel<LOGR, CPL, IN>), dim3((unsigned)blocks), dim3(256), 0, s, in, ld_in,
                        out, ld_out, rows, cols, p, c_final, col_tiles, row_scale, post_scale);
     return hipGetLastError();
 }
 
-// First pass with the side absmax: bf16 in, six stages, fp32 out.
-hipError_t launch_pass_side(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows, int64_t cols, float c_final,
-                            hipStream_t s, const float* side_fold, uint32_t* side_amax) {
-    const int64_t col_tiles = (cols + 511) / 512;
-    const int64_t blocks = col_tiles * (rows >> 6);
-    if (blocks <= 0 || blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((col_fwht_kernel<6, 2, IN_BF16, OUT_F32, true>), dim3((unsigned)blocks), dim3(256), 0, s, in, ld_in, out,
-                       ld_out, rows, cols, 0, c_final, col_tiles, nullptr, nullptr, side_fold, side_amax);
-    return hipGetLastError();
-}
-
-template <int IN, int OUT>
+template <int IN>
 hipError_t launch_pass_by_logr(int logr, const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_t rows,
                                int64_t cols, int p, float c_final, hipStream_t s, const float* row_scale = nullptr,
                                const float* post_scale = nullptr) {
     switch (logr) {
-        case 1: return launch_pass<1, 2, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
-        case 2: return launch_pass<2, 2, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
-        case 3: return launch_pass<3, 2, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
-        case 4: return launch_pass<4, 2, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
-        case 5: return launch_pass<5, 2, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
-        case 6: return launch_pass<6, 2, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+        case 1: return launch_pass<1, 2, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+        case 2: return launch_pass<2, 2, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+        case 3: return launch_pass<3, 2, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+        case 4: return launch_pass<4, 2, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+        case 5: return launch_pass<5, 2, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+        case 6: return launch_pass<6, 2, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
         case 7:
-            if constexpr (IN == IN_F32) return launch_pass<7, 1, IN, OUT>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
+            if constexpr (IN == IN_F32) return launch_pass<7, 1, IN>(in, ld_in, out, ld_out, rows, cols, p, c_final, s, row_scale, post_scale);
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
@@ -293,10 +485,13 @@ col_amax_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols, c
 // into one dword per column, staged in LDS as [col][row/4] with a pitch of 33 dwords, and read back as
 // 16 consecutive rows per lane so that every output row is written in full 128-byte lines.
 constexpr int kTI = 128, kTJ = 128, kPitch = kTI / 4 + 1;
+// amax: `parts` vectors of the columns' partial maxima (non-negative, so their bit patterns order like they do); or one given
+// maximum for all columns.
 __global__ void __launch_bounds__(256)
 col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols, const float* fold,
-                   const uint32_t* amax_bits, int8_t* out_q, int64_t ld_q, float* out_scale, const float* given_amax = nullptr) {
+                   const float* amax, int parts, int8_t* out_q, int64_t ld_q, float* out_scale, const float* given_amax) {
     __shared__ uint32_t s_tile[kTJ * kPitch];
+    __shared__ float s_part[8][kTJ];
     const int tid = threadIdx.x;
     const int64_t j0 = (int64_t)blockIdx.x * kTJ;
     const int64_t i0 = (int64_t)blockIdx.y * kTI;
@@ -305,14 +500,6 @@ col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols
     {
         const int jl = tid & 31;           // 4 columns each
         const int64_t col = j0 + 4 * jl;
-        float inv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float am = 0.0f;
-            if (col + e < cols) am = given_amax ? *given_amax : __uint_as_float(amax_bits[col + e]);   // one maximum for all columns
-            inv[e] = am > 0.0f ? 127.0f / am : 0.0f;
-            if (blockIdx.y == 0 && tid < 32 && col + e < cols) out_scale[col + e] = am > 0.0f ? am / 127.0f : 1.0f;
-        }
         // The 16 rows of this thread (4 quads of 4): all loads first.  A tile inside the matrix takes them with no branch in
         // between (a branch per row makes the compiler wait for each load before it issues the next); a tile on the edge
         // goes element by element.
@@ -353,6 +540,34 @@ col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols
                     }
                     w[s][r] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
                 }
+        }
+        // the columns' maxima, reduced while those loads fly: thread group tid / 32 takes every eighth vector
+        float am[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (given_amax) {
+            am[0] = am[1] = am[2] = am[3] = *given_amax;
+        } else {
+            for (int q = parts > 1 ? tid >> 5 : 0; q < parts; q += 8) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < cols) am[e] = fmaxf(am[e], amax[(int64_t)q * cols + col + e]);
+            }
+            if (parts > 1) {               // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s_part[tid >> 5][4 * jl + e] = am[e];
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    am[e] = s_part[0][4 * jl + e];
+#pragma unroll
+                    for (int q = 1; q < 8; ++q) am[e] = fmaxf(am[e], s_part[q][4 * jl + e]);
+                }
+            }
+        }
+        float inv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            inv[e] = am[e] > 0.0f ? 127.0f / am[e] : 0.0f;
+            if (blockIdx.y == 0 && tid < 32 && col + e < cols) out_scale[col + e] = am[e] > 0.0f ? am[e] / 127.0f : 1.0f;
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -675,16 +890,29 @@ dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, 
 hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0 || a.log_block == 0) return hipSuccess;
     if (a.first_stage < 0 || a.first_stage > a.log_block) return hipErrorInvalidValue;
-    // split the remaining stages into passes of at most 6 (a final 7 is allowed for fp32 input)
+    const float c = a.skip_norm ? 1.0f : (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block)));
+    // The lowest stages in one pass over blocks of rows where the block has more than the six stages of a strided pass (or
+    // its side output is wanted); the other stages in strided passes of at most six, a last one of up to seven.
+    const int low = col_block_stages(a.log_block);
+    const bool blocks = a.first_stage == 0 && low >= (a.side_part ? 6 : 7) && a.cols % 2 == 0 && a.ld_in % 2 == 0 &&
+                        a.ld_out % 2 == 0 && a.ld_tmp % 2 == 0 && std::max(a.ld_in, std::max(a.ld_out, a.ld_tmp)) <= (int64_t(1) << 18);
+    if (a.side_part && (!blocks || a.in_kind != IN_BF16)) return hipErrorInvalidValue;
     int sizes[8], np = 0, left = a.log_block - a.first_stage;
     if (left == 0) return (a.in == a.out && a.skip_norm) ? hipSuccess : hipErrorInvalidValue;   // nothing left to do in place
+    if (blocks) {
+        sizes[np++] = low;
+        left -= low;
+    }
     while (left > 0) {
         int q = left <= 6 ? left : (left == 7 && np > 0 ? 7 : 6);
         sizes[np++] = q;
         left -= q;
         if (np >= 8) return hipErrorInvalidValue;
     }
-    const float c = a.skip_norm ? 1.0f : (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block)));
+    if (a.top_left > 0) {                  // the caller runs the strides above the first pass himself
+        if (!blocks || a.top_left != a.log_block - low) return hipErrorInvalidValue;
+        np = 1;
+    }
     int p = a.first_stage;
     for (int i = 0; i < np; ++i) {
         const bool first = i == 0, last = i == np - 1;
@@ -693,24 +921,25 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
         const InKind ik = first ? a.in_kind : IN_F32;
         void* dst = last ? a.out : (void*)a.tmp;
         const int64_t ld_dst = last ? a.ld_out : a.ld_tmp;
-        const OutKind ok = last ? a.out_kind : OUT_F32;
-        const float cf = last ? c : 1.0f;
+        const float cf = last && a.top_left == 0 ? c : 1.0f;
         hipError_t e;
-        if (first && a.side_amax) {
-            // only the shape the layer uses: bf16 in, a first pass of six stages from stage 0
-            if (ik != IN_BF16 || ok != OUT_F32 || sizes[i] != 6 || p != 0) return hipErrorInvalidValue;
-            e = launch_pass_side(src, ld_src, dst, ld_dst, a.rows, a.cols, cf, s, a.side_fold, a.side_amax);
-        } else if (ik == IN_BF16 && ok == OUT_F32)
-            e = launch_pass_by_logr<IN_BF16, OUT_F32>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s);
-        else if (ik == IN_F32 && ok == OUT_F32)
-            e = launch_pass_by_logr<IN_F32, OUT_F32>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s);
-        else if (ik == IN_F32 && ok == OUT_BF16)
-            e = launch_pass_by_logr<IN_F32, OUT_BF16>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s);
-        else if (ik == IN_I32 && ok == OUT_F32)
-            e = launch_pass_by_logr<IN_I32, OUT_F32>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s, a.row_scale,
-                                                     a.post_scale);
+        if (first && blocks) {
+            float* d = reinterpret_cast<float*>(dst);
+            if (ik == IN_BF16 && a.side_part)
+                e = launch_col_block_by_rows<IN_BF16, true>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, a.side_fold, nullptr, a.side_part);
+            else if (ik == IN_BF16)
+                e = launch_col_block_by_rows<IN_BF16, false>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, nullptr, nullptr, nullptr);
+            else if (ik == IN_F32)
+                e = launch_col_block_by_rows<IN_F32, false>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, nullptr, nullptr, nullptr);
+            else
+                e = launch_col_block_by_rows<IN_I32, false>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, a.row_scale, a.post_scale, nullptr);
+        } else if (ik == IN_BF16)
+            e = launch_pass_by_logr<IN_BF16>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s);
+        else if (ik == IN_F32)
+            e = launch_pass_by_logr<IN_F32>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s);
         else
-            e = hipErrorInvalidValue;
+            e = launch_pass_by_logr<IN_I32>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s, a.row_scale,
+                                                     a.post_scale);
         if (e != hipSuccess) return e;
         p += sizes[i];
     }
@@ -790,21 +1019,16 @@ hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_am
     if (a.rows == 0 || a.cols == 0) return hipSuccess;
     const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
     hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, static_cast<const uint32_t*>(nullptr), a.out_q, a.ld_q, a.out_scale, given_amax);
+                       a.rows, a.cols, a.fold, static_cast<const float*>(nullptr), 0, a.out_q, a.ld_q, a.out_scale, given_amax);
     return hipGetLastError();
 }
 
-hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, 0u);
-    return hipGetLastError();
-}
-
-hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, hipStream_t s) {
+hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0) return hipSuccess;
     const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
     hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, reinterpret_cast<const uint32_t*>(a.amax_ws), a.out_q, a.ld_q, a.out_scale);
+                       a.rows, a.cols, a.fold, static_cast<const float*>(a.amax_ws), parts, a.out_q, a.ld_q, a.out_scale,
+                       static_cast<const float*>(nullptr));
     return hipGetLastError();
 }
 
@@ -821,7 +1045,8 @@ hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
     hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, amax_bits, a.out_q, a.ld_q, a.out_scale);
+                       a.rows, a.cols, a.fold, static_cast<const float*>(a.amax_ws), 1, a.out_q, a.ld_q, a.out_scale,
+                       static_cast<const float*>(nullptr));
     return hipGetLastError();
 }
 

@@ -125,11 +125,33 @@ hipError_t finish_left_unrotation(float* t, int64_t b, int64_t m, int32_t hb, in
         r.left_top = top;
         return launch_row_left_top(r, ok, s);
     }
-    ColFwhtArgs c{t, IN_F32, m, t, OUT_F32, m, t, m, b, m, ilog2_exact(hb)};
+    ColFwhtArgs c{t, IN_F32, m, t, m, t, m, b, m, ilog2_exact(hb)};
     c.first_stage = first_stage; c.skip_norm = 1;
     hipError_t e = launch_col_fwht(c, s);
     if (e != hipSuccess) return e;
     return launch_row_transform(r, IN_F32, ok, s);
+}
+
+// (H_left in) (x) fold, quantised per row: the left-hand rotation into the fp32 scratch tmp [rows x cols], then the row quantiser
+// (with a right-hand rotation if r asks for one).  r: rows, cols, fold, out, ld_out, out_scale and the right-hand block.  The
+// strides above the rotation's first pass run in the row quantiser where it takes them, else in passes of their own.
+// side_part (may be null): as in ColFwhtArgs.
+hipError_t left_rotate_quant(const void* in, InKind ik, int64_t ld_in, float* tmp, int log_left, RowArgs r, const float* side_fold,
+                             float* side_part, hipStream_t s) {
+    ColFwhtArgs c{in, ik, ld_in, tmp, r.cols, tmp, r.cols, r.rows, r.cols, log_left};
+    c.side_fold = side_fold; c.side_part = side_part;
+    const int low = col_block_stages(log_left), top = log_left - low;
+    r.in = tmp; r.ld_in = r.cols;
+    if (r.log_block == 0 && r.kron_m == 0 && row_top_quant_ok(r.cols, top) && r.cols % 4 == 0 && ld_in % 2 == 0 && ld_in <= (int64_t(1) << 18)) {
+        c.top_left = top; c.skip_norm = 1;
+        const hipError_t e = launch_col_fwht(c, s);
+        if (e != hipSuccess) return e;
+        r.left_top = top;
+        r.in_mul = (float)(1.0 / sqrt((double)(int64_t(1) << log_left)));
+        return launch_row_top_quant(r, low, s);
+    }
+    const hipError_t e = launch_col_fwht(c, s);
+    return e != hipSuccess ? e : launch_row_transform(r, IN_F32, OUT_Q8, s);
 }
 
 // Scratch of the HALO-PEFT entry points (one layout for both directions).
@@ -238,12 +260,8 @@ halo_status halo_hadamard_quant(const void* in, halo_dtype in_dt, int64_t rows, 
     // left-hand rotation first (strided passes into fp32 scratch), then the row kernel on the scratch
     if ((cols * 4) % 16) return HALO_EALIGN;   // scratch rows must stay 16-byte aligned
     float* tmp = reinterpret_cast<float*>(workspace);
-    ColFwhtArgs c{in, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, ld_in, tmp, OUT_F32, cols, tmp, cols, rows, cols,
-                  ilog2_exact(had_block_left)};
-    hipError_t e = launch_col_fwht(c, s);
-    if (e != hipSuccess) return HALO_EHIP;
-    r.in = tmp; r.ld_in = cols;
-    return from_hip(launch_row_transform(r, IN_F32, OUT_Q8, s));
+    return from_hip(left_rotate_quant(in, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, ld_in, tmp, ilog2_exact(had_block_left), r, nullptr,
+                                      nullptr, s));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -295,7 +313,7 @@ halo_status halo_hadamard_quant_tensor(const void* in, halo_dtype in_dt, int64_t
     int64_t ld_src = ld_in;
     InKind src_kind = in_dt == HALO_BF16 ? IN_BF16 : IN_F32;
     if (had_block_left > 0) {
-        ColFwhtArgs c{in, src_kind, ld_in, tmp, OUT_F32, cols, tmp, cols, rows, cols, ilog2_exact(had_block_left)};
+        ColFwhtArgs c{in, src_kind, ld_in, tmp, cols, tmp, cols, rows, cols, ilog2_exact(had_block_left)};
         if (launch_col_fwht(c, s) != hipSuccess) return HALO_EHIP;
         src = tmp; ld_src = cols; src_kind = IN_F32;
     }
@@ -506,7 +524,7 @@ halo_status halo_dequant_unrotate(const int32_t* acc, int64_t ld_acc, int64_t ro
     // Left-hand un-rotation first: strided passes from the accumulators into the fp32 scratch (butterflies only), then
     // the row kernel multiplies by 1/sqrt(left block), un-rotates along the rows and converts.
     float* tmp = reinterpret_cast<float*>(workspace);
-    ColFwhtArgs c{acc, IN_I32, ld_acc, tmp, OUT_F32, cols, tmp, cols, rows, cols, ilog2_exact(had_block_left)};
+    ColFwhtArgs c{acc, IN_I32, ld_acc, tmp, cols, tmp, cols, rows, cols, ilog2_exact(had_block_left)};
     c.row_scale = row_scale; c.post_scale = tensor_scale; c.skip_norm = 1;
     if (launch_col_fwht(c, s) != hipSuccess) return HALO_EHIP;
     r.in = tmp; r.ld_in = cols; r.pre_scale = nullptr; r.post_scale = nullptr;
@@ -657,7 +675,7 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
             const void* src = E;
             halo_dtype src_dt = HALO_BF16;
             if (level >= 2) {
-                ColFwhtArgs c{E, IN_BF16, n, f32, OUT_F32, n, f32, n, b, n, ilog2_exact(hb)};
+                ColFwhtArgs c{E, IN_BF16, n, f32, n, f32, n, b, n, ilog2_exact(hb)};
                 if (launch_col_fwht(c, hs) != hipSuccess) return HALO_EHIP;
                 src = f32; src_dt = HALO_F32;
             }
@@ -698,16 +716,11 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
         // takes the column maxima of E (x) s_x that the column quantiser needs (left blocks of at least 64 tokens).
         const bool side = both && level >= 2 && hb >= 64;
         if (side) {
-            uint32_t* amax_bits = reinterpret_cast<uint32_t*>(amax);
-            if (launch_zero_u32(amax_bits, n, hs) != hipSuccess) return HALO_EHIP;
-            ColFwhtArgs c{E, IN_BF16, n, f32, OUT_F32, n, f32, n, b, n, ilog2_exact(hb)};
-            c.side_fold = s_x; c.side_amax = amax_bits;
-            if (launch_col_fwht(c, hs) != hipSuccess) return HALO_EHIP;
             RowArgs r{};
-            r.in = f32; r.ld_in = n; r.rows = b; r.cols = n; r.fold = s_w; r.out = Eq; r.ld_out = n; r.out_scale = s_e;
-            if (launch_row_transform(r, IN_F32, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
+            r.rows = b; r.cols = n; r.fold = s_w; r.out = Eq; r.ld_out = n; r.out_scale = s_e;
+            if (left_rotate_quant(E, IN_BF16, n, f32, ilog2_exact(hb), r, s_x, amax, hs) != hipSuccess) return HALO_EHIP;
             ColQuantArgs q{E, n, b, n, s_x, EqT, b, s_g, amax};
-            if (launch_col_quant_t_ready(q, hs) != hipSuccess) return HALO_EHIP;
+            if (launch_col_quant_t_ready(q, (int)(b >> col_block_stages(ilog2_exact(hb))), hs) != hipSuccess) return HALO_EHIP;
         } else {
             if (EX) {
                 st = halo_hadamard_quant(E, HALO_BF16, b, n, n, HALO_QUANT_ROWS, 0, level >= 2 ? hb : 0, s_w, Eq, n, s_e, f32,
@@ -850,7 +863,7 @@ halo_status halo_peft_bwd(const halo_linear_desc* desc, int32_t rank, const void
     }
     if (!EX) return HALO_OK;
     if (rotate_s && !s_small) {            // left blocks too long for one workgroup's LDS: the strided passes
-        ColFwhtArgs c{S, IN_F32, rank, Sp, OUT_F32, rank, Sp, rank, b, rank, ilog2_exact(hb)};
+        ColFwhtArgs c{S, IN_F32, rank, Sp, rank, Sp, rank, b, rank, ilog2_exact(hb)};
         if (launch_col_fwht(c, hs) != hipSuccess) return HALO_EHIP;
     }
     st = halo_hadamard_quant(E, HALO_BF16, b, n, n, HALO_QUANT_ROWS, 0, level >= 2 ? hb : 0, s_w, Eq, n, s_e, f32,

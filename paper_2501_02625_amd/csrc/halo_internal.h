@@ -57,6 +57,11 @@ hipError_t launch_row_transform(const RowArgs& a, InKind in, OutKind out, hipStr
 // they mix sit in the wavefronts of one workgroup and meet in LDS), multiplies by in_mul, un-rotates each row in blocks
 // of 2^log_block and stores bf16 / fp32.  row_left_top_ok: the shapes it takes.
 hipError_t launch_row_left_top(const RowArgs& a, OutKind out, hipStream_t s);
+// The row quantiser (fp32 in, no right-hand rotation) behind the top strides of a left-hand rotation: rows r, r + 2^low,
+// ... r + (2^left_top - 1) 2^low of a block of 2^(low + left_top) rows are combined, multiplied by in_mul (and fold), and
+// quantised.  row_top_quant_ok: the shapes it takes.
+inline bool row_top_quant_ok(int64_t cols, int left_top) { return left_top >= 1 && left_top <= 2 && cols <= 16 * 1024; }
+hipError_t launch_row_top_quant(const RowArgs& a, int low, hipStream_t s);
 bool row_kron_shape_ok(int64_t cols, int64_t block);
 hipError_t launch_row_kron(const RowArgs& a, InKind in, OutKind out, hipStream_t s);
 
@@ -67,8 +72,7 @@ struct ColFwhtArgs {
     const void* in;
     InKind in_kind;          // IN_BF16 or IN_F32
     int64_t ld_in;
-    void* out;
-    OutKind out_kind;        // OUT_F32 or OUT_BF16
+    void* out;               // fp32
     int64_t ld_out;
     float* tmp;
     int64_t ld_tmp;
@@ -81,14 +85,17 @@ struct ColFwhtArgs {
     const float* post_scale;
     int first_stage;
     int skip_norm;
-    // side_amax != null (bf16 input, log_block >= 6, first_stage 0): the first pass also accumulates, per column, the
-    // absolute maximum of in[r, k] * side_fold[r] (side_fold may be null) over all rows into side_amax[cols], as bit
-    // patterns of non-negative floats; the caller zeroes it beforehand (launch_zero_u32).
+    // side_part != null (bf16 input, log_block >= 6, first_stage 0): the first pass also writes, per column and block of
+    // 2^col_block_stages(log_block) rows, the absolute maximum of in[r, k] * side_fold[r] (side_fold may be null) to
+    // side_part[rows >> col_block_stages(log_block)][cols].
     const float* side_fold;
-    uint32_t* side_amax;
+    float* side_part;
+    // top_left > 0 (log_block - col_block_stages(log_block), with skip_norm): only the first pass; the caller runs the top strides.
+    int top_left;
 };
+// Stages that the first pass over a block of 2^log_block rows takes, from stride 1 on.
+inline int col_block_stages(int log_block) { return log_block < 11 ? log_block : 11; }
 hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s);
-hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t s);
 
 // ---- column-wise absmax quantiser with transposed output (E^T)_Q ----
 struct ColQuantArgs {
@@ -102,8 +109,9 @@ struct ColQuantArgs {
     float* amax_ws;          // [cols] scratch: column absmax accumulated as bit patterns
 };
 hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s);
-// The same with the columns' absolute maxima already in a.amax_ws (bit patterns, from the side output of launch_col_fwht).
-hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, hipStream_t s);
+// The same with `parts` vectors of the columns' partial maxima already in a.amax_ws [parts x cols] (the side output of
+// launch_col_fwht).
+hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_t s);
 // The same with one given absmax (device scalar) for every column instead of the columns' own: the tensor-wide scale.
 hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, hipStream_t s);
 // out[0] = max(in[0..n-1]) (n >= 1, non-negative values).  With in2: out2[0] = max(in2[0..n2-1]) in the same launch.

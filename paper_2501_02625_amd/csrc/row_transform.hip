@@ -677,7 +677,116 @@ hipError_t launch_left_top_by_seg(const RowArgs& a, hipStream_t s) {
     }
 }
 
+// The row quantiser behind the top TOP strides of a left-hand rotation (halo_internal.h): a wavefront holds the same 1024
+// columns of the 2^TOP rows that those strides combine, so the strides are adds in registers, and the fp32 intermediate is
+// not written and read once more for them.  Bound by memory, 4 + 1 bytes an element, as the plain row quantiser is.
+template <int TOP>
+__global__ void __launch_bounds__(1024)
+row_top_quant_kernel(RowArgs a, int segs, int groups_per_wg, int low) {
+    constexpr int NR = 1 << TOP, VPL = 16;
+    __shared__ float s_amax[16][NR];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int seg = wave % segs, local = wave / segs;
+    const int64_t g = (int64_t)blockIdx.x * groups_per_wg + local;
+    const bool ok = g < (a.rows >> TOP);
+    const int64_t row0 = ((g >> low) << (low + TOP)) + (g & ((int64_t(1) << low) - 1));
+    const int64_t kbase = (int64_t)seg * 1024 + lane * 4;
+    const bool fast = ok && (int64_t)(seg + 1) * 1024 <= a.cols;
+    float v[NR][VPL];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) {
+        const float* src = reinterpret_cast<const float*>(a.in) + (row0 + ((int64_t)n << low)) * a.ld_in + kbase;
+        if (fast) {
+#pragma unroll
+            for (int c = 0; c < VPL; c += 4) {
+                const float4 q = *reinterpret_cast<const float4*>(src + c * 64);
+                v[n][c] = q.x; v[n][c + 1] = q.y; v[n][c + 2] = q.z; v[n][c + 3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < VPL; ++c) {
+                const int k = (c >> 2) * 256 + (c & 3);
+                v[n][c] = ok && kbase + k < a.cols ? src[k] : 0.0f;
+            }
+        }
+    }
+#pragma unroll
+    for (int h = 1; h < NR; h <<= 1)
+#pragma unroll
+        for (int n = 0; n < NR; ++n)
+            if ((n & h) == 0) {
+#pragma unroll
+                for (int c = 0; c < VPL; ++c) {
+                    const float x = v[n][c], y = v[n | h][c];
+                    v[n][c] = x + y;
+                    v[n | h][c] = x - y;
+                }
+            }
+#pragma unroll
+    for (int n = 0; n < NR; ++n)
+#pragma unroll
+        for (int c = 0; c < VPL; ++c) v[n][c] *= a.in_mul;
+    if (a.fold) {
+#pragma unroll
+        for (int c = 0; c < VPL; ++c) {
+            const int64_t k = kbase + (c >> 2) * 256 + (c & 3);
+            const float f = fast || k < a.cols ? a.fold[k] : 1.0f;
+#pragma unroll
+            for (int n = 0; n < NR; ++n) v[n][c] *= f;
+        }
+    }
+    const int bperm_addr = (lane ^ 32) << 2;
+    float amax[NR];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) {
+        float m0 = 0.0f, m1 = 0.0f;
+#pragma unroll
+        for (int c = 0; c < VPL; c += 4) {
+            asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m0) : "v"(v[n][c]), "v"(v[n][c + 1]));
+            asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m1) : "v"(v[n][c + 2]), "v"(v[n][c + 3]));
+        }
+        amax[n] = wave_max(__builtin_fmaxf(m0, m1), bperm_addr);
+    }
+    if (segs > 1) {
+        if (lane == 0) {
+#pragma unroll
+            for (int n = 0; n < NR; ++n) s_amax[wave][n] = amax[n];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
+            amax[n] = s_amax[local * segs][n];
+            for (int i = 1; i < segs; ++i) amax[n] = fmaxf(amax[n], s_amax[local * segs + i][n]);
+        }
+    }
+    RowCtx x;
+    x.lane = lane; x.bperm_addr = bperm_addr; x.wave = wave; x.seg = seg; x.xbuf = nullptr;
+    x.kbase = kbase; x.row_ok = ok;
+#pragma unroll
+    for (int n = 0; n < NR; ++n) {
+        const bool nz = amax[n] > 0.0f;
+        const float inv = nz ? 127.0f / amax[n] : 0.0f;
+        x.row = row0 + ((int64_t)n << low);
+        if (ok && seg == 0 && lane == 0) a.out_scale[x.row] = nz ? amax[n] / 127.0f : 1.0f;
+        if (fast) row_phase2<10, IN_F32, OUT_Q8, true>(a, x, v[n], inv);
+        else row_phase2<10, IN_F32, OUT_Q8, false>(a, x, v[n], inv);
+    }
+}
+
 }  // namespace
+
+hipError_t launch_row_top_quant(const RowArgs& a, int low, hipStream_t s) {
+    if (a.rows == 0 || a.cols == 0) return hipSuccess;
+    if (!row_top_quant_ok(a.cols, a.left_top) || a.log_block != 0 || a.kron_m != 0 || a.rows2 != 0 || low < 0 ||
+        a.rows % (int64_t(1) << (low + a.left_top)) != 0)
+        return hipErrorInvalidValue;
+    const int segs = (int)((a.cols + 1023) >> 10), groups_per_wg = segs >= 4 ? 1 : 4 / segs;
+    const int64_t groups = a.rows >> a.left_top, blocks = (groups + groups_per_wg - 1) / groups_per_wg;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    auto* kern = a.left_top == 1 ? row_top_quant_kernel<1> : row_top_quant_kernel<2>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * segs * groups_per_wg), 0, s, a, segs, groups_per_wg, low);
+    return hipGetLastError();
+}
 
 hipError_t launch_row_left_top(const RowArgs& a, OutKind out, hipStream_t s) {
     if (a.kron_m != 0 || a.fold || a.rows2 != 0 || !row_left_top_ok(a.rows, a.cols, a.log_block, a.left_top))

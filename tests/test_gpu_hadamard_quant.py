@@ -107,6 +107,28 @@ def test_left_hadamard_fold_row_quant_bit_exact(rows, cols, hbl):
     gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
 
 
+# The left-hand rotation's first pass (blocks of 128 .. 2048 rows, 32 columns a workgroup) and what follows it: one or two top
+# strides in the row quantiser, or strided passes (more of them, or rows too long); several blocks, column counts off the
+# tile, rows further apart than they are long, fp32 input.
+@pytest.mark.parametrize("rows,cols,hbl", [(384, 36, 128), (512, 100, 256), (1024, 4, 512), (3072, 32, 1024), (4096, 68, 2048),
+                                           (8192, 1028, 4096), (16384, 24, 8192), (16384, 40, 16384), (4096, 16400, 4096),
+                                           (65536, 16, 65536)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_left_rotation_block_sizes_and_edges(rows, cols, hbl, f32):
+    if f32 and cols > 10000:
+        pytest.skip("the bf16 case covers the row length")
+    e = inputs.make_errors(rows, cols, rows + cols)
+    real = orc.bf16_bits_to_real(e)
+    pad = torch.full((rows, cols + 8 + (-cols) % 8), 3.0, dtype=torch.float32 if f32 else torch.bfloat16, device=gu.DEV)
+    pad[:, :cols] = gu.to_dev(real) if f32 else gu.bits_to_dev(e)
+    fold = (np.abs(np.random.default_rng(2).standard_normal(cols)) * 1e-2 + 1e-4).astype(np.float32)
+    q = torch.full((rows, cols + 16 + (-cols) % 16), 99, dtype=torch.int8, device=gu.DEV)
+    _, s = binding.halo_hadamard_quant(pad[:, :cols], had_block_left=hbl, fold=gu.to_dev(fold), out_q=q[:, :cols])
+    wq, ws = oracle_row_quant(real, 0, hbl, fold)
+    gu.assert_codes_equal(q[:, :cols], wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
+    assert bool((q[:, cols:] == 99).all())
+
+
 COLT_CASES = [(256, 384), (128, 128), (130, 200), (2048, 1024), (16, 4096), (1000, 24)]
 
 
@@ -161,7 +183,8 @@ def test_quant_dual_matches_both_single_quantisers(rows, cols):
 
 
 UNROT_CASES = [(64, 512, 512, 0), (33, 4096, 4096, 0), (8, 14336, 2048, 0), (256, 1024, 1024, 256),
-               (4096, 256, 256, 4096), (50, 96, 0, 0), (2048, 512, 0, 2048)]
+               (4096, 256, 256, 4096), (50, 96, 0, 0), (2048, 512, 0, 2048), (384, 36, 0, 128), (2048, 100, 4, 1024),
+               (8192, 32, 32, 8192)]
 
 
 @pytest.mark.parametrize("rows,cols,hb,hbl", UNROT_CASES)

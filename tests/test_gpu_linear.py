@@ -120,6 +120,13 @@ def test_level2_output_side_variants(b, m, n, hm, hb, odt):
     run_and_check(b, m, n, 2, Xb, Wb, Eb, odt=odt, hm=hm, hb=hb)
 
 
+@pytest.mark.parametrize("b,n,hb", [(1920, 80, 128), (2112, 48, 64), (6144, 144, 2048), (8192, 16, 4096)])
+def test_level2_column_maxima_from_several_row_blocks(b, n, hb):
+    """The column quantiser takes its maxima from the partial ones of each row block of the left-hand rotation's first pass."""
+    Xb = inputs.make_activations(b, 256, 0.01, b); Wb = inputs.make_weights(n, 256, b); Eb = inputs.make_errors(b, n, b)
+    run_and_check(b, 256, n, 2, Xb, Wb, Eb, hb=hb)
+
+
 # tokens, in- and out-features, right and left block: the low left-hand strides run in the product's epilogue
 # (test_gemm_plan.py asserts that the rule says so), and every way the rest of the un-rotation can go is there.
 LEFT_IN_EPILOGUE = [
