@@ -8,20 +8,19 @@
 //   1. y_c = +-x_0 +- x_1 ... +- x_27 for each of the 28 columns c of H_28, a running sum in ascending index order, all in
 //      the thread's registers (the signs are compile-time constants, so this is straight-line add/sub code);
 //   2. the butterflies of H_{2^n} over i in ascending stride order: six stages across the lanes of a wavefront
-//      (i's low six bits are the lane), then n - 6 stages across the wavefronts of the workgroup through LDS;
+//      (i's low six bits are the lane's position), then n - 6 stages across the wavefronts of the workgroup through LDS;
 //   3. one multiply by 1/sqrt(28 * 2^n), then the optional per-column fold vector.
 // H_28 is built at compile time by Paley's second construction from the quadratic character modulo 13: with
 // Q[i][j] = chi(i - j) and the conference matrix C = [[0, 1^T], [1, Q]], every 0 of C becomes [[1, -1], [-1, -1]] and
 // every +-1 becomes +-[[1, 1], [1, -1]].  It is symmetric, so rotating and un-rotating are the same transform.
 //
-// The lane stages use x <- x + s * partner(x) with s = -1 in the lane holding the upper element: that lane then
-// carries the exact negation of the wanted difference, later stages pair elements with equal accumulated sign, and the
-// sign (parity of the lane number) is folded into the normalisation multiply.
+// The lane stages (wave_ops.h) leave a sign, parity of the lane's position, which is folded into the normalisation multiply.
 #pragma clang fp contract(off)
 
 #include <utility>
 
 #include "halo_internal.h"
+#include "wave_ops.h"
 
 namespace halo {
 namespace {
@@ -62,36 +61,6 @@ __device__ __forceinline__ void h28_mix(const float (&x)[kM], float (&y)[kM], st
     ((y[C] = h28_column<C>(x, std::make_integer_sequence<int, kM - 1>{})), ...);
 }
 
-template <int J>
-__device__ __forceinline__ float lane_xor(float x, int bperm_addr) {
-    const int xi = __float_as_int(x);
-    int r;
-    if constexpr (J == 0) {
-        r = __builtin_amdgcn_mov_dpp(xi, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-    } else if constexpr (J == 1) {
-        r = __builtin_amdgcn_mov_dpp(xi, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-    } else if constexpr (J == 2) {
-        r = __builtin_amdgcn_ds_swizzle(xi, 0x101F);              // bit mode: xor 4
-    } else if constexpr (J == 3) {
-        r = __builtin_amdgcn_mov_dpp(xi, 0x128, 0xF, 0xF, true);  // row_ror:8 == xor 8 inside a row of 16
-    } else if constexpr (J == 4) {
-        r = __builtin_amdgcn_ds_swizzle(xi, 0x401F);              // bit mode: xor 16
-    } else {
-        r = __builtin_amdgcn_ds_bpermute(bperm_addr, xi);         // lane ^ 32
-    }
-    return __int_as_float(r);
-}
-
-template <int J>
-__device__ __forceinline__ void stage_across_lanes(float (&v)[kM], int lane, int bperm_addr) {
-    const float s = ((lane >> J) & 1) ? -1.0f : 1.0f;
-#pragma unroll
-    for (int r = 0; r < kM; ++r) {
-        const float p = lane_xor<J>(v[r], bperm_addr);
-        v[r] = __builtin_fmaf(p, s, v[r]);      // the product is exact, so this is one rounded add or subtract
-    }
-}
-
 // LOGP: log2 of the Walsh-Hadamard factor (6 .. 9); a Hadamard block is 28 * 2^LOGP elements = 2^(LOGP-6) wavefronts.
 template <int IN, int OUT, int LOGP>
 __global__ void __launch_bounds__(512)
@@ -99,8 +68,8 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     __shared__ float s_amax[8];
     extern __shared__ float s_xbuf[];        // [wavefronts][28][64]: exchange buffer of the stages across wavefronts
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bperm_addr = (lane ^ 32) << 2;
+    const int wave = threadIdx.x >> 6, lane = position_of_lane(threadIdx.x & 63), tid = wave * 64 + lane;
+    const int bperm_addr = ((threadIdx.x & 63) ^ 32) << 2;
     unsigned block = blockIdx.x;
     if (block >= blocks1) {                  // the second matrix of a batched launch
         block -= blocks1;
@@ -152,12 +121,12 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     float v[kM];
     h28_mix(x, v, std::make_integer_sequence<int, kM>{});
 
-    stage_across_lanes<0>(v, lane, bperm_addr);
-    stage_across_lanes<1>(v, lane, bperm_addr);
-    stage_across_lanes<2>(v, lane, bperm_addr);
-    stage_across_lanes<3>(v, lane, bperm_addr);
-    stage_across_lanes<4>(v, lane, bperm_addr);
-    stage_across_lanes<5>(v, lane, bperm_addr);
+    stage_across_lanes<kM, 0>(v, lane, bperm_addr);
+    stage_across_lanes<kM, 1>(v, lane, bperm_addr);
+    stage_across_lanes<kM, 2>(v, lane, bperm_addr);
+    stage_across_lanes<kM, 3>(v, lane, bperm_addr);
+    stage_across_lanes<kM, 4>(v, lane, bperm_addr);
+    stage_across_lanes<kM, 5>(v, lane, bperm_addr);
 #pragma unroll
     for (int xs = 0; xs < LOGP - 6; ++xs) {
         // stride 2^(6+xs) of i pairs this wavefront with wavefront ^ 2^xs (same Hadamard block: blocks are aligned
@@ -166,13 +135,10 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
 #pragma unroll
         for (int j = 0; j < kM; ++j) s_xbuf[(wave * kM + j) * 64 + lane] = v[j];
         __syncthreads();
-        const bool upper = (wave >> xs) & 1;
+        const float sg = (wave >> xs) & 1 ? -1.0f : 1.0f;     // lower half a + b, upper half a - b, one exact product each
         const int pw = wave ^ (1 << xs);
 #pragma unroll
-        for (int j = 0; j < kM; ++j) {
-            const float p = s_xbuf[(pw * kM + j) * 64 + lane];
-            v[j] = upper ? p - v[j] : v[j] + p;
-        }
+        for (int j = 0; j < kM; ++j) v[j] = __builtin_fmaf(v[j], sg, s_xbuf[(pw * kM + j) * 64 + lane]);
     }
     const float c_l = (__builtin_popcount(lane) & 1) ? -c_norm : c_norm;
 #pragma unroll
@@ -191,12 +157,7 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
         float amax = 0.0f;
 #pragma unroll
         for (int j = 0; j < kM; j += 2) asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(amax) : "v"(v[j]), "v"(v[j + 1]));
-        amax = __builtin_fmaxf(amax, lane_xor<0>(amax, bperm_addr));
-        amax = __builtin_fmaxf(amax, lane_xor<1>(amax, bperm_addr));
-        amax = __builtin_fmaxf(amax, lane_xor<2>(amax, bperm_addr));
-        amax = __builtin_fmaxf(amax, lane_xor<3>(amax, bperm_addr));
-        amax = __builtin_fmaxf(amax, lane_xor<4>(amax, bperm_addr));
-        amax = __builtin_fmaxf(amax, lane_xor<5>(amax, bperm_addr));
+        amax = wave_max(amax, bperm_addr);
         const int waves = blockDim.x >> 6;
         if (waves > 1) {
             if (lane == 0) s_amax[wave] = amax;

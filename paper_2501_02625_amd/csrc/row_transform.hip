@@ -10,53 +10,19 @@
 //      the highest strides     in registers again,
 // i.e. in ascending stride order, every add/sub a separately rounded fp32 operation.
 //
-// Cross-lane stages use r = fma(partner, s, own) with s = +1 in the lane holding the lower element and
-// s = -1 in the other one.  The lower lane gets a+b exactly; the upper lane gets b-a = -(a-b), the exact
-// negation of the wanted difference (fp32 add/sub/fma with an exact product are sign-symmetric under
-// round-to-nearest-even).  Two elements that meet in a later butterfly always differ in one index bit
-// only, so they carry the same accumulated sign and every later stage is again exact up to that common
-// sign.  The sign of a lane, parity of (lane & mask-of-cross-lane-stages-run), is folded into the
-// 1/sqrt(d) factor at the end, which costs nothing.
+// Cross-lane stages: wave_ops.h.  They leave a sign, parity of (position & mask of the cross-lane stages run), which is folded
+// into the 1/sqrt(d) factor at the end and costs nothing.
 #pragma clang fp contract(off)
 
 #include <mutex>
 
 #include "halo_internal.h"
+#include "wave_ops.h"
 
 namespace halo {
 namespace {
 
 constexpr float kRoundMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds |x| < 2^22 to an integer, ties to even
-
-template <int J>
-__device__ __forceinline__ float lane_xor(float x, int bperm_addr) {
-    const int xi = __float_as_int(x);
-    int r;
-    if constexpr (J == 0) {
-        r = __builtin_amdgcn_mov_dpp(xi, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-    } else if constexpr (J == 1) {
-        r = __builtin_amdgcn_mov_dpp(xi, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-    } else if constexpr (J == 2) {
-        r = __builtin_amdgcn_ds_swizzle(xi, 0x101F);              // bit mode: xor 4
-    } else if constexpr (J == 3) {
-        r = __builtin_amdgcn_mov_dpp(xi, 0x128, 0xF, 0xF, true);  // row_ror:8 == xor 8 inside a row of 16
-    } else if constexpr (J == 4) {
-        r = __builtin_amdgcn_ds_swizzle(xi, 0x401F);              // bit mode: xor 16
-    } else {
-        r = __builtin_amdgcn_ds_bpermute(bperm_addr, xi);         // lane ^ 32
-    }
-    return __int_as_float(r);
-}
-
-__device__ __forceinline__ float wave_max(float x, int bperm_addr) {
-    x = fmaxf(x, lane_xor<0>(x, bperm_addr));
-    x = fmaxf(x, lane_xor<1>(x, bperm_addr));
-    x = fmaxf(x, lane_xor<2>(x, bperm_addr));
-    x = fmaxf(x, lane_xor<3>(x, bperm_addr));
-    x = fmaxf(x, lane_xor<4>(x, bperm_addr));
-    x = fmaxf(x, lane_xor<5>(x, bperm_addr));
-    return x;
-}
 
 template <int VPL, int RB>
 __device__ __forceinline__ void stage_in_regs(float (&v)[VPL]) {
@@ -67,45 +33,6 @@ __device__ __forceinline__ void stage_in_regs(float (&v)[VPL]) {
             const float a = v[r], b = v[r | H];
             v[r] = a + b;
             v[r | H] = a - b;
-        }
-    }
-}
-
-// Eight  x <- x + s * partner(x)  steps in one asm block: v_fmac_f32 with the partner read through DPP.  The
-// leading s_nop supplies the two wait states a DPP read needs after a VALU write of the same register, whatever
-// the compiler placed before the block; inside the block every register is read and written by one instruction.
-#define HALO_FMAC_DPP8(CTRL)                                                                                   \
-    asm volatile("s_nop 1\n\t"                                                                                 \
-                 "v_fmac_f32_dpp %0, %0, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %1, %1, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %2, %2, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %3, %3, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %4, %4, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %5, %5, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %6, %6, %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"                            \
-                 "v_fmac_f32_dpp %7, %7, %8 " CTRL " row_mask:0xf bank_mask:0xf"                                 \
-                 : "+v"(v[r]), "+v"(v[r + 1]), "+v"(v[r + 2]), "+v"(v[r + 3]), "+v"(v[r + 4]), "+v"(v[r + 5]),   \
-                   "+v"(v[r + 6]), "+v"(v[r + 7])                                                               \
-                 : "v"(s))
-
-template <int VPL, int J>
-__device__ __forceinline__ void stage_across_lanes(float (&v)[VPL], int lane, int bperm_addr) {
-    static_assert(VPL % 8 == 0, "values per lane come in chunks of eight");
-    const float s = ((lane >> J) & 1) ? -1.0f : 1.0f;
-    if constexpr (J == 0) {
-#pragma unroll
-        for (int r = 0; r < VPL; r += 8) HALO_FMAC_DPP8("quad_perm:[1,0,3,2]");
-    } else if constexpr (J == 1) {
-#pragma unroll
-        for (int r = 0; r < VPL; r += 8) HALO_FMAC_DPP8("quad_perm:[2,3,0,1]");
-    } else if constexpr (J == 3) {
-#pragma unroll
-        for (int r = 0; r < VPL; r += 8) HALO_FMAC_DPP8("row_ror:8");
-    } else {
-#pragma unroll
-        for (int r = 0; r < VPL; ++r) {
-            const float p = lane_xor<J>(v[r], bperm_addr);
-            v[r] = __builtin_fmaf(p, s, v[r]);
         }
     }
 }
@@ -138,7 +65,7 @@ struct FwhtStages<VPL, LOGE, LOGSEG, LOGSEG> {
 
 // Per-wave geometry shared by the phases of the kernel.
 struct RowCtx {
-    int lane, bperm_addr;
+    int lane, bperm_addr;   // lane: the lane's position in the element order (wave_ops.h)
     int wave, seg;          // wavefront in the workgroup; segment of the row it owns
     float* xbuf;            // LDS exchange buffer [waves][values per lane][64] (only with cross-wave stages)
     int64_t row, kbase;     // kbase: first element of this lane's chunk 0
@@ -228,13 +155,10 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
 #pragma unroll
                 for (int r = 0; r < VPL; ++r) x.xbuf[(x.wave * VPL + r) * 64 + x.lane] = v[r];
                 __syncthreads();
-                const bool upper = (x.seg >> xs) & 1;
+                const float sg = (x.seg >> xs) & 1 ? -1.0f : 1.0f;
                 const int pw = x.wave ^ (1 << xs);
 #pragma unroll
-                for (int r = 0; r < VPL; ++r) {
-                    const float p = x.xbuf[(pw * VPL + r) * 64 + x.lane];
-                    v[r] = upper ? p - v[r] : v[r] + p;
-                }
+                for (int r = 0; r < VPL; ++r) v[r] = __builtin_fmaf(v[r], sg, x.xbuf[(pw * VPL + r) * 64 + x.lane]);
             }
         }
         // lanes whose (lane & mask) has odd parity hold negated values: the sign rides on the 1/sqrt(d) multiply
@@ -354,7 +278,7 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
             }
             const uint32_t w0 = code[0] | (code[1] << 6) | (code[2] << 12) | (code[3] << 18) | (code[4] << 24) | (code[5] << 30);
             const uint32_t w1 = (code[5] >> 2) | (code[6] << 4) | (code[7] << 10);
-            const uint32_t nb_w0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)w0, 0xF9, 0xF, 0xF, true);   // quad_perm [1,2,3,3]
+            const uint32_t nb_w0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)w0, 0xB1, 0xF, 0xF, true);   // of position ^ 1 (j even: j + 1)
             if (FAST || (x.row_ok && k0 + EPL <= a.cols)) {
                 unsigned char* blk = orow + (k0 >> 5) * 24;          // k0 >> 5 is the same for the four lanes of the quad
                 if ((j & 1) == 0) {
@@ -407,10 +331,16 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
     }
 }
 
+// Wavefronts that a SIMD should hold: the bf16 kernels on long segments would take a few registers more than four (six) of
+// them leave, for their guarded path.  8192 x 14336 in blocks of 2048: 88 -> 79 us; 8192 x 4096 in blocks of 4096: 30.9 -> 28.5.
+constexpr int waves_per_simd(int logseg, int in, int lb) {
+    return in == IN_BF16 && lb == logseg ? (logseg == 12 ? 4 : logseg == 11 ? 6 : 1) : 1;
+}
+
 // LB: log2 of the Hadamard block when it is 0 (no rotation) or LOGSEG (block = segment); -1 = read it at run time.
 // XS: number of butterfly stages that span wavefronts (Hadamard block = 2^(LOGSEG+XS) elements = 2^XS segments).
 template <int LOGSEG, int IN, int OUT, int LB, int XS = 0>
-__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024)
+__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024, waves_per_simd(LOGSEG, IN, LB))
 row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigned blocks1) {
     constexpr int LOGE = (IN == IN_BF16) ? 3 : 2;
     constexpr int EPL = 1 << LOGE;            // consecutive elements per lane per chunk
@@ -427,8 +357,8 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     x.wave = wave;
     x.seg = seg;
     x.xbuf = s_xbuf;
-    x.lane = threadIdx.x & 63;
-    x.bperm_addr = (x.lane ^ 32) << 2;
+    x.lane = position_of_lane(threadIdx.x & 63);
+    x.bperm_addr = ((threadIdx.x & 63) ^ 32) << 2;
     unsigned block = blockIdx.x;
     if (block >= blocks1) {          // the second matrix of a batched launch
         block -= blocks1;
@@ -556,7 +486,7 @@ row_left_top_kernel(RowArgs a, int segs, float c_norm) {
     static_assert(TOP <= 5 && (TOP < 5 || LOGSEG <= 11), "32 rows of 4096 columns do not fit a compute unit");
     extern __shared__ __align__(16) float s_exch[];        // exchange buffer of the stages across wavefronts
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = position_of_lane(threadIdx.x & 63), wave = threadIdx.x >> 6;
     const int64_t g = (int64_t)blockIdx.x / segs;                 // group of 2^TOP rows: g = blk * 256 + q
     const int seg = (int)((int64_t)blockIdx.x % segs);
     const int64_t row0 = ((g >> 8) << (8 + TOP)) + ((int64_t)wave << 8) + (g & 255);
@@ -579,7 +509,7 @@ row_left_top_kernel(RowArgs a, int segs, float c_norm) {
     bool first_round = true;
 #pragma unroll
     for (int st = 0; st < XT; ++st) {
-        const bool upper = (wave >> st) & 1;
+        const float sg = (wave >> st) & 1 ? -1.0f : 1.0f;      // lower row a + b, upper row a - b, one exact product each
         const int pw = wave ^ (1 << st);
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
@@ -595,10 +525,10 @@ row_left_top_kernel(RowArgs a, int segs, float c_norm) {
 #pragma unroll
                 for (int r = 0; r < HALF; r += 4) {
                     const float4 p = xb[(pw * (HALF / 4) + r / 4) * 64 + lane];
-                    v[n][h0 + r + 0] = upper ? p.x - v[n][h0 + r + 0] : v[n][h0 + r + 0] + p.x;
-                    v[n][h0 + r + 1] = upper ? p.y - v[n][h0 + r + 1] : v[n][h0 + r + 1] + p.y;
-                    v[n][h0 + r + 2] = upper ? p.z - v[n][h0 + r + 2] : v[n][h0 + r + 2] + p.z;
-                    v[n][h0 + r + 3] = upper ? p.w - v[n][h0 + r + 3] : v[n][h0 + r + 3] + p.w;
+                    v[n][h0 + r + 0] = __builtin_fmaf(v[n][h0 + r + 0], sg, p.x);
+                    v[n][h0 + r + 1] = __builtin_fmaf(v[n][h0 + r + 1], sg, p.y);
+                    v[n][h0 + r + 2] = __builtin_fmaf(v[n][h0 + r + 2], sg, p.z);
+                    v[n][h0 + r + 3] = __builtin_fmaf(v[n][h0 + r + 3], sg, p.w);
                 }
             }
         }
@@ -611,7 +541,7 @@ row_left_top_kernel(RowArgs a, int segs, float c_norm) {
             v[NR - 1][r] = x - y;
         }
     }
-    const int bperm_addr = (lane ^ 32) << 2;
+    const int bperm_addr = ((threadIdx.x & 63) ^ 32) << 2;
     const float c_l = (__builtin_popcount(lane) & 1) ? -c_norm : c_norm;     // the sign the lane stages leave behind
 #pragma unroll
     for (int n = 0; n < NR; ++n) {
