@@ -911,21 +911,24 @@ gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, 
 // w takes the units w, w + 4, ...  Each has an LDS ring of its own (three stages of A and B, filled and laid out as in the
 // main kernel), so there is no barrier in the loop and three units are in flight per wavefront from the start.  The four
 // partial sums meet in LDS at the end, where every thread also picks up consecutive columns for the store.
-// TM = 1 is for at most 16 rows (decode).  choose_config has the figures.
-template <int TM, bool TRANSB>
+// TM = 1 is for at most 16 rows (decode).  Tiles of 16 or 32 columns are for products whose 64-column tiles would leave compute
+// units idle: there the rate at which the K-contiguous B arrives is the bound, and every compute unit has to fetch (launch_small_by_columns).
+template <int TM, int TN_, bool TRANSB>
 struct SmallCfg {
-    static constexpr int BM = 16 * TM, BN = 64, TN = 4, BK = 128, NS = TM == 4 ? 2 : 3, SPLIT = 4;
+    static constexpr int BM = 16 * TM, TN = TN_, BN = 16 * TN, BK = 128, SPLIT = 4;
     static constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = A_BYTES + B_BYTES;
     static constexpr int LA = A_BYTES / 1024, LB = B_BYTES / 1024, L = LA + LB;  // DMA instructions per stage
+    static constexpr int FIT = 150 / (SPLIT * L), NS = FIT > 8 ? 8 : FIT;        // ring stages: what LDS holds
     static constexpr int PITCH = BN + 4;                         // dwords per row of a partial sum
     static constexpr int RING_BYTES = SPLIT * NS * STAGE, SUM_BYTES = SPLIT * BM * PITCH * 4;
     static constexpr int LDS_BYTES = RING_BYTES > SUM_BYTES ? RING_BYTES : SUM_BYTES;
+    static_assert(TRANSB || TN == 4, "rows of a K-strided B are fetched 64 columns at a time");
 };
 
-template <int TM, bool TRANSB>
+template <int TM, int TN_, bool TRANSB>
 __global__ void __launch_bounds__(256)
 gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigned blocks1) {
-    using Cfg = SmallCfg<TM, TRANSB>;
+    using Cfg = SmallCfg<TM, TN_, TRANSB>;
     constexpr int TN = Cfg::TN, BK = Cfg::BK, LA = Cfg::LA, LB = Cfg::LB, NS = Cfg::NS;
     unsigned bid = blockIdx.x;
     if (bid >= blocks1) {                  // the second product of a paired launch
@@ -940,11 +943,11 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
     const uint32_t ring = (uint32_t)(uintptr_t)HALO_LDS_PTR(smem) + wave * NS * Cfg::STAGE;
 
     // ---- source offsets, as in main_loop, but every wavefront fetches the whole tile at its own K
-    using KMajor = KMajorRequests<Cfg::BN>;
+    using KMajor = KMajorRequests<64>;                           // K-strided B: 16 rows of 64 bytes per request
     const int64_t rows_a = a.M - m0, rows_b = a.N - n0, cols_b = KMajor::columns(a.N, n0);
     const int r8 = lane >> 3, k0 = 16 * ((lane & 7) ^ (r8 >> 1));
     const int kc[2] = {k0, k0 ^ 64};
-    const int krow = KMajor::first_row(0, lane, LB);             // K-strided B: 16 rows of 64 bytes per request
+    const int krow = KMajor::first_row(0, lane, LB);
     uint32_t avo[LA], bvo[LB];
 #pragma unroll
     for (int i = 0; i < LA; ++i)
@@ -998,7 +1001,7 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
         const int row = 16 * g4 + (l16 >> 1);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-            b_addr[j] = ring + Cfg::A_BYTES + row * Cfg::BN + 16 * (j ^ kmajor_swizzle<Cfg::BN>(row)) + 8 * (l16 & 1);
+            b_addr[j] = ring + Cfg::A_BYTES + row * Cfg::BN + 16 * (j ^ kmajor_swizzle<64>(row)) + 8 * (l16 & 1);
     }
     int slot = 0;
     for (int u = 0; u < units; ++u) {
@@ -1060,41 +1063,43 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
         for (int j = 0; j < TN; ++j)
             *reinterpret_cast<v4i*>(sums + (wave * Cfg::BM + 16 * i + l16) * Cfg::PITCH + 16 * j + 4 * g4) = acc[i][j];
     __syncthreads();
-    // ---- every thread: EPT consecutive columns of one row
-    constexpr int EPT = 4 * TM, TPR = Cfg::BN / EPT;
+    // ---- every thread: EPT consecutive columns of one row, VW at a time
+    constexpr int EPT = TM * TN, TPR = Cfg::BN / EPT, VW = EPT < 4 ? EPT : 4, NV = EPT / VW;
+    typedef int vi __attribute__((ext_vector_type(VW)));
     const int row_l = threadIdx.x / TPR, col_l = threadIdx.x % TPR * EPT;
-    v4i v[TM];
+    vi v[NV];
 #pragma unroll
-    for (int q = 0; q < TM; ++q) {
-        v[q] = (v4i){0, 0, 0, 0};
+    for (int q = 0; q < NV; ++q) {
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[q][e] = 0;
 #pragma unroll
         for (int w = 0; w < Cfg::SPLIT; ++w)
-            v[q] += *reinterpret_cast<const v4i*>(sums + (w * Cfg::BM + row_l) * Cfg::PITCH + col_l + 4 * q);
+            v[q] += *reinterpret_cast<const vi*>(sums + (w * Cfg::BM + row_l) * Cfg::PITCH + col_l + VW * q);
     }
     const int64_t row = m0 + row_l, col = n0 + col_l;
     if (row >= a.M || col >= a.N) return;
     const bool whole = col + EPT <= a.N;
-    auto store = [&](int32_t* dst, const v4i(&x)[TM]) {
+    auto store = [&](int32_t* dst, const vi(&x)[NV]) {
 #pragma unroll
-        for (int q = 0; q < TM; ++q) {
+        for (int q = 0; q < NV; ++q) {
             if (whole) {
-                *reinterpret_cast<v4i*>(dst + 4 * q) = x[q];
+                *reinterpret_cast<vi*>(dst + VW * q) = x[q];
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (col + 4 * q + e < a.N) dst[4 * q + e] = x[q][e];
+                for (int e = 0; e < VW; ++e)
+                    if (col + VW * q + e < a.N) dst[VW * q + e] = x[q][e];
             }
         }
     };
     if (a.acc_out) store(a.acc_out + row * a.ld_acc + col, v);
     if (!a.C) return;
     const float rs = a.row_scale ? a.row_scale[row] : 1.0f;
-    v4i f[TM];
+    vi f[NV];
 #pragma unroll
-    for (int q = 0; q < TM; ++q)
+    for (int q = 0; q < NV; ++q)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int64_t c = col + 4 * q + e;
+        for (int e = 0; e < VW; ++e) {
+            const int64_t c = col + VW * q + e;
             const float cs = a.col_scale ? a.col_scale[c < a.N ? c : a.N - 1] : 1.0f;
             f[q][e] = __float_as_int(((float)v[q][e] * rs) * cs);
         }
@@ -1104,15 +1109,19 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
     }
     uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + row * a.ldc + col;
 #pragma unroll
-    for (int q = 0; q < TM; ++q) {
-        const v2u w = {pack_bf16x2(__int_as_float(f[q][0]), __int_as_float(f[q][1])),
-                       pack_bf16x2(__int_as_float(f[q][2]), __int_as_float(f[q][3]))};
-        if (whole) {
-            *reinterpret_cast<v2u*>(dst + 4 * q) = w;
+    for (int q = 0; q < NV; ++q) {
+        uint32_t w[(VW + 1) / 2];
+#pragma unroll
+        for (int h = 0; h < VW / 2; ++h) w[h] = pack_bf16x2(__int_as_float(f[q][2 * h]), __int_as_float(f[q][2 * h + 1]));
+        if constexpr (VW == 1) w[0] = bf16_bits(__int_as_float(f[q][0]));
+        if (VW == 4 && whole) {
+            *reinterpret_cast<v2u*>(dst + 4 * q) = (v2u){w[0], w[(VW - 1) / 2]};
+        } else if (VW == 2 && whole) {
+            *reinterpret_cast<uint32_t*>(dst + 2 * q) = w[0];
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (col + 4 * q + e < a.N) dst[4 * q + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            for (int e = 0; e < VW; ++e)
+                if (col + VW * q + e < a.N) dst[VW * q + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
         }
     }
 }
@@ -1220,13 +1229,13 @@ hipError_t launch_tiles(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = n
     return hipGetLastError();
 }
 
-template <int TM, bool TRANSB>
+template <int TM, bool TRANSB, int TN = 4>
 hipError_t launch_small(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = nullptr) {
-    using Cfg = SmallCfg<TM, TRANSB>;
+    using Cfg = SmallCfg<TM, TN, TRANSB>;
     if (a.left_stages != 0 || a.lr_rank != 0 || (a2 && (a2->left_stages != 0 || a2->lr_rank != 0))) return hipErrorInvalidValue;
     static std::once_flag once;
     static hipError_t attr_result = hipSuccess;
-    auto kern = gemm_i8_small_kernel<TM, TRANSB>;
+    auto kern = gemm_i8_small_kernel<TM, TN, TRANSB>;
     hipError_t e = raise_lds_limit(kern, Cfg::LDS_BYTES, &once, &attr_result);
     if (e != hipSuccess) return e;
     auto tiles = [](int64_t n, int t) { return (n + t - 1) / t; };
@@ -1236,6 +1245,18 @@ hipError_t launch_small(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = n
     hipLaunchKernelGGL(kern, dim3((unsigned)(b1 + b2)), dim3(256), Cfg::LDS_BYTES, s, a, (int)tiles(a.N, Cfg::BN), a2 ? *a2 : a,
                        (int)(a2 ? tiles(a2->N, Cfg::BN) : 1), (unsigned)b1);
     return hipGetLastError();
+}
+
+// Narrower tiles while all of them still run at once, one per compute unit: with B from memory (not the
+// caches), 64 columns and three ring stages against the narrow tile and up to eight: 16 x 4096 x 4096 9.8 -> 7.1 us, 16 x 4096 x
+// 14336 24.9 -> 13.7, 32 x 4096 x 4096 11.3 -> 8.0, 16 x 8192 x 4096 11.1 -> 10.3, 128 x 512 x 512 4.0 -> 3.2.
+template <int TM, bool TRANSB>
+hipError_t launch_small_by_columns(const GemmArgs& a, hipStream_t s) {
+    if constexpr (TRANSB) {
+        if (tiles_of(a, 16 * TM, 16) <= kComputeUnits) return launch_small<TM, true, 1>(a, s);
+        if (tiles_of(a, 16 * TM, 32) <= kComputeUnits) return launch_small<TM, true, 2>(a, s);
+    }
+    return launch_small<TM, TRANSB>(a, s);
 }
 
 inline bool tiles_can_run(const GemmArgs& a) {
@@ -1263,7 +1284,7 @@ hipError_t launch_by_shape(const GemmArgs& a, hipStream_t s) {
         case 3:
         case 4: return launch_tiles<4, 4, TRANSB>(a, s);
         case kSmall64: return launch_small<4, TRANSB>(a, s);
-        case kSmall32: return a.M <= 16 ? launch_small<1, TRANSB>(a, s) : launch_small<2, TRANSB>(a, s);
+        case kSmall32: return a.M <= 16 ? launch_small_by_columns<1, TRANSB>(a, s) : launch_small_by_columns<2, TRANSB>(a, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -120,6 +120,28 @@ def test_small_products(M, N, K, trans_b):
         gu.assert_codes_equal(acc2, orc.gemm_codes(b[:, :N // 16 * 16], g[:N // 16 * 16]), "accumulators, second of a pair")
 
 
+# The small kernel's tiles of 16, 32 and 64 columns (as many as run at once), with ragged rows and columns, K shorter than the
+# ring and longer than one trip through it, every output.
+@pytest.mark.parametrize("M,N", [(1, 16), (16, 4090), (16, 4104), (13, 8200), (17, 2040), (32, 4088), (32, 4104), (100, 500)])
+@pytest.mark.parametrize("K", [16, 656, 4368])
+def test_small_products_narrow_tiles(M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    a = rand_codes(rng, (M, K)); b = rand_codes(rng, (N, K))
+    rs = rng.uniform(1e-3, 1e-2, M).astype(np.float32); cs = rng.uniform(1e-3, 1e-2, N).astype(np.float32)
+    ad, bd = gu.to_dev(a), gu.to_dev(b)
+    want = orc.gemm_codes(a, b.T)
+    pitch = (N + 7) // 8 * 8 + 16
+    acc = torch.full((M + 1, pitch), -7, dtype=torch.int32, device=gu.DEV)
+    binding.halo_gemm_i8_desc(binding.gemm_desc(ad, bd, trans_b=True, acc_out=acc[:M, :N]))
+    gu.assert_codes_equal(acc[:M, :N], want, "accumulators")
+    assert bool((acc[M:] == -7).all()) and bool((acc[:, N:] == -7).all())
+    for dtype, check in ((torch.float32, gu.assert_f32_identical), (torch.bfloat16, gu.assert_bf16_within_one_ulp)):
+        out = torch.full((M + 1, pitch), -7.0, dtype=dtype, device=gu.DEV)
+        binding.halo_gemm_i8(ad, bd, trans_b=True, row_scale=gu.to_dev(rs), col_scale=gu.to_dev(cs), out=out[:M, :N])
+        check(out[:M, :N], orc.dequantize(want, rs, cs), "scaled output")
+        assert bool((out[M:] == -7).all()) and bool((out[:, N:] == -7).all())
+
+
 # Every tile configuration on shapes its K step divides (ragged M and N, several trips through the ring), through
 # halo_gemm_i8_desc: the configurations differ in speed only.
 @pytest.mark.parametrize("name", sorted(binding.HALO_GEMM_CONFIGS))
