@@ -155,7 +155,7 @@ col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_
 // the two halves of the wavefront and v_permlane32_swap_b32 brings a pair together in one lane (one instruction for two values;
 // both results stay where they are, only the row that a register stands for changes).
 // A strided pass takes six stages (col_fwht_kernel), so blocks of 128 to 2048 rows save a round trip of the fp32 intermediate.
-// What bounds it: memory, 2 + 4 bytes an element.  64 values per thread and a 64 KB exchange buffer (one of the two columns at
+// What bounds it: memory, 2 + 4 bytes an element (4096 x 4096: 24 us, 4.1 TB/s; two strided passes took 22 + 22).  64 values per thread and a 64 KB exchange buffer (one of the two columns at
 // a time), so that two workgroups of 1024 rows share a compute unit: one loads or stores while the other exchanges.
 // Neighbouring column tiles, which share cache lines of a bf16 row, run on the same XCD at the same time.
 // SIDE (bf16 input): the pass also writes, per column, the largest |in[r, k] * row_scale[r]| of its rows to
@@ -891,27 +891,24 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0 || a.log_block == 0) return hipSuccess;
     if (a.first_stage < 0 || a.first_stage > a.log_block) return hipErrorInvalidValue;
     const float c = a.skip_norm ? 1.0f : (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block)));
-    // The lowest stages in one pass over blocks of rows where the block has more than the six stages of a strided pass (or
-    // its side output is wanted); the other stages in strided passes of at most six, a last one of up to seven.
-    const int low = col_block_stages(a.log_block);
-    const bool blocks = a.first_stage == 0 && low >= (a.side_part ? 6 : 7) && a.cols % 2 == 0 && a.ld_in % 2 == 0 &&
-                        a.ld_out % 2 == 0 && a.ld_tmp % 2 == 0 && std::max(a.ld_in, std::max(a.ld_out, a.ld_tmp)) <= (int64_t(1) << 18);
-    if (a.side_part && (!blocks || a.in_kind != IN_BF16)) return hipErrorInvalidValue;
+    // The lowest stages in one pass over blocks of rows where the block has more than the six stages of a strided pass (or the
+    // caller asks for it); the other stages in strided passes of at most six, a last one of up to seven.
+    const int low = a.only_low ? a.only_low : std::min(a.log_block, kColBlockStages);
+    const bool blocks = a.first_stage == 0 && low >= (a.only_low ? 6 : 7) && low <= std::min(a.log_block, kColBlockStages) &&
+                        a.cols % 2 == 0 && a.ld_in % 2 == 0 && a.ld_out % 2 == 0 && a.ld_tmp % 2 == 0 &&
+                        std::max(a.ld_in, std::max(a.ld_out, a.ld_tmp)) <= (int64_t(1) << 18);
+    if ((a.only_low && !blocks) || (a.side_part && (!a.only_low || a.in_kind != IN_BF16))) return hipErrorInvalidValue;
     int sizes[8], np = 0, left = a.log_block - a.first_stage;
     if (left == 0) return (a.in == a.out && a.skip_norm) ? hipSuccess : hipErrorInvalidValue;   // nothing left to do in place
     if (blocks) {
         sizes[np++] = low;
-        left -= low;
+        left = a.only_low ? 0 : left - low;
     }
     while (left > 0) {
         int q = left <= 6 ? left : (left == 7 && np > 0 ? 7 : 6);
         sizes[np++] = q;
         left -= q;
         if (np >= 8) return hipErrorInvalidValue;
-    }
-    if (a.top_left > 0) {                  // the caller runs the strides above the first pass himself
-        if (!blocks || a.top_left != a.log_block - low) return hipErrorInvalidValue;
-        np = 1;
     }
     int p = a.first_stage;
     for (int i = 0; i < np; ++i) {
@@ -921,7 +918,7 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
         const InKind ik = first ? a.in_kind : IN_F32;
         void* dst = last ? a.out : (void*)a.tmp;
         const int64_t ld_dst = last ? a.ld_out : a.ld_tmp;
-        const float cf = last && a.top_left == 0 ? c : 1.0f;
+        const float cf = last ? c : 1.0f;
         hipError_t e;
         if (first && blocks) {
             float* d = reinterpret_cast<float*>(dst);

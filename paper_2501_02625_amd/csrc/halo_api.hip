@@ -132,23 +132,43 @@ hipError_t finish_left_unrotation(float* t, int64_t b, int64_t m, int32_t hb, in
     return launch_row_transform(r, IN_F32, ok, s);
 }
 
+// Stages of the left-hand rotation's first pass, and so the number of top strides that the row quantiser behind it runs: as
+// many as the pass takes, but one or two fewer where its workgroups (2048 rows of 32 columns at most) would not fill the chip
+// and the row quantiser takes the others.  With the rule
+// and without, rows x cols of one block: 2048 x 4096 24.5 us against 28.0, 2048 x 1024 12.7 / 19.7, 4096 x 1024 18.4 / 23.0, 1024 x
+// 4096 16.4 / 17.9, 512 x 4096 11.2 / 11.9; blocks of 256 rows are left whole (256 x 512: 2 us
+// slower in two parts; 256 x 4096 no faster).
+int left_pass_stages(int log_left, int64_t rows, int64_t cols, bool row_rotation) {
+    int low = log_left < kColBlockStages ? log_left : kColBlockStages;
+    auto tiles = [&](int l) { return (cols + 31) / 32 * (rows >> l); };
+    while (!row_rotation && low > 8 && tiles(low) < kComputeUnits && row_top_quant_ok(cols, log_left - low + 1)) --low;
+    return low;
+}
+
 // (H_left in) (x) fold, quantised per row: the left-hand rotation into the fp32 scratch tmp [rows x cols], then the row quantiser
-// (with a right-hand rotation if r asks for one).  r: rows, cols, fold, out, ld_out, out_scale and the right-hand block.  The
-// strides above the rotation's first pass run in the row quantiser where it takes them, else in passes of their own.
-// side_part (may be null): as in ColFwhtArgs.
+// (with a right-hand rotation if r asks for one).  r: rows, cols, fold, out, ld_out, out_scale and the right-hand block.
+// side_part (may be null): as in ColFwhtArgs; `parts` receives the number of its vectors.
 hipError_t left_rotate_quant(const void* in, InKind ik, int64_t ld_in, float* tmp, int log_left, RowArgs r, const float* side_fold,
-                             float* side_part, hipStream_t s) {
+                             float* side_part, int* parts, hipStream_t s) {
     ColFwhtArgs c{in, ik, ld_in, tmp, r.cols, tmp, r.cols, r.rows, r.cols, log_left};
-    c.side_fold = side_fold; c.side_part = side_part;
-    const int low = col_block_stages(log_left), top = log_left - low;
     r.in = tmp; r.ld_in = r.cols;
-    if (r.log_block == 0 && r.kron_m == 0 && row_top_quant_ok(r.cols, top) && r.cols % 4 == 0 && ld_in % 2 == 0 && ld_in <= (int64_t(1) << 18)) {
-        c.top_left = top; c.skip_norm = 1;
-        const hipError_t e = launch_col_fwht(c, s);
+    const bool row_rotation = r.log_block != 0 || r.kron_m != 0;
+    const int low = left_pass_stages(log_left, r.rows, r.cols, row_rotation), top = log_left - low;
+    const bool in_quantiser = !row_rotation && row_top_quant_ok(r.cols, top) && ld_in <= (int64_t(1) << 18);
+    if (side_part || in_quantiser) {
+        c.only_low = low; c.side_fold = side_fold; c.side_part = side_part;
+        c.skip_norm = top != 0;
+        hipError_t e = launch_col_fwht(c, s);
         if (e != hipSuccess) return e;
-        r.left_top = top;
-        r.in_mul = (float)(1.0 / sqrt((double)(int64_t(1) << log_left)));
-        return launch_row_top_quant(r, low, s);
+        if (parts) *parts = (int)(r.rows >> low);
+        if (in_quantiser) {
+            r.left_top = top;
+            r.in_mul = (float)(1.0 / sqrt((double)(int64_t(1) << log_left)));
+            return launch_row_top_quant(r, low, s);
+        }
+        if (top == 0) return launch_row_transform(r, IN_F32, OUT_Q8, s);
+        c = ColFwhtArgs{tmp, IN_F32, r.cols, tmp, r.cols, tmp, r.cols, r.rows, r.cols, log_left};
+        c.first_stage = low;
     }
     const hipError_t e = launch_col_fwht(c, s);
     return e != hipSuccess ? e : launch_row_transform(r, IN_F32, OUT_Q8, s);
@@ -261,7 +281,7 @@ halo_status halo_hadamard_quant(const void* in, halo_dtype in_dt, int64_t rows, 
     if ((cols * 4) % 16) return HALO_EALIGN;   // scratch rows must stay 16-byte aligned
     float* tmp = reinterpret_cast<float*>(workspace);
     return from_hip(left_rotate_quant(in, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, ld_in, tmp, ilog2_exact(had_block_left), r, nullptr,
-                                      nullptr, s));
+                                      nullptr, nullptr, s));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -718,9 +738,10 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
         if (side) {
             RowArgs r{};
             r.rows = b; r.cols = n; r.fold = s_w; r.out = Eq; r.ld_out = n; r.out_scale = s_e;
-            if (left_rotate_quant(E, IN_BF16, n, f32, ilog2_exact(hb), r, s_x, amax, hs) != hipSuccess) return HALO_EHIP;
+            int parts = 0;
+            if (left_rotate_quant(E, IN_BF16, n, f32, ilog2_exact(hb), r, s_x, amax, &parts, hs) != hipSuccess) return HALO_EHIP;
             ColQuantArgs q{E, n, b, n, s_x, EqT, b, s_g, amax};
-            if (launch_col_quant_t_ready(q, (int)(b >> col_block_stages(ilog2_exact(hb))), hs) != hipSuccess) return HALO_EHIP;
+            if (launch_col_quant_t_ready(q, parts, hs) != hipSuccess) return HALO_EHIP;
         } else {
             if (EX) {
                 st = halo_hadamard_quant(E, HALO_BF16, b, n, n, HALO_QUANT_ROWS, 0, level >= 2 ? hb : 0, s_w, Eq, n, s_e, f32,

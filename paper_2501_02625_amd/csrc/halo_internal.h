@@ -85,16 +85,15 @@ struct ColFwhtArgs {
     const float* post_scale;
     int first_stage;
     int skip_norm;
-    // side_part != null (bf16 input, log_block >= 6, first_stage 0): the first pass also writes, per column and block of
-    // 2^col_block_stages(log_block) rows, the absolute maximum of in[r, k] * side_fold[r] (side_fold may be null) to
-    // side_part[rows >> col_block_stages(log_block)][cols].
+    // only_low > 0 (6 .. 11, first_stage 0): the strides below 2^only_low, in one pass; the caller runs the others.
+    int only_low;
+    // side_part != null (bf16 input, only_low > 0): the pass also writes, per column and block of 2^only_low rows, the absolute
+    // maximum of in[r, k] * side_fold[r] (side_fold may be null) to side_part[rows >> only_low][cols].
     const float* side_fold;
     float* side_part;
-    // top_left > 0 (log_block - col_block_stages(log_block), with skip_norm): only the first pass; the caller runs the top strides.
-    int top_left;
 };
-// Stages that the first pass over a block of 2^log_block rows takes, from stride 1 on.
-inline int col_block_stages(int log_block) { return log_block < 11 ? log_block : 11; }
+// Stages, from stride 1 on, that one pass over blocks of rows takes at most.
+constexpr int kColBlockStages = 11;
 hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s);
 
 // ---- column-wise absmax quantiser with transposed output (E^T)_Q ----

@@ -609,7 +609,9 @@ hipError_t launch_left_top_by_seg(const RowArgs& a, hipStream_t s) {
 
 // The row quantiser behind the top TOP strides of a left-hand rotation (halo_internal.h): a wavefront holds the same 1024
 // columns of the 2^TOP rows that those strides combine, so the strides are adds in registers, and the fp32 intermediate is
-// not written and read once more for them.  Bound by memory, 4 + 1 bytes an element, as the plain row quantiser is.
+// not written and read once more for them.  Bound by memory, 4 + 1 bytes an element, as the plain row quantiser is;
+// every load, the fold vector's too, is requested under one branch (4096 x 4096: with a branch per row and fold element by element
+// 20.5 us, so 16).
 template <int TOP>
 __global__ void __launch_bounds__(1024)
 row_top_quant_kernel(RowArgs a, int segs, int groups_per_wg, int low) {
@@ -622,22 +624,32 @@ row_top_quant_kernel(RowArgs a, int segs, int groups_per_wg, int low) {
     const int64_t row0 = ((g >> low) << (low + TOP)) + (g & ((int64_t(1) << low) - 1));
     const int64_t kbase = (int64_t)seg * 1024 + lane * 4;
     const bool fast = ok && (int64_t)(seg + 1) * 1024 <= a.cols;
-    float v[NR][VPL];
+    float v[NR][VPL], f[VPL];
+    const float* const src = reinterpret_cast<const float*>(a.in) + row0 * a.ld_in + kbase;
+    const int64_t next = a.ld_in << low;
+    if (fast) {                            // one branch around all loads
 #pragma unroll
-    for (int n = 0; n < NR; ++n) {
-        const float* src = reinterpret_cast<const float*>(a.in) + (row0 + ((int64_t)n << low)) * a.ld_in + kbase;
-        if (fast) {
+        for (int n = 0; n < NR; ++n)
 #pragma unroll
             for (int c = 0; c < VPL; c += 4) {
-                const float4 q = *reinterpret_cast<const float4*>(src + c * 64);
+                const float4 q = *reinterpret_cast<const float4*>(src + n * next + c * 64);
                 v[n][c] = q.x; v[n][c + 1] = q.y; v[n][c + 2] = q.z; v[n][c + 3] = q.w;
             }
-        } else {
+        if (a.fold) {
 #pragma unroll
-            for (int c = 0; c < VPL; ++c) {
-                const int k = (c >> 2) * 256 + (c & 3);
-                v[n][c] = ok && kbase + k < a.cols ? src[k] : 0.0f;
+            for (int c = 0; c < VPL; c += 4) {
+                const float4 q = *reinterpret_cast<const float4*>(a.fold + kbase + c * 64);
+                f[c] = q.x; f[c + 1] = q.y; f[c + 2] = q.z; f[c + 3] = q.w;
             }
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < VPL; ++c) {
+            const int k = (c >> 2) * 256 + (c & 3);
+            const bool in = ok && kbase + k < a.cols;
+#pragma unroll
+            for (int n = 0; n < NR; ++n) v[n][c] = in ? src[n * next + k] : 0.0f;
+            f[c] = in && a.fold ? a.fold[kbase + k] : 1.0f;
         }
     }
 #pragma unroll
@@ -658,12 +670,9 @@ row_top_quant_kernel(RowArgs a, int segs, int groups_per_wg, int low) {
         for (int c = 0; c < VPL; ++c) v[n][c] *= a.in_mul;
     if (a.fold) {
 #pragma unroll
-        for (int c = 0; c < VPL; ++c) {
-            const int64_t k = kbase + (c >> 2) * 256 + (c & 3);
-            const float f = fast || k < a.cols ? a.fold[k] : 1.0f;
+        for (int n = 0; n < NR; ++n)
 #pragma unroll
-            for (int n = 0; n < NR; ++n) v[n][c] *= f;
-        }
+            for (int c = 0; c < VPL; ++c) v[n][c] *= f[c];
     }
     const int bperm_addr = (lane ^ 32) << 2;
     float amax[NR];
