@@ -158,8 +158,10 @@ col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_
 // What bounds it: memory, 2 + 4 bytes an element (4096 x 4096: 24 us, 4.1 TB/s; two strided passes took 22 + 22).  64 values per thread and a 64 KB exchange buffer (one of the two columns at
 // a time), so that two workgroups of 1024 rows share a compute unit: one loads or stores while the other exchanges.
 // Neighbouring column tiles, which share cache lines of a bf16 row, run on the same XCD at the same time.
-// SIDE (bf16 input): the pass also writes, per column, the largest |in[r, k] * row_scale[r]| of its rows to
-// side_part[row block][cols]: what the column quantiser of the same matrix needs, taken from the one read of it.
+// SIDE (bf16 input): the pass also takes, per column, the largest |in[r, k] * row_scale[r]| of its rows, which the column quantiser
+// of the same matrix needs, from the one read of it.  kSideMaxima: it writes them to side_part[row block][cols].  kSideCodes
+// (the rows are one block): it quantises the columns itself; a thread's 32 rows are 32 consecutive bytes of a row of codes.
+enum { kSideNone = 0, kSideMaxima = 1, kSideCodes = 2 };
 struct ColBlockArgs {
     const void* in;
     int64_t ld_in;
@@ -170,7 +172,10 @@ struct ColBlockArgs {
     float c_final;                       // 1.0f: no multiply
     const float* row_scale;              // IN_I32: multiplied in; SIDE: for the side output only.  May be null
     const float* post_scale;             // IN_I32: device scalar, may be null
-    float* side_part;
+    float* side_part;                    // kSideMaxima
+    int8_t* side_q;                      // kSideCodes: [cols][ld_q], and side_scale[cols]
+    int64_t ld_q;
+    float* side_scale;
 };
 template <int LOGR>
 struct ColBlockCfg {
@@ -182,7 +187,7 @@ struct ColBlockCfg {
     static constexpr int XCH = G * 33 * CP, RED = 2 * CP * ((T + 63) / 64);
     static constexpr int LDS_BYTES = 4 * (XCH + R + RED);
 };
-template <int LOGR, int IN, bool SIDE>
+template <int LOGR, int IN, int SIDE>
 __global__ void __launch_bounds__(ColBlockCfg<LOGR>::T, 4)
 col_block_kernel(ColBlockArgs a) {
     using Cfg = ColBlockCfg<LOGR>;
@@ -199,7 +204,7 @@ col_block_kernel(ColBlockArgs a) {
     const bool whole = c0 + 2 * CP <= a.cols;                     // uniform; the number of columns is even
     const bool col_ok = c0 + 2 * cp < a.cols;
 
-    constexpr bool SCALED = IN == IN_I32 || SIDE;
+    constexpr bool SCALED = IN == IN_I32 || SIDE != kSideNone;
     float sc[SCALED ? R / T : 1];
     if constexpr (SCALED) {
 #pragma unroll
@@ -247,7 +252,7 @@ col_block_kernel(ColBlockArgs a) {
             v[t][1] = ((float)w[t].y * rs) * post;
         }
     }
-    if constexpr (SIDE) {
+    if constexpr (SIDE != kSideNone) {
         float m0 = 0.0f, m1 = 0.0f;
 #pragma unroll
         for (int t = 0; t < 32; ++t) {
@@ -263,6 +268,34 @@ col_block_kernel(ColBlockArgs a) {
         if ((tid & 63) < CP) {
             s_red[(tid >> 6) * 2 * CP + 2 * cp] = m0;
             s_red[(tid >> 6) * 2 * CP + 2 * cp + 1] = m1;
+        }
+    }
+    if constexpr (SIDE == kSideCodes) {
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            float am = s_red[2 * cp + c];
+#pragma unroll
+            for (int w = 1; w < (T + 63) / 64; ++w) am = fmaxf(am, s_red[w * 2 * CP + 2 * cp + c]);
+            const float inv = am > 0.0f ? 127.0f / am : 0.0f;
+            uint32_t q[8];
+#pragma unroll
+            for (int t = 0; t < 32; t += 4) {
+                uint32_t b[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    b[e] = __float_as_uint((v[t + e][c] * s_scale[32 * g + t + e]) * inv + 12582912.0f);
+                const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u);
+                const uint32_t hi = __builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u);
+                q[t / 4] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+            }
+            if (col_ok) {
+                const int64_t col = c0 + 2 * cp + c;
+                uint4* dst = reinterpret_cast<uint4*>(a.side_q + col * a.ld_q + 32 * g);
+                dst[0] = make_uint4(q[0], q[1], q[2], q[3]);
+                dst[1] = make_uint4(q[4], q[5], q[6], q[7]);
+                if (g == 0) a.side_scale[col] = am > 0.0f ? am / 127.0f : 1.0f;
+            }
         }
     }
     // ---- strides 1 .. 16
@@ -295,7 +328,7 @@ col_block_kernel(ColBlockArgs a) {
             for (int t = 0; t < (1 << S); ++t)
                 v[(k << S) + t][c] = smem[((t + 32 * half) * 33 + r + (k << S)) * CP + cp];
     }
-    if constexpr (SIDE) {
+    if constexpr (SIDE == kSideMaxima) {
         if (tid < 2 * CP && c0 + tid < a.cols) {
             float m = s_red[tid];
 #pragma unroll
@@ -349,7 +382,7 @@ col_block_kernel(ColBlockArgs a) {
     }
 }
 
-template <int LOGR, int IN, bool SIDE>
+template <int LOGR, int IN, int SIDE>
 hipError_t launch_col_block(const ColBlockArgs& a, hipStream_t s) {
     using Cfg = ColBlockCfg<LOGR>;
     static std::once_flag once;
@@ -365,13 +398,16 @@ hipError_t launch_col_block(const ColBlockArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int IN, bool SIDE>
+template <int IN, int SIDE = kSideNone>
 hipError_t launch_col_block_by_rows(int logr, const void* in, int64_t ld_in, float* out, int64_t ld_out, int64_t rows, int64_t cols,
-                                    float c_final, hipStream_t s, const float* row_scale, const float* post_scale,
-                                    float* side_part) {
+                                    float c_final, hipStream_t s, const float* row_scale = nullptr,
+                                    const float* post_scale = nullptr, const ColQuantArgs* q = nullptr) {
     const int64_t wide = logr == 6 ? 64 : 32, col_tiles = (cols + wide - 1) / wide, tiles = col_tiles * (rows >> logr);
     if (tiles <= 0 || tiles > 0x7FFFFFF0) return hipErrorInvalidValue;
-    const ColBlockArgs a{in, ld_in, out, ld_out, cols, (int)col_tiles, (int)tiles, c_final, row_scale, post_scale, side_part};
+    ColBlockArgs a{in, ld_in, out, ld_out, cols, (int)col_tiles, (int)tiles, c_final, row_scale, post_scale};
+    if constexpr (SIDE != kSideNone) {
+        a.row_scale = q->fold; a.side_part = q->amax_ws; a.side_q = q->out_q; a.ld_q = q->ld_q; a.side_scale = q->out_scale;
+    }
     switch (logr) {
         case 6: return launch_col_block<6, IN, SIDE>(a, s);
         case 7: return launch_col_block<7, IN, SIDE>(a, s);
@@ -897,7 +933,9 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
     const bool blocks = a.first_stage == 0 && low >= (a.only_low ? 6 : 7) && low <= std::min(a.log_block, kColBlockStages) &&
                         a.cols % 2 == 0 && a.ld_in % 2 == 0 && a.ld_out % 2 == 0 && a.ld_tmp % 2 == 0 &&
                         std::max(a.ld_in, std::max(a.ld_out, a.ld_tmp)) <= (int64_t(1) << 18);
-    if ((a.only_low && !blocks) || (a.side_part && (!a.only_low || a.in_kind != IN_BF16))) return hipErrorInvalidValue;
+    if ((a.only_low && !blocks) || (a.columns && (!a.only_low || a.in_kind != IN_BF16))) return hipErrorInvalidValue;
+    const bool all_rows = a.rows == (int64_t(1) << low);
+    if (a.columns && all_rows && a.columns->ld_q % 16 != 0) return hipErrorInvalidValue;
     int sizes[8], np = 0, left = a.log_block - a.first_stage;
     if (left == 0) return (a.in == a.out && a.skip_norm) ? hipSuccess : hipErrorInvalidValue;   // nothing left to do in place
     if (blocks) {
@@ -922,14 +960,16 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
         hipError_t e;
         if (first && blocks) {
             float* d = reinterpret_cast<float*>(dst);
-            if (ik == IN_BF16 && a.side_part)
-                e = launch_col_block_by_rows<IN_BF16, true>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, a.side_fold, nullptr, a.side_part);
+            if (a.columns && all_rows)
+                e = launch_col_block_by_rows<IN_BF16, kSideCodes>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, nullptr, nullptr, a.columns);
+            else if (a.columns)
+                e = launch_col_block_by_rows<IN_BF16, kSideMaxima>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, nullptr, nullptr, a.columns);
             else if (ik == IN_BF16)
-                e = launch_col_block_by_rows<IN_BF16, false>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, nullptr, nullptr, nullptr);
+                e = launch_col_block_by_rows<IN_BF16>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s);
             else if (ik == IN_F32)
-                e = launch_col_block_by_rows<IN_F32, false>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, nullptr, nullptr, nullptr);
+                e = launch_col_block_by_rows<IN_F32>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s);
             else
-                e = launch_col_block_by_rows<IN_I32, false>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, a.row_scale, a.post_scale, nullptr);
+                e = launch_col_block_by_rows<IN_I32>(low, src, ld_src, d, ld_dst, a.rows, a.cols, cf, s, a.row_scale, a.post_scale);
         } else if (ik == IN_BF16)
             e = launch_pass_by_logr<IN_BF16>(sizes[i], src, ld_src, dst, ld_dst, a.rows, a.cols, p, cf, s);
         else if (ik == IN_F32)

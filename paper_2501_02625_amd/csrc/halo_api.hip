@@ -107,29 +107,51 @@ BwdWorkspace bwd_layout(const halo_linear_desc* d) {
     return w;
 }
 
-// The rest of that un-rotation: t [b x m] fp32 holds the product after the eight low left-hand strides.  Either one
-// kernel (top strides across the wavefronts of a workgroup, then each row's right-hand un-rotation), or the remaining
-// strides in place and then the row kernel (1/sqrt(left block), right-hand un-rotation, conversion).
-// first_stage: the left-hand strides below 2^first_stage have run already (8 after the GEMM epilogue that runs them, 0
-// after a plain epilogue).
+// The un-rotation of G beside that of E_X: int32 [rows x m], times scale per row.
+struct GradUnrotation {
+    const int32_t* acc;
+    int64_t rows;
+    const float* scale;
+    void* out;
+};
+// The right-hand part: r holds E_X's fp32 matrix.  g (may be null) shares the launch where the rotation is a power of two: two
+// launches of 1024 x 256 took 3.4 + 3.7 us.
+hipError_t unrotate_rows(RowArgs r, OutKind ok, const GradUnrotation* g, hipStream_t s) {
+    if (g && r.kron_m == 0) {
+        r.rows2 = g->rows; r.in2 = g->acc; r.pre_scale2 = g->scale; r.out2 = g->out;
+        return launch_row_transform(r, IN_F32_I32, ok, s);
+    }
+    const hipError_t e = launch_row_transform(r, IN_F32, ok, s);
+    if (e != hipSuccess || !g) return e;
+    r.in = g->acc; r.rows = g->rows; r.pre_scale = g->scale; r.out = g->out; r.in_mul = 0.0f;
+    return launch_row_transform(r, IN_I32, ok, s);
+}
+
+// The rest of an un-rotation: t [b x m] fp32 holds the product after the left-hand strides below 2^first_stage (8 after the GEMM
+// epilogue that runs them, 0 after a plain epilogue, all of them after strided passes from the accumulators).  Either one kernel
+// (top strides across the wavefronts of a workgroup, then each row's right-hand un-rotation), or the remaining strides in place
+// and then the row kernel (1/sqrt(left block), right-hand un-rotation, conversion).  g: G's un-rotation, may be null.
 hipError_t finish_left_unrotation(float* t, int64_t b, int64_t m, int32_t hb, int32_t hm, void* out, halo_dtype odt,
-                                  hipStream_t s, int first_stage = 8) {
+                                  hipStream_t s, int first_stage = 8, const GradUnrotation* g = nullptr) {
     RowArgs r{};
     r.in = t; r.ld_in = m; r.rows = b; r.cols = m; r.out = out; r.ld_out = m;
     r.in_mul = (float)(1.0 / sqrt((double)hb));
     set_right_block(r, hm);
     const OutKind ok = odt == HALO_BF16 ? OUT_BF16 : OUT_F32;
     // up to four top strides left and a right-hand block of 512 .. 4096: one kernel does the rest
-    const int top = ilog2_exact(hb) - 8;
+    const int log_left = ilog2_exact(hb), top = log_left - 8;
     if (first_stage == 8 && r.kron_m == 0 && row_left_top_ok(b, m, r.log_block, top)) {
-        r.left_top = top;
-        return launch_row_left_top(r, ok, s);
+        RowArgs l = r;
+        l.left_top = top;
+        const hipError_t e = launch_row_left_top(l, ok, s);
+        if (e != hipSuccess || !g) return e;
+        r.in = g->acc; r.rows = g->rows; r.pre_scale = g->scale; r.out = g->out; r.in_mul = 0.0f;
+        return launch_row_transform(r, IN_I32, ok, s);
     }
-    ColFwhtArgs c{t, IN_F32, m, t, m, t, m, b, m, ilog2_exact(hb)};
+    ColFwhtArgs c{t, IN_F32, m, t, m, t, m, b, m, log_left};
     c.first_stage = first_stage; c.skip_norm = 1;
-    hipError_t e = launch_col_fwht(c, s);
-    if (e != hipSuccess) return e;
-    return launch_row_transform(r, IN_F32, ok, s);
+    const hipError_t e = launch_col_fwht(c, s);
+    return e != hipSuccess ? e : unrotate_rows(r, ok, g, s);
 }
 
 // Stages of the left-hand rotation's first pass, and so the number of top strides that the row quantiser behind it runs: as
@@ -137,41 +159,50 @@ hipError_t finish_left_unrotation(float* t, int64_t b, int64_t m, int32_t hb, in
 // and the row quantiser takes the others.  With the rule
 // and without, rows x cols of one block: 2048 x 4096 24.5 us against 28.0, 2048 x 1024 12.7 / 19.7, 4096 x 1024 18.4 / 23.0, 1024 x
 // 4096 16.4 / 17.9, 512 x 4096 11.2 / 11.9; blocks of 256 rows are left whole (256 x 512: 2 us
-// slower in two parts; 256 x 4096 no faster).
-int left_pass_stages(int log_left, int64_t rows, int64_t cols, bool row_rotation) {
+// slower in two parts; 256 x 4096 no faster).  A block that is all of the rows also yields the column codes when the pass keeps
+// it whole (`columns`), which saves a launch and a read of E: it does up to 1024 rows, and 2048 where half of the chip is busy.
+int left_pass_stages(int log_left, int64_t rows, int64_t cols, bool row_rotation, bool columns) {
     int low = log_left < kColBlockStages ? log_left : kColBlockStages;
     auto tiles = [&](int l) { return (cols + 31) / 32 * (rows >> l); };
+    if (columns && rows == (int64_t(1) << low) && (low < 11 || 2 * tiles(low) >= kComputeUnits)) return low;
     while (!row_rotation && low > 8 && tiles(low) < kComputeUnits && row_top_quant_ok(cols, log_left - low + 1)) --low;
     return low;
 }
 
 // (H_left in) (x) fold, quantised per row: the left-hand rotation into the fp32 scratch tmp [rows x cols], then the row quantiser
 // (with a right-hand rotation if r asks for one).  r: rows, cols, fold, out, ld_out, out_scale and the right-hand block.
-// side_part (may be null): as in ColFwhtArgs; `parts` receives the number of its vectors.
-hipError_t left_rotate_quant(const void* in, InKind ik, int64_t ld_in, float* tmp, int log_left, RowArgs r, const float* side_fold,
-                             float* side_part, int* parts, hipStream_t s) {
+// q (may be null; bf16 in, left blocks of at least 64 rows): also the quantiser by columns, of `in` as it is.
+hipError_t left_rotate_quant(const void* in, InKind ik, int64_t ld_in, float* tmp, int log_left, RowArgs r, const ColQuantArgs* q,
+                             hipStream_t s) {
     ColFwhtArgs c{in, ik, ld_in, tmp, r.cols, tmp, r.cols, r.rows, r.cols, log_left};
     r.in = tmp; r.ld_in = r.cols;
     const bool row_rotation = r.log_block != 0 || r.kron_m != 0;
-    const int low = left_pass_stages(log_left, r.rows, r.cols, row_rotation), top = log_left - low;
+    const int low = left_pass_stages(log_left, r.rows, r.cols, row_rotation, q != nullptr), top = log_left - low;
     const bool in_quantiser = !row_rotation && row_top_quant_ok(r.cols, top) && ld_in <= (int64_t(1) << 18);
-    if (side_part || in_quantiser) {
-        c.only_low = low; c.side_fold = side_fold; c.side_part = side_part;
+    hipError_t e;
+    if (q || in_quantiser) {
+        c.only_low = low; c.columns = q;
         c.skip_norm = top != 0;
-        hipError_t e = launch_col_fwht(c, s);
+        e = launch_col_fwht(c, s);
         if (e != hipSuccess) return e;
-        if (parts) *parts = (int)(r.rows >> low);
-        if (in_quantiser) {
-            r.left_top = top;
-            r.in_mul = (float)(1.0 / sqrt((double)(int64_t(1) << log_left)));
-            return launch_row_top_quant(r, low, s);
-        }
-        if (top == 0) return launch_row_transform(r, IN_F32, OUT_Q8, s);
-        c = ColFwhtArgs{tmp, IN_F32, r.cols, tmp, r.cols, tmp, r.cols, r.rows, r.cols, log_left};
-        c.first_stage = low;
     }
-    const hipError_t e = launch_col_fwht(c, s);
-    return e != hipSuccess ? e : launch_row_transform(r, IN_F32, OUT_Q8, s);
+    if (in_quantiser) {
+        r.left_top = top;
+        r.in_mul = (float)(1.0 / sqrt((double)(int64_t(1) << log_left)));
+        e = launch_row_top_quant(r, low, s);
+    } else {
+        if (q && top != 0) {               // the top strides in passes of their own
+            c = ColFwhtArgs{tmp, IN_F32, r.cols, tmp, r.cols, tmp, r.cols, r.rows, r.cols, log_left};
+            c.first_stage = low;
+        }
+        if (!q || top != 0) {
+            e = launch_col_fwht(c, s);
+            if (e != hipSuccess) return e;
+        }
+        e = launch_row_transform(r, IN_F32, OUT_Q8, s);
+    }
+    if (e != hipSuccess || !q || r.rows == (int64_t(1) << low)) return e;
+    return launch_col_quant_t_ready(*q, (int)(r.rows >> low), s);
 }
 
 // Scratch of the HALO-PEFT entry points (one layout for both directions).
@@ -280,8 +311,7 @@ halo_status halo_hadamard_quant(const void* in, halo_dtype in_dt, int64_t rows, 
     // left-hand rotation first (strided passes into fp32 scratch), then the row kernel on the scratch
     if ((cols * 4) % 16) return HALO_EALIGN;   // scratch rows must stay 16-byte aligned
     float* tmp = reinterpret_cast<float*>(workspace);
-    return from_hip(left_rotate_quant(in, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, ld_in, tmp, ilog2_exact(had_block_left), r, nullptr,
-                                      nullptr, nullptr, s));
+    return from_hip(left_rotate_quant(in, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, ld_in, tmp, ilog2_exact(had_block_left), r, nullptr, s));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -738,10 +768,8 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
         if (side) {
             RowArgs r{};
             r.rows = b; r.cols = n; r.fold = s_w; r.out = Eq; r.ld_out = n; r.out_scale = s_e;
-            int parts = 0;
-            if (left_rotate_quant(E, IN_BF16, n, f32, ilog2_exact(hb), r, s_x, amax, &parts, hs) != hipSuccess) return HALO_EHIP;
-            ColQuantArgs q{E, n, b, n, s_x, EqT, b, s_g, amax};
-            if (launch_col_quant_t_ready(q, parts, hs) != hipSuccess) return HALO_EHIP;
+            const ColQuantArgs q{E, n, b, n, s_x, EqT, b, s_g, amax};
+            if (left_rotate_quant(E, IN_BF16, n, f32, ilog2_exact(hb), r, &q, hs) != hipSuccess) return HALO_EHIP;
         } else {
             if (EX) {
                 st = halo_hadamard_quant(E, HALO_BF16, b, n, n, HALO_QUANT_ROWS, 0, level >= 2 ? hb : 0, s_w, Eq, n, s_e, f32,
@@ -785,6 +813,19 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
         r.rows2 = n; r.in2 = acc_g; r.pre_scale2 = s_g; r.out2 = G;
         if (launch_row_transform(r, IN_I32, odt == HALO_BF16 ? OUT_BF16 : OUT_F32, hs) != hipSuccess) return HALO_EHIP;
         return HALO_OK;
+    }
+    if (both && level >= 2) {
+        const GradUnrotation grad{acc_g, n, s_g, G};
+        float* t = reinterpret_cast<float*>(acc);
+        int first_stage = 8;
+        if (!left_fused) {
+            ColFwhtArgs c{acc, IN_I32, m, f32, m, f32, m, b, m, ilog2_exact(hb)};
+            c.row_scale = s_e; c.skip_norm = 1;
+            if (launch_col_fwht(c, hs) != hipSuccess) return HALO_EHIP;
+            t = f32;
+            first_stage = ilog2_exact(hb);
+        }
+        return from_hip(finish_left_unrotation(t, b, m, hb, hm, EX, odt, hs, first_stage, &grad));
     }
     if (left_fused) {
         if (finish_left_unrotation(reinterpret_cast<float*>(acc), b, m, hb, hm, EX, odt, hs) != hipSuccess) return HALO_EHIP;

@@ -9,7 +9,8 @@
 
 namespace halo {
 
-enum InKind { IN_BF16 = 0, IN_F32 = 1, IN_I32 = 2 };
+// IN_F32_I32: the first matrix of a batched launch (rows2 > 0) holds fp32 and the second int32.
+enum InKind { IN_BF16 = 0, IN_F32 = 1, IN_I32 = 2, IN_F32_I32 = 3 };
 enum OutKind { OUT_Q8 = 0, OUT_BF16 = 1, OUT_F32 = 2, OUT_MX6 = 3 };
 
 // ---- row transform: [pre-scale] -> right-hand FWHT -> [fold] -> {absmax+INT8 | bf16 | fp32} ----
@@ -17,14 +18,14 @@ struct RowArgs {
     const void* in;
     int64_t ld_in;
     int64_t rows, cols;
-    const float* pre_scale;  // IN_I32 only: per-row multiplier, may be null
+    const float* pre_scale;  // int32 only: per-row multiplier, may be null
     const float* fold;       // per-column multiplier, may be null
     void* out;
     int64_t ld_out;
     float* out_scale;        // OUT_Q8 only
     int log_block;           // log2 of the Hadamard block, 0 = no rotation
     int kron_m;              // 0, or 28: the block is 28 * 2^log_block elements, rotated by H_{2^log_block} (x) H_28
-    float in_mul;            // IN_F32 only: every element is multiplied by this once when it is loaded; 0 = no multiply
+    float in_mul;            // fp32 only: every element is multiplied by this once when it is loaded; 0 = no multiply
     int left_top;            // launch_row_left_top only: number of top strides of the left-hand rotation still to run (1..5)
     // One scale per tensor (OUT_Q8 only): amax_only writes each row's absmax to out_scale and no codes; given_amax
     // (device scalar) replaces the row's own absmax.  post_scale (IN_I32 only, device scalar) is multiplied in after
@@ -65,6 +66,18 @@ hipError_t launch_row_top_quant(const RowArgs& a, int low, hipStream_t s);
 bool row_kron_shape_ok(int64_t cols, int64_t block);
 hipError_t launch_row_kron(const RowArgs& a, InKind in, OutKind out, hipStream_t s);
 
+// ---- column-wise absmax quantiser with transposed output (E^T)_Q ----
+struct ColQuantArgs {
+    const void* in;          // bf16 [rows x cols]
+    int64_t ld_in;
+    int64_t rows, cols;
+    const float* fold;       // per-row multiplier, may be null
+    int8_t* out_q;           // [cols x rows]
+    int64_t ld_q;
+    float* out_scale;        // [cols]
+    float* amax_ws;          // scratch: column absmax accumulated as bit patterns [cols], or partial maxima (see ColFwhtArgs)
+};
+
 // ---- left-hand (strided axis) FWHT: all stages of block 2^log_block, ascending, possibly several passes ----
 // in/out may alias when in_kind == out_kind == fp32.  tmp (fp32 [rows x ld_tmp]) is used when more than one
 // pass is needed and in/out cannot carry fp32 intermediates.
@@ -87,29 +100,17 @@ struct ColFwhtArgs {
     int skip_norm;
     // only_low > 0 (6 .. 11, first_stage 0): the strides below 2^only_low, in one pass; the caller runs the others.
     int only_low;
-    // side_part != null (bf16 input, only_low > 0): the pass also writes, per column and block of 2^only_low rows, the absolute
-    // maximum of in[r, k] * side_fold[r] (side_fold may be null) to side_part[rows >> only_low][cols].
-    const float* side_fold;
-    float* side_part;
+    // columns != null (bf16 input, only_low > 0): the pass also works for that column quantiser of the same matrix.  A block that is
+    // all of the rows: it writes its codes and scales.  Otherwise it writes the absolute maxima of each block of 2^only_low rows
+    // to columns->amax_ws [rows >> only_low][cols], for launch_col_quant_t_ready.
+    const ColQuantArgs* columns;
 };
 // Stages, from stride 1 on, that one pass over blocks of rows takes at most.
 constexpr int kColBlockStages = 11;
 hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s);
 
-// ---- column-wise absmax quantiser with transposed output (E^T)_Q ----
-struct ColQuantArgs {
-    const void* in;          // bf16 [rows x cols]
-    int64_t ld_in;
-    int64_t rows, cols;
-    const float* fold;       // per-row multiplier, may be null
-    int8_t* out_q;           // [cols x rows]
-    int64_t ld_q;
-    float* out_scale;        // [cols]
-    float* amax_ws;          // [cols] scratch: column absmax accumulated as bit patterns
-};
 hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s);
-// The same with `parts` vectors of the columns' partial maxima already in a.amax_ws [parts x cols] (the side output of
-// launch_col_fwht).
+// The same with `parts` vectors of the columns' partial maxima already in a.amax_ws [parts x cols] (ColFwhtArgs::columns).
 hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_t s);
 // The same with one given absmax (device scalar) for every column instead of the columns' own: the tensor-wide scale.
 hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, hipStream_t s);

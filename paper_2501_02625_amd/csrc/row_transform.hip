@@ -70,6 +70,7 @@ struct RowCtx {
     float* xbuf;            // LDS exchange buffer [waves][values per lane][64] (only with cross-wave stages)
     int64_t row, kbase;     // kbase: first element of this lane's chunk 0
     bool row_ok;
+    bool f32;               // IN_F32_I32: this matrix holds fp32 (uniform over the workgroup)
 };
 
 // Load one segment into registers, rotate it, apply the fold vector; returns the local absmax (quantising kernels).
@@ -83,9 +84,11 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
     constexpr int NCH = VPL / EPL;
 
     float pre = 1.0f;
-    if constexpr (IN == IN_I32) {
-        if (x.row_ok && a.pre_scale) pre = a.pre_scale[x.row];
+    if constexpr (IN == IN_I32 || IN == IN_F32_I32) {
+        if (IN == IN_F32_I32 && x.f32) pre = a.in_mul != 0.0f ? a.in_mul : 1.0f;      // x * 1.0f is x
+        else if (x.row_ok && a.pre_scale) pre = a.pre_scale[x.row];
     }
+    auto widen = [&](int32_t q) { return (IN == IN_F32_I32 && x.f32 ? __int_as_float(q) : (float)q) * pre; };
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const int64_t k0 = x.kbase + (int64_t)c * 64 * EPL;
@@ -106,8 +109,8 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
             } else {
                 const int4 q = *reinterpret_cast<const int4*>(
                     reinterpret_cast<const int32_t*>(a.in) + x.row * a.ld_in + k0);
-                v[c * EPL + 0] = (float)q.x * pre; v[c * EPL + 1] = (float)q.y * pre;
-                v[c * EPL + 2] = (float)q.z * pre; v[c * EPL + 3] = (float)q.w * pre;
+                v[c * EPL + 0] = widen(q.x); v[c * EPL + 1] = widen(q.y);
+                v[c * EPL + 2] = widen(q.z); v[c * EPL + 3] = widen(q.w);
             }
         } else {
 #pragma unroll
@@ -119,7 +122,7 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
                     } else if constexpr (IN == IN_F32) {
                         t = reinterpret_cast<const float*>(a.in)[x.row * a.ld_in + k0 + e];
                     } else {
-                        t = (float)reinterpret_cast<const int32_t*>(a.in)[x.row * a.ld_in + k0 + e] * pre;
+                        t = widen(reinterpret_cast<const int32_t*>(a.in)[x.row * a.ld_in + k0 + e]);
                     }
                 }
                 v[c * EPL + e] = t;
@@ -133,8 +136,8 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
             for (int r = 0; r < VPL; ++r) v[r] *= a.in_mul;
         }
     }
-    if constexpr (IN == IN_I32) {
-        if (a.post_scale) {          // one more (tensor-wide) scale, applied after the per-row one
+    if constexpr (IN == IN_I32 || IN == IN_F32_I32) {
+        if (a.post_scale && !(IN == IN_F32_I32 && x.f32)) {          // one more (tensor-wide) scale, applied after the per-row one
             const float post = *a.post_scale;
 #pragma unroll
             for (int r = 0; r < VPL; ++r) v[r] *= post;
@@ -360,6 +363,7 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     x.lane = position_of_lane(threadIdx.x & 63);
     x.bperm_addr = ((threadIdx.x & 63) ^ 32) << 2;
     unsigned block = blockIdx.x;
+    x.f32 = block < blocks1;
     if (block >= blocks1) {          // the second matrix of a batched launch
         block -= blocks1;
         a.in = a.in2; a.pre_scale = a.pre_scale2; a.out = a.out2; a.out_scale = a.out_scale2; a.rows = a.rows2;
@@ -443,7 +447,7 @@ hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
     // rows would leave the 1024 SIMDs with fewer than four wavefronts each.
     if ((a.log_block == 11 || a.log_block == 12) && a.cols % 1024 == 0 && a.cols <= 16384) {
         const int64_t wavefronts_unsplit = (a.rows + a.rows2) * (a.cols >> a.log_block);
-        const bool want = IN == IN_I32 ? a.log_block == 12 : wavefronts_unsplit < 4096;
+        const bool want = IN == IN_I32 || IN == IN_F32_I32 ? a.log_block == 12 : wavefronts_unsplit < 4096;
         if (want) return a.log_block == 11 ? launch_split<IN, OUT, 1>(a, s) : launch_split<IN, OUT, 2>(a, s);
     }
     // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).
@@ -737,12 +741,14 @@ hipError_t launch_row_left_top(const RowArgs& a, OutKind out, hipStream_t s) {
 
 hipError_t launch_row_transform(const RowArgs& a, InKind in, OutKind out, hipStream_t s) {
     if ((a.rows == 0 && a.rows2 == 0) || a.cols == 0) return hipSuccess;
-    if (a.kron_m != 0) return out == OUT_MX6 ? hipErrorInvalidValue : launch_row_kron(a, in, out, s);
+    if (a.kron_m != 0) return out == OUT_MX6 || in == IN_F32_I32 ? hipErrorInvalidValue : launch_row_kron(a, in, out, s);
     if (a.cols > kMaxRowCols || a.log_block > 12) return hipErrorInvalidValue;
     if (in == IN_BF16 && out == OUT_Q8) return launch_by_seg<IN_BF16, OUT_Q8>(a, s);
     if (in == IN_F32 && out == OUT_Q8) return launch_by_seg<IN_F32, OUT_Q8>(a, s);
     if (in == IN_I32 && out == OUT_BF16) return launch_by_seg<IN_I32, OUT_BF16>(a, s);
     if (in == IN_I32 && out == OUT_F32) return launch_by_seg<IN_I32, OUT_F32>(a, s);
+    if (in == IN_F32_I32 && a.rows2 > 0 && out == OUT_BF16) return launch_by_seg<IN_F32_I32, OUT_BF16>(a, s);
+    if (in == IN_F32_I32 && a.rows2 > 0 && out == OUT_F32) return launch_by_seg<IN_F32_I32, OUT_F32>(a, s);
     if (in == IN_F32 && out == OUT_BF16) return launch_by_seg<IN_F32, OUT_BF16>(a, s);
     if (in == IN_F32 && out == OUT_F32) return launch_by_seg<IN_F32, OUT_F32>(a, s);
     if (in == IN_BF16 && out == OUT_MX6) return a.cols % 32 == 0 ? launch_by_seg<IN_BF16, OUT_MX6>(a, s) : hipErrorInvalidValue;

@@ -127,6 +127,15 @@ def test_level2_column_maxima_from_several_row_blocks(b, n, hb):
     run_and_check(b, 256, n, 2, Xb, Wb, Eb, hb=hb)
 
 
+@pytest.mark.parametrize("b,n", [(64, 80), (128, 48), (512, 144), (1024, 272), (2048, 4096), (2048, 80)])
+@pytest.mark.parametrize("odt", [torch.float32, torch.bfloat16])
+def test_level2_one_left_block(b, n, odt):
+    """All tokens in one left block: the rotation's first pass writes the column codes as well (2048 x 80: it is cut in two and does
+    not).  The un-rotations of E_X (fp32) and G (int32) share a launch."""
+    Xb = inputs.make_activations(b, 256, 0.01, b); Wb = inputs.make_weights(n, 256, b); Eb = inputs.make_errors(b, n, b)
+    run_and_check(b, 256, n, 2, Xb, Wb, Eb, odt=odt)
+
+
 # tokens, in- and out-features, right and left block: the low left-hand strides run in the product's epilogue
 # (test_gemm_plan.py asserts that the rule says so), and every way the rest of the un-rotation can go is there.
 LEFT_IN_EPILOGUE = [
