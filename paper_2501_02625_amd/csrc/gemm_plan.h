@@ -142,25 +142,29 @@ inline double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
 
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
 // left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
-// tiles, followed by strided passes over its accumulators.  gx, gg: the plain forms of the products (gg null: only E_X is
-// wanted).  A pass of six strides costs 3.5 us and 1.5 us per million elements (kernel trace: 2.7 us at 256 x 1024, 7.7 at
-// 1024 x 4096, 14 at 4096 x 2048); the first one, where it starts from the int32 accumulators, 8 and 2 (10, 13 and 16).
+// tiles, followed by a pass over its accumulators that takes up to eleven strides, and a strided pass for the others.  gx, gg: the
+// plain forms of the products (gg null: only E_X is wanted).  Estimates: 3.5 us and 3.5 us per million elements for the first pass
+// where it starts from the int32 accumulators, 5 and 1.5 for the others and for one that starts from fp32.
+// A short reduction, up to 384, keeps to the epilogue unless the passes are estimated 6 us faster.
 // The backward pass timed both ways on 171 shapes, 256 .. 8192 tokens, 512 .. 14336 by 256 .. 4096, each with both products,
-// with E_X alone and with rank-16 adapters: the rule takes the faster way or one within 3 % of it in 491 of 513, 12 % behind
-// at worst.  Both products, in the epilogue against passes: 256 x 1024 x 1024 53.5 us against 48.2, 256 x 8192 x 4096 152 against
-// 126, 1536 x 3072 x 1024 64.7 against 73.8, 4096 x 2048 x 1024 103 against 116.
+// with E_X alone and with rank-16 adapters: the rule takes the faster way or one within 3 % of it in 447 of 513, 20 % behind
+// at worst.  It leans to the epilogue: short reductions are left there as they were, from 25 % faster (4096 x 3072 by 16, E_X alone
+// 58 us against 78) to 15 % slower (512 x 8192 by 256, both 47 / 40), and so is 1536 x 3072 by 1024 (both 55.7 / 52.6).  With the
+// constants of the six-stride passes that came before, 106 were more than 3 % behind, 30 % at worst.  Both products, in the epilogue
+// against passes: 256 x 8192 x 4096 118 us against 100, 1024 x 4096 x 4096 110 / 98, 4096 x 2048 x 1024 90 / 98, 4096 x 4096 x 4096
+// 226 / 255.
 inline bool left_in_epilogue(const GemmArgs& gx, const GemmArgs* gg, int32_t hb, int32_t hm) {
     const int64_t b = gx.M, m = gx.N;
     if (hb < 256 || b % 256) return false;
-    const double melems = (double)b * (double)m / 1e6, pass = 3.5 + 1.5 * melems;
-    const double first = gx.lr_rank ? pass : 8.0 + 2.0 * melems;           // adapters: the product is stored as fp32
+    const double melems = (double)b * (double)m / 1e6, pass = 5.0 + 1.5 * melems;
+    const double first = gx.lr_rank ? pass : 3.5 + 3.5 * melems;           // adapters: the product is stored as fp32
     GemmArgs l = gx, g2 = gg ? *gg : gx;
     l.left_stages = 8; l.config = HALO_GEMM_256x256x64; g2.config = HALO_GEMM_256x256x64;
     const int top = ilog2_exact(hb) - 8, stages = ilog2_exact(hb);
     const bool one_kernel = is_pow2(hm) && row_left_top_ok(b, m, ilog2_exact(hm), top);
     const double fused = gemm_i8_cost(l, gg ? &g2 : nullptr) + (top == 0 || one_kernel ? 0.0 : pass);
-    const double plain = gemm_i8_cost(gx, gg) + first + ((stages + 5) / 6 - 1) * pass;
-    return fused <= plain;
+    const double plain = gemm_i8_cost(gx, gg) + first + (stages > 11 ? pass : 0.0);
+    return fused <= plain + (gx.K <= 384 ? 6.0 : 0.0);
 }
 
 }  // namespace halo
