@@ -223,7 +223,7 @@ def kernel_timings(L, it, dev, copy_gbs):
     wsq = torch.empty((max(1, lib.halo_hadamard_quant_workspace_bytes(b, n, 0, hb)),), dtype=torch.uint8, device=dev)
     add_hbm("hadamard_quant_rows(E,fold=s_w%s)" % (",left" if hb else ""), lambda i: (lambda: binding.halo_hadamard_quant(
         srcs[i], had_block_left=hb, fold=state.s_w, out_q=qs[i], out_scale=ss[i], workspace=wsq)), nbytes, k,
-        passes="left-hand rotation: two strided passes with an fp32 intermediate, then the row quantiser" if hb else None)
+        passes="left-hand rotation: one pass of up to eleven strides into an fp32 intermediate, the others in the row quantiser" if hb else None)
     qts = [torch.empty((n, b), dtype=torch.int8, device=dev) for _ in range(k)]
     sts = [torch.empty((n,), dtype=torch.float32, device=dev) for _ in range(k)]
     wsc = torch.empty((max(256, lib.halo_hadamard_quant_workspace_bytes(b, n, 1, 0)),), dtype=torch.uint8, device=dev)
@@ -248,7 +248,7 @@ def kernel_timings(L, it, dev, copy_gbs):
                               device=dev)
             add_hbm(nm, lambda i, accs=accs, outs=outs, scale=scale, wsu=wsu, left=left: (lambda: binding.halo_dequant_unrotate(
                 accs[i], scale, had_block=hm, had_block_left=left, out=outs[i], workspace=wsu)), nbytes, k,
-                passes=("stand-alone entry point: strided passes from the int32 accumulators, then the row pass; inside the "
+                passes=("stand-alone entry point: one or two passes from the int32 accumulators, then the row pass; inside the "
                         "layer the product's epilogue runs the eight low strides and one strided pass is left") if left else None)
             del accs, outs
     return kernels
