@@ -266,18 +266,19 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
             int shared = (int)(__float_as_uint(bm) >> 23) - 127 - 4;
             shared = shared < -127 ? -127 : shared;               // the upper clamp cannot bind: exponent <= 127 - 4
             if (!(bm > 0.0f)) shared = 0;
+            // Round |x| 2^-shared to E3M2 with one addition: 2^(e + 21), e >= -2 the element's exponent, has units of 2^(e - 2) in
+            // its last place, so that the sum's low bits are the element in those units (four of them to a binade, ties to even)
+            // and its exponent field gives the rest of the code; below 2^-2 the units stay 2^-4.  No code has a negative zero:
+            // up to 2^-5 the element rounds to 0.
+            const float scale = __uint_as_float((uint32_t)(127 - shared) << 23);         // 2^-shared, 3 <= exponent field <= 254
             uint32_t code[EPL];
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
-                const float xs = __builtin_ldexpf(v[c * EPL + e], -shared);
-                const float ax = fabsf(xs);
-                uint32_t bits = __float_as_uint(ax);
-                bits += 0x000FFFFFu + ((bits >> 21) & 1u);          // round to two mantissa bits, ties to even
-                uint32_t q = (bits >> 21) - (124u << 2);            // [exponent + 3 | mantissa]
-                q = q > 31u ? 31u : q;
-                const uint32_t sub = (uint32_t)__builtin_rintf(ax * 16.0f);     // below the smallest normal: steps of 2^-4
-                q = ax < 0.25f ? sub : q;
-                code[e] = q | ((q != 0u && xs < 0.0f) ? 32u : 0u);
+                const float xs = v[c * EPL + e] * scale;
+                const float ax = __builtin_fminf(fabsf(xs), 28.0f);
+                const float pow2 = __uint_as_float(__float_as_uint(__builtin_fmaxf(ax, 0.25f)) & 0x7F800000u);
+                const uint32_t u = __float_as_uint(__builtin_fmaf(pow2, 2097152.0f, ax));
+                code[e] = (u & 15u) + (u >> 21) + (xs < -0.03125f ? 32u - 584u : 0u - 584u);     // 584 = 4 (125 + 21)
             }
             const uint32_t w0 = code[0] | (code[1] << 6) | (code[2] << 12) | (code[3] << 18) | (code[4] << 24) | (code[5] << 30);
             const uint32_t w1 = (code[5] >> 2) | (code[6] << 4) | (code[7] << 10);

@@ -47,6 +47,18 @@ def test_mx6_quantiser_zero_blocks_tiny_and_huge_values():
     quant_and_check(w, 512)
 
 
+# Every bf16 value from 0 past the largest element, both signs, under a block maximum of exponent 4 (so the shared scale is 1),
+# shifted to the ends of the scale range: ties of every binade, the first value that does not round to 0, saturation.
+@pytest.mark.parametrize("exponent", [0, 100, -100, -123])
+def test_mx6_quantiser_rounds_every_value(exponent):
+    mag = np.concatenate([[0], np.arange(0x3C00, 0x4200)]).astype(np.uint32)        # 2^-7 .. below 32
+    mag = np.concatenate([mag, np.zeros(-len(mag) % 31, np.uint32)]).reshape(-1, 31)
+    top = np.full((len(mag), 1), 0x41FF, np.uint32)                                   # 31.875
+    v = (np.concatenate([mag, top], 1) << 16).view(np.float32) * np.float32(2.0) ** np.float32(exponent)
+    row = np.concatenate([v, -v]).reshape(1, -1)
+    quant_and_check(inputs.f32_to_bf16_bits(row), 0)
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 128, 128), (200, 136, 512), (64, 300, 4096), (512, 512, 1024),
                                    (4000, 3100, 256),      # ragged, enough 256 x 256 tiles for the DMA kernel
                                    (3584, 3584, 128),      # one K step: the ring never fills
