@@ -269,7 +269,8 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
             // Round |x| 2^-shared to E3M2 with one addition: 2^(e + 21), e >= -2 the element's exponent, has units of 2^(e - 2) in
             // its last place, so that the sum's low bits are the element in those units (four of them to a binade, ties to even)
             // and its exponent field gives the rest of the code; below 2^-2 the units stay 2^-4.  No code has a negative zero:
-            // up to 2^-5 the element rounds to 0.
+            // up to 2^-5 the element rounds to 0.  Ten VALU instructions an element, which bound this kernel; sixteen, with integer
+            // rounding and a path for subnormals, took 38.5 us at 8192 x 4096 instead of 36.4, 22.8 instead of 20.6 at 4096 x 4096.
             const float scale = __uint_as_float((uint32_t)(127 - shared) << 23);         // 2^-shared, 3 <= exponent field <= 254
             uint32_t code[EPL];
 #pragma unroll
