@@ -425,9 +425,9 @@ __device__ __forceinline__ void store4(int32_t* dst, const v4i& v) {
 // Whole lines.  A lane's four dwords x and y are 16 bytes of row l % 16 of two pieces of 64 bytes that lie next to each other
 // in memory (two column tiles of fp32 or int32, two pairs of bf16 tiles).  Stored one after the other, every request writes 16
 // half lines; instead the lanes of the rows r and r + 8 trade, so that `lower` is 8 rows (r) of whole 128-byte lines, and
-// `upper` the other 8: lane l holds bytes 16 (l / 16) of piece (l / 8) % 2.
+// `upper` the other 8: lane l holds one of the four 16 bytes of piece (l / 8) % 2.
 // 4096 x 4096 x 128, int32 out (67 MB, nothing but stores): 21.4 us with half lines, 16.9 with whole ones; 4096 x 14336 x 4096
-// 229 and 214.
+// 229 and 214.  bf16 that stays in the caches: bf16_whole_lines.
 template <class V>
 __device__ __forceinline__ void whole_lines(const V& x, const V& y, V& lower, V& upper) {
 #pragma unroll
@@ -528,41 +528,45 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const Place<Cfg>& at
         });
         return;
     }
-    // bf16: the four lanes of a row hold 4 x 4 columns of each tile, 8 bytes per lane.  Two column tiles at a time are
-    // regrouped across the lanes (two row-swap instructions per dword) so that a lane holds eight consecutive columns:
-    // lane group g gets columns 8 g .. 8 g + 7 of the 32.
-    const int shift = 4 * (lane >> 4);
+    // bf16: the four lanes of a row hold 4 x 4 columns of each tile, 8 bytes per lane.  Two column tiles at a time trade across
+    // the lanes (one row-swap instruction per dword) so that a lane holds eight consecutive columns: lane groups 0 and 2 get
+    // columns 0 .. 7 and 8 .. 15 of the first tile, groups 1 and 3 those of the second.
+    const int shift = (lane >> 4) & 1 ? 12 : 0;                   // from the lane's first column of the first tile
+    const int rows_left = (int)(a.M - row_lo < 65536 ? a.M - row_lo : 65536);
     auto pair_of = [&](auto ii, auto jj) {
         constexpr int j = decltype(jj)::value;
         const v4f x = values(ii, Int<j>()), y = values(ii, Int<j + 1>());
         v4u w;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint32_t p = pack_bf16x2(x[2 * h], x[2 * h + 1]), q = pack_bf16x2(y[2 * h], y[2 * h + 1]);
-            const v2u s = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(p, q, false, false));
-            const v2u t = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(s[0], s[1], false, false));
+            const v2u t = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(pack_bf16x2(x[2 * h], x[2 * h + 1]),
+                                                                                   pack_bf16x2(y[2 * h], y[2 * h + 1]), false, false));
             w[h] = t[0];
             w[2 + h] = t[1];
         }
         return w;
     };
-    StaticFor<0, TM>::run([&](auto ii) {
+    auto row_of_tiles = [&](auto ii, auto lines) {
         constexpr int i = decltype(ii)::value;
         __builtin_amdgcn_sched_barrier(0);                        // one row of tiles at a time
         hold_accumulators<TM * TN>();
-        if constexpr (RAGGED) {
+        if constexpr (decltype(lines)::value == 0) {
             const bool row_ok = at.row0 + 16 * i < a.M;
             uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (at.row0 + 16 * i) * a.ldc + shift;
             StaticFor<0, TN / 2>::run([&](auto hh) {
                 constexpr int j = 2 * decltype(hh)::value;
                 const v4u w = pair_of(ii, Int<j>());
                 const int left = left_of(j) - shift;
+                if constexpr (RAGGED) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (row_ok && e < left) dst[at.col(j) + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                    for (int e = 0; e < 8; ++e)
+                        if (row_ok && e < left) dst[at.col(j) + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                } else {
+                    if (row_ok && left > 0) __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(dst + at.col(j)));
+                }
             });
         } else {
-            const bool ok_lo = row_lo + 16 * i < a.M, ok_up = row_lo + 16 * i + 8 < a.M;
+            const bool ok_lo = 16 * i < rows_left, ok_up = 16 * i + 8 < rows_left;
             uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (row_lo + 16 * i) * a.ldc + shift + 32 * up;
             StaticFor<0, TN / 4>::run([&](auto hh) {
                 constexpr int j = 4 * decltype(hh)::value;
@@ -573,7 +577,14 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const Place<Cfg>& at
                 if (in && ok_up) __builtin_nontemporal_store(upper, reinterpret_cast<v4u*>(dst + at.col(j) + 8 * a.ldc));
             });
         }
-    });
+    };
+    if constexpr (!RAGGED) {
+        if (a.whole_lines) {
+            StaticFor<0, TM>::run([&](auto ii) { row_of_tiles(ii, Int<1>()); });
+            return;
+        }
+    }
+    StaticFor<0, TM>::run([&](auto ii) { row_of_tiles(ii, Int<0>()); });
 }
 
 // Eight values  x <- x + s * x[partner lane]  for the row stride 2^J inside groups of 16 lanes (row_of_lane), one rounded add or subtract each (the product with
@@ -1224,8 +1235,11 @@ hipError_t launch_tiles(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = n
         tiles_m2 = (int)((a2->M + Cfg::BM - 1) / Cfg::BM);
         tiles_n2 = (int)((a2->N + Cfg::BN - 1) / Cfg::BN);
     }
-    hipLaunchKernelGGL(kern, dim3(blocks1 + (unsigned)(tiles_m2 * tiles_n2)), dim3(Cfg::NT), Cfg::LDS_BYTES, s, a, tiles_m,
-                       tiles_n, a2 ? *a2 : a, tiles_m2, tiles_n2, blocks1);
+    GemmArgs g = a, g2 = a2 ? *a2 : a;
+    g.whole_lines = bf16_whole_lines(g.M, g.N, g.ldc);
+    g2.whole_lines = bf16_whole_lines(g2.M, g2.N, g2.ldc);
+    hipLaunchKernelGGL(kern, dim3(blocks1 + (unsigned)(tiles_m2 * tiles_n2)), dim3(Cfg::NT), Cfg::LDS_BYTES, s, g, tiles_m,
+                       tiles_n, g2, tiles_m2, tiles_n2, blocks1);
     return hipGetLastError();
 }
 

@@ -37,7 +37,17 @@ struct GemmArgs {
     const float* lr_a;
     const void* lr_b;
     int lr_b_bf16;
+    int whole_lines;         // set by the launcher: bf16_whole_lines
 };
+
+// bf16 out, tiled kernel: whole 128-byte lines per store request (the trade between lanes is a tenth of the epilogue's
+// instructions) or half lines.  Whole ones pay where the stores bind, that is where C outgrows the caches, or where the pieces of
+// 64 bytes do not lie on half lines; otherwise the instructions only add up to 0.3 us.  K = 512, half against whole: 1536 x
+// 1056 5.7 us / 6.0, 512 x 4096 5.9 / 6.1, 2048 x 3072 8.0 / 8.2, 1536 x 4224 8.1 / 8.2; 1536 x 5120 10.0 / 9.0, 2048 x 4096 10.3 / 9.4,
+// 8192 x 2048 17.6 / 14.8; pitch 2320: 512 rows 6.1 / 6.4, 1024 6.6 / 6.5, 1536 7.7 / 6.8, 3072 13.4 / 10.5.
+inline bool bf16_whole_lines(int64_t rows, int64_t cols, int64_t pitch) {
+    return rows * cols >= (int64_t)(pitch % 32 == 0 ? 7 : 2) << 20;
+}
 
 inline int ilog2_exact(int64_t v) {
     int l = 0;

@@ -20,18 +20,22 @@ GemmArgs product(long M, long N, long K) {
     return g;
 }
 
-// each line: `one M N K`, `pair M N K M N K` or `left tokens in out right-block left-block both-products rank`
+// each line: `one M N K`, `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?) or `left tokens in out right-block left-block both-products rank`
 int main() {
     char what[8];
     while (std::scanf("%7s", what) == 1) {
         long v[7];
-        const int count = what[0] == 'o' ? 3 : what[0] == 'p' ? 6 : 7;
+        const int count = what[0] == 'o' || what[0] == 'b' ? 3 : what[0] == 'p' ? 6 : 7;
         for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
         if (what[0] == 'l') {
             GemmArgs gx = product(v[0], v[1], v[2]);
             const GemmArgs gg = product(v[2], v[1], v[0]);
             if (v[6]) { gx.lr_rank = (int)v[6]; gx.acc_out = nullptr; gx.C = &somewhere; gx.c_is_f32 = 1; }
             std::printf("%d\n", (int)left_in_epilogue(gx, v[5] ? &gg : nullptr, (int32_t)v[4], (int32_t)v[3]));
+            continue;
+        }
+        if (what[0] == 'b') {
+            std::printf("%d\n", (int)bf16_whole_lines(v[0], v[1], v[2]));
             continue;
         }
         const GemmArgs a = product(v[0], v[1], v[2]), a2 = product(v[3], v[4], v[5]);
@@ -65,6 +69,19 @@ def test_shapes_of_the_small_product_tests(ask):
         assert set(single[i * per:(i + 1) * per]) == {test_gpu_gemm.SMALL_SHAPES[s][0]}, s
     pairs = ask(("pair", M, N, longest, longest, 48, N // 16 * 16) for M, N in shapes)
     assert dict(zip(shapes, pairs)) == {s: test_gpu_gemm.SMALL_SHAPES[s][1] for s in shapes}
+
+
+# rows, cols of a dense bf16 output and whether whole lines were the faster store (K = 512, 2 % and more apart, on an MI355X)
+WHOLE_LINES = [(288, 4560, False), (6880, 352, False), (1792, 1024, False), (2048, 1024, False), (512, 4096, False),
+               (1024, 1056, False), (3072, 1056, False), (512, 2320, False), (2048, 3072, False), (4096, 1536, False),
+               (1024, 5120, False), (1536, 4224, False), (1024, 14336, True), (1536, 5120, True), (2048, 4096, True),
+               (4096, 2048, True), (8192, 2048, True), (1536, 2320, True), (3072, 2320, True)]
+
+
+def test_bf16_whole_lines_where_they_are_faster(ask):
+    assert ask(("bf16", M, N, N) for M, N, faster in WHOLE_LINES) == [str(int(faster)) for M, N, faster in WHOLE_LINES]
+    lines = test_gpu_gemm.LINES
+    assert ask(("bf16", M, N, pitch) for M, N, pitch, whole in lines) == [str(int(whole)) for M, N, pitch, whole in lines]
 
 
 def left(b, m, n, hm, hb, both, rank=0):

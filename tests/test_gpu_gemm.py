@@ -69,6 +69,25 @@ def test_scaled_outputs_at_tile_edges(M, N, config, dtype):
     assert bool((out[M:] == -7).all()) and bool((out[:, N:] == -7).all())
 
 
+# bf16 outputs on both sides of the rule for whole lines (bf16_whole_lines: 2 Mi elements with a pitch off the half lines, 7 Mi
+# otherwise), every tile size, the edge tiles a few rows and columns wide.  The fp32 output of the same product is the same
+# number before its one rounding.  rows, cols, pitch, whole lines
+LINES = [(1033, 2032, 2048, False), (1033, 2032, 2056, True), (3595, 2048, 2048, True), (3583, 2048, 2080, False), (455, 16144, 16160, True)]
+
+
+@pytest.mark.parametrize("M,N,pitch,whole", LINES)
+@pytest.mark.parametrize("config", [0, 2, 4])
+def test_bf16_outputs_in_whole_and_half_lines(M, N, pitch, whole, config):
+    K = 128
+    rng = np.random.default_rng(M + N)
+    a, b = gu.to_dev(rand_codes(rng, (M, K))), gu.to_dev(rand_codes(rng, (N, K)))
+    rs = gu.to_dev(rng.uniform(1e-3, 1e-2, M).astype(np.float32)); cs = gu.to_dev(rng.uniform(1e-3, 1e-2, N).astype(np.float32))
+    outs = [torch.full((M + 1, pitch), -7.0, dtype=dtype, device=gu.DEV) for dtype in (torch.float32, torch.bfloat16)]
+    for out in outs:
+        binding.halo_gemm_i8_desc(binding.gemm_desc(a, b, trans_b=True, row_scale=rs, col_scale=cs, out=out[:M, :N], config=config))
+    assert torch.equal(outs[1], outs[0].bfloat16())
+
+
 # B as a column slice that ends with its allocation (K-strided: the last row's pitch reaches past the end): the tiled kernels
 # and the split-K kernel, N below, at and beyond a tile.
 @pytest.mark.parametrize("M,config", [(48, -1), (130, 4), (130, 2), (130, 0)])
