@@ -929,8 +929,8 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
     const float c = a.skip_norm ? 1.0f : (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block)));
     // The lowest stages in one pass over blocks of rows where the block has more than the six stages of a strided pass (or the
     // caller asks for it); the other stages in strided passes of at most six, a last one of up to seven.
-    const int low = a.only_low ? a.only_low : std::min(a.log_block, kColBlockStages);
-    const bool blocks = a.first_stage == 0 && low >= (a.only_low ? 6 : 7) && low <= std::min(a.log_block, kColBlockStages) &&
+    const int low = a.only_low ? a.only_low : left_first_pass(a.log_block, a.rows, a.cols);
+    const bool blocks = a.first_stage == 0 && low >= (a.only_low ? 6 : 7) && low <= a.log_block && low <= kColBlockStages &&
                         a.cols % 2 == 0 && a.ld_in % 2 == 0 && a.ld_out % 2 == 0 && a.ld_tmp % 2 == 0 &&
                         std::max(a.ld_in, std::max(a.ld_out, a.ld_tmp)) <= (int64_t(1) << 18);
     if ((a.only_low && !blocks) || (a.columns && (!a.only_low || a.in_kind != IN_BF16))) return hipErrorInvalidValue;

@@ -150,6 +150,22 @@ inline double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
     return t + 3.0 + 4.0 * std::min(1.0, fill);
 }
 
+// Stages, from stride 1 on, that one pass over blocks of rows takes at most.
+constexpr int kColBlockStages = 11;
+// Stages of the first pass of a left-hand rotation that runs all of its strides in passes of its own (log_block >= 7): all of
+// them where that pass alone fills the chip enough; otherwise seven or eight, which many small workgroups run, and a strided pass
+// for the rest.  A workgroup of the first pass holds 2^stages rows of 32 columns, so with eleven stages 2048 x 1024 is 32 of them.
+// Un-rotation of int32, rows x cols of one block, all stages (or eleven) in the first pass / eight / seven: 1024 x 256 10.7 us / 9.8
+// / 9.3, 1024 x 1024 12.6 / 13.0 / 12.7, 1024 x 4096 21.0 / 26.5 / 26.1, 2048 x 256 16.3 / 10.6 / 10.6, 2048 x 1024 20.8 / 18.5 /
+// 18.7, 2048 x 4096 26.6 / 34.7 / 32.7, 4096 x 1024 35.3 / 26.4 / 28.9, 8192 x 256 27.7 / 20.0 / 23.9, 4096 x 4096 63.4 / 63.5 / 59.3,
+// 8192 x 4096 127 / 131 / 119, 16384 x 4096 285 / 296 / 272.
+inline int left_first_pass(int log_block, int64_t rows, int64_t cols) {
+    if (log_block <= 9 || (log_block <= kColBlockStages && (((cols + 31) / 32) * (rows >> log_block)) >> (log_block - 5) > 0))
+        return log_block;
+    const bool large = rows * cols >= (int64_t(1) << 24);
+    return std::max(large || log_block <= kColBlockStages ? 7 : 8, log_block - (large ? 7 : 6));
+}
+
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
 // left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
 // tiles, followed by a pass over its accumulators that takes up to eleven strides, and a strided pass for the others.  gx, gg: the

@@ -105,8 +105,6 @@ struct ColFwhtArgs {
     // to columns->amax_ws [rows >> only_low][cols], for launch_col_quant_t_ready.
     const ColQuantArgs* columns;
 };
-// Stages, from stride 1 on, that one pass over blocks of rows takes at most.
-constexpr int kColBlockStages = 11;
 hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s);
 
 hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s);

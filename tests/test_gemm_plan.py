@@ -20,18 +20,23 @@ GemmArgs product(long M, long N, long K) {
     return g;
 }
 
-// each line: `one M N K`, `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?) or `left tokens in out right-block left-block both-products rank`
+// each line: `one M N K`, `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
+// `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
 int main() {
     char what[8];
     while (std::scanf("%7s", what) == 1) {
         long v[7];
-        const int count = what[0] == 'o' || what[0] == 'b' ? 3 : what[0] == 'p' ? 6 : 7;
+        const int count = what[0] == 'o' || what[0] == 'b' || what[0] == 'f' ? 3 : what[0] == 'p' ? 6 : 7;
         for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
         if (what[0] == 'l') {
             GemmArgs gx = product(v[0], v[1], v[2]);
             const GemmArgs gg = product(v[2], v[1], v[0]);
             if (v[6]) { gx.lr_rank = (int)v[6]; gx.acc_out = nullptr; gx.C = &somewhere; gx.c_is_f32 = 1; }
             std::printf("%d\n", (int)left_in_epilogue(gx, v[5] ? &gg : nullptr, (int32_t)v[4], (int32_t)v[3]));
+            continue;
+        }
+        if (what[0] == 'f') {
+            std::printf("%d\n", left_first_pass((int)v[0], v[1], v[2]));
             continue;
         }
         if (what[0] == 'b') {
@@ -82,6 +87,23 @@ def test_bf16_whole_lines_where_they_are_faster(ask):
     assert ask(("bf16", M, N, N) for M, N, faster in WHOLE_LINES) == [str(int(faster)) for M, N, faster in WHOLE_LINES]
     lines = test_gpu_gemm.LINES
     assert ask(("bf16", M, N, pitch) for M, N, pitch, whole in lines) == [str(int(whole)) for M, N, pitch, whole in lines]
+
+
+# rows, cols, left block and microseconds of the un-rotation with the first pass taking all stages (eleven at most), eight and
+# seven, on an MI355X
+FIRST_PASS = [(512, 256, 512, 7.9, 8.8, 8.3), (512, 4096, 512, 13.2, 18.3, 18.1), (1024, 256, 1024, 10.7, 9.8, 9.3),
+              (1024, 1024, 1024, 12.6, 13.0, 12.7), (1024, 4096, 1024, 21.0, 26.5, 26.1), (2048, 64, 2048, 16.0, 9.5, 9.4),
+              (2048, 256, 2048, 16.3, 10.6, 10.6), (2048, 1024, 2048, 20.8, 18.5, 18.7), (2048, 4096, 2048, 26.6, 34.7, 32.7),
+              (4096, 256, 4096, 22.0, 14.0, 14.4), (4096, 1024, 4096, 35.3, 26.4, 28.9), (4096, 4096, 4096, 63.4, 63.5, 59.3),
+              (8192, 512, 8192, 34.9, 27.3, 31.6), (8192, 4096, 8192, 126.6, 131.1, 118.9), (4096, 256, 2048, 17.9, 13.5, 13.2),
+              (8192, 1024, 2048, 26.8, 33.3, 33.0), (8192, 256, 1024, 16.5, 19.0, 18.7), (16384, 4096, 16384, 284.5, 296.4, 272.4)]
+
+
+def test_the_first_pass_of_a_left_hand_rotation_is_the_faster_one(ask):
+    said = ask(("first", hb.bit_length() - 1, rows, cols) for rows, cols, hb, *us in FIRST_PASS)
+    for (rows, cols, hb, whole, eight, seven), stages in zip(FIRST_PASS, said):
+        us = {min(hb.bit_length() - 1, 11): whole, 8: eight, 7: seven}
+        assert us[int(stages)] <= 1.04 * min(us.values()), (rows, cols, hb, stages)
 
 
 def left(b, m, n, hm, hb, both, rank=0):

@@ -111,7 +111,7 @@ def test_left_hadamard_fold_row_quant_bit_exact(rows, cols, hbl):
 # strides in the row quantiser, or strided passes (more of them, or rows too long); several blocks, column counts off the
 # tile, rows further apart than they are long, fp32 input.
 @pytest.mark.parametrize("rows,cols,hbl", [(384, 36, 128), (512, 100, 256), (1024, 4, 512), (3072, 32, 1024), (4096, 68, 2048),
-                                           (8192, 1028, 4096), (8192, 1040, 512), (8192, 1040, 1024),
+                                           (8192, 1028, 4096), (8192, 1040, 512), (8192, 1040, 1024), (8192, 2052, 4096),
                                            (16384, 24, 8192), (16384, 40, 16384), (4096, 16400, 4096),
                                            (65536, 16, 65536)])
 @pytest.mark.parametrize("f32", [False, True])
@@ -185,7 +185,9 @@ def test_quant_dual_matches_both_single_quantisers(rows, cols):
 
 UNROT_CASES = [(64, 512, 512, 0), (33, 4096, 4096, 0), (8, 14336, 2048, 0), (256, 1024, 1024, 256),
                (4096, 256, 256, 4096), (50, 96, 0, 0), (2048, 512, 0, 2048), (384, 36, 0, 128), (2048, 100, 4, 1024), (1024, 64, 0, 512),
-               (8192, 32, 32, 8192)]
+               (8192, 32, 32, 8192),
+               (2048, 544, 32, 1024), (4096, 1028, 4, 2048),      # ten and eleven strides in one pass
+               (1024, 36, 4, 1024), (16384, 12, 4, 16384), (32768, 20, 4, 32768)]
 
 
 @pytest.mark.parametrize("rows,cols,hb,hbl", UNROT_CASES)
