@@ -517,6 +517,24 @@ col_amax_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols, c
     }
 }
 
+// The columns' maxima out of `parts` vectors of partial ones, left in the first vector; 64 columns per workgroup, which are read
+// and written by it alone.
+__global__ void __launch_bounds__(1024)
+col_part_max_kernel(float* part, int parts, int64_t cols) {
+    __shared__ float s_part[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t col = (int64_t)blockIdx.x * 64 + lane;
+    float m = 0.0f;
+    if (col < cols)
+        for (int q = wave; q < parts; q += 16) m = fmaxf(m, part[(int64_t)q * cols + col]);
+    s_part[wave][lane] = m;
+    __syncthreads();
+    if (wave != 0 || col >= cols) return;
+#pragma unroll
+    for (int w = 1; w < 16; ++w) m = fmaxf(m, s_part[w][lane]);
+    part[col] = m;
+}
+
 // Quantise a 128(rows) x 128(cols) tile and write it transposed.  Codes of four consecutive rows are packed
 // into one dword per column, staged in LDS as [col][row/4] with a pitch of 33 dwords, and read back as
 // 16 consecutive rows per lane so that every output row is written in full 128-byte lines.
@@ -1062,6 +1080,12 @@ hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_am
 
 hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0) return hipSuccess;
+    if (column_maxima_first(a.rows, a.cols, parts)) {
+        hipLaunchKernelGGL(col_part_max_kernel, dim3((unsigned)((a.cols + 63) / 64)), dim3(1024), 0, s, a.amax_ws, parts, a.cols);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        parts = 1;
+    }
     const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
     hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
                        a.rows, a.cols, a.fold, static_cast<const float*>(a.amax_ws), parts, a.out_q, a.ld_q, a.out_scale,

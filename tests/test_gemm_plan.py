@@ -21,12 +21,12 @@ GemmArgs product(long M, long N, long K) {
 }
 
 // each line: `one M N K`, `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
-// `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
+// `max rows cols parts` (column maxima reduced first?), // `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
 int main() {
     char what[8];
     while (std::scanf("%7s", what) == 1) {
         long v[7];
-        const int count = what[0] == 'o' || what[0] == 'b' || what[0] == 'f' ? 3 : what[0] == 'p' ? 6 : 7;
+        const int count = what[0] == 'o' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' ? 3 : what[0] == 'p' ? 6 : 7;
         for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
         if (what[0] == 'l') {
             GemmArgs gx = product(v[0], v[1], v[2]);
@@ -37,6 +37,10 @@ int main() {
         }
         if (what[0] == 'f') {
             std::printf("%d\n", left_first_pass((int)v[0], v[1], v[2]));
+            continue;
+        }
+        if (what[0] == 'm') {
+            std::printf("%d\n", (int)column_maxima_first(v[0], v[1], v[2]));
             continue;
         }
         if (what[0] == 'b') {
@@ -104,6 +108,22 @@ def test_the_first_pass_of_a_left_hand_rotation_is_the_faster_one(ask):
     for (rows, cols, hb, whole, eight, seven), stages in zip(FIRST_PASS, said):
         us = {min(hb.bit_length() - 1, 11): whole, 8: eight, 7: seven}
         assert us[int(stages)] <= 1.04 * min(us.values()), (rows, cols, hb, stages)
+
+
+# tokens, out-features, left block, microseconds of the level-2 backward pass with the column maxima read by every tile and
+# reduced first, on an MI355X
+COLUMN_MAXIMA = [(960, 4096, 64, 52.9, 55.1), (2112, 1536, 64, 47.4, 48.2), (2112, 14336, 64, 180.7, 178.5), (4160, 4096, 64, 93.7, 86.4),
+                 (8128, 512, 64, 78.3, 76.6), (8128, 4096, 64, 189.6, 167.2), (1920, 4096, 128, 54.4, 55.8),
+                 (8064, 4096, 128, 164.4, 153.2), (7936, 512, 256, 65.8, 65.7), (8192, 1536, 512, 87.2, 88.2),
+                 (8192, 4096, 512, 156.6, 154.9), (8192, 4096, 2048, 166.9, 168.2)]
+
+
+def test_column_maxima_are_reduced_first_where_that_is_faster(ask):
+    said = ask(("max", b, n, b // hb) for b, n, hb, *us in COLUMN_MAXIMA)
+    for (b, n, hb, *us), first in zip(COLUMN_MAXIMA, said):
+        assert us[int(first)] <= 1.01 * min(us), (b, n, hb)
+    lines = test_gpu_linear.MAXIMA          # the first pass takes 64 or 128 rows, or up to 2048 of them
+    assert ask(("max", b, n, b // hb) for b, n, hb, first in lines) == [str(int(first)) for b, n, hb, first in lines]
 
 
 def left(b, m, n, hm, hb, both, rank=0):

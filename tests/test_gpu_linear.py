@@ -120,8 +120,13 @@ def test_level2_output_side_variants(b, m, n, hm, hb, odt):
     run_and_check(b, m, n, 2, Xb, Wb, Eb, odt=odt, hm=hm, hb=hb)
 
 
-@pytest.mark.parametrize("b,n,hb", [(1920, 80, 128), (2112, 48, 64), (6144, 144, 2048), (8192, 16, 4096)])
-def test_level2_column_maxima_from_several_row_blocks(b, n, hb):
+# tokens, out-features, left block, and whether a launch of its own reduces the partial maxima (test_gemm_plan.py asserts it)
+MAXIMA = [(1920, 80, 128, False), (2112, 48, 64, False), (6144, 144, 2048, False), (8192, 16, 4096, False), (7744, 400, 64, True),
+          (8064, 656, 128, True)]
+
+
+@pytest.mark.parametrize("b,n,hb,first", MAXIMA)
+def test_level2_column_maxima_from_several_row_blocks(b, n, hb, first):
     """The column quantiser takes its maxima from the partial ones of each row block of the left-hand rotation's first pass."""
     Xb = inputs.make_activations(b, 256, 0.01, b); Wb = inputs.make_weights(n, 256, b); Eb = inputs.make_errors(b, n, b)
     run_and_check(b, 256, n, 2, Xb, Wb, Eb, hb=hb)
