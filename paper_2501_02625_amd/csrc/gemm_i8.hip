@@ -918,12 +918,11 @@ gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, 
 
 // ------------------------------------------------------------------------------------------------ small products
 // Products with too few 128 x 128 tiles to fill the chip: what bounds them is latency (of the first loads, of every unit of
-// K, of the launch), not the matrix pipes.  A workgroup computes a 16 TM x 64 tile and its four wavefronts SPLIT K: wavefront
-// w takes the units w, w + 4, ...  Each has an LDS ring of its own (three stages of A and B, filled and laid out as in the
-// main kernel), so there is no barrier in the loop and three units are in flight per wavefront from the start.  The four
-// partial sums meet in LDS at the end, where every thread also picks up consecutive columns for the store.
-// TM = 1 is for at most 16 rows (decode).  Tiles of 16 or 32 columns are for products whose 64-column tiles would leave compute
-// units idle: there the rate at which the K-contiguous B arrives is the bound, and every compute unit has to fetch (launch_small_by_columns).
+// K, of the launch), not the matrix pipes.  A workgroup computes a 16 TM x 16 TN tile and its four wavefronts SPLIT K: wavefront
+// w takes the units w, w + 4, ...  Each has an LDS ring of its own (two to eight stages of A and B, as many as LDS holds, filled
+// and laid out as in the main kernel), so there is no barrier in the loop and all but one of the stages are in flight per wavefront
+// from the start.  The four partial sums meet in LDS at the end, where every thread also picks up consecutive columns for the store.
+// TM = 1 is for at most 16 rows (decode).  Tiles of 16 or 32 columns (TM up to 2, K-contiguous B): small_tile_columns.
 template <int TM, int TN_, bool TRANSB>
 struct SmallCfg {
     static constexpr int BM = 16 * TM, TN = TN_, BN = 16 * TN, BK = 128, SPLIT = 4;
@@ -972,8 +971,19 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
         }
     }
     const int64_t b_unit = TRANSB ? (int64_t)BK : (int64_t)BK * a.ldb;
-    v4u abuf = make_buffer(a.A + m0 * a.lda + wave * BK);
-    v4u bbuf = make_buffer((TRANSB ? a.B + n0 * a.ldb : a.B + n0) + wave * b_unit);
+    const int units = (int)((a.K + Cfg::SPLIT * BK - 1) / (Cfg::SPLIT * BK));
+    // 32-column tiles of a B whose rows lie a multiple of 8 KB apart: the tiles start at different K and go round, because at one
+    // K all rows lie in the same few memory channels.  16 x 8192 x 8192, B in the caches 16.5 -> 12.5 us, from memory 17.5 -> 15.2;
+    // 16 x 8192 x 16384 30.4 -> 22.1.  At other pitches, and with 16 columns, all tiles at one K are as fast or faster (16 x 4096 x
+    // 8192 from memory 10.2 us, going round 13.3).
+    constexpr bool ROUND = TRANSB && TN == 2;
+    int first = 0;
+    if constexpr (ROUND) {
+        if (a.ldb % 8192 == 0 && a.K % (Cfg::SPLIT * BK) == 0) first = (int)(bid % tiles_n % (unsigned)units);
+    }
+    int to_end = units - first;
+    v4u abuf = make_buffer(a.A + m0 * a.lda + wave * BK + first * (Cfg::SPLIT * BK));
+    v4u bbuf = make_buffer((TRANSB ? a.B + n0 * a.ldb : a.B + n0) + wave * b_unit + first * (Cfg::SPLIT * BK));
     int64_t left = a.K - wave * BK;
     auto trim = [&]() {
         if (left >= BK) return;
@@ -992,8 +1002,13 @@ gemm_i8_small_kernel(GemmArgs a, int tiles_n, GemmArgs a2, int tiles_n2, unsigne
         advance(abuf, Cfg::SPLIT * BK);
         advance(bbuf, Cfg::SPLIT * b_unit);
         left -= Cfg::SPLIT * BK;
+        if constexpr (ROUND) {
+            if (--to_end == 0 && first != 0) {
+                advance(abuf, -a.K);
+                advance(bbuf, -a.K);
+            }
+        }
     };
-    const int units = (int)((a.K + Cfg::SPLIT * BK - 1) / (Cfg::SPLIT * BK));
 #pragma unroll
     for (int i = 0; i + 1 < NS; ++i) request(i);
 
@@ -1261,14 +1276,12 @@ hipError_t launch_small(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = n
     return hipGetLastError();
 }
 
-// Narrower tiles while all of them still run at once, one per compute unit: with B from memory (not the
-// caches), 64 columns and three ring stages against the narrow tile and up to eight: 16 x 4096 x 4096 9.8 -> 7.1 us, 16 x 4096 x
-// 14336 24.9 -> 13.7, 32 x 4096 x 4096 11.3 -> 8.0, 16 x 8192 x 4096 11.1 -> 10.3, 128 x 512 x 512 4.0 -> 3.2.
 template <int TM, bool TRANSB>
 hipError_t launch_small_by_columns(const GemmArgs& a, hipStream_t s) {
     if constexpr (TRANSB) {
-        if (tiles_of(a, 16 * TM, 16) <= kComputeUnits) return launch_small<TM, true, 1>(a, s);
-        if (tiles_of(a, 16 * TM, 32) <= kComputeUnits) return launch_small<TM, true, 2>(a, s);
+        const int columns = small_tile_columns(a);
+        if (columns == 16) return launch_small<TM, true, 1>(a, s);
+        if (columns == 32) return launch_small<TM, true, 2>(a, s);
     }
     return launch_small<TM, TRANSB>(a, s);
 }

@@ -118,7 +118,7 @@ inline double pair_cost(const GemmArgs& a1, const GemmArgs& a2, int config) {
 }
 
 // The configuration of one product, or of a pair (a2).  A product whose 32 x 64 (64 x 64) tiles fit the compute units once
-// goes to the small kernel: 16 x 4096 x 4096 5.5 us warm, 7.2 cold (128 x 128 tiles: 15.7, 18), 256 x 1024 x 512 4.3 (6.3),
+// goes to the small kernel: 16 x 4096 x 4096 4.9 us warm, 7.2 cold (128 x 128 tiles: 15.7, 18), 256 x 1024 x 512 4.3 (6.3),
 // 256 x 4096 x 4096 10.3 (16.3), 1024 x 1024 x 1024 6.4 (7.8); at twice as many tiles it is level with the 128 x 128 tiles or
 // behind.  A pair takes 128 x 128 tiles where their estimate is 15 % lower: the estimate of a full chip of 128 x 128 tiles is
 // too high by about as much as that of a part-filled one of 256 x 256 (measured, 256 x 256 against 128 x 128: two of 4096 x 4096
@@ -135,6 +135,20 @@ inline int choose_config(const GemmArgs& a, const GemmArgs* a2) {
     for (const int c : {kTiles256x128, kTiles128})
         if (product_cost(a, c) < product_cost(a, best)) best = c;
     return best;
+}
+
+// Columns of the small kernel's tiles of 16 and 32 rows (kSmall32), one product with a K-contiguous B: 16 or 32 instead of 64 while
+// all tiles still run at once, one per compute unit.  There the rate at which B arrives is the bound, and every compute unit has to
+// fetch; narrow tiles also leave room for more ring stages.  They read A two or four times as often, which stays in the caches.
+// 64 columns against the narrow tile, B from memory: 16 x 4096 x 4096 9.8 us / 7.2, 16 x 4096 x 14336 25.8 / 14.8, 32 x 4096 x
+// 4096 10.8 / 8.0, 64 x 4096 x 4096 10.9 / 8.9, 128 x 2048 x 4096 7.8 / 6.5, 16 x 8192 x 4096 11.2 / 10.5.  With B in the caches:
+// 16 x 4096 x 4096 5.4 / 4.9, 32 x 4096 x 4096 6.5 / 6.1, 128 x 2048 x 4096 6.5 / 5.9, 16 x 8192 x 4096 6.6 / 6.3; of 176 shapes, 16 .. 128
+// rows by 1024 .. 14336 by 2048 .. 14336, each both ways, 64 x 4096 x 4096 alone is more than 2 % slower, 6.7 / 7.0; of others tried, 16 x 8192 x 8064 (12.8 / 13.5; from
+// memory 17.6 / 14.7).
+inline int small_tile_columns(const GemmArgs& a) {
+    if (!a.transB) return 64;
+    const int rows = a.M <= 16 ? 16 : 32;
+    return tiles_of(a, rows, 16) <= kComputeUnits ? 16 : tiles_of(a, rows, 32) <= kComputeUnits ? 32 : 64;
 }
 
 // Estimated microseconds of launch_gemm_i8(a) / launch_gemm_i8_pair(a, *a2), for choices between ways to split the work.

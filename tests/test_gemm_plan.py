@@ -20,13 +20,13 @@ GemmArgs product(long M, long N, long K) {
     return g;
 }
 
-// each line: `one M N K`, `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
+// each line: `one M N K`, `small M N K` (columns of the small tiles), `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
 // `max rows cols parts` (column maxima reduced first?), // `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
 int main() {
     char what[8];
     while (std::scanf("%7s", what) == 1) {
         long v[7];
-        const int count = what[0] == 'o' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' ? 3 : what[0] == 'p' ? 6 : 7;
+        const int count = what[0] == 'o' || what[0] == 's' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' ? 3 : what[0] == 'p' ? 6 : 7;
         for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
         if (what[0] == 'l') {
             GemmArgs gx = product(v[0], v[1], v[2]);
@@ -37,6 +37,12 @@ int main() {
         }
         if (what[0] == 'f') {
             std::printf("%d\n", left_first_pass((int)v[0], v[1], v[2]));
+            continue;
+        }
+        if (what[0] == 's') {
+            GemmArgs g = product(v[0], v[1], v[2]);
+            g.transB = 1;
+            std::printf("%d\n", choose_config(g, nullptr) == kSmall32 ? small_tile_columns(g) : 0);
             continue;
         }
         if (what[0] == 'm') {
@@ -78,6 +84,12 @@ def test_shapes_of_the_small_product_tests(ask):
         assert set(single[i * per:(i + 1) * per]) == {test_gpu_gemm.SMALL_SHAPES[s][0]}, s
     pairs = ask(("pair", M, N, longest, longest, 48, N // 16 * 16) for M, N in shapes)
     assert dict(zip(shapes, pairs)) == {s: test_gpu_gemm.SMALL_SHAPES[s][1] for s in shapes}
+
+
+def test_columns_of_the_small_tiles(ask):
+    shapes = test_gpu_gemm.NARROW_SHAPES
+    assert dict(zip(shapes, map(int, ask(("small", M, N, 4368) for M, N in shapes)))) == shapes
+    assert set(ask(("small", M, N, K) for M, N, K, pitch in test_gpu_gemm.ROUND_SHAPES)) == {"32"}
 
 
 # rows, cols of a dense bf16 output and whether whole lines were the faster store (K = 512, 2 % and more apart, on an MI355X)

@@ -139,9 +139,17 @@ def test_small_products(M, N, K, trans_b):
         gu.assert_codes_equal(acc2, orc.gemm_codes(b[:, :N // 16 * 16], g[:N // 16 * 16]), "accumulators, second of a pair")
 
 
+# M, N of test_small_products_narrow_tiles and the columns of the tile that the rule takes (test_gemm_plan.py)
+NARROW_SHAPES = {(1, 16): 16, (16, 4090): 16, (16, 4104): 32, (13, 8200): 64, (17, 2040): 16, (32, 4088): 16, (32, 4104): 32,
+                 (100, 500): 16, (128, 2030): 32}
+# M, N, K, pitch: tiles of 32 columns that start at different K (small kernel), one unit per wavefront and several, fewer than the
+# ring's stages and more
+ROUND_SHAPES = [(16, 8192, 8192, 8192), (13, 8100, 512, 8192), (32, 5100, 1536, 16384), (48, 4096, 6656, 8192), (128, 2030, 4608, 8192)]
+
+
 # The small kernel's tiles of 16, 32 and 64 columns (as many as run at once), with ragged rows and columns, K shorter than the
 # ring and longer than one trip through it, every output.
-@pytest.mark.parametrize("M,N", [(1, 16), (16, 4090), (16, 4104), (13, 8200), (17, 2040), (32, 4088), (32, 4104), (100, 500)])
+@pytest.mark.parametrize("M,N", sorted(NARROW_SHAPES))
 @pytest.mark.parametrize("K", [16, 656, 4368])
 def test_small_products_narrow_tiles(M, N, K):
     rng = np.random.default_rng(M + N + K)
@@ -159,6 +167,17 @@ def test_small_products_narrow_tiles(M, N, K):
         binding.halo_gemm_i8(ad, bd, trans_b=True, row_scale=gu.to_dev(rs), col_scale=gu.to_dev(cs), out=out[:M, :N])
         check(out[:M, :N], orc.dequantize(want, rs, cs), "scaled output")
         assert bool((out[M:] == -7).all()) and bool((out[:, N:] == -7).all())
+
+
+@pytest.mark.parametrize("M,N,K,pitch", ROUND_SHAPES)
+def test_small_products_that_go_round_k(M, N, K, pitch):
+    rng = np.random.default_rng(M + N + K)
+    a = rand_codes(rng, (M, K)); b = rand_codes(rng, (N, K))
+    bd = torch.full((N, pitch), 77, dtype=torch.int8, device=gu.DEV)
+    bd[:, :K] = gu.to_dev(b)
+    acc = torch.full((M, (N + 3) // 4 * 4), -7, dtype=torch.int32, device=gu.DEV)
+    binding.halo_gemm_i8_desc(binding.gemm_desc(gu.to_dev(a), bd[:, :K], trans_b=True, acc_out=acc[:, :N]))
+    gu.assert_codes_equal(acc[:, :N], orc.gemm_codes(a, b.T), "accumulators")
 
 
 # Every tile configuration on shapes its K step divides (ragged M and N, several trips through the ring), through
