@@ -336,16 +336,10 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
     }
 }
 
-// Wavefronts that a SIMD should hold: the bf16 kernels on long segments would take a few registers more than four (six) of
-// them leave, for their guarded path.  8192 x 14336 in blocks of 2048: 88 -> 79 us; 8192 x 4096 in blocks of 4096: 30.9 -> 28.5.
-constexpr int waves_per_simd(int logseg, int in, int lb) {
-    return in == IN_BF16 && lb == logseg ? (logseg == 12 ? 4 : logseg == 11 ? 6 : 1) : 1;
-}
-
 // LB: log2 of the Hadamard block when it is 0 (no rotation) or LOGSEG (block = segment); -1 = read it at run time.
 // XS: number of butterfly stages that span wavefronts (Hadamard block = 2^(LOGSEG+XS) elements = 2^XS segments).
 template <int LOGSEG, int IN, int OUT, int LB, int XS = 0>
-__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024, waves_per_simd(LOGSEG, IN, LB))
+__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024)
 row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigned blocks1) {
     constexpr int LOGE = (IN == IN_BF16) ? 3 : 2;
     constexpr int EPL = 1 << LOGE;            // consecutive elements per lane per chunk
@@ -377,9 +371,20 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     x.kbase = (int64_t)seg * SEG + (int64_t)x.lane * EPL;
     const bool fast = x.row_ok && ((int64_t)(seg + 1) * SEG <= a.cols);   // uniform over the wavefront
 
+    // A block that is the segment divides the row: a wavefront has a whole segment or, past the last row, nothing.  Without a
+    // guarded path the bf16 kernels fit the registers that four (4096) and eight or seven wavefronts (2048) of a SIMD leave, with none
+    // in scratch memory; a bound on the registers alone left 3 to 8 of them there.  8192 x 14336 in blocks of 2048, quantised to
+    // INT8: 82 us with neither, 69 with the bound, 67 so; 4096 x 8192 in blocks of 4096 23.8, 23.0, 21.2.  Shorter segments need no more
+    // registers than they have; their guarded path stays (with 1024 it is 1 % faster).
+    constexpr bool WHOLE = LB >= 11 && LB == LOGSEG;
     float v[VPL];
-    float amax = fast ? row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v)
-                      : row_phase1<LOGSEG, IN, OUT, false, LB, XS>(a, x, c_norm, v);
+    float amax = 0.0f;
+    if constexpr (WHOLE) {
+        if (fast) amax = row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v);
+    } else {
+        amax = fast ? row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v)
+                    : row_phase1<LOGSEG, IN, OUT, false, LB, XS>(a, x, c_norm, v);
+    }
 
     float inv_l = 0.0f;
     if constexpr (OUT == OUT_Q8) {
@@ -402,7 +407,7 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
         if (x.row_ok && seg == 0 && x.lane == 0) a.out_scale[x.row] = nz ? amax / 127.0f : 1.0f;
     }
     if (fast) row_phase2<LOGSEG, IN, OUT, true>(a, x, v, inv_l);
-    else row_phase2<LOGSEG, IN, OUT, false>(a, x, v, inv_l);
+    else if constexpr (!WHOLE) row_phase2<LOGSEG, IN, OUT, false>(a, x, v, inv_l);
 }
 
 // Hadamard block of 2^(10+XS) elements handled by 2^XS wavefronts of 1024 elements each: four times the
