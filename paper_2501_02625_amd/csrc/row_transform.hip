@@ -450,11 +450,13 @@ hipError_t launch_one(const RowArgs& a, int segs, hipStream_t s) {
 template <int IN, int OUT>
 hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
     // Split blocks of 2048 / 4096 over 2 / 4 wavefronts (measured): the 32-bit-input un-rotation gains at every size
-    // for 4096-blocks (5.7 vs 5.2 TB/s at 32768 rows, 12.7 vs 16.0 us at 2048 rows); the quantiser only when whole
-    // rows would leave the 1024 SIMDs with fewer than four wavefronts each.
+    // for 4096-blocks (5.7 vs 5.2 TB/s at 32768 rows, 12.7 vs 16.0 us at 2048 rows); the others, and 2048-blocks of the paired
+    // un-rotation, when whole rows would leave the 1024 SIMDs with fewer than four wavefronts each (level-2 backward, 2048
+    // in-features, 256 tokens by 256 22.6 -> 21.9 us, 1024 by 2048 51.6 -> 51.0, 4096 by 512 90.1 either way).
     if ((a.log_block == 11 || a.log_block == 12) && a.cols % 1024 == 0 && a.cols <= 16384) {
         const int64_t wavefronts_unsplit = (a.rows + a.rows2) * (a.cols >> a.log_block);
-        const bool want = IN == IN_I32 || IN == IN_F32_I32 ? a.log_block == 12 : wavefronts_unsplit < 4096;
+        const bool few = wavefronts_unsplit < 4096;
+        const bool want = IN == IN_I32 ? a.log_block == 12 : IN == IN_F32_I32 ? a.log_block == 12 || few : few;
         if (want) return a.log_block == 11 ? launch_split<IN, OUT, 1>(a, s) : launch_split<IN, OUT, 2>(a, s);
     }
     // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).

@@ -113,6 +113,8 @@ def test_small_layers_all_levels(b, m, n, level):
     (512, 4096, 64, 0, 0, torch.float32),          # right block 4096 (64 values per lane)
     (4096, 4096, 128, 0, 0, torch.bfloat16),       # four top strides, right block 4096
     (2048, 8192, 64, 4096, 1024, torch.float32),   # two left blocks of 1024, two right blocks of 4096
+    (272, 2048, 48, 0, 0, torch.float32),          # right block 2048, both un-rotations in one launch: a block per two wavefronts,
+    (4224, 2048, 32, 0, 0, torch.float32),         # and with more rows a block per wavefront
 ])
 def test_level2_output_side_variants(b, m, n, hm, hb, odt):
     """Level 2: left and right blocks of every size, whichever way the rule sends their un-rotation."""
