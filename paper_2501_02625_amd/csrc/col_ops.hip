@@ -409,7 +409,9 @@ hipError_t launch_col_block_by_rows(int logr, const void* in, int64_t ld_in, flo
         a.row_scale = q->fold; a.side_part = q->amax_ws; a.side_q = q->out_q; a.ld_q = q->ld_q; a.side_scale = q->out_scale;
     }
     switch (logr) {
-        case 6: return launch_col_block<6, IN, SIDE>(a, s);
+        case 6:
+            if constexpr (SIDE != kSideNone) return launch_col_block<6, IN, SIDE>(a, s);
+            else return hipErrorInvalidValue;
         case 7: return launch_col_block<7, IN, SIDE>(a, s);
         case 8: return launch_col_block<8, IN, SIDE>(a, s);
         case 9: return launch_col_block<9, IN, SIDE>(a, s);
@@ -948,7 +950,7 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s) {
     // The lowest stages in one pass over blocks of rows where the block has more than the six stages of a strided pass (or the
     // caller asks for it); the other stages in strided passes of at most six, a last one of up to seven.
     const int low = a.only_low ? a.only_low : left_first_pass(a.log_block, a.rows, a.cols);
-    const bool blocks = a.first_stage == 0 && low >= (a.only_low ? 6 : 7) && low <= a.log_block && low <= kColBlockStages &&
+    const bool blocks = a.first_stage == 0 && low >= (a.columns ? 6 : 7) && low <= a.log_block && low <= kColBlockStages &&
                         a.cols % 2 == 0 && a.ld_in % 2 == 0 && a.ld_out % 2 == 0 && a.ld_tmp % 2 == 0 &&
                         std::max(a.ld_in, std::max(a.ld_out, a.ld_tmp)) <= (int64_t(1) << 18);
     if ((a.only_low && !blocks) || (a.columns && (!a.only_low || a.in_kind != IN_BF16))) return hipErrorInvalidValue;

@@ -435,10 +435,12 @@ hipError_t launch_one(const RowArgs& a, int segs, hipStream_t s) {
     const int64_t blocks1 = (a.rows + rows_per_wg - 1) / rows_per_wg;
     const int64_t blocks = blocks1 + (a.rows2 + rows_per_wg - 1) / rows_per_wg;
     const float c_norm = a.log_block > 0 ? (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block))) : 1.0f;
-    if (a.log_block == 0)
-        hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 0>), dim3((unsigned)blocks), dim3(threads), 0, s,
-                           a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
-    else if (a.log_block == LOGSEG)
+    if (a.log_block == 0) {
+        if constexpr (IN == IN_F32_I32) return hipErrorInvalidValue;      // only the paired un-rotation, which has a block
+        else
+            hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 0>), dim3((unsigned)blocks), dim3(threads), 0, s,
+                               a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
+    } else if (a.log_block == LOGSEG)
         hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, LOGSEG>), dim3((unsigned)blocks), dim3(threads), 0, s,
                            a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
     else
