@@ -130,6 +130,31 @@ def test_left_rotation_block_sizes_and_edges(rows, cols, hbl, f32):
     assert bool((q[:, cols:] == 99).all())
 
 
+# Rows so far apart that the first pass is a strided one from stride 1 on: six stages, then the others, up to seven.
+@pytest.mark.parametrize("rows,hbl", [(256, 128), (1024, 1024), (8192, 8192)])
+def test_left_rotation_of_rows_far_apart(rows, hbl):
+    cols, pitch = 24, (1 << 18) + 8
+    e = inputs.make_errors(rows, cols, rows)
+    wide = torch.empty((rows, pitch), dtype=torch.bfloat16, device=gu.DEV)
+    wide[:, :cols] = gu.bits_to_dev(e)
+    q, s = binding.halo_hadamard_quant(wide[:, :cols], had_block_left=hbl)
+    wq, ws = oracle_row_quant(orc.bf16_bits_to_real(e), 0, hbl, None)
+    gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
+
+
+@pytest.mark.parametrize("rows,hbl", [(384, 128), (1024, 1024)])
+def test_dequant_unrotate_of_rows_far_apart(rows, hbl):
+    cols, pitch = 36, (1 << 18) + 4
+    rng = np.random.default_rng(rows)
+    acc = rng.integers(-(1 << 27), 1 << 27, size=(rows, cols), dtype=np.int32)
+    scale = (np.abs(rng.standard_normal(rows)) * 1e-6 + 1e-8).astype(np.float32)
+    wide = torch.empty((rows, pitch), dtype=torch.int32, device=gu.DEV)
+    wide[:, :cols] = gu.to_dev(acc)
+    near = binding.halo_dequant_unrotate(gu.to_dev(acc), gu.to_dev(scale), had_block_left=hbl, out_dtype=torch.float32)
+    far = binding.halo_dequant_unrotate(wide[:, :cols], gu.to_dev(scale), had_block_left=hbl, out_dtype=torch.float32)
+    assert torch.equal(near, far)
+
+
 COLT_CASES = [(256, 384), (128, 128), (130, 200), (2048, 1024), (16, 4096), (1000, 24)]
 
 
