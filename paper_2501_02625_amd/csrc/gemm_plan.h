@@ -191,29 +191,30 @@ inline bool column_maxima_first(int64_t rows, int64_t cols, int64_t parts) {
 
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
 // left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
-// tiles, followed by a pass over its accumulators that takes up to eleven strides, and a strided pass for the others.  gx, gg: the
-// plain forms of the products (gg null: only E_X is wanted).  Estimates: 3.5 us and 3.5 us per million elements for the first pass
-// where it starts from the int32 accumulators, 5 and 1.5 for the others and for one that starts from fp32.
-// A short reduction, up to 384, keeps to the epilogue unless the passes are estimated 6 us faster.
-// The backward pass timed both ways on 171 shapes, 256 .. 8192 tokens, 512 .. 14336 by 256 .. 4096, each with both products,
-// with E_X alone and with rank-16 adapters: the rule takes the faster way or one within 3 % of it in 447 of 513, 20 % behind
-// at worst.  It leans to the epilogue: short reductions are left there as they were, from 25 % faster (4096 x 3072 by 16, E_X alone
-// 58 us against 78) to 15 % slower (512 x 8192 by 256, both 47 / 40), and so is 1536 x 3072 by 1024 (both 55.7 / 52.6).  With the
-// constants of the six-stride passes that came before, 106 were more than 3 % behind, 30 % at worst.  Both products, in the epilogue
-// against passes: 256 x 8192 x 4096 118 us against 100, 1024 x 4096 x 4096 110 / 98, 4096 x 2048 x 1024 90 / 98, 4096 x 4096 x 4096
-// 226 / 255.
+// tiles, followed by a pass over its accumulators, or two (left_first_pass).  gx, gg: the plain forms of the products (gg null: only
+// E_X is wanted).  Microseconds, fitted to the measurement below: half of the difference between the products' estimates (which are
+// high where the chip is not full); 4 for the epilogue, and 1 per million elements for a strided pass behind it where no one kernel
+// finishes; for the passes 1 per million elements, 2 beyond 30 million (the caches), 5.5 where the first one starts from int32
+// accumulators, 3.5 where it takes eleven strides, 2.5 and 0.5 per million elements for a second one.
+// The backward pass timed both ways on 379 shapes, 256 .. 8192 tokens, 512 .. 14336 by 64 .. 4096, each with both products, with E_X
+// alone and with rank-16 adapters: the rule takes the faster way or one within 3 % of it in 1102 of 1137; five are more than 10 %
+// behind, 17 % at worst (1536 x 5632 by 64, E_X and G, 54 us in the epilogue and 63 in passes).  Both products, in the epilogue against
+// passes: 256 x 8192 x 4096 120 us / 96, 1024 x 4096 x 4096 109 / 96, 512 x 8192 x 256 47 / 41, 4096 x 2048 x 1024 92 / 90, 2048 x 3072 x
+// 1024 65 / 74, 4096 x 4096 x 4096 227 / 256, 8192 x 14336 x 1024 576 / 854.
 inline bool left_in_epilogue(const GemmArgs& gx, const GemmArgs* gg, int32_t hb, int32_t hm) {
     const int64_t b = gx.M, m = gx.N;
     if (hb < 256 || b % 256) return false;
-    const double melems = (double)b * (double)m / 1e6, pass = 5.0 + 1.5 * melems;
-    const double first = gx.lr_rank ? pass : 3.5 + 3.5 * melems;           // adapters: the product is stored as fp32
     GemmArgs l = gx, g2 = gg ? *gg : gx;
     l.left_stages = 8; l.config = HALO_GEMM_256x256x64; g2.config = HALO_GEMM_256x256x64;
-    const int top = ilog2_exact(hb) - 8, stages = ilog2_exact(hb);
+    const int stages = ilog2_exact(hb), top = stages - 8;
     const bool one_kernel = is_pow2(hm) && row_left_top_ok(b, m, ilog2_exact(hm), top);
-    const double fused = gemm_i8_cost(l, gg ? &g2 : nullptr) + (top == 0 || one_kernel ? 0.0 : pass);
-    const double plain = gemm_i8_cost(gx, gg) + first + (stages > 11 ? pass : 0.0);
-    return fused <= plain + (gx.K <= 384 ? 6.0 : 0.0);
+    const bool second = left_first_pass(stages, b, m) < stages;
+    const double melems = (double)b * (double)m / 1e6;
+    const double products = 0.5 * (gemm_i8_cost(l, gg ? &g2 : nullptr) - gemm_i8_cost(gx, gg));
+    const double epilogue = 4.0 + (top == 0 || one_kernel ? 0.0 : melems);
+    const double passes = melems + std::max(0.0, melems - 30.0) + (gx.lr_rank ? 0.0 : 5.5) +
+                          (second ? 2.5 + 0.5 * melems : stages == kColBlockStages ? 3.5 : 0.0);
+    return products + epilogue <= passes;
 }
 
 }  // namespace halo

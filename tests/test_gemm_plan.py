@@ -148,18 +148,25 @@ def test_shapes_of_the_left_epilogue_tests(ask):
     lines += [left(b, m, n, hm, hb, both=False, rank=rank) for b, m, n, rank, level, hm, hb in test_gpu_peft.LEFT_IN_EPILOGUE]
     for line, said in zip(lines, ask(lines)):
         assert said == "1", line
+    lines = [left(*s, both=True) for s in test_gpu_linear.LEFT_IN_PASSES]
+    lines += [left(b, m, n, min(m & -m, 4096), b & -b, both=False) for b, m, n in test_gpu_per_tensor.LEFT_IN_PASSES]
+    lines += [left(b, m, n, hm, hb, both=False, rank=rank) for b, m, n, rank, level, hm, hb in test_gpu_peft.LEFT_IN_PASSES]
+    for line, said in zip(lines, ask(lines)):
+        assert said == "0", line
     # one top stride to five, and none, each on every right block that one kernel finishes or that needs a pass of its own
     tops = {hb.bit_length() - 9 for b, m, n, hm, hb in test_gpu_linear.LEFT_IN_EPILOGUE}
     blocks = {hm for b, m, n, hm, hb in test_gpu_linear.LEFT_IN_EPILOGUE}
-    assert tops == {0, 1, 2, 3, 4, 5} and blocks == {512, 1024, 2048, 4096, 14336}
+    assert tops == {0, 1, 2, 3, 4, 5} and blocks == {512, 1024, 2048, 4096, 3584}
 
 
-# tokens, in- and out-features, and whether the backward pass of both products is faster with the strides in the epilogue:
-# shapes where the two ways, timed on an MI355X, lie 10 % or more apart
-MEASURED = [(4096, 2048, 1024, True), (1536, 3072, 1024, True), (512, 5632, 256, True), (768, 5632, 256, True),
-            (1024, 3072, 256, True), (2048, 3072, 256, True), (256, 1024, 1024, False), (256, 8192, 4096, False)]
+# tokens, in- and out-features, and microseconds of the backward pass of both products with the strides in the epilogue and in
+# passes: shapes where the two ways, timed on an MI355X, lie 10 % or more apart
+MEASURED = [(256, 1024, 1024, 39.1, 26.1), (256, 8192, 4096, 120.3, 95.8), (512, 8192, 256, 47.2, 41.4), (768, 3072, 1024, 49.4, 42.1),
+            (1024, 4096, 4096, 109.2, 96.0), (2048, 1024, 512, 60.8, 51.3), (8192, 2048, 512, 168.2, 147.2),
+            (768, 14336, 2048, 136.3, 155.7), (1536, 8192, 64, 62.5, 74.3), (2048, 3072, 1024, 64.9, 74.3),
+            (4096, 4096, 4096, 227.1, 256.4), (8192, 14336, 1024, 575.8, 854.0)]
 
 
 def test_the_faster_way_of_the_left_hand_un_rotation(ask):
-    lines = [left(b, m, n, min(m & -m, 4096), b & -b, both=True) for b, m, n, faster in MEASURED]
-    assert ask(lines) == [str(int(faster)) for b, m, n, faster in MEASURED]
+    lines = [left(b, m, n, min(m & -m, 4096), b & -b, both=True) for b, m, n, epilogue, passes in MEASURED]
+    assert ask(lines) == [str(int(epilogue < passes)) for b, m, n, epilogue, passes in MEASURED]

@@ -146,22 +146,28 @@ def test_level2_one_left_block(b, n, odt):
 # tokens, in- and out-features, right and left block: the low left-hand strides run in the product's epilogue
 # (test_gemm_plan.py asserts that the rule says so), and every way the rest of the un-rotation can go is there.
 LEFT_IN_EPILOGUE = [
-    (768, 9216, 16, 1024, 256),       # left block 256: nothing left after the epilogue
-    (512, 9216, 144, 512, 512),       # one top stride
-    (1536, 4096, 144, 4096, 512),
-    (1024, 5120, 80, 1024, 1024),     # two
-    (2048, 3584, 16, 512, 2048),      # three
+    (512, 13312, 16, 1024, 256),      # left block 256: nothing left after the epilogue
+    (1024, 8704, 16, 512, 512),       # one top stride
+    (1536, 8192, 16, 4096, 512),
+    (1024, 9216, 80, 1024, 1024),     # two
+    (2048, 4608, 16, 512, 2048),      # three
     (2048, 4096, 272, 2048, 2048),
     (4096, 3072, 16, 1024, 4096),     # four
     (4096, 4096, 32, 4096, 4096),
-    (8192, 1536, 16, 512, 8192),      # five
-    (8192, 2048, 32, 2048, 8192),
-    (8192, 4096, 16, 4096, 8192),     # five, with a right block that leaves them to a strided pass
-    (512, 14336, 144, 14336, 512),    # a Kronecker block: a strided pass, then its own kernel
+    (8192, 3072, 16, 512, 8192),      # five
+    (8192, 4096, 32, 2048, 8192),
+    (8192, 4096, 1536, 4096, 8192),   # five, with a right block that leaves them to a strided pass
+    (2048, 3584, 1536, 3584, 2048),   # a Kronecker block: a strided pass, then its own kernel
+]
+# and these do not: passes over the accumulators are the faster way
+LEFT_IN_PASSES = [
+    (768, 9216, 16, 1024, 256), (512, 9216, 144, 512, 512), (1536, 4096, 144, 4096, 512), (1024, 5120, 80, 1024, 1024),
+    (2048, 3584, 16, 512, 2048), (8192, 1536, 16, 512, 8192), (8192, 2048, 32, 2048, 8192), (8192, 4096, 16, 4096, 8192),
+    (512, 14336, 144, 14336, 512),
 ]
 
 
-@pytest.mark.parametrize("b,m,n,hm,hb", LEFT_IN_EPILOGUE)
+@pytest.mark.parametrize("b,m,n,hm,hb", LEFT_IN_EPILOGUE + LEFT_IN_PASSES)
 def test_level2_low_left_strides_in_the_epilogue(b, m, n, hm, hb):
     Xb = inputs.make_activations(b, m, 0.01, b + m); Wb = inputs.make_weights(n, m, b + m); Eb = inputs.make_errors(b, n, b + m)
     run_and_check(b, m, n, 2, Xb, Wb, Eb, odt=torch.bfloat16 if n == 32 else torch.float32, hm=hm, hb=hb)

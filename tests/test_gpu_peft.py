@@ -123,14 +123,17 @@ SHAPES = [
 ]
 # the low left-hand strides and the low-rank product share the epilogue (test_gemm_plan.py asserts that the rule says so)
 LEFT_IN_EPILOGUE = [
-    (1536, 2560, 192, 8, 2, 512, 512),     # rank 8: most of a 32-deep matrix instruction is masked
-    (2048, 2048, 128, 64, 2, 1024, 2048),  # rank 64: two trips of 32
-    (1024, 4096, 64, 24, 2, 2048, 1024),   # rank 24
-    (768, 5120, 64, 32, 2, 512, 256),      # left block 256: nothing left after the epilogue
+    (4096, 2048, 192, 8, 2, 512, 2048),    # rank 8: most of a 32-deep matrix instruction is masked
+    (2048, 4096, 128, 64, 2, 1024, 2048),  # rank 64: two trips of 32
+    (2560, 4096, 64, 24, 2, 2048, 512),    # rank 24
+    (1280, 8192, 64, 32, 2, 512, 256),     # left block 256: nothing left after the epilogue
 ]
+# and the low strides in passes of their own
+LEFT_IN_PASSES = [(1536, 2560, 192, 8, 2, 512, 512), (2048, 2048, 128, 64, 2, 1024, 2048), (1024, 4096, 64, 24, 2, 2048, 1024),
+                  (768, 5120, 64, 32, 2, 512, 256)]
 
 
-@pytest.mark.parametrize("shape", SHAPES + LEFT_IN_EPILOGUE, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + LEFT_IN_EPILOGUE + LEFT_IN_PASSES, ids=lambda s: "x".join(map(str, s)))
 def test_peft_module_fp32_outputs(shape):
     b, m, n, rank, level, hm, hb = shape
     run_peft(b, m, n, rank, level, seed=b + rank, hm=hm, hb=hb)

@@ -69,10 +69,11 @@ def test_config_c7_full_size_per_tensor():
 
 # tokens, in- and out-features: at level 2 the product's epilogue runs the low left-hand strides with the tensor scale
 # (test_gemm_plan.py asserts that the rule says so)
-LEFT_IN_EPILOGUE = [(768, 5120, 16), (512, 8192, 144), (1024, 4096, 272), (4096, 1024, 80)]
+LEFT_IN_EPILOGUE = [(1280, 5120, 16), (1536, 4096, 144), (1024, 6144, 272), (4096, 1024, 80)]
+LEFT_IN_PASSES = [(768, 5120, 16), (512, 8192, 144), (1024, 4096, 272)]
 
 
-@pytest.mark.parametrize("b,m,n", LEFT_IN_EPILOGUE)
+@pytest.mark.parametrize("b,m,n", LEFT_IN_EPILOGUE + LEFT_IN_PASSES)
 def test_per_tensor_low_left_strides_in_the_epilogue(b, m, n):
     run_per_tensor(b, m, n, 2, b + n)
 
