@@ -249,7 +249,7 @@ def kernel_timings(L, it, dev, copy_gbs):
             add_hbm(nm, lambda i, accs=accs, outs=outs, scale=scale, wsu=wsu, left=left: (lambda: binding.halo_dequant_unrotate(
                 accs[i], scale, had_block=hm, had_block_left=left, out=outs[i], workspace=wsu)), nbytes, k,
                 passes=("stand-alone entry point: one or two passes from the int32 accumulators, then the row pass; inside the "
-                        "layer the product's epilogue runs the eight low strides and one strided pass is left") if left else None)
+                        "layer the product's epilogue may run the eight low strides") if left else None)
             del accs, outs
     return kernels
 

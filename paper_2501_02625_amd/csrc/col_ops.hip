@@ -149,14 +149,16 @@ col_fwht_kernel(const void* in, int64_t ld_in, void* out, int64_t ld_out, int64_
 
 // ------------------------------------------------------------------------------------------------
 // The lowest LOGR stages (strides 1 .. 2^(LOGR-1)) of the left-hand FWHT in one pass over memory: a workgroup keeps 2^LOGR
-// consecutive rows of 32 columns (64 for LOGR 6) in registers, 32 rows x 2 columns per thread, and the rows change hands once,
+// consecutive rows of 32 columns (64 for LOGR 6, with SIDE only) in registers, 32 rows x 2 columns per thread, and the rows change hands once,
 // through LDS.  First the thread holds 32 consecutive rows (five stages in registers), then, after the exchange, 32 rows that
 // lie 32 apart (the stages from stride 32 on).  LOGR 11 has one stage more than that: the halves of the 2048 rows then sit in
 // the two halves of the wavefront and v_permlane32_swap_b32 brings a pair together in one lane (one instruction for two values;
 // both results stay where they are, only the row that a register stands for changes).
-// A strided pass takes six stages (col_fwht_kernel), so blocks of 128 to 2048 rows save a round trip of the fp32 intermediate.
-// What bounds it: memory, 2 + 4 bytes an element (4096 x 4096: 24 us, 4.1 TB/s; two strided passes took 22 + 22).  64 values per thread and a 64 KB exchange buffer (one of the two columns at
-// a time), so that two workgroups of 1024 rows share a compute unit: one loads or stores while the other exchanges.
+// A strided pass takes six stages (col_fwht_kernel), so blocks of 128 to 2048 rows save a round trip of the fp32 intermediate;
+// how many stages a rotation gives to this pass: left_first_pass, left_pass_stages.
+// What bounds it: memory, 2 + 4 bytes an element (4096 x 4096: 24 us, 4.1 TB/s; two strided passes took 22 + 22).  64 values per
+// thread and a 64 KB exchange buffer (one of the two columns at a time), so that two workgroups of 1024 rows share a compute unit:
+// one loads or stores while the other exchanges.
 // Neighbouring column tiles, which share cache lines of a bf16 row, run on the same XCD at the same time.
 // SIDE (bf16 input): the pass also takes, per column, the largest |in[r, k] * row_scale[r]| of its rows, which the column quantiser
 // of the same matrix needs, from the one read of it.  kSideMaxima: it writes them to side_part[row block][cols].  kSideCodes

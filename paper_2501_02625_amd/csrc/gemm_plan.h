@@ -154,7 +154,8 @@ inline int small_tile_columns(const GemmArgs& a) {
 // Estimated microseconds of launch_gemm_i8(a) / launch_gemm_i8_pair(a, *a2), for choices between ways to split the work.
 inline double gemm_i8_cost(const GemmArgs& a, const GemmArgs* a2) {
     const int c = a.config < 0 ? choose_config(a, a2) : a.config;
-    // 16 x 512 x 512 3.9 us, 256 x 1024 x 2048 5.5, 256 x 4096 x 4096 10.3 and 13.8 with a K-strided B
+    // 64 columns: 16 x 512 x 512 3.9 us, 256 x 1024 x 2048 5.5, 256 x 4096 x 4096 10.3 and 13.8 with a K-strided B.  Narrow tiles
+    // are not in it: a product with a K-contiguous B has no other way than one launch.
     if (c == kSmall32 || c == kSmall64) return 3.5 + 0.8 * units_of(a) / 4 + (a2 ? 0.8 * units_of(*a2) / 4 : 0.0);
     const double t = a2 ? pair_cost(a, *a2, c) : product_cost(a, c);
     if (!a.left_stages && !(a2 && a2->left_stages)) return t;
@@ -191,7 +192,7 @@ inline bool column_maxima_first(int64_t rows, int64_t cols, int64_t parts) {
 
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
 // left block covers whole 256-row tiles.  They do when that is the faster way: a small product is better off in smaller
-// tiles, followed by a pass over its accumulators, or two (left_first_pass).  gx, gg: the plain forms of the products (gg null: only
+// tiles, followed by one pass over its accumulators or two (left_first_pass).  gx, gg: the plain forms of the products (gg null: only
 // E_X is wanted).  Microseconds, fitted to the measurement below: half of the difference between the products' estimates (which are
 // high where the chip is not full); 4 for the epilogue, and 1 per million elements for a strided pass behind it where no one kernel
 // finishes; for the passes 1 per million elements, 2 beyond 30 million (the caches), 5.5 where the first one starts from int32

@@ -128,7 +128,7 @@ hipError_t unrotate_rows(RowArgs r, OutKind ok, const GradUnrotation* g, hipStre
 }
 
 // The rest of an un-rotation: t [b x m] fp32 holds the product after the left-hand strides below 2^first_stage (8 after the GEMM
-// epilogue that runs them, 0 after a plain epilogue, all of them after strided passes from the accumulators).  Either one kernel
+// epilogue that runs them, 0 after a plain epilogue, all of them after passes from the accumulators).  Either one kernel
 // (top strides across the wavefronts of a workgroup, then each row's right-hand un-rotation), or the remaining strides in place
 // and then the row kernel (1/sqrt(left block), right-hand un-rotation, conversion).  g: G's un-rotation, may be null.
 hipError_t finish_left_unrotation(float* t, int64_t b, int64_t m, int32_t hb, int32_t hm, void* out, halo_dtype odt,
@@ -308,7 +308,7 @@ halo_status halo_hadamard_quant(const void* in, halo_dtype in_dt, int64_t rows, 
         r.in = in; r.ld_in = ld_in;
         return from_hip(launch_row_transform(r, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, OUT_Q8, s));
     }
-    // left-hand rotation first (strided passes into fp32 scratch), then the row kernel on the scratch
+    // left-hand rotation first (into fp32 scratch), then the row quantiser on the scratch
     if ((cols * 4) % 16) return HALO_EALIGN;   // scratch rows must stay 16-byte aligned
     float* tmp = reinterpret_cast<float*>(workspace);
     return from_hip(left_rotate_quant(in, in_dt == HALO_BF16 ? IN_BF16 : IN_F32, ld_in, tmp, ilog2_exact(had_block_left), r, nullptr, s));
@@ -571,7 +571,7 @@ halo_status halo_dequant_unrotate(const int32_t* acc, int64_t ld_acc, int64_t ro
         r.out = out; r.ld_out = ld_out;
         return from_hip(launch_row_transform(r, IN_I32, out_dt == HALO_BF16 ? OUT_BF16 : OUT_F32, s));
     }
-    // Left-hand un-rotation first: strided passes from the accumulators into the fp32 scratch (butterflies only), then
+    // Left-hand un-rotation first: one pass or two from the accumulators into the fp32 scratch (butterflies only), then
     // the row kernel multiplies by 1/sqrt(left block), un-rotates along the rows and converts.
     float* tmp = reinterpret_cast<float*>(workspace);
     ColFwhtArgs c{acc, IN_I32, ld_acc, tmp, cols, tmp, cols, rows, cols, ilog2_exact(had_block_left)};
@@ -762,8 +762,8 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
         st = halo_quant_dual(E, b, n, n, s_w, s_x, Eq, n, s_e, EqT, b, s_g, amax, halo_quant_dual_workspace_bytes(b, n), stream);
         if (st != HALO_OK) return st;
     } else {
-        // Level 2, both products: the first strided pass of E's left-hand rotation reads all of E anyway and also
-        // takes the column maxima of E (x) s_x that the column quantiser needs (left blocks of at least 64 tokens).
+        // Level 2, both products: the first pass of E's left-hand rotation reads all of E anyway and also takes the
+        // column maxima of E (x) s_x, or writes the column codes itself (left blocks of at least 64 tokens).
         const bool side = both && level >= 2 && hb >= 64;
         if (side) {
             RowArgs r{};
@@ -924,7 +924,7 @@ halo_status halo_peft_bwd(const halo_linear_desc* desc, int32_t rank, const void
             return HALO_EHIP;
     }
     if (!EX) return HALO_OK;
-    if (rotate_s && !s_small) {            // left blocks too long for one workgroup's LDS: the strided passes
+    if (rotate_s && !s_small) {            // left blocks too long for one workgroup's LDS: passes of their own
         ColFwhtArgs c{S, IN_F32, rank, Sp, rank, Sp, rank, b, rank, ilog2_exact(hb)};
         if (launch_col_fwht(c, hs) != hipSuccess) return HALO_EHIP;
     }

@@ -79,11 +79,11 @@ struct ColQuantArgs {
 };
 
 // ---- left-hand (strided axis) FWHT: all stages of block 2^log_block, ascending, possibly several passes ----
-// in/out may alias when in_kind == out_kind == fp32.  tmp (fp32 [rows x ld_tmp]) is used when more than one
-// pass is needed and in/out cannot carry fp32 intermediates.
+// The first pass works on blocks of consecutive rows where it can (left_first_pass), the others are strided.  out is fp32; in
+// may be out when it is fp32 too.  tmp (fp32 [rows x ld_tmp], may be out) carries what is between two passes.
 struct ColFwhtArgs {
     const void* in;
-    InKind in_kind;          // IN_BF16 or IN_F32
+    InKind in_kind;          // IN_BF16, IN_F32 or IN_I32
     int64_t ld_in;
     void* out;               // fp32
     int64_t ld_out;
@@ -98,7 +98,7 @@ struct ColFwhtArgs {
     const float* post_scale;
     int first_stage;
     int skip_norm;
-    // only_low > 0 (6 .. 11, first_stage 0): the strides below 2^only_low, in one pass; the caller runs the others.
+    // only_low > 0 (7 .. 11, with columns 6 .. 11; first_stage 0): the strides below 2^only_low, in one pass; the caller runs the others.
     int only_low;
     // columns != null (bf16 input, only_low > 0): the pass also works for that column quantiser of the same matrix.  A block that is
     // all of the rows: it writes its codes and scales.  Otherwise it writes the absolute maxima of each block of 2^only_low rows
