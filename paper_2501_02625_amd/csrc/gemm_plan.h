@@ -185,9 +185,10 @@ inline int left_first_pass(int log_block, int64_t rows, int64_t cols) {
 // of rows: every tile (128 x 128) reads the vectors of its columns, or one launch more reduces them first.  The launch costs 1 to 2
 // us, the reading some 6 TB/s from the second-level caches.  Level-2 backward, 256 in-features, tokens x out-features and vectors,
 // read by every tile / reduced first: 2112 x 1536, 33 47.4 us / 48.2, 4160 x 512, 65 57.6 / 57.6, 4160 x 4096 93.7 / 86.4, 8128 x 4096,
-// 127 189.6 / 167.2 (169.3 with atomic maxima), 8192 x 4096, 16 156.6 / 154.9, 8192 x 4096, 4 166.9 / 168.2.
+// 127 189.6 / 167.2 (169.3 with atomic maxima), 8192 x 4096, 16 156.6 / 154.9, 8192 x 4096, 4 166.9 / 168.2.  A few
+// vectors are next to nothing beside a tile: at 8192 x 14336, 4 the launch takes 4.9 us and saves 3, with 8 both ways take 490.
 inline bool column_maxima_first(int64_t rows, int64_t cols, int64_t parts) {
-    return ((rows + 127) / 128) * ((cols + 127) / 128) * parts * 512 > (int64_t(10) << 20);
+    return parts > 8 && ((rows + 127) / 128) * ((cols + 127) / 128) * parts * 512 > (int64_t(10) << 20);
 }
 
 // Level 2: the low eight strides of the left-hand un-rotation of E_X can run in the epilogue of the E product when the
