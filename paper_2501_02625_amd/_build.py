@@ -45,8 +45,9 @@ def _run(cmd, cwd=None):
     return err
 
 
-# Kernels whose accumulators are accumulation registers named in the text of inline assembly (csrc/gemm_i8.hip).
+# Kernels whose accumulators are accumulation registers named in the text of inline assembly (csrc/matrix_asm.h), by source.
 ACCUMULATOR_KERNELS = "gemm_i8_kernel"
+ACCUMULATOR_SOURCES = {"gemm_i8.hip": ACCUMULATOR_KERNELS, "gemm_mx6.hip": "gemm_mx6_lines_kernel"}
 
 
 def accumulator_faults(asm: str, kernel: str = ACCUMULATOR_KERNELS):
@@ -80,12 +81,12 @@ def accumulator_faults(asm: str, kernel: str = ACCUMULATOR_KERNELS):
 
 def _compile(src: str, obj: str) -> str:
     cmd = [_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-    if src != "gemm_i8.hip":
+    if src not in ACCUMULATOR_SOURCES:
         return _run(cmd)
     with tempfile.TemporaryDirectory() as tmp:
         log = _run(cmd + ["-save-temps"], cwd=tmp)
-        with open(os.path.join(tmp, "gemm_i8-hip-amdgcn-amd-amdhsa-gfx950.s")) as f:
-            count, faults = accumulator_faults(f.read())
+        with open(os.path.join(tmp, src.replace(".hip", "-hip-amdgcn-amd-amdhsa-gfx950.s"))) as f:
+            count, faults = accumulator_faults(f.read(), ACCUMULATOR_SOURCES[src])
     if not count or faults:
         raise RuntimeError("%s: the compiler uses registers or scratch memory of %d kernels that hold their accumulators in "
                            "registers it does not know of:\n%s" % (src, count, "\n".join(faults[:20])))

@@ -6,7 +6,7 @@
 // scaling block, as 192 bits packed least-significant element first in six registers, plus that block's E8M0 byte in
 // byte 0 of the scale register.  Accumulator: lane l holds column (l % 16), rows 4 * (l / 16) + r, r = 0..3.
 // So the packed codes in memory ([row][block][24 bytes]) are the register image: nothing is unpacked or shuffled.
-// Two kernels: the one below for small products, a 256 x 256-tile one with DMA-fed LDS further down for large ones.
+// Three kernels: the one below for small products, and two of 256 x 256 tiles with DMA-fed LDS further down for large ones.
 //
 // Small products: workgroup = 4 wavefronts (2 x 2), macro tile 128 x 128, each wavefront 64 x 64 = 4 x 4 instruction tiles; K step 128
 // elements = 96 code bytes + 4 scale bytes per row.  Two LDS stages: the 256 rows of a K step (128 of A, 128 of B) lie
@@ -15,16 +15,14 @@
 // scale dword per thread) while the current one is multiplied, then registers -> LDS, one barrier per K step.  A lane
 // reads its block as three 8-byte LDS loads: the code bytes in memory are the register image, nothing is unpacked.
 #include <mutex>
-#include <type_traits>
 
 #include "halo_internal.h"
+#include "matrix_asm.h"
 
 namespace halo {
 namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kFmtE3M2 = 3;     // "bf6" in the instruction's format field (0 E4M3, 1 E5M2, 2 E2M3, 3 E3M2, 4 E2M1)
 constexpr int kPitch = 112;                         // LDS bytes per row and K step
@@ -167,6 +165,7 @@ __global__ void __launch_bounds__(256, 2) gemm_mx6_kernel(Mx6GemmArgs a, int til
 // chunks of a row.  What bounds the kernel is the rate at which requests are turned into cache lines, and only lanes
 // next to each other share one.  With planes of [16 rows][16 bytes] instead, where neighbouring lanes are 16 different
 // rows, 8192 x 4096 x 4096 with both quantisers took 178.6 us; this way it takes 165.7.
+// (Superblocks of 512 elements travel better: gemm_mx6_lines_kernel.)
 // Rows r and r + 8 start on the same banks and rows 0..7 on eight different even groups of four, so rows with bit 3
 // set have their chunks rotated by one place (big_place / big_chunk): a chunk of 16 rows then covers all 64 banks.  A
 // lane reads its 24 bytes as three 8-byte pieces: the two halves of the wavefront (K blocks 2s and 2s+1 of sub-step s)
@@ -181,20 +180,9 @@ constexpr int kBigLoads = 7;                                // DMA instructions 
 constexpr int kBigEpiPitch = 64 + 8;
 constexpr int kBigLds = kBigNS * kBigStage;
 static_assert(kBigLds <= 160 * 1024 && 8 * 32 * kBigEpiPitch * 4 <= kBigLds, "LDS budget");
-// WIDE form (K a multiple of 512, 16-byte aligned scale rows): the stages hold codes only, and the scale bytes of FOUR K
-// steps travel as one 16-byte chunk per row into one of two buffers behind the stages - a quarter of the scale requests,
-// each of which touches 64 different cache lines.
-constexpr int kWideStage = 2 * kBigOpBytes;
-constexpr int kWideScaleOff = kBigNS * kWideStage;
-constexpr int kWideLds = kWideScaleOff + 2 * 512 * 16;
-static_assert(kWideLds <= 160 * 1024, "LDS budget");
-
 #define HALO_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
-#define HALO_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 typedef float v16f __attribute__((ext_vector_type(16)));
-
-typedef int v2i __attribute__((ext_vector_type(2)));
 
 // The three 8-byte pieces of each of the six fragments (four of A, two of B) of one K sub-step.
 struct BigFrags {
@@ -248,9 +236,7 @@ __device__ __forceinline__ void big_mma(const BigFrags& f, const int (&sca)[4], 
                                                                         2 * KS, sca[i], 2 * KS, scb[j]);
 }
 
-template <bool WIDE>
 __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int tiles_m, int tiles_n) {
-    constexpr int kStage = WIDE ? kWideStage : kBigStage;
     extern __shared__ __align__(16) unsigned char smem_big[];
     unsigned char* smem = smem_big;
     const int tid = threadIdx.x;
@@ -258,22 +244,8 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
     const int wave_m = wave >> 2, wave_n = wave & 3;
     const int lrow = lane & 31, half = lane >> 5;
 
-    // consecutive workgroups go to different XCDs: give each XCD a contiguous range of tiles, walked four tile-rows
-    // at a time so that its resident tiles share operand panels in its L2
     int tile_m, tile_n;
-    {
-        const int bid = blockIdx.x;
-        const int ntiles = tiles_m * tiles_n;
-        const int xcd = bid & 7, q = bid >> 3;
-        const int base = ntiles >> 3, rem = ntiles & 7;
-        const int pid = xcd * base + (xcd < rem ? xcd : rem) + q;
-        const int per_group = 4 * tiles_n;
-        const int group = pid / per_group, first_m = group * 4;
-        const int gsize = (tiles_m - first_m) < 4 ? (tiles_m - first_m) : 4;
-        const int in_group = pid % per_group;
-        tile_m = first_m + in_group % gsize;
-        tile_n = in_group / gsize;
-    }
+    tile_of_block<4>(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * 256, n0 = (int64_t)tile_n * 256;
     const int nk = (int)(a.K / 128);
 
@@ -298,10 +270,9 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
         if (tid < 256) { gr = m0 + tid; gr = gr < a.M ? gr : a.M - 1; s_src = a.SA + gr * a.ldsa; }
         else { gr = n0 + tid - 256; gr = gr < a.N ? gr : a.N - 1; s_src = a.SB + gr * a.ldsb; }
     }
-    // K step t (codes of step `src`) into ring slot t % NS.  with_scales: in the WIDE form, also the scale chunk of the
-    // group of four K steps that starts at t (t a multiple of 4) into scale buffer (t / 4) % 2.
-    auto issue_dma = [&](int t, int src, bool with_scales) {
-        unsigned char* st = smem + (t % kBigNS) * kStage;
+    // K step t (codes and scales of step `src`) into ring slot t % NS
+    auto issue_dma = [&](int t, int src) {
+        unsigned char* st = smem + (t % kBigNS) * kBigStage;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
             __builtin_amdgcn_global_load_lds(HALO_GLOBAL_PTR(a_src[i] + (int64_t)src * 96),
@@ -310,14 +281,8 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
         for (int i = 0; i < 3; ++i)
             __builtin_amdgcn_global_load_lds(HALO_GLOBAL_PTR(b_src[i] + (int64_t)src * 96),
                                              HALO_LDS_PTR(st + kBigOpBytes + (wave * 64 + i * 512) * 16), 16, 0, 0);
-        if constexpr (!WIDE) {
-            __builtin_amdgcn_global_load_lds(HALO_GLOBAL_PTR(s_src + (int64_t)src * 4),
-                                             HALO_LDS_PTR(st + kBigScaleOff + wave * 64 * 4), 4, 0, 0);
-        } else if (with_scales) {
-            const int g = src / 4;
-            __builtin_amdgcn_global_load_lds(HALO_GLOBAL_PTR(s_src + (int64_t)g * 16),
-                                             HALO_LDS_PTR(smem + kWideScaleOff + ((t / 4) & 1) * 8192 + wave * 64 * 16), 16, 0, 0);
-        }
+        __builtin_amdgcn_global_load_lds(HALO_GLOBAL_PTR(s_src + (int64_t)src * 4),
+                                         HALO_LDS_PTR(st + kBigScaleOff + wave * 64 * 4), 4, 0, 0);
     };
 
     // ---- this lane's three 8-byte pieces of K block 2 * ks + half, as byte offsets inside a stage
@@ -331,9 +296,8 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
             off_a[ks][j] = (uint32_t)(wave_m * 4 * 3072) + in_block;
             off_b[ks][j] = (uint32_t)(kBigOpBytes + wave_n * 2 * 3072) + in_block;
         }
-    off_sa = WIDE ? (uint32_t)(kWideScaleOff + (wave_m * 128 + lrow) * 16) : (uint32_t)(kBigScaleOff + (wave_m * 128 + lrow) * 4);
-    off_sb = WIDE ? (uint32_t)(kWideScaleOff + (256 + wave_n * 64 + lrow) * 16)
-                  : (uint32_t)(kBigScaleOff + (256 + wave_n * 64 + lrow) * 4);
+    off_sa = (uint32_t)(kBigScaleOff + (wave_m * 128 + lrow) * 4);
+    off_sb = (uint32_t)(kBigScaleOff + (256 + wave_n * 64 + lrow) * 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)HALO_LDS_PTR(smem);
 
     v16f acc[4][2];
@@ -346,18 +310,15 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
 
     if (nk > 0) {
         constexpr int D = kBigNS - 1;
-        // One K step.  PH: kt % 4 in the WIDE form (it fixes which steps carry a scale chunk, hence the wait count and the
-        // byte of the chunk to use), -1 otherwise.
-        auto k_step = [&](auto ph, int kt) {
-            constexpr int PH = decltype(ph)::value;
-            // outstanding afterwards: the loads of step kt + 1 only (6 code chunks, plus its scale request)
-            constexpr int kAllowed = WIDE ? (PH == 3 ? 7 : 6) : (D - 1) * kBigLoads;
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kAllowed) : "memory");
+        for (int t = 0; t < D; ++t) issue_dma(t, t < nk ? t : nk - 1);
+        for (int kt = 0; kt < nk; ++kt) {
+            // outstanding afterwards: the loads of step kt + 1 only
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((D - 1) * kBigLoads) : "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             // ring slot (kt - 1) % NS: everyone is past reading it
-            issue_dma(kt + D, kt + D < nk ? kt + D : nk - 1, PH == 2);
-            const uint32_t st = lds0 + (uint32_t)((kt % kBigNS) * kStage);
+            issue_dma(kt + D, kt + D < nk ? kt + D : nk - 1);
+            const uint32_t st = lds0 + (uint32_t)((kt % kBigNS) * kBigStage);
             uint32_t addr_a[2][3], addr_b[2][3];
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
@@ -365,18 +326,10 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
                 for (int j = 0; j < 3; ++j) { addr_a[ks][j] = st + off_a[ks][j]; addr_b[ks][j] = st + off_b[ks][j]; }
             // the four scale bytes of each of this lane's six rows (same inline-assembly reasoning as the fragments)
             int sca[4], scb[2];
-            if constexpr (WIDE) {
-                const uint32_t sbase = lds0 + (uint32_t)(((kt / 4) & 1) * 8192 + PH * 4);
-                asm volatile("ds_read_b32 %0, %6\n\tds_read_b32 %1, %6 offset:512\n\tds_read_b32 %2, %6 offset:1024\n\t"
-                             "ds_read_b32 %3, %6 offset:1536\n\tds_read_b32 %4, %7\n\tds_read_b32 %5, %7 offset:512"
-                             : "=&v"(sca[0]), "=&v"(sca[1]), "=&v"(sca[2]), "=&v"(sca[3]), "=&v"(scb[0]), "=&v"(scb[1])
-                             : "v"(sbase + off_sa), "v"(sbase + off_sb));
-            } else {
-                asm volatile("ds_read_b32 %0, %6\n\tds_read_b32 %1, %6 offset:128\n\tds_read_b32 %2, %6 offset:256\n\t"
-                             "ds_read_b32 %3, %6 offset:384\n\tds_read_b32 %4, %7\n\tds_read_b32 %5, %7 offset:128"
-                             : "=&v"(sca[0]), "=&v"(sca[1]), "=&v"(sca[2]), "=&v"(sca[3]), "=&v"(scb[0]), "=&v"(scb[1])
-                             : "v"(st + off_sa), "v"(st + off_sb));
-            }
+            asm volatile("ds_read_b32 %0, %6\n\tds_read_b32 %1, %6 offset:128\n\tds_read_b32 %2, %6 offset:256\n\t"
+                         "ds_read_b32 %3, %6 offset:384\n\tds_read_b32 %4, %7\n\tds_read_b32 %5, %7 offset:128"
+                         : "=&v"(sca[0]), "=&v"(sca[1]), "=&v"(sca[2]), "=&v"(sca[3]), "=&v"(scb[0]), "=&v"(scb[1])
+                         : "v"(st + off_sa), "v"(st + off_sb));
             BigFrags f0, f1;
             big_load_frags<0>(addr_a, addr_b, f0);
             big_wait_frags(f0);              // the hardware counts at most 15 outstanding LDS reads: no partial wait here
@@ -389,20 +342,6 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
             big_mma<0>(f0, sca, scb, acc);
             big_wait_frags(f1);
             big_mma<1>(f1, sca, scb, acc);
-        };
-        if constexpr (WIDE) {
-            // nk is a multiple of 4 here.  Step 0 carries the first scale chunk; step 1 none.
-            issue_dma(0, 0, true);
-            issue_dma(1, 1, false);
-            for (int kt = 0; kt < nk; kt += 4) {
-                k_step(std::integral_constant<int, 0>{}, kt);
-                k_step(std::integral_constant<int, 1>{}, kt + 1);
-                k_step(std::integral_constant<int, 2>{}, kt + 2);
-                k_step(std::integral_constant<int, 3>{}, kt + 3);
-            }
-        } else {
-            for (int t = 0; t < D; ++t) issue_dma(t, t < nk ? t : nk - 1, false);
-            for (int kt = 0; kt < nk; ++kt) k_step(std::integral_constant<int, -1>{}, kt);
         }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     }
@@ -455,38 +394,420 @@ __global__ void __launch_bounds__(512) gemm_mx6_big_kernel(Mx6GemmArgs a, int ti
     }
 }
 
+// ------------------------------------------------------------------------------------------------ large products, whole lines
+// K a multiple of 512.  256 x 256 macro tile, four wavefronts (2 x 2) of 128 x 128 = 4 x 4 tiles of 32 x 32, one per SIMD, the
+// 256 accumulators in named accumulation registers as in the INT8 kernel.
+//
+// What travels is not a K step (96 bytes of a row, which touch 1.5 cache lines on average, and every line is fetched again for
+// the next step) but a LINE: 128 bytes of each of the 512 rows.  Nothing but the transfers of 8192 x 4096 x 4096 takes 63 us in
+// pieces of 96 bytes with two K steps on their way, 48 in lines with one line on its way.
+// A SUPERBLOCK is three lines = 512 elements = 16 scaling blocks = eight GROUPS of 64 elements (one matrix instruction deep).  The
+// bytes of group g are 48 g .. 48 g + 47 of the superblock: groups 0, 1 lie in line 0; 3, 4 in line 1; 6, 7 in line 2; 2 and 5
+// across two of them.  LDS holds two lines of both operands, line n of the product in slot n % 2.  A slot is wanted again for the
+// line after next, so what a straddling group has in the older line is read ahead: group 2 is read whole from line 0, with garbage
+// where line 1 has not come, and the two pieces of its upper half-wavefront that lie in line 1 are read again under an execution
+// mask; group 5 likewise.  Fragments live in three register sets, group g in set kLineSet[g].
+// By the group that is being multiplied (16 matrix instructions), what is read meanwhile, and at which barrier a line is requested:
+//   0: group 1
+//   1: [line 1 has landed and line 0's slot is free: line 2 is requested] the rest of 2, 3
+//   2: 3, 4
+//   3: 4, 5 as far as line 1 goes
+//   4: [line 2 has landed, line 1's slot is free: line 0 and the scales of the next superblock] the rest of 5, 6
+//   5: 6, 7
+//   6: [that line 0 has landed, line 2's slot is free: line 1 of the next superblock] the next group 2
+//   7: the next group 0
+// Three barriers a superblock, each behind a wait for everything requested: one line (64 KB) is always on its way.  As in the INT8
+// kernel everything is inline assembly in program order.
+//
+// What bounds it: power.  The matrix instructions alone, operands in registers, sustain 5.3 PFLOP/s on random codes (9.2 on zeros),
+// and the parts add up rather than overlap: 8192 x 4096 x 4096, bf16 out, 90 us; without the transfers 78, without the LDS reads 76,
+// matrix instructions only 55, transfers only 69, reads only 53; barriers and requests earlier, later or denser change nothing.  The
+// eight-wavefront kernel above takes 118.
+//
+// LDS: row r of a line at 128 r, its 16-byte chunk c at place (c + r / 2) % 8.  A lane's 24 bytes of a group are three 8-byte pieces;
+// the two halves of a wavefront always sit on complementary halves of the chunks, and sixteen rows on sixteen different groups of
+// banks.  B is passed as the instruction's first operand: a lane holds row l % 32 of C, columns 8 q + 4 (l / 32) .. + 3.
+constexpr int kLineSlot = 256 * 128;                        // one operand's line
+constexpr int kLineScales = 4 * kLineSlot;                  // two buffers of 512 rows x 16 scale bytes (one superblock)
+constexpr int kLinesLds = kLineScales + 2 * 512 * 16;
+constexpr int kLineEpiPitch = 128 + 4;                      // dwords
+static_assert(kLinesLds <= 160 * 1024 && 4 * 32 * kLineEpiPitch * 4 <= kLinesLds, "LDS budget");
+constexpr int kLineSet[8] = {0, 1, 2, 0, 1, 2, 0, 1};
+
+typedef int v6i __attribute__((ext_vector_type(6)));
+
+struct LineFrags {
+    v2i a[4][3], b[4][3];
+};
+
+// What a wavefront reads while it multiplies a group: a list of fragment pieces.  Fragment f: 0 .. 3 of B, 4 .. 7 of A.
+enum LineRead { kScale, kWhole, kHigh12, kLow01, kPiece2, kHigh01 };
+struct LineOp {
+    int kind, group, f;
+};
+struct LineOps {
+    int n;
+    LineOp op[40];
+};
+// The reads of slot g in order.  kWhole: three pieces of a fragment (24 bytes of a lane); kHigh12, kHigh01: two pieces, upper half-wavefront
+// only; kLow01: two pieces; kPiece2: one.
+constexpr LineOps line_ops(int g) {
+    LineOps r{};
+    auto add = [&r](int kind, int group, int from, int to) {
+        for (int f = from; f < to; ++f) r.op[r.n++] = LineOp{kind, group, f};
+    };
+    if (g & 1) add(kScale, (g + 1) & 7, 0, 8);
+    switch (g) {
+        case 0: add(kWhole, 1, 0, 8); break;
+        case 1: add(kHigh12, 2, 0, 8); add(kWhole, 3, 0, 3); break;
+        case 2: add(kWhole, 3, 3, 8); add(kWhole, 4, 0, 5); break;
+        case 3: add(kWhole, 4, 5, 8); add(kLow01, 5, 0, 8); break;
+        case 4: add(kPiece2, 5, 0, 8); add(kHigh01, 5, 0, 8); add(kWhole, 6, 0, 4); break;
+        case 5: add(kWhole, 6, 4, 8); add(kWhole, 7, 0, 8); break;
+        case 6: add(kWhole, 2, 0, 8); break;
+        default: add(kWhole, 0, 0, 8); break;
+    }
+    return r;
+}
+constexpr int line_reads(int kind) { return kind == kWhole ? 3 : kind == kScale || kind == kPiece2 ? 1 : 2; }
+// LDS reads that are requested after the last one of group g until slot g begins: what a wait for that group may leave
+// outstanding (the counter holds 15).
+constexpr int line_reads_after(int g) {
+    int n = 0;
+    for (int s = g + 7;; --s) {
+        const LineOps o = line_ops(s & 7);
+        for (int q = o.n - 1; q >= 0; --q) {
+            if (o.op[q].kind != kScale && o.op[q].group == g) return n < 15 ? n : 15;
+            n += line_reads(o.op[q].kind);
+        }
+    }
+}
+// What slot g requests after its matrix instructions 0 .. m - 1 have been issued, `first` being the first that is followed by reads.
+constexpr int line_ops_before(int g, int first, int m) { return m <= first ? 0 : (m - first) * line_ops(g).n / (14 - first); }
+constexpr int line_reads_before(int g, int first, int m) {
+    const LineOps o = line_ops(g);
+    int n = 0;
+    for (int q = 0; q < line_ops_before(g, first, m); ++q) n += line_reads(o.op[q].kind);
+    return n < 15 ? n : 15;
+}
+template <int G>
+struct LineSlot {
+    static constexpr LineOps OPS = line_ops(G);
+};
+
+template <int T, int HI>
+__device__ __forceinline__ void line_mfma(const v6i& b, const v6i& a, int sb, int sa) {
+    if constexpr (HI)
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 a[%4:%5], %0, %1, a[%4:%5], %2, %3 op_sel_hi:[1,1,0] cbsz:3 blgp:3" ::"v"(b),
+                     "v"(a), "v"(sb), "v"(sa), "n"(16 * T), "n"(16 * T + 15));
+    else
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 a[%4:%5], %0, %1, a[%4:%5], %2, %3 op_sel_hi:[0,0,0] cbsz:3 blgp:3" ::"v"(b),
+                     "v"(a), "v"(sb), "v"(sa), "n"(16 * T), "n"(16 * T + 15));
+}
+template <int OFF>
+__device__ __forceinline__ void line_read(v2i& d, uint32_t addr) {
+    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
+}
+// Two reads for lanes 32 .. 63 only.
+template <int OFF>
+__device__ __forceinline__ void line_read_high(v2i& d0, v2i& d1, uint32_t addr0, uint32_t addr1) {
+    asm volatile("s_mov_b32 exec_lo, 0\n\tds_read_b64 %0, %2 offset:%4\n\tds_read_b64 %1, %3 offset:%4\n\ts_mov_b32 exec_lo, -1"
+                 : "+v"(d0), "+v"(d1)
+                 : "v"(addr0), "v"(addr1), "n"(OFF));
+}
+template <int OFF>
+__device__ __forceinline__ void line_read_scale(int& d, uint32_t addr) {
+    asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
+}
+
+__global__ void __launch_bounds__(256, 1) gemm_mx6_lines_kernel(Mx6GemmArgs a, int tiles_m, int tiles_n) {
+    extern __shared__ __align__(128) unsigned char smem_big[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_m = wave >> 1, wave_n = wave & 1;
+    const int lrow = lane & 31, half = lane >> 5;
+    int tile_m, tile_n;
+    tile_of_block<4>(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    const int64_t m0 = (int64_t)tile_m * 256, n0 = (int64_t)tile_n * 256;
+    const uint32_t lds = (uint32_t)(uintptr_t)HALO_LDS_PTR(smem_big);
+
+    // ---- requests: eight of 8 rows x 128 bytes per operand and line, two of 64 rows x 16 scale bytes per superblock.  Rows beyond
+    // the matrix come as zeros, and so does everything once the last line has been requested.
+    uint32_t avo[8], bvo[8], svo[2];
+    {
+        const int r8 = lane >> 3, k0 = 16 * (((lane & 7) - (r8 >> 1)) & 7), row = wave * 64 + r8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t k = (uint32_t)(k0 ^ ((i & 1) << 6)), r = (uint32_t)(row + 8 * i);
+            avo[i] = m0 + r < a.M ? r * (uint32_t)a.lda + k : kOutside;
+            bvo[i] = n0 + r < a.N ? r * (uint32_t)a.ldb + k : kOutside;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = (wave & 1) * 128 + 64 * i + lane;
+            svo[i] = wave < 2 ? (m0 + r < a.M ? (uint32_t)r * (uint32_t)a.ldsa : kOutside)
+                              : (n0 + r < a.N ? (uint32_t)r * (uint32_t)a.ldsb : kOutside);
+        }
+    }
+    v4u abuf = make_buffer(a.A + m0 * a.lda), bbuf = make_buffer(a.B + n0 * a.ldb);
+    v4u sbuf = make_buffer(wave < 2 ? a.SA + m0 * a.ldsa : a.SB + n0 * a.ldsb);
+    int supers = (int)(a.K / 512), lines = 3 * supers, scales = supers;      // still to do / to be requested
+    auto request = [&](auto slot, auto dd) {                     // request dd of a line into a slot
+        constexpr int d = decltype(dd)::value, i = d & 7, at = (decltype(slot)::value + (d >> 3) * 2) * kLineSlot + i * 1024;
+        if constexpr (d < 8) dma16(avo[i], abuf, lds + at + wave * 8192);
+        else dma16(bvo[i], bbuf, lds + at + wave * 8192);
+    };
+    auto next_line = [&]() {
+        advance(abuf, 128);
+        advance(bbuf, 128);
+        if (--lines == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) avo[i] = bvo[i] = kOutside;
+        }
+    };
+    auto request_scales = [&](auto buffer) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            dma16(svo[i], sbuf, lds + kLineScales + decltype(buffer)::value * 8192 + wave * 2048 + i * 1024);
+        advance(sbuf, 16);
+        if (--scales == 0) svo[0] = svo[1] = kOutside;
+    };
+    request_scales(Int<0>());
+    StaticFor<0, 16>::run([&](auto d) { request(Int<0>(), d); });
+    next_line();
+    StaticFor<0, 16>::run([&](auto d) { request(Int<1>(), d); });
+    next_line();
+    hold_accumulators<64>();
+    StaticFor<0, 64>::run([&](auto t) { clear_acc<decltype(t)::value>(); });
+
+    // ---- where a lane's pieces lie: piece j of group g in chunk 3 g + d, d and the half of the chunk fixed by j and the half-wavefront
+    uint32_t piece[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int byte = 24 * half + 8 * j;
+        piece[j] = (uint32_t)(16 * (byte / 16 + ((lrow >> 1) & 7)) + byte % 16);
+    }
+    const uint32_t rows_a = lds + (uint32_t)(wave_m * 128 + lrow) * 128;
+    const uint32_t rows_b = lds + 2 * kLineSlot + (uint32_t)(wave_n * 128 + lrow) * 128;
+    const uint32_t scale_a = lds + kLineScales + (uint32_t)(wave_m * 128 + lrow) * 16;
+    const uint32_t scale_b = lds + kLineScales + (uint32_t)(256 + wave_n * 128 + lrow) * 16;
+    const int shift = 8 * half;
+    LineFrags f[3];
+    int sc[2][8];                                                // scale bytes of a pair of groups: B's four rows, A's four
+    struct Addr {
+        uint32_t a[3], b[3];
+    };
+    auto address = [&](auto gg, Addr& at) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            asm volatile("" : "+v"(piece[j]));                   // not hoisted out of the loop: 48 registers
+            const uint32_t in_row = (piece[j] + 48u * decltype(gg)::value) & 127u;
+            at.a[j] = in_row | rows_a;
+            at.b[j] = in_row | rows_b;
+        }
+    };
+    // one entry of line_ops(G); P: parity of the superblock
+    auto read = [&](auto gg, auto pp, auto qq, const Addr& at) {
+        constexpr int G = decltype(gg)::value, P = decltype(pp)::value;
+        constexpr LineOp op = LineSlot<G>::OPS.op[decltype(qq)::value];
+        constexpr int fr = op.f & 3, set = kLineSet[op.group];
+        if constexpr (op.kind == kScale) {
+            constexpr int off = (op.group == 0 ? 1 - P : P) * 8192 + fr * 512 + (op.group / 2) * 4;
+            line_read_scale<off>(sc[(op.group / 2) & 1][op.f], op.f < 4 ? scale_b : scale_a);
+        } else {
+            // the line the pieces come from: of this superblock 0, 1, 2 in slots P, 1 - P, P; the next one's line 0 in 1 - P
+            constexpr int slot = G == 0 || (G >= 4 && G <= 5) ? P : 1 - P;
+            constexpr int off = slot * kLineSlot + fr * 4096;
+            auto& ad = op.f < 4 ? at.b : at.a;
+            auto& d = op.f < 4 ? f[set].b[fr] : f[set].a[fr];
+            if constexpr (op.kind == kWhole || op.kind == kLow01) {
+                line_read<off>(d[0], ad[0]);
+                line_read<off>(d[1], ad[1]);
+            }
+            if constexpr (op.kind == kWhole || op.kind == kPiece2) line_read<off>(d[2], ad[2]);
+            if constexpr (op.kind == kHigh12) line_read_high<off>(d[1], d[2], ad[1], ad[2]);
+            if constexpr (op.kind == kHigh01) line_read_high<off>(d[0], d[1], ad[0], ad[1]);
+        }
+    };
+    // Fragments [from, to) of a set: valid from here on, and each in six registers in a row.  The nop: whatever the compiler copies to
+    // bring that about stands before it, and a vector write needs two wait states before a matrix instruction reads it.
+    auto settle = [&](auto ss, auto from, auto to, v6i (&t)[8]) {
+        auto& fs = f[decltype(ss)::value];
+#pragma unroll
+        for (int i = decltype(from)::value; i < decltype(to)::value; ++i) {
+            v2i(&p)[3] = i < 4 ? fs.b[i & 3] : fs.a[i & 3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) asm volatile("" : "+v"(p[j]));
+            t[i] = (v6i){p[0][0], p[0][1], p[1][0], p[1][1], p[2][0], p[2][1]};
+            asm volatile("" : "+v"(t[i]));
+        }
+        asm volatile("s_nop 1" ::: "memory");
+    };
+
+    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");            // line 0 and the scales
+    asm volatile("s_barrier" ::: "memory");
+    {
+        Addr at;
+        StaticFor<0, 8>::run([&](auto q) { read(Int<7>(), Int<1>(), q, at); });          // the scales of groups 0 and 1
+        address(Int<2>(), at);
+        StaticFor<0, LineSlot<6>::OPS.n>::run([&](auto q) { read(Int<6>(), Int<1>(), q, at); });
+        address(Int<0>(), at);
+        StaticFor<8, LineSlot<7>::OPS.n>::run([&](auto q) { read(Int<7>(), Int<1>(), q, at); });
+    }
+
+    // One group: 16 matrix instructions, row by row of A's fragments, the other instructions between them.
+    auto group = [&](auto gg, auto pp) {
+        constexpr int G = decltype(gg)::value, P = decltype(pp)::value, SET = kLineSet[G];
+        constexpr LineOps ops = LineSlot<G>::OPS;
+        // the first group whose pieces are read here, and the second
+        constexpr int G1 = ops.op[(G & 1) ? 8 : 0].group, G2 = ops.op[ops.n - 1].group;
+        constexpr int barrier = (G == 1 || G == 4) ? 4 : G == 6 ? 6 : -1;      // before this matrix instruction
+        constexpr int slot = G == 4 ? 1 - P : P;                 // of the line requested behind the barrier
+        constexpr int first = barrier < 0 ? 0 : barrier;         // matrix instruction behind which the reads begin
+        // groups 0 and 1 were read last: all but the last two fragments of A
+        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(G <= 1 ? 6 : line_reads_after(G)) : "memory");
+        hold_accumulators<64>();
+        if constexpr ((G & 1) == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                asm volatile("v_lshrrev_b32 %0, %1, %0" : "+v"(sc[(G / 2) & 1][i]) : "v"(shift));
+            }
+        }
+        Addr at1, at2;
+        address(Int<G1>(), at1);
+        if constexpr (G2 != G1) address(Int<G2>(), at2);
+        v6i t[8];
+        settle(Int<SET>(), Int<0>(), Int<(G <= 1 ? 6 : 8)>(), t);
+        StaticFor<0, 16>::run([&](auto mm) {
+            constexpr int m = decltype(mm)::value, i = m >> 2, j = (i & 1) ? 3 - (m & 3) : m & 3;
+            if constexpr (m == barrier) {
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+                asm volatile("s_barrier" ::: "memory");
+                hold_accumulators<64>();
+            }
+            if constexpr (G <= 1 && m == 8) {
+                asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(line_reads_before(G, first, m)) : "memory");
+                settle(Int<SET>(), Int<6>(), Int<8>(), t);
+            }
+            line_mfma<4 * i + j, G & 1>(t[j], t[4 + i], sc[(G / 2) & 1][j], sc[(G / 2) & 1][4 + i]);
+            if constexpr (m >= first && m < 14) {
+                StaticFor<line_ops_before(G, first, m), line_ops_before(G, first, m + 1)>::run([&](auto q) {
+                    constexpr LineOp op = LineSlot<G>::OPS.op[decltype(q)::value];
+                    if constexpr (op.group == G1 || op.kind == kScale) read(gg, pp, q, at1);
+                    else read(gg, pp, q, at2);
+                });
+            }
+            if constexpr (barrier >= 0 && m >= barrier) {
+                constexpr int n = 16 - barrier, at = m - barrier;
+                StaticFor<at * 16 / n, (at + 1) * 16 / n>::run([&](auto d) { request(Int<slot>(), d); });
+            }
+        });
+        if constexpr (G == 4) request_scales(Int<1 - P>());
+        if constexpr (barrier >= 0) next_line();
+    };
+    auto superblock = [&](auto pp) { StaticFor<0, 8>::run([&](auto g) { group(g, pp); }); };
+    for (;;) {
+        superblock(Int<0>());
+        if (--supers == 0) break;
+        superblock(Int<1>());
+        if (--supers == 0) break;
+    }
+    // the last results need 18 wait states before a vector instruction reads them; the requests past the end have landed
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+    hold_accumulators<64>();
+    __syncthreads();
+
+    // ---- epilogue: 32 rows at a time through a private LDS region, then eight (bf16) or four consecutive columns per lane: whole
+    // lines per request
+    float* region = reinterpret_cast<float*>(smem_big) + wave * 32 * kLineEpiPitch;
+    const int64_t row0 = m0 + wave_m * 128, col0 = n0 + wave_n * 128;
+    StaticFor<0, 4>::run([&](auto ii) {
+        constexpr int i = decltype(ii)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        hold_accumulators<64>();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        StaticFor<0, 16>::run([&](auto qq) {                     // tile 4 i + q / 4, columns 8 (q % 4) + 4 half
+            constexpr int q = decltype(qq)::value;
+            *reinterpret_cast<v4i*>(region + lrow * kLineEpiPitch + 32 * (q >> 2) + 8 * (q & 3) + 4 * half) = read_acc<16 * i + q>();
+        });
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (a.c_is_f32) {
+            const int cc = 4 * lrow;
+            const int64_t left = a.N - (col0 + cc);
+#pragma unroll
+            for (int p = 0; p < 16; ++p) {
+                const int rr = 2 * p + half;
+                const v4f v = *reinterpret_cast<const v4f*>(region + rr * kLineEpiPitch + cc);
+                float* dst = reinterpret_cast<float*>(a.C) + (row0 + 32 * i + rr) * a.ldc + col0 + cc;
+                if (row0 + 32 * i + rr >= a.M) continue;
+                if (left >= 4) {
+                    __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(dst));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (e < left) dst[e] = v[e];
+                }
+            }
+        } else {
+            const int cc = 8 * (lane & 15);
+            const int64_t left = a.N - (col0 + cc);
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int rr = 4 * p + (lane >> 4);
+                const v4f x = *reinterpret_cast<const v4f*>(region + rr * kLineEpiPitch + cc);
+                const v4f y = *reinterpret_cast<const v4f*>(region + rr * kLineEpiPitch + cc + 4);
+                const v4u w = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+                uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (row0 + 32 * i + rr) * a.ldc + col0 + cc;
+                if (row0 + 32 * i + rr >= a.M) continue;
+                if (left >= 8) {
+                    __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(dst));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (e < left) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        }
+    });
+}
+
 }  // namespace
 
 hipError_t launch_gemm_mx6(const Mx6GemmArgs& a, hipStream_t s) {
     if (a.M == 0 || a.N == 0) return hipSuccess;
     if (a.K % 128 != 0) return hipErrorInvalidValue;
-    // Enough 256 x 256 tiles to give most compute units one: the DMA kernel.  Its 16-byte stores need aligned rows of C.
     const int64_t big_m = (a.M + 255) / 256, big_n = (a.N + 255) / 256;
+    const int64_t tiles_m = (a.M + 127) / 128, tiles_n = (a.N + 127) / 128;
+    if (tiles_m * tiles_n > 0x7FFFFFFF) return hipErrorInvalidValue;
     const int64_t c_bytes = a.c_is_f32 ? 4 : 2;
-    if (big_m * big_n >= 192 && big_m * big_n <= 0x7FFFFFFF && (a.ldc * c_bytes) % 16 == 0 &&
-        (reinterpret_cast<uintptr_t>(a.C) & 15u) == 0) {
+    // What the DMA kernels take: 16-byte stores need aligned rows of C.  Whole lines: K in superblocks of 384 code bytes, scale rows in
+    // 16-byte chunks, the rows of a tile inside one buffer.
+    const bool big = (a.ldc * c_bytes) % 16 == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15u) == 0;
+    const int64_t most = ((int64_t(1) << 32) - 1024) / 256;
+    const bool lines = a.K > 0 && a.K % 512 == 0 && a.lda <= most && a.ldb <= most && a.ldsa <= most && a.ldsb <= most &&
+                       a.ldsa % 16 == 0 && a.ldsb % 16 == 0 && (reinterpret_cast<uintptr_t>(a.SA) & 15u) == 0 &&
+                       (reinterpret_cast<uintptr_t>(a.SB) & 15u) == 0;
+    // In whole lines as soon as a compute unit would get two of the small tiles: a round of 256 x 256 tiles takes as long as 1.2 of
+    // 128 x 128.  Small tiles against whole lines, tokens x out-features x in-features: 1024 x 4096 x 4096 (256 small tiles) 31.5 us /
+    // 36.4, 2048 x 3072 x 4096 50.3 / 36.3, 768 x 14336 x 4096 77.1 / 38.2, 2304 x 4096 x 512 20.1 / 12.5, 640 x 14336 x 8192 137 / 65.
+    // Other K: the eight-wavefront kernel where its tiles fill most of the chip.
+    if (big && (lines ? tiles_m * tiles_n > kComputeUnits : big_m * big_n >= 192)) {
         static std::once_flag once;
         static hipError_t attr_result = hipSuccess;
         std::call_once(once, [&] {
-            attr_result = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_mx6_big_kernel<false>),
+            attr_result = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_mx6_big_kernel),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
             if (attr_result == hipSuccess)
-                attr_result = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_mx6_big_kernel<true>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kWideLds);
+                attr_result = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_mx6_lines_kernel),
+                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLinesLds);
         });
         if (attr_result != hipSuccess) return attr_result;
-        const bool wide = a.K % 512 == 0 && a.ldsa % 16 == 0 && a.ldsb % 16 == 0 &&
-                          (reinterpret_cast<uintptr_t>(a.SA) & 15u) == 0 && (reinterpret_cast<uintptr_t>(a.SB) & 15u) == 0;
-        if (wide)
-            hipLaunchKernelGGL(gemm_mx6_big_kernel<true>, dim3((unsigned)(big_m * big_n)), dim3(512), kWideLds, s, a, (int)big_m,
-                               (int)big_n);
-        else
-            hipLaunchKernelGGL(gemm_mx6_big_kernel<false>, dim3((unsigned)(big_m * big_n)), dim3(512), kBigLds, s, a, (int)big_m,
-                               (int)big_n);
+        const dim3 grid((unsigned)(big_m * big_n));
+        if (lines) hipLaunchKernelGGL(gemm_mx6_lines_kernel, grid, dim3(256), kLinesLds, s, a, (int)big_m, (int)big_n);
+        else hipLaunchKernelGGL(gemm_mx6_big_kernel, grid, dim3(512), kBigLds, s, a, (int)big_m, (int)big_n);
         return hipGetLastError();
     }
-    const int64_t tiles_m = (a.M + 127) / 128, tiles_n = (a.N + 127) / 128;
-    if (tiles_m * tiles_n > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipLaunchKernelGGL(gemm_mx6_kernel, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s, a, (int)tiles_n);
     return hipGetLastError();
 }

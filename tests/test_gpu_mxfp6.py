@@ -80,6 +80,37 @@ def test_mx6_gemm_against_exact_product(M, N, K):
     gu.assert_bf16_within_one_ulp(out16, got.astype(np.float32), "bf16 output")
 
 
+# The kernel that moves whole 128-byte lines (K a multiple of 512, more than 256 tiles of 128 x 128): one superblock of 512, an odd
+# and an even number of them; rows and columns one past a tile, a lone row of the last tile, columns that no store divides; views whose
+# row pitches are not whole lines, and one whose scale rows are not whole 16-byte chunks (the other kernel takes it).
+@pytest.mark.parametrize("M,N,K,pad,scale_pad", [(2049, 2050, 512, 0, 0), (1281, 3336, 1024, 48, 16), (2300, 2561, 1536, 0, 0),
+                                                 (2047, 2303, 2048, 16, 0), (3329, 3585, 512, 0, 4)])
+def test_mx6_gemm_in_whole_lines(M, N, K, pad, scale_pad):
+    def operand(bits):
+        codes, scales, want_c, want_s = quant_and_check(bits, 512)       # rotated: the bound below is for blocks of like magnitude
+        wide = torch.full((codes.shape[0], codes.shape[1] + pad), 255, dtype=torch.uint8, device=gu.DEV)
+        wide[:, :codes.shape[1]] = codes
+        wide_s = torch.full((scales.shape[0], scales.shape[1] + scale_pad), 255, dtype=torch.uint8, device=gu.DEV)
+        wide_s[:, :scales.shape[1]] = scales
+        return wide[:, :codes.shape[1]], wide_s[:, :scales.shape[1]], mx.mx_dequantize(want_c, want_s)
+    a, sa, xd = operand(inputs.make_activations(M, K, 0.01, M + N))
+    b, sb, wd = operand(inputs.make_weights(N, K, M + N))
+    got = binding.halo_gemm_mx6(a, sa, b, sb)
+    rng = np.random.default_rng(M)
+    ri = np.unique(np.concatenate([rng.choice(M, 64), [0, 127, 128, 255, 256, M - 2, M - 1]]))
+    ci = np.unique(np.concatenate([rng.choice(N, 64), [0, 127, 128, 255, 256, N - 2, N - 1]]))
+    part = got[torch.as_tensor(ri, device=gu.DEV)][:, torch.as_tensor(ci, device=gu.DEV)].cpu().numpy().astype(np.float64)
+    # the bound of test_mx6_gemm_against_exact_product
+    bound = np.abs(xd[ri]) @ np.abs(wd[ci]).T * 2.0 ** -16 + 1e-30
+    assert np.all(np.abs(part - xd[ri] @ wd[ci].T) <= bound)
+    # all of it against the same product in slices of at most 256 small tiles, which the kernel of small products takes
+    rows = torch.cat([binding.halo_gemm_mx6(a[i:i + 1024], sa[i:i + 1024], b, sb) for i in range(0, M, 1024)])
+    mag = torch.as_tensor(np.abs(xd), dtype=torch.float32, device=gu.DEV) @ torch.as_tensor(np.abs(wd), dtype=torch.float32, device=gu.DEV).T
+    assert bool(((got - rows).abs() <= mag * 2.0 ** -14).all())         # each within 2^-16 of the exact product, and the bound is rounded
+    out16 = binding.halo_gemm_mx6(a, sa, b, sb, out_dtype=torch.bfloat16)
+    gu.assert_bf16_within_one_ulp(out16, got.cpu().numpy(), "bf16 output")
+
+
 def test_mx6_forward_on_config_c5_shape_sampled():
     """Config c5: X 8192 x 4096, W 4096 x 4096, FWHT over K = 4096, MXFP6, fp32 accumulation.  Codes and scales of both
     operands in full; the product on sampled rows and columns (each output element is an independent dot product)."""
