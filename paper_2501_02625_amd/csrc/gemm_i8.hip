@@ -64,6 +64,11 @@ struct GemmCfg {
     static constexpr int LA = A_BYTES / 4096, LB = B_BYTES / 4096;   // DMA instructions per wavefront and stage
     static constexpr int LDS_BYTES = NSA * A_BYTES + NSB * B_BYTES;
     static constexpr int ROW = 2 * TN;                           // matrix instructions per row of tiles
+    // TN a multiple of 4: a wavefront's columns lie together.  Six column tiles (192 columns): four together and, behind all of those,
+    // two, so that the whole lines that the epilogue stores start at a line.
+    static constexpr int LOW_STEP = TN % 4 ? TN - 2 : TN;        // column tiles between the two wavefronts' first ones
+    static __device__ __forceinline__ int high_column(int wave_n) { return 16 * (2 * LOW_STEP + 2 * wave_n); }
+    static_assert(TN % 4 == 0 || (TN % 4 == 2 && TRANSB), "column tiles");
     static constexpr int READS_B = TRANSB ? 2 * TN : 4 * TN;     // LDS read instructions for B's fragments of one unit
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
 };
@@ -86,21 +91,20 @@ __device__ __forceinline__ int row_of_lane(int l16) { return (l16 & 4) ? l16 ^ 3
 
 // Where the accumulators of a lane lie in C.  Register tile (i, j) holds row row0 + 16 i and the four columns from
 // col(j); the first and the second half of the column tiles have their own base: with SWAP, the two wavefronts that share
-// columns hold the halves in opposite order (epilogue_left8).
+// columns hold the halves in opposite order (epilogue_left8).  192-column tiles: GemmCfg::high_column.
 template <class Cfg>
 struct Place {
     int64_t row0, col_lo, col_hi;
+    static constexpr int LOW = Cfg::TN % 4 ? Cfg::TN - 2 : Cfg::TN / 2;      // column tiles of the first part
     __device__ __forceinline__ Place(int64_t m0, int64_t n0, int wave, int lane, bool swap) {
         const int wave_m = wave >> 1, wave_n = wave & 1;
         row0 = m0 + wave_m * Cfg::WM + row_of_lane(lane & 15);
+        const int64_t c = n0 + wave_n * 16 * Cfg::LOW_STEP + 4 * (lane >> 4);
         const bool s = swap && wave_m;
-        const int64_t c = n0 + wave_n * Cfg::WN + 4 * (lane >> 4);
         col_lo = c + (s ? Cfg::WN / 2 : 0);
-        col_hi = c + (s ? 0 : Cfg::WN / 2);
+        col_hi = Cfg::TN % 4 ? n0 + Cfg::high_column(wave_n) + 4 * (lane >> 4) : c + (s ? 0 : Cfg::WN / 2);
     }
-    __device__ __forceinline__ int64_t col(int j) const {
-        return j < Cfg::TN / 2 ? col_lo + 16 * j : col_hi + 16 * (j - Cfg::TN / 2);
-    }
+    __device__ __forceinline__ int64_t col(int j) const { return j < LOW ? col_lo + 16 * j : col_hi + 16 * (j - LOW); }
 };
 
 // Register fragments of one wavefront: A's of the current unit (replaced row by row), B's of this unit and the next; bt are
@@ -199,13 +203,16 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
     hold_accumulators<TM * TN>();
     StaticFor<0, TM * TN>::run([&](auto t) { clear_acc<decltype(t)::value>(); });
     // ---- fragment addresses inside stage 0 (for K-strided B the K half and the second row block are immediate offsets)
-    uint32_t a_addr[2], b_addr[TRANSB ? 2 : TN];
+    uint32_t a_addr[2], b_addr[TRANSB ? 2 : TN], b_high[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) a_addr[k] = lds_a + (wave_m * Cfg::WM + lrow) * BK + 16 * ((4 * k + g4) ^ (lrow >> 1));
     if constexpr (TRANSB) {
         static_assert(!SWAP, "the left-hand epilogue is for K-strided B");
 #pragma unroll
-        for (int k = 0; k < 2; ++k) b_addr[k] = lds_b + (wave_n * Cfg::WN + l16) * BK + 16 * ((4 * k + g4) ^ (l16 >> 1));
+        for (int k = 0; k < 2; ++k) {
+            b_addr[k] = lds_b + (wave_n * 16 * Cfg::LOW_STEP + l16) * BK + 16 * ((4 * k + g4) ^ (l16 >> 1));
+            b_high[k] = lds_b + (Cfg::high_column(wave_n) + l16) * BK + 16 * ((4 * k + g4) ^ (l16 >> 1));
+        }
     } else {
         const int row = 16 * g4 + (l16 >> 1);
         const int turn = kmajor_swizzle<BN>(row) ^ (wave_n * TN) ^ (SWAP && wave_m ? TN / 2 : 0);
@@ -223,7 +230,8 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
         constexpr int s = decltype(ss)::value, q = decltype(qq)::value;
         if constexpr (TRANSB) {
             constexpr int k = q & 1, j = q >> 1;
-            lds_read16<j * 16 * BK>(f.b[s][k][j], b_addr[k] + stage);
+            if constexpr (TN % 4 && j >= Cfg::LOW_STEP) lds_read16<(j - Cfg::LOW_STEP) * 16 * BK>(f.b[s][k][j], b_high[k] + stage);
+            else lds_read16<j * 16 * BK>(f.b[s][k][j], b_addr[k] + stage);
         } else {
             constexpr int h = q & 1, k = (q >> 1) & 1, j = q >> 2;
             lds_read8_tr<k * 64 * BN + h * 8 * BN>(f.bt[s][k][j][h], b_addr[j] + stage);
@@ -467,6 +475,12 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const Place<Cfg>& at
                 if (in && ok_lo) __builtin_nontemporal_store(lower, reinterpret_cast<v4u*>(dst + at.col(j)));
                 if (in && ok_up) __builtin_nontemporal_store(upper, reinterpret_cast<v4u*>(dst + at.col(j) + 8 * a.ldc));
             });
+            if constexpr (TN % 4 != 0) {                          // two more, half a line that the other wavefront completes
+                constexpr int j = TN - 2;
+                const v4u w = pair_of(ii, Int<j>());
+                uint16_t* half = reinterpret_cast<uint16_t*>(a.C) + (at.row0 + 16 * i) * a.ldc + shift + at.col(j);
+                if (at.row0 + 16 * i < a.M && left_of(j) > shift) __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(half));
+            }
         }
     };
     if constexpr (!RAGGED) {
@@ -772,23 +786,8 @@ __device__ __forceinline__ void lowrank_prepare(const GemmArgs& a, const Place<C
 }
 
 // ------------------------------------------------------------------------------------------------ kernel
-// LEFT: this instance also carries the epilogue that runs the low strides of a left-hand rotation.
-// LR: this instance also carries the low-rank side product (lowrank_prepare).
-// RAGGED: N (of either product) is not a multiple of 16.
-template <int TM, int TN, bool TRANSB, bool LEFT, bool LR, bool RAGGED>
-__global__ void __launch_bounds__(256, 1)
-gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, int tiles_n2, unsigned blocks1) {
-    using Cfg = GemmCfg<TM, TN, TRANSB>;
-    // A second, independent product may ride in the same launch (workgroups from blocks1 on): the tail and the
-    // epilogue of one then overlap the main loop of the other.
-    int bid = blockIdx.x;
-    if (blockIdx.x >= blocks1) {
-        bid -= blocks1;
-        a = a2;
-        tiles_m = tiles_m2;
-        tiles_n = tiles_n2;
-    }
-    extern __shared__ __align__(16) unsigned char smem[];
+template <class Cfg, bool TRANSB, bool LEFT, bool LR, bool RAGGED>
+__device__ __forceinline__ void one_tile(const GemmArgs& a, int bid, int tiles_m, int tiles_n, unsigned char* smem) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile_m, tile_n;
@@ -805,6 +804,30 @@ gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, 
         }
     }
     epilogue<Cfg, LR, RAGGED>(a, at, lane);
+}
+
+// LEFT: this instance also carries the epilogue that runs the low strides of a left-hand rotation.
+// LR: this instance also carries the low-rank side product (lowrank_prepare).
+// RAGGED: N (of either product) is not a multiple of 16.
+// TN2: the second product of the launch has tiles of that width.
+template <int TM, int TN, bool TRANSB, bool LEFT, bool LR, bool RAGGED, int TN2 = TN>
+__global__ void __launch_bounds__(256, 1)
+gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, int tiles_n2, unsigned blocks1) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    // A second, independent product may ride in the same launch (workgroups from blocks1 on): the tail and the
+    // epilogue of one then overlap the main loop of the other.
+    int bid = blockIdx.x;
+    if (blockIdx.x >= blocks1) {
+        bid -= blocks1;
+        if constexpr (TN2 != TN) {
+            one_tile<GemmCfg<TM, TN2, TRANSB>, TRANSB, LEFT, LR, RAGGED>(a2, bid, tiles_m2, tiles_n2, smem);
+            return;
+        }
+        a = a2;
+        tiles_m = tiles_m2;
+        tiles_n = tiles_n2;
+    }
+    one_tile<GemmCfg<TM, TN, TRANSB>, TRANSB, LEFT, LR, RAGGED>(a, bid, tiles_m, tiles_n, smem);
 }
 
 // ------------------------------------------------------------------------------------------------ small products
@@ -1149,6 +1172,30 @@ hipError_t launch_tiles(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = n
     return hipGetLastError();
 }
 
+// The first `wide` columns in tiles of 256 x 256, the others in 256 x 192 (two_widths).
+hipError_t launch_two_widths(const GemmArgs& a, int64_t wide, hipStream_t s) {
+    if (a.left_stages != 0 || a.lr_rank != 0 || a.N % 16 != 0 || wide % 256 != 0 || wide >= a.N) return hipErrorInvalidValue;
+    static std::once_flag once;
+    static hipError_t attr_result = hipSuccess;
+    constexpr int lds = GemmCfg<8, 8, true>::LDS_BYTES;
+    auto kern = gemm_i8_kernel<8, 8, true, false, false, false, 6>;
+    hipError_t e = raise_lds_limit(kern, lds, &once, &attr_result);
+    if (e != hipSuccess) return e;
+    GemmArgs g = a, g2 = a;
+    g.whole_lines = bf16_whole_lines(a.M, a.N, a.ldc);
+    g2.whole_lines = g.whole_lines;
+    g.N = wide;
+    g2.N -= wide;
+    g2.B += wide * a.ldb;
+    if (a.col_scale) g2.col_scale += wide;
+    if (a.acc_out) g2.acc_out += wide;
+    if (a.C) g2.C = static_cast<char*>(a.C) + wide * (a.c_is_f32 ? 4 : 2);
+    const int tiles_m = (int)((a.M + 255) / 256), n1 = (int)(wide / 256), n2 = (int)((g2.N + 191) / 192);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * (n1 + n2))), dim3(256), lds, s, g, tiles_m, n1, g2, tiles_m, n2,
+                       (unsigned)(tiles_m * n1));
+    return hipGetLastError();
+}
+
 template <int TM, bool TRANSB, int TN = 4>
 hipError_t launch_small(const GemmArgs& a, hipStream_t s, const GemmArgs* a2 = nullptr) {
     using Cfg = SmallCfg<TM, TN, TRANSB>;
@@ -1195,6 +1242,10 @@ constexpr int kStepOfConfig[4] = {64, 128, 128, 64};
 
 template <bool TRANSB>
 hipError_t launch_by_shape(const GemmArgs& a, hipStream_t s) {
+    if constexpr (TRANSB) {
+        const int64_t wide = two_widths(a);
+        if (wide >= 0) return launch_two_widths(a, wide, s);
+    }
     switch (a.config < 0 ? choose_config(a, nullptr) : a.config) {
         case 0:
         case 1: return launch_tiles<8, 8, TRANSB>(a, s);

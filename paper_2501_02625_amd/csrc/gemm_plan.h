@@ -94,27 +94,30 @@ inline double product_cost(const GemmArgs& a, int config) {
     const int64_t tiles = config == kTiles256 ? tiles_of(a, 256, 256) : tiles_of(a, 256, 128);
     return 4.0 + (double)((tiles + kComputeUnits - 1) / kComputeUnits) * t;
 }
-// Two products in one launch.  256 x 256 tiles are dispatched in order, the first product's first: the time at which the
-// last of the second product's tiles is done, when each compute unit takes the next tile as it gets free.
+// Tiles of two kinds in one launch, dispatched in order, n1 of the first kind and then n2 of the second: the time at which the last
+// one is done, when each compute unit takes the next tile as it gets free.
+inline double two_kinds_done(int64_t n1, double t1, int64_t n2, double t2) {
+    const double f = (double)(n1 / kComputeUnits) * t1;           // when the first compute units are free of the first kind
+    const int64_t late = n1 % kComputeUnits;                      // compute units that take one more of it
+    auto done = [&](double x) {
+        const double e = (x - f) / t2 + 1e-6, l = (x - f - t1) / t2 + 1e-6;
+        return (kComputeUnits - late) * (int64_t)(e > 0 ? e : 0) + late * (int64_t)(l > 0 ? l : 0);
+    };
+    const int64_t rounds = n2 / kComputeUnits;                    // lower bound of the rounds of the second kind
+    double best = 1e30;
+    for (int64_t k = rounds; k <= rounds + 3 + (int64_t)(t1 / t2); ++k)
+        for (const double x : {f + k * t2, f + t1 + k * t2})
+            if (x < best && done(x) >= n2) best = x;
+    return std::max(best, f + (late ? t1 : 0.0));
+}
+// Two products in one launch, the first product's tiles first.
 inline double pair_cost(const GemmArgs& a1, const GemmArgs& a2, int config) {
     const double t1 = tile_cost(a1, config), t2 = tile_cost(a2, config);
     if (config == kTiles128) {
         const int64_t n1 = tiles_of(a1, 128, 128), n2 = tiles_of(a2, 128, 128);
         return 3.0 + std::max(std::max(t1, t2), (n1 * t1 + n2 * t2) / kComputeUnits);
     }
-    const int64_t n1 = tiles_of(a1, 256, 256), n2 = tiles_of(a2, 256, 256);
-    const double f = (double)(n1 / kComputeUnits) * t1;           // when the first compute units are free of the first product
-    const int64_t late = n1 % kComputeUnits;                      // compute units that take one more of its tiles
-    auto done = [&](double x) {
-        const double e = (x - f) / t2 + 1e-6, l = (x - f - t1) / t2 + 1e-6;
-        return (kComputeUnits - late) * (int64_t)(e > 0 ? e : 0) + late * (int64_t)(l > 0 ? l : 0);
-    };
-    const int64_t rounds = n2 / kComputeUnits;                    // lower bound of the rounds of the second product
-    double best = 1e30;
-    for (int64_t k = rounds; k <= rounds + 3 + (int64_t)(t1 / t2); ++k)
-        for (const double x : {f + k * t2, f + t1 + k * t2})
-            if (x < best && done(x) >= n2) best = x;
-    return 4.0 + std::max(best, f + (late ? t1 : 0.0));
+    return 4.0 + two_kinds_done(tiles_of(a1, 256, 256), t1, tiles_of(a2, 256, 256), t2);
 }
 
 // The configuration of one product, or of a pair (a2).  A product whose 32 x 64 (64 x 64) tiles fit the compute units once
@@ -135,6 +138,37 @@ inline int choose_config(const GemmArgs& a, const GemmArgs* a2) {
     for (const int c : {kTiles256x128, kTiles128})
         if (product_cost(a, c) < product_cost(a, best)) best = c;
     return best;
+}
+
+// Tiles of two widths in one launch (one product, K-contiguous B): the first `wide` columns in tiles of 256 x 256, the others in
+// 256 x 192, so that the last round fills the compute units or is a shorter one.  Returns `wide` where that is the faster way by
+// estimate, otherwise -1.  The estimate of a narrow tile where all run at once and where they do not, and how far that of the 128 x 128
+// tiles is above what they take there, are fitted to 180 products, sizes drawn over 256 .. 8192 by 256 .. 14336 by 256 .. 14336, timed
+// in one width and in two: those that go in two widths gain 10 % in the mean, the worst loses 3 % (2992 x 8192 x 4352, fp32 out).  bf16 out, one width / two:
+// 2560 x 4096 x 4096 46.2 us / 38.5, 2048 x 5120 x 4096 45.4 / 36.4, 2896 x 3072 x 8192 82.9 / 67.4, 5120 x 7296 x 4096 134.5 / 112.5,
+// 4608 x 5120 x 14336 270 / 226, 6112 x 14336 x 832 124.5 / 126.1 (not taken); fp32 out 2048 x 14336 x 4096 115.7 / 105.6.  (224 columns
+// fill 2048 x 14336 in two equal rounds, but a bf16 row of a tile is then no whole number of cache lines: 118 us against 107 with 256.)
+inline int64_t two_widths(const GemmArgs& a) {
+    if (a.config >= 0 || a.left_stages || a.lr_rank || a.N % 16 != 0 || !a.transB) return -1;
+    const int c = choose_config(a, nullptr);
+    if (c == kSmall32 || c == kSmall64) return -1;
+    const int64_t panels = (a.M + 255) / 256;
+    const double u = units_of(a), wide_out = (a.acc_out || a.c_is_f32) ? 3.0 : 0.0, one_width = product_cost(a, c);
+    double best = 1e30;
+    int64_t wide = -1;
+    for (int64_t n1 = 0; n1 * 256 < a.N; ++n1) {
+        const int64_t n2 = (a.N - n1 * 256 + 191) / 192;
+        const bool at_once = panels * (n1 + n2) <= kComputeUnits;
+        if (at_once && n1 > 0) continue;
+        const double t = 4.0 + wide_out + (at_once ? 8.5 + 0.84 * u : two_kinds_done(panels * n1, tile_cost(a, kTiles256), panels * n2,
+                                                                                       7.0 + wide_out + 0.95 * u) - wide_out);
+        const double limit = one_width * (c != kTiles128 ? 1.0 : !at_once ? 0.88 : u < 12 ? 0.85 : 0.92);
+        if (t < limit && t < best) {
+            best = t;
+            wide = n1 * 256;
+        }
+    }
+    return wide;
 }
 
 // Columns of the small kernel's tiles of 16 and 32 rows (kSmall32), one product with a K-contiguous B: 16 or 32 instead of 64 while

@@ -20,19 +20,27 @@ GemmArgs product(long M, long N, long K) {
     return g;
 }
 
-// each line: `one M N K`, `small M N K` (columns of the small tiles), `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
+// each line: `two M N K` (columns in wide tiles, bf16 out and fp32 out), `one M N K`, `small M N K` (columns of the small tiles), `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
 // `max rows cols parts` (column maxima reduced first?), // `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
 int main() {
     char what[8];
     while (std::scanf("%7s", what) == 1) {
         long v[7];
-        const int count = what[0] == 'o' || what[0] == 's' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' ? 3 : what[0] == 'p' ? 6 : 7;
+        const int count = what[0] == 'o' || what[0] == 's' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' || what[0] == 't' ? 3 : what[0] == 'p' ? 6 : 7;
         for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
         if (what[0] == 'l') {
             GemmArgs gx = product(v[0], v[1], v[2]);
             const GemmArgs gg = product(v[2], v[1], v[0]);
             if (v[6]) { gx.lr_rank = (int)v[6]; gx.acc_out = nullptr; gx.C = &somewhere; gx.c_is_f32 = 1; }
             std::printf("%d\n", (int)left_in_epilogue(gx, v[5] ? &gg : nullptr, (int32_t)v[4], (int32_t)v[3]));
+            continue;
+        }
+        if (what[0] == 't') {
+            GemmArgs g = product(v[0], v[1], v[2]);
+            g.transB = 1;
+            const long with_sums = (long)two_widths(g);
+            g.acc_out = nullptr; g.C = &somewhere;
+            std::printf("%ld,%ld\n", (long)two_widths(g), with_sums);
             continue;
         }
         if (what[0] == 'f') {
@@ -137,6 +145,22 @@ def test_column_maxima_are_reduced_first_where_that_is_faster(ask):
     assert ask([("max", 8192, 14336, 4), ("max", 8192, 14336, 16)]) == ["0", "1"]      # the launch 4.9 us and 3 saved; 488 us and 478
     lines = test_gpu_linear.MAXIMA          # the first pass takes 64 or 128 rows, or up to 2048 of them
     assert ask(("max", b, n, b // hb) for b, n, hb, first in lines) == [str(int(first)) for b, n, hb, first in lines]
+
+
+# rows, columns, K and microseconds of a bf16 product in tiles of one width and in the two widths that the rule or a near one takes,
+# on an MI355X
+TIMED_WIDTHS = [(2048, 14336, 4096, 107.0, 100.0), (2560, 4096, 4096, 46.2, 38.5), (2048, 5120, 4096, 45.4, 36.4),
+                (5120, 7296, 4096, 134.5, 112.5), (4608, 5120, 14336, 270.4, 226.0),
+                (2896, 3072, 8192, 82.9, 67.4), (816, 10768, 6464, 77.0, 62.0), (1840, 10256, 2432, 49.8, 54.6),
+                (4096, 4720, 4096, 74.3, 80.7), (4864, 2256, 1024, 17.8, 19.8), (5888, 1936, 1024, 17.5, 19.4),
+                (4096, 4096, 4096, 52.3, 73.2), (8192, 4096, 4096, 104.0, 117.7), (2048, 4096, 4096, 29.5, 35.0)]
+
+
+def test_tiles_of_two_widths_where_they_are_faster(ask):
+    said = [int(s.split(",")[0]) >= 0 for s in ask(("two", M, N, K) for M, N, K, *us in TIMED_WIDTHS)]
+    assert said == [one > two for M, N, K, one, two in TIMED_WIDTHS]
+    shapes = test_gpu_gemm.TWO_WIDTHS
+    assert ask(("two", M, N, K) for M, N, K, *wide in shapes) == ["%d,%d" % (bf16, f32) for M, N, K, bf16, f32 in shapes]
 
 
 def left(b, m, n, hm, hb, both, rank=0):

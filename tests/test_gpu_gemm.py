@@ -102,6 +102,32 @@ def test_b_is_a_column_slice(M, N, config):
     gu.assert_codes_equal(acc[:, :N], orc.gemm_codes(a, wide[:, c0:c0 + N]), "accumulators")
 
 
+# Tiles of 256 and of 192 columns in one launch (two_widths): M, N, K and the columns in wide tiles with bf16 and with fp32 out, -1 where
+# one width is taken.  All narrow and mixed; last narrow tiles of 32, 80, 144 and 192 columns; odd rows; odd, even and ragged units.
+TWO_WIDTHS = [(1845, 11168, 1040, 0, -1), (1363, 7760, 2064, 0, -1), (2048, 14336, 1168, 8192, 8192), (1923, 13840, 656, 6400, -1),
+              (1536, 8016, 1680, 0, 0)]
+
+
+@pytest.mark.parametrize("M,N,K", [t[:3] for t in TWO_WIDTHS])
+@pytest.mark.parametrize("pad", [0, 24])
+def test_tiles_of_two_widths(M, N, K, pad):
+    rng = np.random.default_rng(M + N)
+    a, b = gu.to_dev(rand_codes(rng, (M, K))), gu.to_dev(rand_codes(rng, (N, K)))
+    rs = gu.to_dev(rng.uniform(1e-3, 1e-2, M).astype(np.float32)); cs = gu.to_dev(rng.uniform(1e-3, 1e-2, N).astype(np.float32))
+    acc = torch.full((M + 1, N + pad), -7, dtype=torch.int32, device=gu.DEV)
+    outs = [torch.full((M + 1, N + pad), -7.0, dtype=dtype, device=gu.DEV) for dtype in (torch.float32, torch.bfloat16)]
+    for out in outs:
+        binding.halo_gemm_i8_desc(binding.gemm_desc(a, b, trans_b=True, row_scale=rs, col_scale=cs, out=out[:M, :N]))
+    binding.halo_gemm_i8_desc(binding.gemm_desc(a, b, trans_b=True, acc_out=acc[:M, :N]))
+    # sums of codes are integers below 2^31 and exact in float64
+    want = torch.cat([(a[i:i + 512].double() @ b.double().T).to(torch.int32) for i in range(0, M, 512)])
+    assert torch.equal(acc[:M, :N], want)
+    assert torch.equal(outs[0][:M, :N], want.float() * rs[:, None] * cs[None, :])
+    assert torch.equal(outs[1][:M, :N], outs[0][:M, :N].bfloat16())
+    for out in outs + [acc]:
+        assert bool((out[M:] == -7).all()) and bool((out[:, N:] == -7).all())
+
+
 # The split-K kernel for small products (16, 32 or 64 rows of a tile by 64 columns, K dealt to four wavefronts in units of
 # 128) and the first shape beyond it: fewer units than wavefronts, partial units, several trips, ragged rows and columns;
 # sums, scaled outputs and the pair.
