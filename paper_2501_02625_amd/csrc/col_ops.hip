@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "halo_internal.h"
+#include "wave_ops.h"
 
 namespace halo {
 namespace {
@@ -461,7 +462,7 @@ __global__ void __launch_bounds__(256) fill_u32_kernel(uint32_t* p, int64_t n, u
     if (i < n) p[i] = value;
 }
 
-// out[0] = max over in[0..n-1]: one workgroup (the vectors reduced here are per-row maxima, a few thousand entries).
+// out[0] = max over in[0..n-1]: one workgroup (the vectors reduced here are per-row maxima, more than kMaxGivenParts of them).
 __global__ void __launch_bounds__(1024) reduce_max_kernel(const float* in, int64_t n, float* out, const float* in2, int64_t n2,
                                                           float* out2) {
     __shared__ float s_part[16];
@@ -543,8 +544,8 @@ col_part_max_kernel(float* part, int parts, int64_t cols) {
 // into one dword per column, staged in LDS as [col][row/4] with a pitch of 33 dwords, and read back as
 // 16 consecutive rows per lane so that every output row is written in full 128-byte lines.
 constexpr int kTI = 128, kTJ = 128, kPitch = kTI / 4 + 1;
-// amax: `parts` vectors of the columns' partial maxima (non-negative, so their bit patterns order like they do); or one given
-// maximum for all columns.
+// amax: `parts` vectors of the columns' partial maxima (non-negative, so their bit patterns order like they do); or, given_amax, `parts`
+// values the largest of which is the maximum of all columns.
 __global__ void __launch_bounds__(256)
 col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols, const float* fold,
                    const float* amax, int parts, int8_t* out_q, int64_t ld_q, float* out_scale, const float* given_amax) {
@@ -602,7 +603,7 @@ col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols
         // the columns' maxima, reduced while those loads fly: thread group tid / 32 takes every eighth vector
         float am[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if (given_amax) {
-            am[0] = am[1] = am[2] = am[3] = *given_amax;
+            am[0] = am[1] = am[2] = am[3] = workgroup_max(given_amax, parts, s_part[0]);
         } else {
             for (int q = parts > 1 ? tid >> 5 : 0; q < parts; q += 8) {
 #pragma unroll
@@ -799,6 +800,8 @@ dual_amax_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, i
     }
 }
 
+// GIVEN: one maximum for everything, the largest of the row_tiles values at row_part, and no fold vectors.
+template <bool GIVEN>
 __global__ void __launch_bounds__(256)
 dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, int64_t cols,
                   const float* __restrict__ fold_c, const float* __restrict__ fold_r, const float* __restrict__ row_part,
@@ -844,7 +847,14 @@ dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, 
     }
     // Absmax of this tile's 128 columns and 128 rows from the partial maxima of pass 1 (every workgroup redoes the
     // reduction it needs: a few KB of L2 hits instead of one more kernel between the passes).
-    {
+    float inv_all = 0.0f;
+    if constexpr (GIVEN) {
+        const float am = workgroup_max(row_part, row_tiles, s_amax_r);
+        inv_all = am > 0.0f ? 127.0f / am : 0.0f;
+        const float scale = am > 0.0f ? am / 127.0f : 1.0f;
+        if (blockIdx.y == 0 && tid < 128 && j0 + tid < cols) col_scale[j0 + tid] = scale;
+        if (blockIdx.x == 0 && tid >= 128 && i0 + tid - 128 < rows) row_scale[i0 + tid - 128] = scale;
+    } else {
         const int o = tid & 127, h = tid >> 7;
         float tc = 0.0f, tr = 0.0f;
         if (j0 + o < cols) {
@@ -875,7 +885,7 @@ dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, 
     for (int e = 0; e < 8; ++e) {
         const bool ok = col + e < cols;
         fc[e] = (fold_c && ok) ? fold_c[col + e] : 1.0f;
-        const float am = s_amax_c[8 * jl + e];
+        const float am = GIVEN ? 0.0f : s_amax_c[8 * jl + e];
         inv_c[e] = am > 0.0f ? 127.0f / am : 0.0f;
     }
 #pragma unroll
@@ -891,13 +901,17 @@ dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, 
             const int64_t row = row0 + r;
             const bool rok = row < rows;
             const float fr = frow[s][r];
-            const float am = s_amax_r[4 * iq + r];
+            const float am = GIVEN ? 0.0f : s_amax_r[4 * iq + r];
             const float inv_r = am > 0.0f ? 127.0f / am : 0.0f;
             uint32_t br[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                br[e] = __float_as_uint((x[r][e] * fc[e]) * inv_r + 12582912.0f);
-                bc[r][e] = __float_as_uint((x[r][e] * fr) * inv_c[e] + 12582912.0f);
+                if constexpr (GIVEN) {
+                    br[e] = bc[r][e] = __float_as_uint(x[r][e] * inv_all + 12582912.0f);
+                } else {
+                    br[e] = __float_as_uint((x[r][e] * fc[e]) * inv_r + 12582912.0f);
+                    bc[r][e] = __float_as_uint((x[r][e] * fr) * inv_c[e] + 12582912.0f);
+                }
             }
             if (rok && col < cols) {
                 const uint32_t p0 = __builtin_amdgcn_perm(__builtin_amdgcn_perm(br[3], br[2], 0x0c0c0400u),
@@ -1032,8 +1046,18 @@ hipError_t launch_dual_quant(const DualQuantArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(amax, grid_a, dim3(256), 0, s, in, a.ld_in, a.rows, a.cols, a.fold_c, a.fold_r, row_part, col_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(dual_quant_kernel, grid, dim3(256), 0, s, in, a.ld_in, a.rows, a.cols, a.fold_c, a.fold_r, row_part,
+    hipLaunchKernelGGL(dual_quant_kernel<false>, grid, dim3(256), 0, s, in, a.ld_in, a.rows, a.cols, a.fold_c, a.fold_r, row_part,
                        col_part, (int)col_tiles, (int)row_tiles, a.out_q, a.ld_q, a.row_scale, a.out_qt, a.ld_qt, a.col_scale);
+    return hipGetLastError();
+}
+
+hipError_t launch_dual_quant_given(const DualQuantArgs& a, const float* given_amax, int parts, hipStream_t s) {
+    if (a.rows == 0 || a.cols == 0) return hipSuccess;
+    if (a.fold_c || a.fold_r || parts <= 0) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((a.cols + kDC - 1) / kDC), (unsigned)((a.rows + kDR - 1) / kDR));
+    hipLaunchKernelGGL(dual_quant_kernel<true>, grid, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in, a.rows,
+                       a.cols, static_cast<const float*>(nullptr), static_cast<const float*>(nullptr), given_amax,
+                       static_cast<const float*>(nullptr), 0, parts, a.out_q, a.ld_q, a.row_scale, a.out_qt, a.ld_qt, a.col_scale);
     return hipGetLastError();
 }
 
@@ -1068,17 +1092,24 @@ hipError_t launch_dual_quant_static(DualQuantArgs a, hipStream_t s) {
     return launch_dual_quant(a, s);
 }
 
-hipError_t launch_reduce_max(const float* in, int64_t n, float* out, hipStream_t s, const float* in2, int64_t n2, float* out2) {
+hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const float*& in2, int64_t& n2, float* out2, hipStream_t s) {
     if (n <= 0 || (in2 && n2 <= 0)) return hipErrorInvalidValue;
+    if (n <= kMaxGivenParts && (!in2 || n2 <= kMaxGivenParts)) return hipSuccess;
     hipLaunchKernelGGL(reduce_max_kernel, dim3(in2 ? 2 : 1), dim3(1024), 0, s, in, n, out, in2, n2, out2);
+    in = out;
+    n = 1;
+    if (in2) {
+        in2 = out2;
+        n2 = 1;
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, hipStream_t s) {
+hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, int parts, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0) return hipSuccess;
     const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
     hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, static_cast<const float*>(nullptr), 0, a.out_q, a.ld_q, a.out_scale, given_amax);
+                       a.rows, a.cols, a.fold, static_cast<const float*>(nullptr), parts, a.out_q, a.ld_q, a.out_scale, given_amax);
     return hipGetLastError();
 }
 

@@ -373,13 +373,15 @@ halo_status halo_hadamard_quant_tensor(const void* in, halo_dtype in_dt, int64_t
     set_right_block(r, had_block);
     r.out = out_q; r.ld_out = ld_q; r.out_scale = row_max; r.amax_only = 1;
     if (launch_row_transform(r, src_kind, OUT_Q8, s) != hipSuccess) return HALO_EHIP;
-    if (launch_reduce_max(row_max, rows, tensor_max, s) != hipSuccess) return HALO_EHIP;
+    const float *maxima = row_max, *none = nullptr;
+    int64_t parts = rows, no_parts = 0;
+    if (tensor_max_parts(maxima, parts, tensor_max, none, no_parts, nullptr, s) != hipSuccess) return HALO_EHIP;
     // phase 2: rotate again and quantise with the tensor's absmax
     if (axis == HALO_QUANT_COLS_T) {
         ColQuantArgs a{in, ld_in, rows, cols, nullptr, out_q, ld_q, out_scale, col_ws};
-        return from_hip(launch_col_quant_t_given(a, tensor_max, s));
+        return from_hip(launch_col_quant_t_given(a, maxima, (int)parts, s));
     }
-    r.amax_only = 0; r.given_amax = tensor_max; r.out_scale = out_scale;
+    r.amax_only = 0; r.given_amax = maxima; r.given_parts = (int)parts; r.out_scale = out_scale;
     return from_hip(launch_row_transform(r, src_kind, OUT_Q8, s));
 }
 
@@ -611,8 +613,7 @@ halo_status halo_linear_fwd(const halo_linear_desc* desc, const void* X, const v
         unsigned char* tq = reinterpret_cast<unsigned char*>(workspace) + L.tq;
         const size_t tq_bytes = L.total - L.tq;
         if (X && W) {
-            // X and W get the same treatment: one launch for the row maxima of both, one for the two tensor maxima, one
-            // that rotates again and quantises both
+            // X and W get the same treatment: one launch for the row maxima of both, one that rotates again and quantises both
             hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
             float* row_max_x = reinterpret_cast<float*>(tq);
             float* row_max_w = row_max_x + b;
@@ -624,8 +625,11 @@ halo_status halo_linear_fwd(const halo_linear_desc* desc, const void* X, const v
             r.rows2 = n; r.in2 = W; r.out2 = Wq; r.out_scale2 = row_max_w;
             r.amax_only = 1;
             if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
-            if (launch_reduce_max(row_max_x, b, tmax, hs, row_max_w, n, tmax + 64) != hipSuccess) return HALO_EHIP;
-            r.amax_only = 0; r.given_amax = tmax; r.given_amax2 = tmax + 64; r.out_scale = s_x; r.out_scale2 = s_w;
+            const float *max_x = row_max_x, *max_w = row_max_w;
+            int64_t parts_x = b, parts_w = n;
+            if (tensor_max_parts(max_x, parts_x, tmax, max_w, parts_w, tmax + 64, hs) != hipSuccess) return HALO_EHIP;
+            r.amax_only = 0; r.given_amax = max_x; r.given_parts = (int)parts_x; r.out_scale = s_x;
+            r.given_amax2 = max_w; r.given_parts2 = (int)parts_w; r.out_scale2 = s_w;
             if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
             return halo_gemm_i8(Xq, m, Wq, m, 1, b, n, m, s_x, s_w, Y, odt, n, nullptr, 0, stream);
         }
@@ -695,21 +699,18 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
         unsigned char* tq = ws + L.tq;
         const size_t tq_bytes = L.total - L.tq;
         if (both && level <= 1) {
-            // No left-hand rotation: both quantisations of E share the tensor's maximum.  One absmax pass and one reduction,
-            // then the row and the (transposed) column quantiser with that maximum, both products in one launch, both
-            // un-rotations in one launch.
-            if (tq_bytes < round256(((size_t)b + 64) * 4) + round256((size_t)n * 4)) return HALO_EWORKSPACE;
+            // No left-hand rotation: both quantisations of E share the tensor's maximum, and their codes.  One absmax pass, one
+            // pass that quantises and writes the codes both ways, both products in one launch, both un-rotations in one.
+            if (tq_bytes < round256(((size_t)b + 64) * 4)) return HALO_EWORKSPACE;
             float* row_max = reinterpret_cast<float*>(tq);
-            float* tmax = row_max + b;
-            float* col_ws = reinterpret_cast<float*>(tq + round256(((size_t)b + 64) * 4));
             RowArgs r{};
             r.in = E; r.ld_in = n; r.rows = b; r.cols = n; r.out = Eq; r.ld_out = n; r.out_scale = row_max; r.amax_only = 1;
             if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
-            if (launch_reduce_max(row_max, b, tmax, hs) != hipSuccess) return HALO_EHIP;
-            r.amax_only = 0; r.given_amax = tmax; r.out_scale = s_e;
-            if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
-            ColQuantArgs q{E, n, b, n, nullptr, EqT, b, s_g, col_ws};
-            if (launch_col_quant_t_given(q, tmax, hs) != hipSuccess) return HALO_EHIP;
+            const float *maxima = row_max, *none = nullptr;
+            int64_t parts = b, no_parts = 0;
+            if (tensor_max_parts(maxima, parts, row_max + b, none, no_parts, nullptr, hs) != hipSuccess) return HALO_EHIP;
+            const DualQuantArgs q{E, n, b, n, nullptr, nullptr, Eq, n, s_e, EqT, b, s_g, nullptr};
+            if (launch_dual_quant_given(q, maxima, (int)parts, hs) != hipSuccess) return HALO_EHIP;
             GemmArgs gx{Eq, n, Wq, m, 0, b, m, n, nullptr, nullptr, nullptr, 0, m, acc, m, HALO_GEMM_AUTO};
             GemmArgs gg{EqT, b, Xq, m, 0, n, m, b, nullptr, nullptr, nullptr, 0, m, acc_g, m, HALO_GEMM_AUTO};
             if (launch_gemm_i8_pair(gx, gg, hs) != hipSuccess) return HALO_EHIP;

@@ -27,11 +27,12 @@ struct RowArgs {
     int kron_m;              // 0, or 28: the block is 28 * 2^log_block elements, rotated by H_{2^log_block} (x) H_28
     float in_mul;            // fp32 only: every element is multiplied by this once when it is loaded; 0 = no multiply
     int left_top;            // launch_row_left_top only: number of top strides of the left-hand rotation still to run (1..5)
-    // One scale per tensor (OUT_Q8 only): amax_only writes each row's absmax to out_scale and no codes; given_amax
-    // (device scalar) replaces the row's own absmax.  post_scale (IN_I32 only, device scalar) is multiplied in after
-    // pre_scale.  All three apply to both matrices of a batched launch.
+    // One scale per tensor (OUT_Q8 only): amax_only writes each row's absmax to out_scale and no codes; the largest of the
+    // given_parts values at given_amax (device memory) replaces the row's own absmax.  post_scale (IN_I32 only, device scalar) is
+    // multiplied in after pre_scale.  All three apply to both matrices of a batched launch.
     int amax_only;
     const float* given_amax;
+    int given_parts;
     const float* post_scale;
     // OUT_MX6 only (bf16 input, cols a multiple of 32): `out` receives the packed FP6 E3M2 codes (24 bytes per block of
     // 32 elements, ld_out in BYTES per row), mx_scales the E8M0 scale bytes [rows x cols/32] with ld_mx_scales bytes per row.
@@ -46,6 +47,7 @@ struct RowArgs {
     void* out2;
     float* out_scale2;
     const float* given_amax2;    // the second matrix's own given_amax / post_scale; null: those of the first
+    int given_parts2;
     const float* post_scale2;
 };
 // Largest row length the row kernels accept.
@@ -110,11 +112,16 @@ hipError_t launch_col_fwht(const ColFwhtArgs& a, hipStream_t s);
 hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s);
 // The same with `parts` vectors of the columns' partial maxima already in a.amax_ws [parts x cols] (ColFwhtArgs::columns).
 hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_t s);
-// The same with one given absmax (device scalar) for every column instead of the columns' own: the tensor-wide scale.
-hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, hipStream_t s);
-// out[0] = max(in[0..n-1]) (n >= 1, non-negative values).  With in2: out2[0] = max(in2[0..n2-1]) in the same launch.
-hipError_t launch_reduce_max(const float* in, int64_t n, float* out, hipStream_t s, const float* in2 = nullptr,
-                             int64_t n2 = 0, float* out2 = nullptr);
+// The same with one absmax for every column instead of the columns' own, the largest of `parts` values in device memory: the
+// tensor-wide scale.
+hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, int parts, hipStream_t s);
+// What the kernels that take a tensor's absmax in parts are given: the rows' maxima as they are, or, where there are more than
+// kMaxGivenParts, reduced to one value at `out` first by a launch of their own (in2, n2, out2: of a second tensor in the same
+// launch).  Returns the parts by changing in / n (in2 / n2).  The launch takes 2 to 4 us; that every workgroup reads 4096 values, which
+// stay in the caches, takes less.  The step of 2048 x 4096 x 4096, HALO-1: 176.8 us with two such launches and a pass of its own for
+// each of E's codes, 173.9 with neither launch and one pass for both.
+constexpr int64_t kMaxGivenParts = 4096;
+hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const float*& in2, int64_t& n2, float* out2, hipStream_t s);
 
 // ---- both quantisations of E for the backward pass from one tiling (rows for E_X, transposed columns for G) ----
 struct DualQuantArgs {
@@ -133,6 +140,9 @@ struct DualQuantArgs {
 };
 size_t dual_quant_workspace_floats(int64_t rows, int64_t cols);
 hipError_t launch_dual_quant(const DualQuantArgs& a, hipStream_t s);
+// The same with one absmax for all rows and columns, the largest of `parts` values in device memory, and no fold vectors: the codes of
+// the two outputs are the same ones.  amax_ws is not used.
+hipError_t launch_dual_quant_given(const DualQuantArgs& a, const float* given_amax, int parts, hipStream_t s);
 // The same with the partial maxima in a file-scope device array instead of a.amax_ws (which is ignored): no allocation,
 // no workspace argument.  Sizes whose partial maxima exceed kStaticScratchBytes are refused by the caller.
 constexpr size_t kStaticScratchBytes = size_t(8) << 20;

@@ -74,7 +74,7 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     if (block >= blocks1) {                  // the second matrix of a batched launch
         block -= blocks1;
         a.in = a.in2; a.pre_scale = a.pre_scale2; a.out = a.out2; a.out_scale = a.out_scale2; a.rows = a.rows2;
-        if (a.given_amax2) a.given_amax = a.given_amax2;
+        if (a.given_amax2) { a.given_amax = a.given_amax2; a.given_parts = a.given_parts2; }
         if (a.post_scale2) a.post_scale = a.post_scale2;
     }
     const int64_t row = block;               // the grid holds exactly one workgroup per row
@@ -170,7 +170,10 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
             if (tid == 0) a.out_scale[row] = amax;
             return;
         }
-        if (a.given_amax) amax = *a.given_amax;
+        if (a.given_amax) {
+            __shared__ float s_given[8];
+            amax = workgroup_max(a.given_amax, a.given_parts, s_given);
+        }
         const bool nz = amax > 0.0f;
         const float inv = nz ? 127.0f / amax : 0.0f;
         if (tid == 0) a.out_scale[row] = nz ? amax / 127.0f : 1.0f;

@@ -363,7 +363,7 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     if (block >= blocks1) {          // the second matrix of a batched launch
         block -= blocks1;
         a.in = a.in2; a.pre_scale = a.pre_scale2; a.out = a.out2; a.out_scale = a.out_scale2; a.rows = a.rows2;
-        if (a.given_amax2) a.given_amax = a.given_amax2;
+        if (a.given_amax2) { a.given_amax = a.given_amax2; a.given_parts = a.given_parts2; }
         if (a.post_scale2) a.post_scale = a.post_scale2;
     }
     x.row = (int64_t)block * rows_per_wg + row_local;
@@ -401,7 +401,10 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
             if (x.row_ok && seg == 0 && x.lane == 0) a.out_scale[x.row] = amax;
             return;
         }
-        if (a.given_amax) amax = *a.given_amax;          // second phase: the tensor's absmax for every row
+        if (a.given_amax) {                              // second phase: the tensor's absmax for every row
+            __shared__ float s_given[16];
+            amax = workgroup_max(a.given_amax, a.given_parts, s_given);
+        }
         const bool nz = amax > 0.0f;
         inv_l = nz ? 127.0f / amax : 0.0f;
         if (x.row_ok && seg == 0 && x.lane == 0) a.out_scale[x.row] = nz ? amax / 127.0f : 1.0f;

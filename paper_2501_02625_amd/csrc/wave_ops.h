@@ -49,6 +49,21 @@ __device__ __forceinline__ float wave_max(float x, int bperm_addr) {
     return x;
 }
 
+// The largest of n non-negative values (0 of none), for every thread of the workgroup.  s_red: a float of LDS per wavefront that
+// nothing else uses.
+__device__ __forceinline__ float workgroup_max(const float* p, int n, float* s_red) {
+    float m = 0.0f;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n; i += blockDim.x) m = __builtin_fmaxf(m, p[i]);
+    m = wave_max(m, (int)((threadIdx.x & 63) ^ 32) << 2);
+    const int waves = (blockDim.x + 63) >> 6;
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = s_red[0];
+    for (int i = 1; i < waves; ++i) m = __builtin_fmaxf(m, s_red[i]);
+    return m;
+}
+
 // Four  x <- x + s * partner(x)  in one asm block: v_fmac_f32 with the partner read through DPP.  The leading s_nop supplies
 // the two wait states a DPP read needs after a vector write of the same register, whatever the compiler placed before the
 // block; inside the block every register is read and written by one instruction.

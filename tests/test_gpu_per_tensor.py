@@ -35,6 +35,24 @@ def test_tensor_quantiser_transposed_and_zero_tensor():
     assert not q.any() and torch.all(s == 1.0)
 
 
+# The quantising kernels take the tensor's maximum as the rows' maxima up to 4096 of them, and as one reduced value beyond: the
+# largest element in the first row, the last, and the last that a workgroup's round of 256 threads reads.
+@pytest.mark.parametrize("rows", [255, 257, 4096, 4097])
+@pytest.mark.parametrize("axis", [binding.HALO_QUANT_ROWS, binding.HALO_QUANT_COLS_T])
+def test_tensor_maximum_anywhere(rows, axis):
+    bits = inputs.make_weights(rows, 64, rows)
+    for at in (0, 254, rows - 1):
+        x = inputs.bf16_bits_to_f32(bits).copy()
+        x[at, 63] = -3.0
+        e = inputs.f32_to_bf16_bits(x)
+        xd = torch.zeros((rows, 64), dtype=torch.bfloat16, device=gu.DEV)
+        xd[:] = gu.bits_to_dev(e)
+        r = orc.bf16_bits_to_real(e)
+        wq, ws = orc.quantize_tensor(np.ascontiguousarray(r.T) if axis == binding.HALO_QUANT_COLS_T else r)
+        q, s = binding.halo_hadamard_quant_tensor(xd, axis=axis)
+        gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
+
+
 def run_per_tensor(b, m, n, level, seed, odt=torch.float32):
     Xb = inputs.make_activations(b, m, 0.01, seed); Wb = inputs.make_weights(n, m, seed); Eb = inputs.make_errors(b, n, seed)
     hm, hb = min(m & -m, 4096), b & -b
@@ -56,6 +74,13 @@ def run_per_tensor(b, m, n, level, seed, odt=torch.float32):
 @pytest.mark.parametrize("level", [0, 1, 2])
 def test_per_tensor_layers_all_levels(b, m, n, level):
     run_per_tensor(b, m, n, level, b + m + n)
+
+
+# more tokens, or more out-features, than maxima that the quantising kernels read themselves; tiles of the two-way quantiser that
+# end inside the matrix
+@pytest.mark.parametrize("b,m,n", [(4112, 64, 144), (272, 128, 4112)])
+def test_per_tensor_layers_of_many_rows(b, m, n):
+    run_per_tensor(b, m, n, 1, b + n)
 
 
 def test_config_c7_full_size_per_tensor():
