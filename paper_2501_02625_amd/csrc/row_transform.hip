@@ -350,7 +350,7 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
     }
 }
 
-// LB: log2 of the Hadamard block when it is 0 (no rotation) or LOGSEG (block = segment); -1 = read it at run time.
+// LB: log2 of the Hadamard block when it is 0 (no rotation), LOGSEG (block = segment) or 9; -1 = read it at run time.
 // XS: number of butterfly stages that span wavefronts (Hadamard block = 2^(LOGSEG+XS) elements = 2^XS segments).
 template <int LOGSEG, int IN, int OUT, int LB, int XS = 0>
 __global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024)
@@ -457,6 +457,10 @@ hipError_t launch_one(const RowArgs& a, int segs, hipStream_t s) {
         else
             hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 0>), dim3((unsigned)blocks), dim3(threads), 0, s,
                                a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
+    } else if (IN == IN_BF16 && LOGSEG == 10 && a.log_block == 9) {
+        if constexpr (IN == IN_BF16 && LOGSEG == 10)
+            hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 9>), dim3((unsigned)blocks), dim3(threads), 0, s,
+                               a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
     } else if (a.log_block == LOGSEG)
         hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, LOGSEG>), dim3((unsigned)blocks), dim3(threads), 0, s,
                            a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
@@ -478,8 +482,13 @@ hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
         const bool want = IN == IN_I32 ? a.log_block == 12 : IN == IN_F32_I32 ? a.log_block == 12 || few : few;
         if (want) return a.log_block == 11 ? launch_split<IN, OUT, 1>(a, s) : launch_split<IN, OUT, 2>(a, s);
     }
-    // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).
+    // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).  The quantisers of bf16
+    // rows are bound by how much a compute unit has on its way: with blocks up to 512, segments of 1024, two loads per lane, are the
+    // faster ones where a row has more than three of them (512 against 1024: 4096 x 2304 in blocks of 256 11.35 us / 11.31, x 1280 7.2
+    // / 8.0; 4096 x 3584 in blocks of 512 13.3 / 12.0, 8192 x 5632 40.5 / 32.1; 4096 x 5696 in blocks of 64 20.7 / 17.6).  The
+    // un-rotations have 4-byte inputs, and 512 is the faster one for them throughout.
     int logseg = a.log_block < 9 ? 9 : a.log_block;
+    if (IN == IN_BF16 && logseg == 9 && a.cols > 3072) logseg = 10;
     if (a.log_block == 0) {
         // no rotation: any segmentation is valid; 1024-element segments keep register use low
         logseg = a.cols <= 512 ? 9 : 10;

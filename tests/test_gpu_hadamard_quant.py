@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from oracle import halo_oracle as orc
+from oracle import mxfp6_oracle as mx
 from paper_2501_02625_amd import binding, inputs
 from tests import gpu_util as gu
 
@@ -54,6 +55,26 @@ def test_row_quant_bf16_bit_exact(rows, cols, hb, frac):
     gu.assert_f32_identical(s, ws, "scales")
     if ldq > cols:
         assert torch.all(out_q[:, cols:] == 55), "padding columns were overwritten"
+
+
+# Blocks of up to 512 in segments of 1024 (more than 3072 columns): the first width beyond the line and the last one on it, a last segment of
+# one block, of half a segment and of all but one block; as many segments as a workgroup takes, and one more.  MXFP6 codes and
+# INT8 codes of one scale per tensor go the same way.
+@pytest.mark.parametrize("rows,cols,hb", [(6, 3072, 512), (7, 3080, 8), (9, 3136, 64), (5, 3584, 512), (3, 4032, 64), (5, 5632, 512), (4, 15872, 512),
+                                          (3, 16384, 256), (2, 16896, 512)])
+def test_row_quant_short_blocks_of_long_rows(rows, cols, hb):
+    bits = inputs.make_activations(rows, cols, 0.002, seed=rows + cols)
+    rotated = orc.fwht(orc.bf16_bits_to_real(bits), hb, 1)
+    q, s = binding.halo_hadamard_quant(gu.bits_to_dev(bits), had_block=hb)
+    wq, ws = orc.quantize_rows(rotated)
+    gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
+    q, s = binding.halo_hadamard_quant_tensor(gu.bits_to_dev(bits), had_block=hb)
+    wq, ws = orc.quantize_tensor(rotated)
+    gu.assert_codes_equal(q, wq, "codes, one scale"); gu.assert_f32_identical(s, ws, "one scale")
+    if cols % 32 == 0:
+        codes, scales = binding.halo_mx6_quant(gu.bits_to_dev(bits), had_block=hb)
+        want_c, want_s = mx.mx_quantize_rows(rotated)
+        assert np.array_equal(scales.cpu().numpy(), want_s) and np.array_equal(codes.cpu().numpy(), mx.pack_fp6(want_c))
 
 
 def test_row_quant_weights_and_errors_distributions():
