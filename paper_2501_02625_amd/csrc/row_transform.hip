@@ -73,11 +73,23 @@ struct RowCtx {
     bool f32;               // IN_F32_I32: this matrix holds fp32 (uniform over the workgroup)
 };
 
+// Quantising blocks of 4096: 1/sqrt(block) is a power of two, and the multiply by it (and the lanes' signs) is not made on every
+// value but once, on the factor that quantises them, 127 / absmax or a power of two.  Scaling by a power of two is exact, so the
+// codes are the same ones as long as nothing on the way leaves the normal range: kTiny < absmax < kHuge; otherwise every value
+// is multiplied after all.  One vector instruction of some 22 (INT8) or 26 (MXFP6) per element in kernels that are bound by
+// them: 4096 x 4096 to INT8 14.0 -> 13.5 us, 8192 x 4096 to MXFP6 32.4 -> 30.9.  (Blocks of 1024 and 256 are bound by their loads, and
+// 3 % slower that way.)
+template <int OUT, int LB>
+constexpr bool kDeferNorm = (OUT == OUT_Q8 || OUT == OUT_MX6) && LB == 12;
+constexpr float kTiny = 0x1p-100f, kHuge = 0x1p100f;
+__device__ __forceinline__ bool may_defer(float amax) { return amax > kTiny && amax < kHuge; }
+
 // Load one segment into registers, rotate it, apply the fold vector; returns the local absmax (quantising kernels).
 // FAST: the row exists and the whole segment lies inside it, so nothing is bounds-checked.
+// deferred: what the values are still to be multiplied by (kDeferNorm; the absmax is not), otherwise 1.
 template <int LOGSEG, int IN, int OUT, bool FAST, int LB, int XS>
 __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, float c_norm,
-                                            float (&v)[1 << (LOGSEG - 6)]) {
+                                            float (&v)[1 << (LOGSEG - 6)], float& deferred) {
     constexpr int LOGE = (IN == IN_BF16) ? 3 : 2;
     constexpr int EPL = 1 << LOGE;
     constexpr int VPL = 1 << (LOGSEG - 6);
@@ -157,24 +169,30 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
             // bf16 11.1 -> 10.4, 16384 x 4096 71.5 -> 71.2.
             static_assert(XS <= 2 && VPL % 4 == 0, "wavefronts of a block");
             float4* xb = reinterpret_cast<float4*>(x.xbuf) + x.lane;
-#pragma unroll
-            for (int r = 0; r < VPL; r += 4)
-                xb[(x.wave * VPL + r) * 16] = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
-            __syncthreads();
             const float sg0 = x.seg & 1 ? -1.0f : 1.0f, sg1 = x.seg & 2 ? -1.0f : 1.0f;
+            constexpr bool AT_ONCE = XS == 2 && IN == IN_BF16;
 #pragma unroll
-            for (int r = 0; r < VPL; r += 4) {
-                const float4 p = xb[((x.wave ^ 1) * VPL + r) * 16];
-                v[r] = __builtin_fmaf(v[r], sg0, p.x);
-                v[r + 1] = __builtin_fmaf(v[r + 1], sg0, p.y);
-                v[r + 2] = __builtin_fmaf(v[r + 2], sg0, p.z);
-                v[r + 3] = __builtin_fmaf(v[r + 3], sg0, p.w);
-                if constexpr (XS == 2) {
-                    const float4 q = xb[((x.wave ^ 2) * VPL + r) * 16], o = xb[((x.wave ^ 3) * VPL + r) * 16];
-                    v[r] = __builtin_fmaf(v[r], sg1, __builtin_fmaf(q.x, sg0, o.x));
-                    v[r + 1] = __builtin_fmaf(v[r + 1], sg1, __builtin_fmaf(q.y, sg0, o.y));
-                    v[r + 2] = __builtin_fmaf(v[r + 2], sg1, __builtin_fmaf(q.z, sg0, o.z));
-                    v[r + 3] = __builtin_fmaf(v[r + 3], sg1, __builtin_fmaf(q.w, sg0, o.w));
+            for (int xs = 0; xs < (AT_ONCE ? 1 : XS); ++xs) {
+                if (xs > 0) __syncthreads();        // everyone has read the previous round
+#pragma unroll
+                for (int r = 0; r < VPL; r += 4)
+                    xb[(x.wave * VPL + r) * 16] = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+                __syncthreads();
+                const float sg = xs == 0 ? sg0 : sg1;
+#pragma unroll
+                for (int r = 0; r < VPL; r += 4) {
+                    const float4 p = xb[((x.wave ^ (1 << xs)) * VPL + r) * 16];
+                    v[r] = __builtin_fmaf(v[r], sg, p.x);
+                    v[r + 1] = __builtin_fmaf(v[r + 1], sg, p.y);
+                    v[r + 2] = __builtin_fmaf(v[r + 2], sg, p.z);
+                    v[r + 3] = __builtin_fmaf(v[r + 3], sg, p.w);
+                    if constexpr (AT_ONCE) {
+                        const float4 q = xb[((x.wave ^ 2) * VPL + r) * 16], o = xb[((x.wave ^ 3) * VPL + r) * 16];
+                        v[r] = __builtin_fmaf(v[r], sg1, __builtin_fmaf(q.x, sg0, o.x));
+                        v[r + 1] = __builtin_fmaf(v[r + 1], sg1, __builtin_fmaf(q.y, sg0, o.y));
+                        v[r + 2] = __builtin_fmaf(v[r + 2], sg1, __builtin_fmaf(q.z, sg0, o.z));
+                        v[r + 3] = __builtin_fmaf(v[r + 3], sg1, __builtin_fmaf(q.w, sg0, o.w));
+                    }
                 }
             }
         }
@@ -184,8 +202,12 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
         const int mask = (1 << nlane_stages) - 1;
         const float sign_l = (__builtin_popcount(x.lane & mask) & 1) ? -1.0f : 1.0f;
         const float c_l = sign_l * c_norm;
+        if (kDeferNorm<OUT, LB> && !a.fold) {                     // uniform
+            deferred = c_l;
+        } else {
 #pragma unroll
-        for (int r = 0; r < VPL; ++r) v[r] *= c_l;
+            for (int r = 0; r < VPL; ++r) v[r] *= c_l;
+        }
     }
 
     // ---- fold
@@ -219,12 +241,14 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
             asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(amax2) : "v"(v[r + 2]), "v"(v[r + 3]));
         }
         amax = __builtin_fmaxf(amax, amax2);
+        if (kDeferNorm<OUT, LB> && !a.fold) amax *= c_norm;
         amax = wave_max(amax, x.bperm_addr);
     }
     return amax;
 }
 
 // Quantise (inv_l = per-lane signed 127/absmax) or convert, and store the segment.
+// MXFP6: inv_l is what the values are still to be multiplied by (kDeferNorm), or 1.
 template <int LOGSEG, int IN, int OUT, bool FAST>
 __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, const float (&v)[1 << (LOGSEG - 6)],
                                            float inv_l) {
@@ -276,7 +300,7 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
 #pragma unroll
             for (int e = 0; e < EPL; ++e) bm = __builtin_fmaxf(bm, fabsf(v[c * EPL + e]));
             bm = __builtin_fmaxf(bm, lane_xor<0>(bm, x.bperm_addr));
-            bm = __builtin_fmaxf(bm, lane_xor<1>(bm, x.bperm_addr));
+            bm = __builtin_fmaxf(bm, lane_xor<1>(bm, x.bperm_addr)) * fabsf(inv_l);
             int shared = (int)(__float_as_uint(bm) >> 23) - 127 - 4;
             shared = shared < -127 ? -127 : shared;               // the upper clamp cannot bind: exponent <= 127 - 4
             if (!(bm > 0.0f)) shared = 0;
@@ -285,11 +309,20 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
             // and its exponent field gives the rest of the code; below 2^-2 the units stay 2^-4.  No code has a negative zero:
             // up to 2^-5 the element rounds to 0.  Ten VALU instructions an element, which bound this kernel; sixteen, with integer
             // rounding and a path for subnormals, took 38.5 us at 8192 x 4096 instead of 36.4, 22.8 instead of 20.6 at 4096 x 4096.
-            const float scale = __uint_as_float((uint32_t)(127 - shared) << 23);         // 2^-shared, 3 <= exponent field <= 254
+            float scale = __uint_as_float((uint32_t)(127 - shared) << 23);               // 2^-shared, 3 <= exponent field <= 254
+            float w[EPL];
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) w[e] = v[c * EPL + e];
+            if (__all(bm == 0.0f || may_defer(bm))) {
+                scale *= inv_l;
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) w[e] *= inv_l;
+            }
             uint32_t code[EPL];
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
-                const float xs = v[c * EPL + e] * scale;
+                const float xs = w[e] * scale;
                 const float ax = __builtin_fminf(fabsf(xs), 28.0f);
                 const float pow2 = __uint_as_float(__float_as_uint(__builtin_fmaxf(ax, 0.25f)) & 0x7F800000u);
                 const uint32_t u = __float_as_uint(__builtin_fmaf(pow2, 2097152.0f, ax));
@@ -392,12 +425,12 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     // registers than they have; their guarded path stays (with 1024 it is 1 % faster).
     constexpr bool WHOLE = LB >= 11 && LB == LOGSEG;
     float v[VPL];
-    float amax = 0.0f;
+    float amax = 0.0f, deferred = 1.0f;
     if constexpr (WHOLE) {
-        if (fast) amax = row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v);
+        if (fast) amax = row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v, deferred);
     } else {
-        amax = fast ? row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v)
-                    : row_phase1<LOGSEG, IN, OUT, false, LB, XS>(a, x, c_norm, v);
+        amax = fast ? row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v, deferred)
+                    : row_phase1<LOGSEG, IN, OUT, false, LB, XS>(a, x, c_norm, v, deferred);
     }
 
     float inv_l = 0.0f;
@@ -422,7 +455,16 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
         const bool nz = amax > 0.0f;
         inv_l = nz ? 127.0f / amax : 0.0f;
         if (x.row_ok && seg == 0 && x.lane == 0) a.out_scale[x.row] = nz ? amax / 127.0f : 1.0f;
+        if constexpr (kDeferNorm<OUT, LB>) {
+            if (may_defer(amax)) {                        // uniform over the wavefront
+                inv_l *= deferred;
+            } else {
+#pragma unroll
+                for (int r = 0; r < VPL; ++r) v[r] *= deferred;
+            }
+        }
     }
+    if constexpr (OUT == OUT_MX6) inv_l = deferred;
     if (fast) row_phase2<LOGSEG, IN, OUT, true>(a, x, v, inv_l);
     else if constexpr (!WHOLE) row_phase2<LOGSEG, IN, OUT, false>(a, x, v, inv_l);
 }
@@ -457,8 +499,8 @@ hipError_t launch_one(const RowArgs& a, int segs, hipStream_t s) {
         else
             hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 0>), dim3((unsigned)blocks), dim3(threads), 0, s,
                                a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
-    } else if (IN == IN_BF16 && LOGSEG == 10 && a.log_block == 9) {
-        if constexpr (IN == IN_BF16 && LOGSEG == 10)
+    } else if (IN == IN_BF16 && OUT == OUT_Q8 && LOGSEG == 10 && a.log_block == 9) {
+        if constexpr (IN == IN_BF16 && OUT == OUT_Q8 && LOGSEG == 10)
             hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 9>), dim3((unsigned)blocks), dim3(threads), 0, s,
                                a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
     } else if (a.log_block == LOGSEG)
@@ -482,13 +524,13 @@ hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
         const bool want = IN == IN_I32 ? a.log_block == 12 : IN == IN_F32_I32 ? a.log_block == 12 || few : few;
         if (want) return a.log_block == 11 ? launch_split<IN, OUT, 1>(a, s) : launch_split<IN, OUT, 2>(a, s);
     }
-    // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).  The quantisers of bf16
-    // rows are bound by how much a compute unit has on its way: with blocks up to 512, segments of 1024, two loads per lane, are the
+    // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).  The INT8 quantiser of bf16
+    // rows is bound by how much a compute unit has on its way: with blocks up to 512, segments of 1024, two loads per lane, are the
     // faster ones where a row has more than three of them (512 against 1024: 4096 x 2304 in blocks of 256 11.35 us / 11.31, x 1280 7.2
     // / 8.0; 4096 x 3584 in blocks of 512 13.3 / 12.0, 8192 x 5632 40.5 / 32.1; 4096 x 5696 in blocks of 64 20.7 / 17.6).  The
-    // un-rotations have 4-byte inputs, and 512 is the faster one for them throughout.
+    // un-rotations have 4-byte inputs, the MXFP6 quantiser more to do with a value, and 512 is the faster one for both throughout.
     int logseg = a.log_block < 9 ? 9 : a.log_block;
-    if (IN == IN_BF16 && logseg == 9 && a.cols > 3072) logseg = 10;
+    if (IN == IN_BF16 && OUT == OUT_Q8 && logseg == 9 && a.cols > 3072) logseg = 10;
     if (a.log_block == 0) {
         // no rotation: any segmentation is valid; 1024-element segments keep register use low
         logseg = a.cols <= 512 ? 9 : 10;

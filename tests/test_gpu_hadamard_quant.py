@@ -58,8 +58,8 @@ def test_row_quant_bf16_bit_exact(rows, cols, hb, frac):
 
 
 # Blocks of up to 512 in segments of 1024 (more than 3072 columns): the first width beyond the line and the last one on it, a last segment of
-# one block, of half a segment and of all but one block; as many segments as a workgroup takes, and one more.  MXFP6 codes and
-# INT8 codes of one scale per tensor go the same way.
+# one block, of half a segment and of all but one block; as many segments as a workgroup takes, and one more.  One scale per tensor
+# goes the same way.
 @pytest.mark.parametrize("rows,cols,hb", [(6, 3072, 512), (7, 3080, 8), (9, 3136, 64), (5, 3584, 512), (3, 4032, 64), (5, 5632, 512), (4, 15872, 512),
                                           (3, 16384, 256), (2, 16896, 512)])
 def test_row_quant_short_blocks_of_long_rows(rows, cols, hb):
@@ -71,10 +71,29 @@ def test_row_quant_short_blocks_of_long_rows(rows, cols, hb):
     q, s = binding.halo_hadamard_quant_tensor(gu.bits_to_dev(bits), had_block=hb)
     wq, ws = orc.quantize_tensor(rotated)
     gu.assert_codes_equal(q, wq, "codes, one scale"); gu.assert_f32_identical(s, ws, "one scale")
-    if cols % 32 == 0:
-        codes, scales = binding.halo_mx6_quant(gu.bits_to_dev(bits), had_block=hb)
-        want_c, want_s = mx.mx_quantize_rows(rotated)
-        assert np.array_equal(scales.cpu().numpy(), want_s) and np.array_equal(codes.cpu().numpy(), mx.pack_fp6(want_c))
+
+
+# Blocks of 4096, whose normalisation is left to the quantising factor, with rows whose absmax is far below, at and far above the
+# range in which that is exact, and zero (the oracle takes an absmax whose 127 / absmax is finite); in one wavefront (4096 rows and
+# more) and in four.
+@pytest.mark.parametrize("rows", [24, 4104])
+def test_row_quant_normalisation_of_extreme_rows(rows):
+    x = inputs.bf16_bits_to_f32(inputs.make_activations(rows, 4096, 0.001, rows))
+    with np.errstate(all="ignore"):
+        for r, e in enumerate([-118, -115, -112, -107, -106, -105, -100, -93, -60, 60, 93, 100, 105, 110, 118]):
+            x[r] *= np.float32(2.0) ** np.float32(e)
+    x[15] = 0
+    x[16] = 0; x[16, 5] = 2.0 ** -113
+    x[17] = 0; x[17, 7] = 2.0 ** 120
+    x[18] *= np.float32(2.0) ** -98; x[18, 3] = 1.0    # most values far below the absmax
+    bits = inputs.f32_to_bf16_bits(x)
+    rotated = orc.fwht(orc.bf16_bits_to_real(bits), 4096, 1)
+    q, s = binding.halo_hadamard_quant(gu.bits_to_dev(bits), had_block=4096)
+    wq, ws = orc.quantize_rows(rotated)
+    gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
+    codes, scales = binding.halo_mx6_quant(gu.bits_to_dev(bits), had_block=4096)
+    want_c, want_s = mx.mx_quantize_rows(rotated)
+    assert np.array_equal(scales.cpu().numpy(), want_s) and np.array_equal(codes.cpu().numpy(), mx.pack_fp6(want_c))
 
 
 def test_row_quant_weights_and_errors_distributions():
