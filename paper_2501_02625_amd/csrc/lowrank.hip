@@ -314,14 +314,19 @@ constexpr H28Rows make_h28_rows() {
 }
 __device__ const H28Rows kH28Rows = make_h28_rows();
 
-// Rotations of thin matrices, each vector in LDS: a job is a set of vectors of `block` elements (block = 2^n, or
-// 28 * 2^n: H_{2^n} (x) H_28 with element i * 28 + j indexed by i in the Walsh-Hadamard factor; block 64 with
-// log_p = -1: no rotation, only the conversion), element e of vector (a, b) at  a * stride_a + b * stride_b + e * stride_e
-// in the source and at the same expression with the dst_ strides in the destination.  bf16 or fp32 in, fp32 out, normalised.  One workgroup per vector; the first
-// job's vectors come first in the grid.  The order of the additions is not that of the row kernels; nothing here needs to
-// be reproducible to the bit against a reference.  Used for U H (rows of the adapter U) and H S (columns of S = E V).
+// Rotations of thin matrices, each vector in LDS: a job is a set of vectors of `block` elements (block = 2^n, or 28 * 2^n:
+// H_{2^n} (x) H_28 with element i * 28 + j indexed by i in the Walsh-Hadamard factor; block 64 with log_p = -1: no
+// rotation, only the conversion), element e of vector (a, b) at  a * stride_a + b * stride_b + e * stride_e in the source
+// and at the same expression with the dst_ strides in the destination.  bf16 or fp32 in, fp32 out, normalised.  One
+// workgroup per vector; the first job's vectors come first in the grid.  A vector is a serial chain (scattered loads,
+// strides with a barrier after each trip, scattered stores) on one compute unit, so what counts is the length of the chain:
+// four loads of a thread on their way at once and two strides per trip through LDS.  With one of each, backward passes took
+// 169.5 us at 4096 tokens, 4096 x 4096, rank 16 (now 166.7) and 217.5 at 16384 tokens, 1024 x 1024 (now 212.1).  In front
+// of the gradient products' workgroups the rotations cost more than they hide: those fill the chip exactly once, and 32
+// more start a second round (16.9 -> 24.6 us).  The order of the additions is not that of the row kernels; nothing here
+// needs to be reproducible to the bit against a reference.  Used for U H (rows of the adapter U) and H S (columns of S = E
+// V).
 constexpr int kSmallFwhtMax = 16384;
-constexpr int kSmallFwhtThreads = kTailThreads;
 
 struct FwhtJob {
     const void* src;
@@ -353,17 +358,24 @@ lr_tail_kernel(ReduceJob r0, ReduceJob r1, int nb0, int nb1, FwhtJob j0, FwhtJob
     const int64_t va = vec / g.count_b, vb = vec % g.count_b;
     const int64_t base = va * g.stride_a + vb * g.stride_b;
     const int block = g.block, unit = g.unit;
-    if (g.src_bf16) {
-        const uint16_t* src = reinterpret_cast<const uint16_t*>(g.src) + base;
-        for (int i = threadIdx.x; i < block; i += kSmallFwhtThreads) s_x[i] = bf16_to_f32(src[i * g.stride_e]);
-    } else {
-        const float* src = reinterpret_cast<const float*>(g.src) + base;
-        for (int i = threadIdx.x; i < block; i += kSmallFwhtThreads) s_x[i] = src[i * g.stride_e];
+    const uint16_t* src16 = reinterpret_cast<const uint16_t*>(g.src) + base;
+    const float* src32 = reinterpret_cast<const float*>(g.src) + base;
+    // four loads of a thread on their way at once: each may be a line of its own
+    for (int i0 = threadIdx.x; i0 < block; i0 += 4 * kTailThreads) {
+        float x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kTailThreads < block ? i0 + u * kTailThreads : i0;
+            x[u] = g.src_bf16 ? bf16_to_f32(src16[i * g.stride_e]) : src32[i * g.stride_e];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u * kTailThreads < block) s_x[i0 + u * kTailThreads] = x[u];
     }
     __syncthreads();
     const int p = g.log_p >= 0 ? 1 << g.log_p : 0;       // length of the Walsh-Hadamard factor
     if (unit == 28) {
-        for (int run = threadIdx.x; run < p; run += kSmallFwhtThreads) {
+        for (int run = threadIdx.x; run < p; run += kTailThreads) {
             float x[28], y[28];
 #pragma unroll
             for (int j = 0; j < 28; ++j) x[j] = s_x[run * 28 + j];
@@ -380,29 +392,34 @@ lr_tail_kernel(ReduceJob r0, ReduceJob r1, int nb0, int nb1, FwhtJob j0, FwhtJob
         }
         __syncthreads();
     }
-    for (int lh = 0; lh < g.log_p; ++lh) {
-        const int h = 1 << lh;
-        if (unit == 1) {
-            for (int ii = threadIdx.x; ii < (p >> 1); ii += kSmallFwhtThreads) {
-                const int i = ((ii >> lh) << (lh + 1)) | (ii & (h - 1));
-                const float a = s_x[i], b = s_x[i + h];
-                s_x[i] = a + b;
-                s_x[i + h] = a - b;
-            }
-        } else {
-            // pairs (ii, j): 28 consecutive threads share one ii
-            for (int q = threadIdx.x; q < (p >> 1) * 28; q += kSmallFwhtThreads) {
-                const int ii = q / 28, j = q - ii * 28;
-                const int i = ((ii >> lh) << (lh + 1)) | (ii & (h - 1));
-                const float a = s_x[i * 28 + j], b = s_x[(i + h) * 28 + j];
-                s_x[i * 28 + j] = a + b;
-                s_x[(i + h) * 28 + j] = a - b;
-            }
+    // Two strides, h and 2 h, per trip through LDS: the four elements of quad q are runs ii, ii + h, ii + 2 h, ii + 3 h,
+    // element j of each (28 consecutive threads share one ii).
+    int lh = 0;
+    for (; lh + 1 < g.log_p; lh += 2) {
+        const int step = unit << lh;
+        for (int q = threadIdx.x; q < (p >> 2) * unit; q += kTailThreads) {
+            const int ii = unit == 1 ? q : q / 28, j = unit == 1 ? 0 : q - ii * 28;
+            float* x = s_x + (((ii >> lh) << (lh + 2)) | (ii & ((1 << lh) - 1))) * unit + j;
+            const float a = x[0], b = x[step], c = x[2 * step], d = x[3 * step];
+            const float ab = a + b, amb = a - b, cd = c + d, cmd = c - d;
+            x[0] = ab + cd;
+            x[step] = amb + cmd;
+            x[2 * step] = ab - cd;
+            x[3 * step] = amb - cmd;
+        }
+        __syncthreads();
+    }
+    if (lh < g.log_p) {                    // the last of an odd number of strides
+        const int step = unit << lh;
+        for (int q = threadIdx.x; q < step; q += kTailThreads) {
+            const float a = s_x[q], b = s_x[q + step];
+            s_x[q] = a + b;
+            s_x[q + step] = a - b;
         }
         __syncthreads();
     }
     float* dst = g.dst + va * g.dst_a + vb * g.dst_b;
-    for (int i = threadIdx.x; i < block; i += kSmallFwhtThreads) dst[i * g.dst_e] = s_x[i] * g.c_norm;
+    for (int i = threadIdx.x; i < block; i += kTailThreads) dst[i * g.dst_e] = s_x[i] * g.c_norm;
 }
 
 template <bool KMAJOR>

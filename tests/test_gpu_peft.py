@@ -133,10 +133,29 @@ LEFT_IN_PASSES = [(1536, 2560, 192, 8, 2, 512, 512), (2048, 2048, 128, 64, 2, 10
                   (768, 5120, 64, 32, 2, 512, 256)]
 
 
+# the rotations of the thin operands: even and odd numbers of strides, vectors shorter and longer than the workgroup's 1024
+# threads and than the 4096 elements of one trip of loads, the largest block at the largest rank, fewer tokens than the rank
+THIN_ROTATIONS = [(32, 64, 64, 40, 2, 64, 32), (96, 320, 64, 8, 2, 64, 16), (192, 192, 64, 56, 2, 64, 64), (384, 448, 64, 24, 2, 64, 128),
+                  (16384, 64, 64, 64, 2, 64, 16384), (288, 192, 128, 48, 1, 64, 0)]
+
+
 @pytest.mark.parametrize("shape", SHAPES + LEFT_IN_EPILOGUE + LEFT_IN_PASSES, ids=lambda s: "x".join(map(str, s)))
 def test_peft_module_fp32_outputs(shape):
     b, m, n, rank, level, hm, hb = shape
     run_peft(b, m, n, rank, level, seed=b + rank, hm=hm, hb=hb)
+
+
+@pytest.mark.parametrize("shape", THIN_ROTATIONS, ids=lambda s: "x".join(map(str, s)))
+def test_thin_rotations(shape):
+    """E_X, with and without the gradients, whose sums share the launch of the rotations."""
+    b, m, n, rank, level, hm, hb = shape
+    r = run_peft(b, m, n, rank, level, seed=b + rank, hm=hm, hb=hb)
+    desc, X, E, U, V, Wq, s_w, ws = r["args"]
+    for gu_too, gv_too in ((False, False), (True, False), (False, True)):
+        ex, gu_, gv_ = binding.halo_peft_bwd(desc, E, X, r["T"], Wq, s_w, U, V, want_gu=gu_too, want_gv=gv_too, workspace=ws)
+        assert torch.equal(ex, r["EX"])
+        assert gu_ is None if not gu_too else torch.equal(gu_, r["GU"])
+        assert gv_ is None if not gv_too else torch.equal(gv_, r["GV"])
 
 
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[3], SHAPES[4]], ids=lambda s: "x".join(map(str, s)))
