@@ -79,6 +79,98 @@ def accumulator_faults(asm: str, kernel: str = ACCUMULATOR_KERNELS):
     return len(seen), faults
 
 
+def _vector_registers(operands: str):
+    """Numbers of the vector registers that the operands name."""
+    regs = set()
+    for lo, hi, one in re.findall(r"\bv(?:\[(\d+):(\d+)\]|(\d+)\b)", operands):
+        regs.update(range(int(lo), int(hi) + 1) if lo else (int(one),))
+    return frozenset(regs)
+
+
+def _blocks_of_kernels(asm: str):
+    """Yields (kernel, blocks) for every kernel whose inline assembly reads LDS.  blocks: basic blocks in the order of the text, each
+    (labels, instructions, jump target or None, falls through to the next?); an instruction is (text, inline?)."""
+    name = None
+    for line in asm.splitlines():
+        code = line.split(";")[0].strip()
+        label = re.match(r"([.\w$]+):", line)
+        if label and not label.group(1).startswith(".L"):
+            name, blocks, reads = label.group(1), [([], [], None, True)], False
+            inline = False
+        elif name is None:
+            continue
+        elif line.startswith(".Lfunc_end"):
+            if reads:
+                yield name, blocks
+            name = None
+        elif label:
+            if blocks[-1][1]:
+                blocks.append(([], [], None, True))
+            blocks[-1][0].append(label.group(1))
+        elif "#ASMSTART" in line:
+            inline = True
+        elif "#ASMEND" in line:
+            inline = False
+        elif code and not code.startswith("."):
+            labels, instructions, _, _ = blocks[-1]
+            instructions.append((code, inline))
+            reads = reads or (inline and code.startswith("ds_read"))
+            jump = re.match(r"s_(c?)branch\w*\s+(\S+)", code)
+            if jump or code.startswith(("s_endpgm", "s_setpc")):
+                # a block that is nothing but "jump if there is an active lane": entered with all of them, left by the jump
+                falls = bool(jump and jump.group(1)) and not (code.startswith("s_cbranch_execnz") and len(instructions) == 1)
+                blocks[-1] = (labels, instructions, jump and jump.group(2), falls)
+                blocks.append(([], [], None, True))
+
+
+def outstanding_read_faults(asm: str):
+    """LDS reads written in inline assembly deliver their registers at a later wait, but the compiler takes them as written at once,
+    and as free once nothing uses them.  Returns (number of kernels with such reads, list of faults): instructions that touch the
+    destination of a read for which, on some way there, nothing has waited.  (Another read into the same registers is none: reads
+    of one wavefront arrive in order.)"""
+    seen, faults = set(), set()
+    limit = 63                                # reads that a state keeps apart, newest first; older ones are taken together
+    for name, blocks in _blocks_of_kernels(asm):
+        seen.add(name)
+        where = {label: n for n, block in enumerate(blocks) for label in block[0]}
+        before = {0: ()}                      # block -> LDS instructions on their way at its start: the registers each one brings
+        todo = [0]
+        while todo:
+            n = todo.pop()
+            _, instructions, target, falls = blocks[n]
+            flying = list(before[n])
+            for code, inline in instructions:
+                mnemonic, _, operands = code.partition(" ") if " " in code else code.partition("\t")
+                operands = operands.strip()
+                if mnemonic == "s_waitcnt":
+                    count = re.search(r"lgkmcnt\((\d+)\)", operands)
+                    if count:
+                        del flying[int(count.group(1)):]
+                    continue
+                read = inline and mnemonic.startswith("ds_read")
+                dest, _, rest = operands.partition(",")
+                touched = _vector_registers(rest if read else operands)
+                for regs in flying:
+                    if regs & touched:
+                        faults.add("%s: %s" % (name, code))
+                if mnemonic.startswith("ds_"):
+                    flying.insert(0, _vector_registers(dest) if read else frozenset())
+                    if len(flying) > limit:
+                        flying[limit - 1:] = [frozenset().union(*flying[limit - 1:])]
+            for m in ([where[target]] if target in where else []) + ([n + 1] if falls and n + 1 < len(blocks) else []):
+                old = before.get(m)
+                if old is None:
+                    new = tuple(flying)
+                else:
+                    size = max(len(old), len(flying))
+                    pad = lambda state: list(state) + [frozenset()] * (size - len(state))
+                    new = tuple(a | b for a, b in zip(pad(old), pad(flying)))
+                if new != old:
+                    before[m] = new
+                    todo.append(m)
+    return len(seen), sorted(faults)
+
+
 def _compile(src: str, obj: str) -> str:
     cmd = [_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
     if src not in ACCUMULATOR_SOURCES:
@@ -86,10 +178,15 @@ def _compile(src: str, obj: str) -> str:
     with tempfile.TemporaryDirectory() as tmp:
         log = _run(cmd + ["-save-temps"], cwd=tmp)
         with open(os.path.join(tmp, src.replace(".hip", "-hip-amdgcn-amd-amdhsa-gfx950.s"))) as f:
-            count, faults = accumulator_faults(f.read(), ACCUMULATOR_SOURCES[src])
+            asm = f.read()
+    count, faults = accumulator_faults(asm, ACCUMULATOR_SOURCES[src])
     if not count or faults:
         raise RuntimeError("%s: the compiler uses registers or scratch memory of %d kernels that hold their accumulators in "
                            "registers it does not know of:\n%s" % (src, count, "\n".join(faults[:20])))
+    count, faults = outstanding_read_faults(asm)
+    if not count or faults:
+        raise RuntimeError("%s: in %d kernels that read LDS in inline assembly, instructions touch registers that a read has yet "
+                           "to deliver:\n%s" % (src, count, "\n".join(faults[:20])))
     return log
 
 
