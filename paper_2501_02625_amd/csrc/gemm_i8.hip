@@ -160,14 +160,12 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
     // left_a / left_b: K bytes from the stage that the offsets stand for to the end.  What lies beyond K is not fetched.
     int64_t left_a = a.K, left_b = a.K;
     auto trim_a = [&]() {
-        const int left = (int)left_a;                             // below BK, and the requests end a few units past the end
 #pragma unroll
-        for (int i = 0; i < LA; ++i) avo[i] = kc[i & 1] < left ? avo[i] : kOutside;
+        for (int i = 0; i < LA; ++i) avo[i] = kc[i & 1] < left_a ? avo[i] : kOutside;
     };
     auto trim_b = [&]() {
-        const int left = (int)left_b;
 #pragma unroll
-        for (int i = 0; i < LB; ++i) bvo[i] = (TRANSB ? kc[i & 1] : krow + i * RPI) < left ? bvo[i] : kOutside;
+        for (int i = 0; i < LB; ++i) bvo[i] = (TRANSB ? kc[i & 1] : krow + i * RPI) < left_b ? bvo[i] : kOutside;
     };
     auto dma_a = [&](int slot, int i) { dma16(avo[i], abuf, lds_a + slot * Cfg::A_BYTES + (wave * LA + i) * 1024); };
     auto dma_b = [&](int slot, int i) { dma16(bvo[i], bbuf, lds_b + slot * Cfg::B_BYTES + (wave * LB + i) * 1024); };
@@ -311,21 +309,15 @@ __device__ __forceinline__ void main_loop(const GemmArgs& a, int64_t m0, int64_t
         unit(Int<1>());
         if (++u == units) break;
     }
-    // the last results need 18 wait states before a vector instruction reads them; the requests past the end have landed
+    // The last unit has read fragments of one that does not exist.  Nothing uses their registers, so they are free for the epilogue's
+    // values from the read on, and a read that arrives late would overwrite those: nothing may be scheduled above the wait.  (The build
+    // checks that no instruction touches them before it.  Used behind the wait as operands, so that they are not free, they take
+    // the compiler's copies where the two ways out of the loop meet, in front of the wait, and spills.)
+    // The last results need 18 wait states before a vector instruction reads them; the requests past the end have landed.
+    __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     hold_accumulators<TM * TN>();
-    // The last unit has read fragments of one that does not exist.  Their registers are in use up to the wait: used no further, they
-    // would be free for the epilogue's values from the read on, and a read that arrives late would overwrite those.
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) asm volatile("" ::"v"(f.a[k][i]));
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            if constexpr (TRANSB) asm volatile("" ::"v"(f.b[0][k][j]), "v"(f.b[1][k][j]));
-            else asm volatile("" ::"v"(f.bt[0][k][j][0]), "v"(f.bt[0][k][j][1]), "v"(f.bt[1][k][j][0]), "v"(f.bt[1][k][j][1]));
-        }
-    }
 }
 
 // ------------------------------------------------------------------------------------------------ epilogues

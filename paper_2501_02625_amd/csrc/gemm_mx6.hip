@@ -711,18 +711,12 @@ __global__ void __launch_bounds__(256, 1) gemm_mx6_lines_kernel(Mx6GemmArgs a, i
         superblock(Int<1>());
         if (--supers == 0) break;
     }
-    // the last results need 18 wait states before a vector instruction reads them; the requests past the end have landed
+    // The last superblock has read fragments of one that does not exist: nothing may be scheduled above the wait (main_loop of
+    // gemm_i8.hip).  The last results need 18 wait states before a vector instruction reads them; the requests past the end have landed.
+    __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     hold_accumulators<64>();
-    // The last superblock has read groups 0 and 2 of one that does not exist, and its scales: these registers are in use up to the
-    // wait (main_loop of gemm_i8.hip).
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            asm volatile("" ::"v"(f[kLineSet[0]].a[i][j]), "v"(f[kLineSet[0]].b[i][j]), "v"(f[kLineSet[2]].a[i][j]), "v"(f[kLineSet[2]].b[i][j]));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) asm volatile("" ::"v"(sc[0][i]));
     __syncthreads();
 
     // ---- epilogue: 32 rows at a time through a private LDS region, then eight (bf16) or four consecutive columns per lane: whole
