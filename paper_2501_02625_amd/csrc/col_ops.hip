@@ -462,7 +462,7 @@ __global__ void __launch_bounds__(256) fill_u32_kernel(uint32_t* p, int64_t n, u
     if (i < n) p[i] = value;
 }
 
-// out[0] = max over in[0..n-1]: one workgroup (the vectors reduced here are per-row maxima, more than kMaxGivenParts of them).
+// out[0] = max over in[0..n-1]: one workgroup, and one for a second vector (tensor_max_parts).
 __global__ void __launch_bounds__(1024) reduce_max_kernel(const float* in, int64_t n, float* out, const float* in2, int64_t n2,
                                                           float* out2) {
     __shared__ float s_part[16];
@@ -544,16 +544,20 @@ col_part_max_kernel(float* part, int parts, int64_t cols) {
 // into one dword per column, staged in LDS as [col][row/4] with a pitch of 33 dwords, and read back as
 // 16 consecutive rows per lane so that every output row is written in full 128-byte lines.
 constexpr int kTI = 128, kTJ = 128, kPitch = kTI / 4 + 1;
-// amax: `parts` vectors of the columns' partial maxima (non-negative, so their bit patterns order like they do); or, given_amax, `parts`
+// amax: `parts` vectors of the columns' partial maxima (non-negative, so their bit patterns order like they do); or, GIVEN, `parts`
 // values the largest of which is the maximum of all columns.
+template <bool GIVEN>
 __global__ void __launch_bounds__(256)
 col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols, const float* fold,
-                   const float* amax, int parts, int8_t* out_q, int64_t ld_q, float* out_scale, const float* given_amax) {
+                   const float* amax, int parts, int8_t* out_q, int64_t ld_q, float* out_scale) {
     __shared__ uint32_t s_tile[kTJ * kPitch];
     __shared__ float s_part[8][kTJ];
     const int tid = threadIdx.x;
     const int64_t j0 = (int64_t)blockIdx.x * kTJ;
     const int64_t i0 = (int64_t)blockIdx.y * kTI;
+
+    float given = 0.0f;
+    if (GIVEN && parts > 1) given = part_of_given<kTileGivenLoads>(amax, parts);     // ahead of the tile: waiting for these leaves its loads on their way
 
     // phase 1: load, scale, round, pack along rows
     {
@@ -602,8 +606,8 @@ col_quant_t_kernel(const uint16_t* in, int64_t ld_in, int64_t rows, int64_t cols
         }
         // the columns' maxima, reduced while those loads fly: thread group tid / 32 takes every eighth vector
         float am[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (given_amax) {
-            am[0] = am[1] = am[2] = am[3] = workgroup_max(given_amax, parts, s_part[0]);
+        if constexpr (GIVEN) {
+            am[0] = am[1] = am[2] = am[3] = parts > 1 ? given_max(given, s_part[0]) : amax[0];
         } else {
             for (int q = parts > 1 ? tid >> 5 : 0; q < parts; q += 8) {
 #pragma unroll
@@ -814,6 +818,8 @@ dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, 
     const int jl = tid & 15, rq = tid >> 4;             // 16 column groups of 8, 16 row quads (two rounds)
     const int64_t j0 = (int64_t)blockIdx.x * kDC, i0 = (int64_t)blockIdx.y * kDR;
     const int64_t col = j0 + 8 * jl;
+    float given = 0.0f;
+    if (GIVEN && row_tiles > 1) given = part_of_given<kTileGivenLoads>(row_part, row_tiles);
     // E first (cache-hot after pass 1): all eight loads of the thread are in flight while the maxima are reduced.
     uint4 raw[2][4];
     float frow[2][4];
@@ -849,7 +855,7 @@ dual_quant_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows, 
     // reduction it needs: a few KB of L2 hits instead of one more kernel between the passes).
     float inv_all = 0.0f;
     if constexpr (GIVEN) {
-        const float am = workgroup_max(row_part, row_tiles, s_amax_r);
+        const float am = row_tiles > 1 ? given_max(given, s_amax_r) : row_part[0];
         inv_all = am > 0.0f ? 127.0f / am : 0.0f;
         const float scale = am > 0.0f ? am / 127.0f : 1.0f;
         if (blockIdx.y == 0 && tid < 128 && j0 + tid < cols) col_scale[j0 + tid] = scale;
@@ -1053,7 +1059,7 @@ hipError_t launch_dual_quant(const DualQuantArgs& a, hipStream_t s) {
 
 hipError_t launch_dual_quant_given(const DualQuantArgs& a, const float* given_amax, int parts, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0) return hipSuccess;
-    if (a.fold_c || a.fold_r || parts <= 0) return hipErrorInvalidValue;
+    if (a.fold_c || a.fold_r || parts <= 0 || parts > kMaxTileGivenParts) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((a.cols + kDC - 1) / kDC), (unsigned)((a.rows + kDR - 1) / kDR));
     hipLaunchKernelGGL(dual_quant_kernel<true>, grid, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in, a.rows,
                        a.cols, static_cast<const float*>(nullptr), static_cast<const float*>(nullptr), given_amax,
@@ -1092,9 +1098,10 @@ hipError_t launch_dual_quant_static(DualQuantArgs a, hipStream_t s) {
     return launch_dual_quant(a, s);
 }
 
-hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const float*& in2, int64_t& n2, float* out2, hipStream_t s) {
+hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const float*& in2, int64_t& n2, float* out2, int64_t most,
+                            hipStream_t s) {
     if (n <= 0 || (in2 && n2 <= 0)) return hipErrorInvalidValue;
-    if (n <= kMaxGivenParts && (!in2 || n2 <= kMaxGivenParts)) return hipSuccess;
+    if (n <= most && (!in2 || n2 <= most)) return hipSuccess;
     hipLaunchKernelGGL(reduce_max_kernel, dim3(in2 ? 2 : 1), dim3(1024), 0, s, in, n, out, in2, n2, out2);
     in = out;
     n = 1;
@@ -1105,12 +1112,18 @@ hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const floa
     return hipGetLastError();
 }
 
+template <bool GIVEN>
+static hipError_t launch_col_quant_tiles(const ColQuantArgs& a, const float* amax, int parts, hipStream_t s) {
+    const dim3 grid((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
+    hipLaunchKernelGGL(col_quant_t_kernel<GIVEN>, grid, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in, a.rows,
+                       a.cols, a.fold, amax, parts, a.out_q, a.ld_q, a.out_scale);
+    return hipGetLastError();
+}
+
 hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, int parts, hipStream_t s) {
     if (a.rows == 0 || a.cols == 0) return hipSuccess;
-    const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
-    hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, static_cast<const float*>(nullptr), parts, a.out_q, a.ld_q, a.out_scale, given_amax);
-    return hipGetLastError();
+    if (parts <= 0 || parts > kMaxTileGivenParts) return hipErrorInvalidValue;
+    return launch_col_quant_tiles<true>(a, given_amax, parts, s);
 }
 
 hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_t s) {
@@ -1121,11 +1134,7 @@ hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_
         if (e != hipSuccess) return e;
         parts = 1;
     }
-    const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
-    hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, static_cast<const float*>(a.amax_ws), parts, a.out_q, a.ld_q, a.out_scale,
-                       static_cast<const float*>(nullptr));
-    return hipGetLastError();
+    return launch_col_quant_tiles<false>(a, a.amax_ws, parts, s);
 }
 
 hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s) {
@@ -1139,11 +1148,7 @@ hipError_t launch_col_quant_t(const ColQuantArgs& a, hipStream_t s) {
                        a.rows, a.cols, a.fold, amax_bits);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 g2((unsigned)((a.cols + kTJ - 1) / kTJ), (unsigned)((a.rows + kTI - 1) / kTI));
-    hipLaunchKernelGGL(col_quant_t_kernel, g2, dim3(256), 0, s, reinterpret_cast<const uint16_t*>(a.in), a.ld_in,
-                       a.rows, a.cols, a.fold, static_cast<const float*>(a.amax_ws), 1, a.out_q, a.ld_q, a.out_scale,
-                       static_cast<const float*>(nullptr));
-    return hipGetLastError();
+    return launch_col_quant_tiles<false>(a, a.amax_ws, 1, s);
 }
 
 }  // namespace halo

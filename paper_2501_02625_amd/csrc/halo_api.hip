@@ -367,21 +367,22 @@ halo_status halo_hadamard_quant_tensor(const void* in, halo_dtype in_dt, int64_t
         if (launch_col_fwht(c, s) != hipSuccess) return HALO_EHIP;
         src = tmp; ld_src = cols; src_kind = IN_F32;
     }
-    // phase 1: rotate, absmax of every row; then the maximum of those
+    // phase 1: rotate, absmax of every workgroup's rows; the maximum of those
     RowArgs r{};
     r.in = src; r.ld_in = ld_src; r.rows = rows; r.cols = cols;
     set_right_block(r, had_block);
-    r.out = out_q; r.ld_out = ld_q; r.out_scale = row_max; r.amax_only = 1;
-    if (launch_row_transform(r, src_kind, OUT_Q8, s) != hipSuccess) return HALO_EHIP;
+    r.out = out_q; r.ld_out = ld_q; r.out_scale = row_max;
+    int64_t parts[2];
+    if (launch_row_max(r, src_kind, parts, s) != hipSuccess) return HALO_EHIP;
     const float *maxima = row_max, *none = nullptr;
-    int64_t parts = rows, no_parts = 0;
-    if (tensor_max_parts(maxima, parts, tensor_max, none, no_parts, nullptr, s) != hipSuccess) return HALO_EHIP;
+    const int64_t most = axis == HALO_QUANT_COLS_T ? kMaxTileGivenParts : max_given_parts(r, src_kind);
+    if (tensor_max_parts(maxima, parts[0], tensor_max, none, parts[1], nullptr, most, s) != hipSuccess) return HALO_EHIP;
     // phase 2: rotate again and quantise with the tensor's absmax
     if (axis == HALO_QUANT_COLS_T) {
         ColQuantArgs a{in, ld_in, rows, cols, nullptr, out_q, ld_q, out_scale, col_ws};
-        return from_hip(launch_col_quant_t_given(a, maxima, (int)parts, s));
+        return from_hip(launch_col_quant_t_given(a, maxima, (int)parts[0], s));
     }
-    r.amax_only = 0; r.given_amax = maxima; r.given_parts = (int)parts; r.out_scale = out_scale;
+    r.given_amax = maxima; r.given_parts = (int)parts[0]; r.out_scale = out_scale;
     return from_hip(launch_row_transform(r, src_kind, OUT_Q8, s));
 }
 
@@ -613,7 +614,7 @@ halo_status halo_linear_fwd(const halo_linear_desc* desc, const void* X, const v
         unsigned char* tq = reinterpret_cast<unsigned char*>(workspace) + L.tq;
         const size_t tq_bytes = L.total - L.tq;
         if (X && W) {
-            // X and W get the same treatment: one launch for the row maxima of both, one that rotates again and quantises both
+            // X and W get the same treatment: one launch for the maxima of both, one that rotates again and quantises both
             hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
             float* row_max_x = reinterpret_cast<float*>(tq);
             float* row_max_w = row_max_x + b;
@@ -623,13 +624,13 @@ halo_status halo_linear_fwd(const halo_linear_desc* desc, const void* X, const v
             r.in = X; r.ld_in = m; r.rows = b; r.cols = m; r.out = Xq; r.ld_out = m; r.out_scale = row_max_x;
             set_right_block(r, hm);
             r.rows2 = n; r.in2 = W; r.out2 = Wq; r.out_scale2 = row_max_w;
-            r.amax_only = 1;
-            if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
+            int64_t parts[2];
+            if (launch_row_max(r, IN_BF16, parts, hs) != hipSuccess) return HALO_EHIP;
             const float *max_x = row_max_x, *max_w = row_max_w;
-            int64_t parts_x = b, parts_w = n;
-            if (tensor_max_parts(max_x, parts_x, tmax, max_w, parts_w, tmax + 64, hs) != hipSuccess) return HALO_EHIP;
-            r.amax_only = 0; r.given_amax = max_x; r.given_parts = (int)parts_x; r.out_scale = s_x;
-            r.given_amax2 = max_w; r.given_parts2 = (int)parts_w; r.out_scale2 = s_w;
+            if (tensor_max_parts(max_x, parts[0], tmax, max_w, parts[1], tmax + 64, max_given_parts(r, IN_BF16), hs) != hipSuccess)
+                return HALO_EHIP;
+            r.given_amax = max_x; r.given_parts = (int)parts[0]; r.out_scale = s_x;
+            r.given_amax2 = max_w; r.given_parts2 = (int)parts[1]; r.out_scale2 = s_w;
             if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
             return halo_gemm_i8(Xq, m, Wq, m, 1, b, n, m, s_x, s_w, Y, odt, n, nullptr, 0, stream);
         }
@@ -704,13 +705,14 @@ halo_status halo_linear_bwd(const halo_linear_desc* desc, const void* E, const i
             if (tq_bytes < round256(((size_t)b + 64) * 4)) return HALO_EWORKSPACE;
             float* row_max = reinterpret_cast<float*>(tq);
             RowArgs r{};
-            r.in = E; r.ld_in = n; r.rows = b; r.cols = n; r.out = Eq; r.ld_out = n; r.out_scale = row_max; r.amax_only = 1;
-            if (launch_row_transform(r, IN_BF16, OUT_Q8, hs) != hipSuccess) return HALO_EHIP;
+            r.in = E; r.ld_in = n; r.rows = b; r.cols = n; r.out = Eq; r.ld_out = n; r.out_scale = row_max;
+            int64_t parts[2];
+            if (launch_row_max(r, IN_BF16, parts, hs) != hipSuccess) return HALO_EHIP;
             const float *maxima = row_max, *none = nullptr;
-            int64_t parts = b, no_parts = 0;
-            if (tensor_max_parts(maxima, parts, row_max + b, none, no_parts, nullptr, hs) != hipSuccess) return HALO_EHIP;
+            if (tensor_max_parts(maxima, parts[0], row_max + b, none, parts[1], nullptr, kMaxTileGivenParts, hs) != hipSuccess)
+                return HALO_EHIP;
             const DualQuantArgs q{E, n, b, n, nullptr, nullptr, Eq, n, s_e, EqT, b, s_g, nullptr};
-            if (launch_dual_quant_given(q, maxima, (int)parts, hs) != hipSuccess) return HALO_EHIP;
+            if (launch_dual_quant_given(q, maxima, (int)parts[0], hs) != hipSuccess) return HALO_EHIP;
             GemmArgs gx{Eq, n, Wq, m, 0, b, m, n, nullptr, nullptr, nullptr, 0, m, acc, m, HALO_GEMM_AUTO};
             GemmArgs gg{EqT, b, Xq, m, 0, n, m, b, nullptr, nullptr, nullptr, 0, m, acc_g, m, HALO_GEMM_AUTO};
             if (launch_gemm_i8_pair(gx, gg, hs) != hipSuccess) return HALO_EHIP;

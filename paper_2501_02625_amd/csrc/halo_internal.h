@@ -12,6 +12,9 @@ namespace halo {
 // IN_F32_I32: the first matrix of a batched launch (rows2 > 0) holds fp32 and the second int32.
 enum InKind { IN_BF16 = 0, IN_F32 = 1, IN_I32 = 2, IN_F32_I32 = 3 };
 enum OutKind { OUT_Q8 = 0, OUT_BF16 = 1, OUT_F32 = 2, OUT_MX6 = 3 };
+// Where the row quantisers' absmax comes from.  OWN_MAX: the row's own.  One scale per tensor takes two launches: MAX_ONLY writes the
+// largest |value| of each workgroup's rows and no codes, GIVEN_MAX quantises with the largest of those.
+enum RowMax { OWN_MAX, MAX_ONLY, GIVEN_MAX };
 
 // ---- row transform: [pre-scale] -> right-hand FWHT -> [fold] -> {absmax+INT8 | bf16 | fp32} ----
 struct RowArgs {
@@ -27,12 +30,11 @@ struct RowArgs {
     int kron_m;              // 0, or 28: the block is 28 * 2^log_block elements, rotated by H_{2^log_block} (x) H_28
     float in_mul;            // fp32 only: every element is multiplied by this once when it is loaded; 0 = no multiply
     int left_top;            // launch_row_left_top only: number of top strides of the left-hand rotation still to run (1..5)
-    // One scale per tensor (OUT_Q8 only): amax_only writes each row's absmax to out_scale and no codes; the largest of the
-    // given_parts values at given_amax (device memory) replaces the row's own absmax.  post_scale (IN_I32 only, device scalar) is
-    // multiplied in after pre_scale.  All three apply to both matrices of a batched launch.
-    int amax_only;
-    const float* given_amax;
+    // One scale per tensor (OUT_Q8 only): the largest of the given_parts values at given_amax (device memory; launch_row_max,
+    // tensor_max_parts) replaces the row's own absmax.  post_scale (IN_I32 only, device scalar) is multiplied in after pre_scale.
+    // Both apply to both matrices of a batched launch.
     int given_parts;
+    const float* given_amax;
     const float* post_scale;
     // OUT_MX6 only (bf16 input, cols a multiple of 32): `out` receives the packed FP6 E3M2 codes (24 bytes per block of
     // 32 elements, ld_out in BYTES per row), mx_scales the E8M0 scale bytes [rows x cols/32] with ld_mx_scales bytes per row.
@@ -47,12 +49,16 @@ struct RowArgs {
     void* out2;
     float* out_scale2;
     const float* given_amax2;    // the second matrix's own given_amax / post_scale; null: those of the first
-    int given_parts2;
     const float* post_scale2;
+    int given_parts2;
 };
 // Largest row length the row kernels accept.
 constexpr int64_t kMaxRowCols = 32768;
 hipError_t launch_row_transform(const RowArgs& a, InKind in, OutKind out, hipStream_t s);
+// The first of the two launches of a quantiser with one scale per tensor (bf16 or fp32 in): no codes, but the largest |rotated value| of
+// the rows of each workgroup, written to out_scale (and out_scale2).  parts[0] (parts[1]) are set to how many those are, at most one
+// per row.
+hipError_t launch_row_max(const RowArgs& a, InKind in, int64_t* parts, hipStream_t s);
 // Kronecker blocks (kron_m == 28): true if a row of `cols` elements can be rotated in blocks of `block` = 28 * 2^n
 // elements (64 <= 2^n <= 512, block divides cols, cols <= 14336).  launch_row_transform forwards such launches.
 // The end of a left+right un-rotation in one kernel.  `in` is fp32 [rows x cols] on which all strides of a left-hand
@@ -67,6 +73,7 @@ inline bool row_top_quant_ok(int64_t cols, int left_top) { return left_top >= 1 
 hipError_t launch_row_top_quant(const RowArgs& a, int low, hipStream_t s);
 bool row_kron_shape_ok(int64_t cols, int64_t block);
 hipError_t launch_row_kron(const RowArgs& a, InKind in, OutKind out, hipStream_t s);
+hipError_t launch_row_kron_max(const RowArgs& a, InKind in, int64_t* parts, hipStream_t s);
 
 // ---- column-wise absmax quantiser with transposed output (E^T)_Q ----
 struct ColQuantArgs {
@@ -115,13 +122,24 @@ hipError_t launch_col_quant_t_ready(const ColQuantArgs& a, int parts, hipStream_
 // The same with one absmax for every column instead of the columns' own, the largest of `parts` values in device memory: the
 // tensor-wide scale.
 hipError_t launch_col_quant_t_given(const ColQuantArgs& a, const float* given_amax, int parts, hipStream_t s);
-// What the kernels that take a tensor's absmax in parts are given: the rows' maxima as they are, or, where there are more than
-// kMaxGivenParts, reduced to one value at `out` first by a launch of their own (in2, n2, out2: of a second tensor in the same
-// launch).  Returns the parts by changing in / n (in2 / n2).  The launch takes 2 to 4 us; that every workgroup reads 4096 values, which
-// stay in the caches, takes less.  The step of 2048 x 4096 x 4096, HALO-1: 176.8 us with two such launches and a pass of its own for
-// each of E's codes, 173.9 with neither launch and one pass for both.
-constexpr int64_t kMaxGivenParts = 4096;
-hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const float*& in2, int64_t& n2, float* out2, hipStream_t s);
+// What the kernels that take a tensor's absmax in parts are given: the parts as launch_row_max left them, or, where there are more
+// than `most`, reduced to one value at `out` first by a launch of their own (in2, n2, out2: of a second tensor in the same launch, which
+// is made for both if one of them has too many).  Returns the parts by changing in / n (in2 / n2).
+hipError_t tensor_max_parts(const float*& in, int64_t& n, float* out, const float*& in2, int64_t& n2, float* out2, int64_t most,
+                            hipStream_t s);
+// `most`: what the threads of a workgroup read in so many loads each, all on their way with the first loads of what is quantised; 256
+// threads for the kernels that quantise tiles.  Read in a loop at the end of the row quantiser, behind the rotation, 2048 and 4096 parts
+// cost more than the launch that reduces them (X and W of 2048 x 4096 x 4096: 23.4 us, the reduction 4.7 + 18.9; so 19.2 without one).
+// Calls, reduced / read at the end / so: forward 4096 x 512 x 512 17.4 us / 18.4 / 15.2, 2048 x 4096 x 4096 61.5 / 62.8 / 58.2;
+// transposed codes of 4096 x 4096 18.1 / 21.1 / 16.0, of 4096 x 64 12.9 / 13.9 / 10.4.  Loads a thread: rows of 2048 x 4096 with 4 (so
+// reduced) 16.7, with 8 14.8, with 16 15.4; tiles of 4096 x 4096 with 8 (reduced) 18.6, with 16 16.0.
+constexpr int kRowGivenLoads = 8, kTileGivenLoads = 16;
+constexpr int64_t kMaxTileGivenParts = kTileGivenLoads * 256;
+int64_t max_given_parts(const RowArgs& a, InKind in);
+inline bool bad_given_parts(const RowArgs& a, InKind in) {
+    const int64_t most = max_given_parts(a, in);
+    return a.given_parts <= 0 || a.given_parts > most || (a.given_amax2 && (a.given_parts2 <= 0 || a.given_parts2 > most));
+}
 
 // ---- both quantisations of E for the backward pass from one tiling (rows for E_X, transposed columns for G) ----
 struct DualQuantArgs {

@@ -62,7 +62,8 @@ __device__ __forceinline__ void h28_mix(const float (&x)[kM], float (&y)[kM], st
 }
 
 // LOGP: log2 of the Walsh-Hadamard factor (6 .. 9); a Hadamard block is 28 * 2^LOGP elements = 2^(LOGP-6) wavefronts.
-template <int IN, int OUT, int LOGP>
+// MAX: RowMax, as in the row kernels.
+template <int IN, int OUT, int LOGP, int MAX = OWN_MAX>
 __global__ void __launch_bounds__(512)
 row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     __shared__ float s_amax[8];
@@ -74,12 +75,16 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     if (block >= blocks1) {                  // the second matrix of a batched launch
         block -= blocks1;
         a.in = a.in2; a.pre_scale = a.pre_scale2; a.out = a.out2; a.out_scale = a.out_scale2; a.rows = a.rows2;
-        if (a.given_amax2) { a.given_amax = a.given_amax2; a.given_parts = a.given_parts2; }
+        if constexpr (MAX == GIVEN_MAX) {
+            if (a.given_amax2) { a.given_amax = a.given_amax2; a.given_parts = a.given_parts2; }
+        }
         if (a.post_scale2) a.post_scale = a.post_scale2;
     }
     const int64_t row = block;               // the grid holds exactly one workgroup per row
     const int64_t k0 = (int64_t)tid * kM;
 
+    float given = 0.0f;
+    if constexpr (MAX == GIVEN_MAX) given = part_of_given<kRowGivenLoads>(a.given_amax, a.given_parts);
     float x[kM];
     if constexpr (IN == IN_BF16) {
         const uint2* src = reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(a.in) + row * a.ld_in + k0);
@@ -154,25 +159,25 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     }
 
     if constexpr (OUT == OUT_Q8) {
-        float amax = 0.0f;
+        float amax = given;
+        if constexpr (MAX == GIVEN_MAX) {
+            amax = given_max(amax, s_amax);
+        } else {
 #pragma unroll
-        for (int j = 0; j < kM; j += 2) asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(amax) : "v"(v[j]), "v"(v[j + 1]));
-        amax = wave_max(amax, bperm_addr);
-        const int waves = blockDim.x >> 6;
-        if (waves > 1) {
-            if (lane == 0) s_amax[wave] = amax;
-            __syncthreads();
-            float t = s_amax[0];
-            for (int i = 1; i < waves; ++i) t = fmaxf(t, s_amax[i]);
-            amax = t;
-        }
-        if (a.amax_only) {
-            if (tid == 0) a.out_scale[row] = amax;
-            return;
-        }
-        if (a.given_amax) {
-            __shared__ float s_given[8];
-            amax = workgroup_max(a.given_amax, a.given_parts, s_given);
+            for (int j = 0; j < kM; j += 2) asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(amax) : "v"(v[j]), "v"(v[j + 1]));
+            amax = wave_max(amax, bperm_addr);
+            const int waves = blockDim.x >> 6;
+            if (waves > 1) {
+                if (lane == 0) s_amax[wave] = amax;
+                __syncthreads();
+                float t = s_amax[0];
+                for (int i = 1; i < waves; ++i) t = fmaxf(t, s_amax[i]);
+                amax = t;
+            }
+            if constexpr (MAX == MAX_ONLY) {
+                if (tid == 0) a.out_scale[row] = amax;
+                return;
+            }
         }
         const bool nz = amax > 0.0f;
         const float inv = nz ? 127.0f / amax : 0.0f;
@@ -200,24 +205,24 @@ row_kron28_kernel(RowArgs a, float c_norm, unsigned blocks1) {
     }
 }
 
-template <int IN, int OUT, int LOGP>
+template <int IN, int OUT, int LOGP, int MAX>
 hipError_t launch_logp(const RowArgs& a, hipStream_t s) {
     const int threads = (int)(a.cols / kM);
     const int64_t blocks = a.rows + a.rows2;
     const float c_norm = (float)(1.0 / sqrt((double)(kM << LOGP)));
     const size_t lds = LOGP > 6 ? (size_t)(threads / 64) * kM * 64 * sizeof(float) : 0;
-    hipLaunchKernelGGL((row_kron28_kernel<IN, OUT, LOGP>), dim3((unsigned)blocks), dim3(threads), lds, s, a, c_norm,
+    hipLaunchKernelGGL((row_kron28_kernel<IN, OUT, LOGP, MAX>), dim3((unsigned)blocks), dim3(threads), lds, s, a, c_norm,
                        (unsigned)a.rows);
     return hipGetLastError();
 }
 
-template <int IN, int OUT>
+template <int IN, int OUT, int MAX = OWN_MAX>
 hipError_t launch_kind(const RowArgs& a, hipStream_t s) {
     switch (a.log_block) {
-        case 6: return launch_logp<IN, OUT, 6>(a, s);
-        case 7: return launch_logp<IN, OUT, 7>(a, s);
-        case 8: return launch_logp<IN, OUT, 8>(a, s);
-        case 9: return launch_logp<IN, OUT, 9>(a, s);
+        case 6: return launch_logp<IN, OUT, 6, MAX>(a, s);
+        case 7: return launch_logp<IN, OUT, 7, MAX>(a, s);
+        case 8: return launch_logp<IN, OUT, 8, MAX>(a, s);
+        case 9: return launch_logp<IN, OUT, 9, MAX>(a, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -231,10 +236,28 @@ bool row_kron_shape_ok(int64_t cols, int64_t block) {
     return cols > 0 && cols % block == 0 && cols / kM <= 512;
 }
 
+static bool bad_kron_args(const RowArgs& a) {
+    return a.kron_m != kM || !row_kron_shape_ok(a.cols, (int64_t)kM << a.log_block) || a.rows + a.rows2 > 0x7fffffffll;
+}
+
+hipError_t launch_row_kron_max(const RowArgs& a, InKind in, int64_t* parts, hipStream_t s) {
+    if (bad_kron_args(a)) return hipErrorInvalidValue;
+    parts[0] = a.rows;
+    parts[1] = a.rows2;
+    if (in == IN_BF16) return launch_kind<IN_BF16, OUT_Q8, MAX_ONLY>(a, s);
+    if (in == IN_F32) return launch_kind<IN_F32, OUT_Q8, MAX_ONLY>(a, s);
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_row_kron(const RowArgs& a, InKind in, OutKind out, hipStream_t s) {
     if ((a.rows == 0 && a.rows2 == 0) || a.cols == 0) return hipSuccess;
-    if (a.kron_m != kM || !row_kron_shape_ok(a.cols, (int64_t)kM << a.log_block)) return hipErrorInvalidValue;
-    if (a.rows + a.rows2 > 0x7fffffffll) return hipErrorInvalidValue;
+    if (bad_kron_args(a)) return hipErrorInvalidValue;
+    if (a.given_amax) {
+        if (out != OUT_Q8 || bad_given_parts(a, in)) return hipErrorInvalidValue;
+        if (in == IN_BF16) return launch_kind<IN_BF16, OUT_Q8, GIVEN_MAX>(a, s);
+        if (in == IN_F32) return launch_kind<IN_F32, OUT_Q8, GIVEN_MAX>(a, s);
+        return hipErrorInvalidValue;
+    }
     if (in == IN_BF16 && out == OUT_Q8) return launch_kind<IN_BF16, OUT_Q8>(a, s);
     if (in == IN_F32 && out == OUT_Q8) return launch_kind<IN_F32, OUT_Q8>(a, s);
     if (in == IN_I32 && out == OUT_BF16) return launch_kind<IN_I32, OUT_BF16>(a, s);

@@ -14,6 +14,7 @@
 // into the 1/sqrt(d) factor at the end and costs nothing.
 #pragma clang fp contract(off)
 
+#include <algorithm>
 #include <mutex>
 
 #include "halo_internal.h"
@@ -84,10 +85,10 @@ constexpr bool kDeferNorm = (OUT == OUT_Q8 || OUT == OUT_MX6) && LB == 12;
 constexpr float kTiny = 0x1p-100f, kHuge = 0x1p100f;
 __device__ __forceinline__ bool may_defer(float amax) { return amax > kTiny && amax < kHuge; }
 
-// Load one segment into registers, rotate it, apply the fold vector; returns the local absmax (quantising kernels).
+// Load one segment into registers, rotate it, apply the fold vector; returns the local absmax (quantising kernels but GIVEN_MAX).
 // FAST: the row exists and the whole segment lies inside it, so nothing is bounds-checked.
 // deferred: what the values are still to be multiplied by (kDeferNorm; the absmax is not), otherwise 1.
-template <int LOGSEG, int IN, int OUT, bool FAST, int LB, int XS>
+template <int LOGSEG, int IN, int OUT, bool FAST, int LB, int XS, int MAX>
 __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, float c_norm,
                                             float (&v)[1 << (LOGSEG - 6)], float& deferred) {
     constexpr int LOGE = (IN == IN_BF16) ? 3 : 2;
@@ -231,7 +232,7 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
     }
 
     float amax = 0.0f;
-    if constexpr (OUT == OUT_Q8) {
+    if constexpr (OUT == OUT_Q8 && MAX != GIVEN_MAX) {
         // one v_max3_f32 with |.| source modifiers per pair of values (written out: the compiler's fmaxf chain takes
         // four instructions per pair), in two chains
         float amax2 = 0.0f;
@@ -385,9 +386,8 @@ __device__ __forceinline__ void row_phase2(const RowArgs& a, const RowCtx& x, co
 
 // LB: log2 of the Hadamard block when it is 0 (no rotation), LOGSEG (block = segment) or 9; -1 = read it at run time.
 // XS: number of butterfly stages that span wavefronts (Hadamard block = 2^(LOGSEG+XS) elements = 2^XS segments).
-template <int LOGSEG, int IN, int OUT, int LB, int XS = 0>
-__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024)
-row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigned blocks1) {
+template <int LOGSEG, int IN, int OUT, int LB, int XS, int MAX>
+__device__ __forceinline__ void row_transform(RowArgs& a, int segs, int rows_per_wg, float c_norm, unsigned blocks1) {
     constexpr int LOGE = (IN == IN_BF16) ? 3 : 2;
     constexpr int EPL = 1 << LOGE;            // consecutive elements per lane per chunk
     constexpr int VPL = 1 << (LOGSEG - 6);    // values per lane
@@ -410,7 +410,9 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     if (block >= blocks1) {          // the second matrix of a batched launch
         block -= blocks1;
         a.in = a.in2; a.pre_scale = a.pre_scale2; a.out = a.out2; a.out_scale = a.out_scale2; a.rows = a.rows2;
-        if (a.given_amax2) { a.given_amax = a.given_amax2; a.given_parts = a.given_parts2; }
+        if constexpr (MAX == GIVEN_MAX) {
+            if (a.given_amax2) { a.given_amax = a.given_amax2; a.given_parts = a.given_parts2; }
+        }
         if (a.post_scale2) a.post_scale = a.post_scale2;
     }
     x.row = (int64_t)block * rows_per_wg + row_local;
@@ -424,33 +426,32 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     // INT8: 82 us with neither, 69 with the bound, 67 so; 4096 x 8192 in blocks of 4096 23.8, 23.0, 21.2.  Shorter segments need no more
     // registers than they have; their guarded path stays (with 1024 it is 1 % faster).
     constexpr bool WHOLE = LB >= 11 && LB == LOGSEG;
+    float given = 0.0f;
+    if constexpr (MAX == GIVEN_MAX) given = part_of_given<kRowGivenLoads>(a.given_amax, a.given_parts);      // on their way with the row
     float v[VPL];
     float amax = 0.0f, deferred = 1.0f;
     if constexpr (WHOLE) {
-        if (fast) amax = row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v, deferred);
+        if (fast) amax = row_phase1<LOGSEG, IN, OUT, true, LB, XS, MAX>(a, x, c_norm, v, deferred);
     } else {
-        amax = fast ? row_phase1<LOGSEG, IN, OUT, true, LB, XS>(a, x, c_norm, v, deferred)
-                    : row_phase1<LOGSEG, IN, OUT, false, LB, XS>(a, x, c_norm, v, deferred);
+        amax = fast ? row_phase1<LOGSEG, IN, OUT, true, LB, XS, MAX>(a, x, c_norm, v, deferred)
+                    : row_phase1<LOGSEG, IN, OUT, false, LB, XS, MAX>(a, x, c_norm, v, deferred);
     }
 
     float inv_l = 0.0f;
     if constexpr (OUT == OUT_Q8) {
-        if (segs > 1) {
+        if constexpr (MAX == GIVEN_MAX) {
+            amax = given_max(given, s_amax);
+        } else if constexpr (MAX == MAX_ONLY) {
+            amax = workgroup_max(amax, s_amax);
+            if (threadIdx.x == 0) a.out_scale[block] = amax;
+            return;
+        } else if (segs > 1) {
             if (x.lane == 0) s_amax[wave] = amax;
             __syncthreads();
             const int w0 = row_local * segs;
             float t = s_amax[w0];
             for (int i = 1; i < segs; ++i) t = fmaxf(t, s_amax[w0 + i]);
             amax = t;
-        }
-        if (a.amax_only) {
-            // first phase of the one-scale-per-tensor quantiser: the row's absmax, nothing else
-            if (x.row_ok && seg == 0 && x.lane == 0) a.out_scale[x.row] = amax;
-            return;
-        }
-        if (a.given_amax) {                              // second phase: the tensor's absmax for every row
-            __shared__ float s_given[16];
-            amax = workgroup_max(a.given_amax, a.given_parts, s_given);
         }
         const bool nz = amax > 0.0f;
         inv_l = nz ? 127.0f / amax : 0.0f;
@@ -469,51 +470,84 @@ row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigne
     else if constexpr (!WHOLE) row_phase2<LOGSEG, IN, OUT, false>(a, x, v, inv_l);
 }
 
+template <int LOGSEG, int IN, int OUT, int LB, int XS = 0>
+__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024)
+row_transform_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigned blocks1) {
+    row_transform<LOGSEG, IN, OUT, LB, XS, OWN_MAX>(a, segs, rows_per_wg, c_norm, blocks1);
+}
+
+// One scale per tensor, in kernels of its own: as branches of the kernel above it lengthened every INT8 quantiser, by 0.1 us for the 512
+// x 1024 W and 256 x 1024 X of a small level-2 step (level 2, 256 x 640 x 720, fp32 out: 33.2 us with the branches, 32.9 without).
+template <int LOGSEG, int IN, int MAX, int LB, int XS = 0>
+__global__ void __launch_bounds__(LOGSEG >= 11 ? 512 : 1024)
+row_tensor_kernel(RowArgs a, int segs, int rows_per_wg, float c_norm, unsigned blocks1) {
+    row_transform<LOGSEG, IN, OUT_Q8, LB, XS, MAX>(a, segs, rows_per_wg, c_norm, blocks1);
+}
+
+template <int LOGSEG, int IN, int OUT, int MAX, int LB, int XS = 0>
+constexpr auto row_kernel() {
+    if constexpr (MAX == OWN_MAX) return row_transform_kernel<LOGSEG, IN, OUT, LB, XS>;
+    else return row_tensor_kernel<LOGSEG, IN, MAX, LB, XS>;
+}
+
+// How a launch cuts its rows: segments of 2^logseg elements, `stages` butterfly stages across wavefronts.
+struct RowShape {
+    int logseg, segs, stages;
+    int rows_per_wg() const { return segs >= 4 || segs == 0 ? 1 : 4 / segs; }
+    int threads() const { return 64 * segs * rows_per_wg(); }
+};
+
+// Workgroups of a launch, of the first matrix and of both.
+struct RowGrid {
+    int64_t blocks1, blocks;
+    RowGrid(const RowArgs& a, int rows_per_wg)
+        : blocks1((a.rows + rows_per_wg - 1) / rows_per_wg), blocks(blocks1 + (a.rows2 + rows_per_wg - 1) / rows_per_wg) {}
+    // MAX_ONLY writes one value per workgroup
+    void parts(int64_t* out) const {
+        if (out) { out[0] = blocks1; out[1] = blocks - blocks1; }
+    }
+};
+
 // Hadamard block of 2^(10+XS) elements handled by 2^XS wavefronts of 1024 elements each: four times the
 // wavefronts of the one-wavefront-per-block layout and a quarter of the registers, at the price of XS round trips
 // through LDS.  It pays when there are too few rows to fill the machine otherwise.
-template <int IN, int OUT, int XS>
-hipError_t launch_split(const RowArgs& a, hipStream_t s) {
+template <int IN, int OUT, int MAX, int XS>
+hipError_t launch_split(const RowArgs& a, const RowShape& shape, hipStream_t s, int64_t* parts) {
     constexpr int LOGSEG = 10;
-    const int segs = (int)(a.cols >> LOGSEG);
-    const int rows_per_wg = segs >= 4 ? 1 : 4 / segs;
-    const int threads = 64 * segs * rows_per_wg;
-    const int64_t blocks1 = (a.rows + rows_per_wg - 1) / rows_per_wg;
-    const int64_t blocks = blocks1 + (a.rows2 + rows_per_wg - 1) / rows_per_wg;
+    const int threads = shape.threads(), rows_per_wg = shape.rows_per_wg();
+    const RowGrid g(a, rows_per_wg);
+    g.parts(parts);
     const float c_norm = (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block)));
     const size_t lds = (size_t)(threads / 64) * (1 << (LOGSEG - 6)) * 64 * sizeof(float);
-    hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, LOGSEG + XS, XS>), dim3((unsigned)blocks), dim3(threads), lds,
-                       s, a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
+    constexpr auto kern = row_kernel<LOGSEG, IN, OUT, MAX, LOGSEG + XS, XS>();
+    hipLaunchKernelGGL(kern, dim3((unsigned)g.blocks), dim3(threads), lds, s, a, shape.segs, rows_per_wg, c_norm, (unsigned)g.blocks1);
     return hipGetLastError();
 }
 
-template <int LOGSEG, int IN, int OUT>
-hipError_t launch_one(const RowArgs& a, int segs, hipStream_t s) {
-    const int rows_per_wg = segs >= 4 ? 1 : 4 / segs;
-    const int threads = 64 * segs * rows_per_wg;
-    const int64_t blocks1 = (a.rows + rows_per_wg - 1) / rows_per_wg;
-    const int64_t blocks = blocks1 + (a.rows2 + rows_per_wg - 1) / rows_per_wg;
+template <int LOGSEG, int IN, int OUT, int MAX>
+hipError_t launch_one(const RowArgs& a, const RowShape& shape, hipStream_t s, int64_t* parts) {
+    const int threads = shape.threads(), rows_per_wg = shape.rows_per_wg();
+    const RowGrid g(a, rows_per_wg);
+    g.parts(parts);
     const float c_norm = a.log_block > 0 ? (float)(1.0 / sqrt((double)(int64_t(1) << a.log_block))) : 1.0f;
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)g.blocks), dim3(threads), 0, s, a, shape.segs, rows_per_wg, c_norm, (unsigned)g.blocks1);
+        return hipGetLastError();
+    };
     if (a.log_block == 0) {
         if constexpr (IN == IN_F32_I32) return hipErrorInvalidValue;      // only the paired un-rotation, which has a block
-        else
-            hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 0>), dim3((unsigned)blocks), dim3(threads), 0, s,
-                               a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
-    } else if (IN == IN_BF16 && OUT == OUT_Q8 && LOGSEG == 10 && a.log_block == 9) {
-        if constexpr (IN == IN_BF16 && OUT == OUT_Q8 && LOGSEG == 10)
-            hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, 9>), dim3((unsigned)blocks), dim3(threads), 0, s,
-                               a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
-    } else if (a.log_block == LOGSEG)
-        hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, LOGSEG>), dim3((unsigned)blocks), dim3(threads), 0, s,
-                           a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
-    else
-        hipLaunchKernelGGL((row_transform_kernel<LOGSEG, IN, OUT, -1>), dim3((unsigned)blocks), dim3(threads), 0, s,
-                           a, segs, rows_per_wg, c_norm, (unsigned)blocks1);
-    return hipGetLastError();
+        else return launch(row_kernel<LOGSEG, IN, OUT, MAX, 0>());
+    }
+    if constexpr (IN == IN_BF16 && OUT == OUT_Q8 && LOGSEG == 10) {
+        if (a.log_block == 9) return launch(row_kernel<LOGSEG, IN, OUT, MAX, 9>());
+    }
+    if (a.log_block == LOGSEG) return launch(row_kernel<LOGSEG, IN, OUT, MAX, LOGSEG>());
+    return launch(row_kernel<LOGSEG, IN, OUT, MAX, -1>());
 }
 
+// logseg == 0: no shape fits.
 template <int IN, int OUT>
-hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
+RowShape row_shape(const RowArgs& a) {
     // Split blocks of 2048 / 4096 over 2 / 4 wavefronts (measured): the 32-bit-input un-rotation gains at every size
     // for 4096-blocks (5.7 vs 5.2 TB/s at 32768 rows, 12.7 vs 16.0 us at 2048 rows); the others, and 2048-blocks of the paired
     // un-rotation, when whole rows would leave the 1024 SIMDs with fewer than four wavefronts each (level-2 backward, 2048
@@ -522,7 +556,7 @@ hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
         const int64_t wavefronts_unsplit = (a.rows + a.rows2) * (a.cols >> a.log_block);
         const bool few = wavefronts_unsplit < 4096;
         const bool want = IN == IN_I32 ? a.log_block == 12 : IN == IN_F32_I32 ? a.log_block == 12 || few : few;
-        if (want) return a.log_block == 11 ? launch_split<IN, OUT, 1>(a, s) : launch_split<IN, OUT, 2>(a, s);
+        if (want) return {10, (int)(a.cols >> 10), a.log_block - 10};
     }
     // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).  The INT8 quantiser of bf16
     // rows is bound by how much a compute unit has on its way: with blocks up to 512, segments of 1024, two loads per lane, are the
@@ -536,16 +570,23 @@ hipError_t launch_by_seg(const RowArgs& a, hipStream_t s) {
         logseg = a.cols <= 512 ? 9 : 10;
     }
     for (;; ++logseg) {
-        if (logseg > 12) return hipErrorInvalidValue;
+        if (logseg > 12) return {0, 0, 0};
         const int64_t segs = (a.cols + (int64_t(1) << logseg) - 1) >> logseg;
-        if (segs <= (logseg >= 11 ? 8 : 16)) break;
+        if (segs <= (logseg >= 11 ? 8 : 16)) return {logseg, (int)segs, 0};
     }
-    const int segs = (int)((a.cols + (int64_t(1) << logseg) - 1) >> logseg);
-    switch (logseg) {
-        case 9: return launch_one<9, IN, OUT>(a, segs, s);
-        case 10: return launch_one<10, IN, OUT>(a, segs, s);
-        case 11: return launch_one<11, IN, OUT>(a, segs, s);
-        default: return launch_one<12, IN, OUT>(a, segs, s);
+}
+
+template <int IN, int OUT, int MAX = OWN_MAX>
+hipError_t launch_by_seg(const RowArgs& a, hipStream_t s, int64_t* parts = nullptr) {
+    const RowShape shape = row_shape<IN, OUT>(a);
+    if (shape.stages == 1) return launch_split<IN, OUT, MAX, 1>(a, shape, s, parts);
+    if (shape.stages == 2) return launch_split<IN, OUT, MAX, 2>(a, shape, s, parts);
+    switch (shape.logseg) {
+        case 9: return launch_one<9, IN, OUT, MAX>(a, shape, s, parts);
+        case 10: return launch_one<10, IN, OUT, MAX>(a, shape, s, parts);
+        case 11: return launch_one<11, IN, OUT, MAX>(a, shape, s, parts);
+        case 12: return launch_one<12, IN, OUT, MAX>(a, shape, s, parts);
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -818,10 +859,33 @@ hipError_t launch_row_left_top(const RowArgs& a, OutKind out, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
+int64_t max_given_parts(const RowArgs& a, InKind in) {
+    int threads = 0;
+    if (a.kron_m != 0) threads = (int)(a.cols / 28);
+    else if (in == IN_BF16) threads = row_shape<IN_BF16, OUT_Q8>(a).threads();
+    else if (in == IN_F32) threads = row_shape<IN_F32, OUT_Q8>(a).threads();
+    return (int64_t)kRowGivenLoads * std::min(threads, 256);
+}
+
+hipError_t launch_row_max(const RowArgs& a, InKind in, int64_t* parts, hipStream_t s) {
+    if (a.rows == 0 || a.cols == 0 || a.given_amax) return hipErrorInvalidValue;
+    if (a.kron_m != 0) return launch_row_kron_max(a, in, parts, s);
+    if (a.cols > kMaxRowCols || a.log_block > 12) return hipErrorInvalidValue;
+    if (in == IN_BF16) return launch_by_seg<IN_BF16, OUT_Q8, MAX_ONLY>(a, s, parts);
+    if (in == IN_F32) return launch_by_seg<IN_F32, OUT_Q8, MAX_ONLY>(a, s, parts);
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_row_transform(const RowArgs& a, InKind in, OutKind out, hipStream_t s) {
     if ((a.rows == 0 && a.rows2 == 0) || a.cols == 0) return hipSuccess;
     if (a.kron_m != 0) return out == OUT_MX6 || in == IN_F32_I32 ? hipErrorInvalidValue : launch_row_kron(a, in, out, s);
     if (a.cols > kMaxRowCols || a.log_block > 12) return hipErrorInvalidValue;
+    if (a.given_amax) {
+        if (out != OUT_Q8 || bad_given_parts(a, in)) return hipErrorInvalidValue;
+        if (in == IN_BF16) return launch_by_seg<IN_BF16, OUT_Q8, GIVEN_MAX>(a, s);
+        if (in == IN_F32) return launch_by_seg<IN_F32, OUT_Q8, GIVEN_MAX>(a, s);
+        return hipErrorInvalidValue;
+    }
     if (in == IN_BF16 && out == OUT_Q8) return launch_by_seg<IN_BF16, OUT_Q8>(a, s);
     if (in == IN_F32 && out == OUT_Q8) return launch_by_seg<IN_F32, OUT_Q8>(a, s);
     if (in == IN_I32 && out == OUT_BF16) return launch_by_seg<IN_I32, OUT_BF16>(a, s);

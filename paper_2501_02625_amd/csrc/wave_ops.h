@@ -49,19 +49,32 @@ __device__ __forceinline__ float wave_max(float x, int bperm_addr) {
     return x;
 }
 
-// The largest of n non-negative values (0 of none), for every thread of the workgroup.  s_red: a float of LDS per wavefront that
-// nothing else uses.
-__device__ __forceinline__ float workgroup_max(const float* p, int n, float* s_red) {
-    float m = 0.0f;
-#pragma unroll 8
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = __builtin_fmaxf(m, p[i]);
-    m = wave_max(m, (int)((threadIdx.x & 63) ^ 32) << 2);
-    const int waves = (blockDim.x + 63) >> 6;
+// The largest of the workgroup's values, for every thread.  m: the largest of the thread's wavefront, non-negative; s_red: a float of
+// LDS per wavefront, of which there are at most 16, that nothing else uses.
+__device__ __forceinline__ float workgroup_max(float m, float* s_red) {
+    const int waves = (int)(blockDim.x + 63) >> 6, i = (int)(threadIdx.x & 15);
     if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = m;
     __syncthreads();
-    m = s_red[0];
-    for (int i = 1; i < waves; ++i) m = __builtin_fmaxf(m, s_red[i]);
+    m = s_red[i < waves ? i : 0];
+    m = __builtin_fmaxf(m, lane_xor<0>(m, 0));
+    m = __builtin_fmaxf(m, lane_xor<1>(m, 0));
+    m = __builtin_fmaxf(m, lane_xor<2>(m, 0));
+    return __builtin_fmaxf(m, lane_xor<3>(m, 0));
+}
+// One scale per tensor: the largest of n non-negative values in memory, 1 <= n <= LOADS * threads.  Here a thread's part of them,
+// without a loop or a branch, so that the loads are on their way together with whatever is loaded next; then the workgroup's.
+template <int LOADS>
+__device__ __forceinline__ float part_of_given(const float* p, int n) {
+    float m = 0.0f;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+        const int i = (int)(threadIdx.x + u * blockDim.x);
+        m = __builtin_fmaxf(m, p[i < n ? i : n - 1]);
+    }
     return m;
+}
+__device__ __forceinline__ float given_max(float part, float* s_red) {
+    return workgroup_max(wave_max(part, (int)((threadIdx.x & 63) ^ 32) << 2), s_red);
 }
 
 // Four  x <- x + s * partner(x)  in one asm block: v_fmac_f32 with the partner read through DPP.  The leading s_nop supplies

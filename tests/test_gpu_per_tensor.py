@@ -35,8 +35,8 @@ def test_tensor_quantiser_transposed_and_zero_tensor():
     assert not q.any() and torch.all(s == 1.0)
 
 
-# The quantising kernels take the tensor's maximum as the rows' maxima up to 4096 of them, and as one reduced value beyond: the
-# largest element in the first row, the last, and the last that a workgroup's round of 256 threads reads.
+# The quantising kernels take the tensor's maximum in parts, one for the four rows of a workgroup here: the largest element in the
+# first row, the last, and one in the middle, which is the last of its workgroup's wavefronts or not.
 @pytest.mark.parametrize("rows", [255, 257, 4096, 4097])
 @pytest.mark.parametrize("axis", [binding.HALO_QUANT_ROWS, binding.HALO_QUANT_COLS_T])
 def test_tensor_maximum_anywhere(rows, axis):
@@ -50,6 +50,24 @@ def test_tensor_maximum_anywhere(rows, axis):
         r = orc.bf16_bits_to_real(e)
         wq, ws = orc.quantize_tensor(np.ascontiguousarray(r.T) if axis == binding.HALO_QUANT_COLS_T else r)
         q, s = binding.halo_hadamard_quant_tensor(xd, axis=axis)
+        gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
+
+
+# As many parts as the quantising kernels read themselves, and one more, for which they are reduced first: four rows, two and one to a
+# workgroup of 256 threads; 192 threads; blocks over four wavefronts; Kronecker blocks in one wavefront and in two; transposed tiles.
+@pytest.mark.parametrize("rows,cols,hb,axis", [
+    (rows, cols, hb, axis) for most, cols, hb, axis in [(8192, 64, 64, 0), (4096, 1024, 512, 0), (1536, 1536, 512, 0), (2048, 2048, 512, 0),
+                                                        (2048, 4096, 4096, 0), (512, 1792, 1792, 0), (1024, 3584, 3584, 0), (16384, 64, 0, 1)]
+    for rows in (most, most + 1)])
+def test_tensor_maximum_in_as_many_parts_as_are_read(rows, cols, hb, axis):
+    e = inputs.make_weights(rows, cols, rows)
+    for at in (0, rows - 1):
+        x = inputs.bf16_bits_to_f32(e).copy()
+        x[at] *= 8.0
+        bits = inputs.f32_to_bf16_bits(x)
+        r = orc.fwht(orc.bf16_bits_to_real(bits), hb, 1)
+        wq, ws = orc.quantize_tensor(np.ascontiguousarray(r.T) if axis == binding.HALO_QUANT_COLS_T else r)
+        q, s = binding.halo_hadamard_quant_tensor(gu.bits_to_dev(bits), axis=axis, had_block=hb)
         gu.assert_codes_equal(q, wq, "codes"); gu.assert_f32_identical(s, ws, "scales")
 
 
