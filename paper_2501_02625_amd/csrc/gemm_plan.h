@@ -95,19 +95,20 @@ inline double product_cost(const GemmArgs& a, int config) {
     return 4.0 + (double)((tiles + kComputeUnits - 1) / kComputeUnits) * t;
 }
 // Tiles of two kinds in one launch, dispatched in order, n1 of the first kind and then n2 of the second: the time at which the last
-// one is done, when each compute unit takes the next tile as it gets free.
+// one is done, when each compute unit takes the next tile as it gets free.  `late` compute units take one more of the first kind than
+// the others, so the second kind's tiles end at f + k t2 on the early ones and at f + t1 + k t2 on the late ones; the first of
+// these times at which n2 of them have.  (Times of the late ones count from k = n2 / kComputeUnits on, as when the rules below were
+// fitted: where a tile of the first kind takes longer than two of the second, the true one can be earlier.)
 inline double two_kinds_done(int64_t n1, double t1, int64_t n2, double t2) {
     const double f = (double)(n1 / kComputeUnits) * t1;           // when the first compute units are free of the first kind
-    const int64_t late = n1 % kComputeUnits;                      // compute units that take one more of it
-    auto done = [&](double x) {
-        const double e = (x - f) / t2 + 1e-6, l = (x - f - t1) / t2 + 1e-6;
-        return (kComputeUnits - late) * (int64_t)(e > 0 ? e : 0) + late * (int64_t)(l > 0 ? l : 0);
-    };
-    const int64_t rounds = n2 / kComputeUnits;                    // lower bound of the rounds of the second kind
-    double best = 1e30;
-    for (int64_t k = rounds; k <= rounds + 3 + (int64_t)(t1 / t2); ++k)
-        for (const double x : {f + k * t2, f + t1 + k * t2})
-            if (x < best && done(x) >= n2) best = x;
+    const int64_t late = n1 % kComputeUnits, early = kComputeUnits - late;
+    if (n2 == 0) return f + (late ? t1 : 0.0);
+    const int64_t below = (int64_t)(t1 / t2 + 1e-6), above = (int64_t)(t1 / t2 + 1.0 - 1e-6);      // t1 in whole t2
+    auto rounds = [](int64_t n, int64_t of) { return n <= 0 ? int64_t(0) : (n + of - 1) / of; };
+    int64_t k = rounds(n2, early);                                // if they end before the late ones have done any
+    if (k > above) k = rounds(n2 + late * above, kComputeUnits);
+    double best = f + (double)k * t2;
+    if (late) best = std::min(best, f + t1 + (double)std::max(n2 / kComputeUnits, rounds(n2 - early * below, kComputeUnits)) * t2);
     return std::max(best, f + (late ? t1 : 0.0));
 }
 // Two products in one launch, the first product's tiles first.
@@ -148,21 +149,25 @@ inline int choose_config(const GemmArgs& a, const GemmArgs* a2) {
 // 2560 x 4096 x 4096 46.2 us / 38.5, 2048 x 5120 x 4096 45.4 / 36.4, 2896 x 3072 x 8192 82.9 / 67.4, 5120 x 7296 x 4096 134.5 / 112.5,
 // 4608 x 5120 x 14336 270 / 226, 6112 x 14336 x 832 124.5 / 126.1 (not taken); fp32 out 2048 x 14336 x 4096 115.7 / 105.6.  (224 columns
 // fill 2048 x 14336 in two equal rounds, but a bf16 row of a tile is then no whole number of cache lines: 118 us against 107 with 256.)
+// The search runs on the host before every such launch: 0.5 us at 14336 columns, 2 at 128256, 0.02 where 4096 by 4096 fit once.
 inline int64_t two_widths(const GemmArgs& a) {
     if (a.config >= 0 || a.left_stages || a.lr_rank || a.N % 16 != 0 || !a.transB) return -1;
     const int c = choose_config(a, nullptr);
     if (c == kSmall32 || c == kSmall64) return -1;
     const int64_t panels = (a.M + 255) / 256;
     const double u = units_of(a), wide_out = (a.acc_out || a.c_is_f32) ? 3.0 : 0.0, one_width = product_cost(a, c);
+    const double wide_tile = tile_cost(a, kTiles256), narrow_tile = 7.0 + wide_out + 0.95 * u;
     double best = 1e30;
     int64_t wide = -1;
     for (int64_t n1 = 0; n1 * 256 < a.N; ++n1) {
         const int64_t n2 = (a.N - n1 * 256 + 191) / 192;
         const bool at_once = panels * (n1 + n2) <= kComputeUnits;
         if (at_once && n1 > 0) continue;
-        const double t = 4.0 + wide_out + (at_once ? 8.5 + 0.84 * u : two_kinds_done(panels * n1, tile_cost(a, kTiles256), panels * n2,
-                                                                                       7.0 + wide_out + 0.95 * u) - wide_out);
         const double limit = one_width * (c != kTiles128 ? 1.0 : !at_once ? 0.88 : u < 12 ? 0.85 : 0.92);
+        // no split is done before all compute units have shared its work evenly: most are out without the estimate
+        const double evenly = (double)panels * ((double)n1 * wide_tile + (double)n2 * narrow_tile) / (double)kComputeUnits;
+        if (!at_once && 4.0 + evenly > std::min(best, limit) + 1e-3) continue;
+        const double t = 4.0 + (at_once ? wide_out + 8.5 + 0.84 * u : two_kinds_done(panels * n1, wide_tile, panels * n2, narrow_tile));
         if (t < limit && t < best) {
             best = t;
             wide = n1 * 256;

@@ -1,5 +1,7 @@
 """CPU test of which way the rules in csrc/gemm_plan.h send the shapes of the GPU tests: a test that is there for one kernel
 keeps reaching it when a rule changes, or fails here."""
+import heapq
+import random
 import shutil
 import subprocess
 
@@ -21,18 +23,22 @@ GemmArgs product(long M, long N, long K) {
 }
 
 // each line: `two M N K` (columns in wide tiles, bf16 out and fp32 out), `one M N K`, `small M N K` (columns of the small tiles), `pair M N K M N K`, `bf16 rows cols pitch` (whole lines?),
-// `max rows cols parts` (column maxima reduced first?), // `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
+// `done n1 t1 n2 t2` (two kinds of tiles, times in tenths), `max rows cols parts` (column maxima reduced first?), // `first log-block rows cols` (stages of the first pass) or `left tokens in out right-block left-block both-products rank`
 int main() {
     char what[8];
     while (std::scanf("%7s", what) == 1) {
         long v[7];
-        const int count = what[0] == 'o' || what[0] == 's' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' || what[0] == 't' ? 3 : what[0] == 'p' ? 6 : 7;
+        const int count = what[0] == 'o' || what[0] == 's' || what[0] == 'b' || what[0] == 'f' || what[0] == 'm' || what[0] == 't' ? 3 : what[0] == 'd' ? 4 : what[0] == 'p' ? 6 : 7;
         for (int i = 0; i < count; ++i) if (std::scanf("%ld", v + i) != 1) return 1;
         if (what[0] == 'l') {
             GemmArgs gx = product(v[0], v[1], v[2]);
             const GemmArgs gg = product(v[2], v[1], v[0]);
             if (v[6]) { gx.lr_rank = (int)v[6]; gx.acc_out = nullptr; gx.C = &somewhere; gx.c_is_f32 = 1; }
             std::printf("%d\n", (int)left_in_epilogue(gx, v[5] ? &gg : nullptr, (int32_t)v[4], (int32_t)v[3]));
+            continue;
+        }
+        if (what[0] == 'd') {
+            std::printf("%.0f\n", 10 * two_kinds_done(v[0], v[1] / 10.0, v[2], v[3] / 10.0));
             continue;
         }
         if (what[0] == 't') {
@@ -161,6 +167,19 @@ def test_tiles_of_two_widths_where_they_are_faster(ask):
     assert said == [one > two for M, N, K, one, two in TIMED_WIDTHS]
     shapes = test_gpu_gemm.TWO_WIDTHS
     assert ask(("two", M, N, K) for M, N, K, *wide in shapes) == ["%d,%d" % (bf16, f32) for M, N, K, bf16, f32 in shapes]
+
+
+def test_tiles_of_two_kinds_are_done_when_a_dispatch_in_order_is(ask):
+    rng = random.Random(5)
+    lines = [(rng.randrange(1200), rng.randrange(60, 1600), rng.randrange(1200)) for _ in range(150)] + [(512, 700, 256), (0, 900, 257), (300, 500, 0)]
+    lines = [(n1, t1, n2, max(1, round(t1 / rng.uniform(0.4, 1.95)))) for n1, t1, n2 in lines if n1 + n2]
+    want = []
+    for n1, t1, n2, t2 in lines:
+        free = [0] * 256
+        for t in [t1] * n1 + [t2] * n2:
+            heapq.heapreplace(free, free[0] + t)
+        want.append(str(max(free)))
+    assert ask(("done", *line) for line in lines) == want
 
 
 def left(b, m, n, hm, hb, both, rank=0):
