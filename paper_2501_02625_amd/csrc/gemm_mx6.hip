@@ -720,7 +720,8 @@ __global__ void __launch_bounds__(256, 1) gemm_mx6_lines_kernel(Mx6GemmArgs a, i
     __syncthreads();
 
     // ---- epilogue: 32 rows at a time through a private LDS region, then eight (bf16) or four consecutive columns per lane: whole
-    // lines per request
+    // lines per request.  A lane beyond the matrix skips its store: through the stores of single columns, masked one by one, 2048 x 2176 x
+    // 1024 took 18.7 us instead of 15.4.
     float* region = reinterpret_cast<float*>(smem_big) + wave * 32 * kLineEpiPitch;
     const int64_t row0 = m0 + wave_m * 128, col0 = n0 + wave_n * 128;
     StaticFor<0, 4>::run([&](auto ii) {
@@ -743,7 +744,7 @@ __global__ void __launch_bounds__(256, 1) gemm_mx6_lines_kernel(Mx6GemmArgs a, i
                 const int rr = 2 * p + half;
                 const v4f v = *reinterpret_cast<const v4f*>(region + rr * kLineEpiPitch + cc);
                 float* dst = reinterpret_cast<float*>(a.C) + (row0 + 32 * i + rr) * a.ldc + col0 + cc;
-                if (row0 + 32 * i + rr >= a.M) continue;
+                if (row0 + 32 * i + rr >= a.M || left <= 0) continue;
                 if (left >= 4) {
                     __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(dst));
                 } else {
@@ -762,7 +763,7 @@ __global__ void __launch_bounds__(256, 1) gemm_mx6_lines_kernel(Mx6GemmArgs a, i
                 const v4f y = *reinterpret_cast<const v4f*>(region + rr * kLineEpiPitch + cc + 4);
                 const v4u w = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
                 uint16_t* dst = reinterpret_cast<uint16_t*>(a.C) + (row0 + 32 * i + rr) * a.ldc + col0 + cc;
-                if (row0 + 32 * i + rr >= a.M) continue;
+                if (row0 + 32 * i + rr >= a.M || left <= 0) continue;
                 if (left >= 8) {
                     __builtin_nontemporal_store(w, reinterpret_cast<v4u*>(dst));
                 } else {
@@ -791,11 +792,17 @@ hipError_t launch_gemm_mx6(const Mx6GemmArgs& a, hipStream_t s) {
     const bool lines = a.K > 0 && a.K % 512 == 0 && a.lda <= most && a.ldb <= most && a.ldsa <= most && a.ldsb <= most &&
                        a.ldsa % 16 == 0 && a.ldsb % 16 == 0 && (reinterpret_cast<uintptr_t>(a.SA) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(a.SB) & 15u) == 0;
-    // In whole lines as soon as a compute unit would get two of the small tiles: a round of 256 x 256 tiles takes as long as 1.2 of
-    // 128 x 128.  Small tiles against whole lines, tokens x out-features x in-features: 1024 x 4096 x 4096 (256 small tiles) 31.5 us /
-    // 36.4, 2048 x 3072 x 4096 50.3 / 36.3, 768 x 14336 x 4096 77.1 / 38.2, 2304 x 4096 x 512 20.1 / 12.5, 640 x 14336 x 8192 137 / 65.
-    // Other K: the eight-wavefront kernel where its tiles fill most of the chip.
-    if (big && (lines ? tiles_m * tiles_n > kComputeUnits : big_m * big_n >= 192)) {
+    // In whole lines as soon as a compute unit would get two of the small tiles, where the product is long enough: about 10 us + 0.006
+    // for each element of K as long as the 256 x 256 tiles fit the chip once, against 7 + 0.01 for up to two small tiles a compute unit,
+    // less for narrow ones.  Small tiles against whole lines, tokens x out-features x in-features: 1024 x 4096 x 4096 (256 small tiles)
+    // 31.5 us / 36.4, 2048 x 3072 x 4096 50.3 / 36.3, 768 x 14336 x 4096 77.1 / 38.2, 640 x 14336 x 8192 137 / 65; K = 2048: 33024 x 16
+    // 23.9 / 24.2, 2048 x 2176 29.1 / 21.6; K = 1536: 33024 x 16 19.1 / 20.6, x 64 21.6 / 19.8; K = 1024: 2048 x 2176 17.9 / 15.4, 1040 x
+    // 3712 15.2 / 15.2, 129 x 16640 14.5 / 15.2, 33024 x 16 13.7 / 16.7; K = 512: 2304 x 4096 (576 small tiles) 20.8 / 13.0, 384 x 14336
+    // (336) 13.7 / 13.0, 1040 x 3712 (261) 11.1 / 13.6, 129 x 16640 10.5 / 13.3, 33024 x 16 8.6 / 13.1.
+    // Other K: the eight-wavefront kernel where its tiles fill most of the chip; whole lines are as fast or faster than that at any K.
+    const int64_t small_tiles = tiles_m * tiles_n;
+    const bool long_enough = a.K >= 2048 || (a.N > 64 && (a.K >= 1536 || (a.M > 256 && (a.K >= 1024 || small_tiles > 320))));
+    if (big && (big_m * big_n >= 192 || (lines && small_tiles > kComputeUnits && long_enough))) {
         static std::once_flag once;
         static hipError_t attr_result = hipSuccess;
         std::call_once(once, [&] {

@@ -80,11 +80,12 @@ def test_mx6_gemm_against_exact_product(M, N, K):
     gu.assert_bf16_within_one_ulp(out16, got.astype(np.float32), "bf16 output")
 
 
-# The kernel that moves whole 128-byte lines (K a multiple of 512, more than 256 tiles of 128 x 128): one superblock of 512, an odd
+# The kernel that moves whole 128-byte lines (K a multiple of 512, more than 256 tiles of 128 x 128, with K = 512 more than 320): one superblock of 512, an odd
 # and an even number of them; rows and columns one past a tile, a lone row of the last tile, columns that no store divides; views whose
 # row pitches are not whole lines, and one whose scale rows are not whole 16-byte chunks (the other kernel takes it).
 @pytest.mark.parametrize("M,N,K,pad,scale_pad", [(2049, 2050, 512, 0, 0), (1281, 3336, 1024, 48, 16), (2300, 2561, 1536, 0, 0),
-                                                 (2047, 2303, 2048, 16, 0), (3329, 3585, 512, 0, 4)])
+                                                 (2047, 2303, 2048, 16, 0), (3329, 3585, 512, 0, 4),
+                                                 (2305, 2561, 512, 0, 0)])
 def test_mx6_gemm_in_whole_lines(M, N, K, pad, scale_pad):
     def operand(bits):
         codes, scales, want_c, want_s = quant_and_check(bits, 512)       # rotated: the bound below is for blocks of like magnitude
