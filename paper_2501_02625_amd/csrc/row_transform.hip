@@ -560,11 +560,15 @@ RowShape row_shape(const RowArgs& a) {
     }
     // Segment = max(Hadamard block, 512), grown until the row fits the workgroup (16 waves, 8 from 2048 up).  The INT8 quantiser of bf16
     // rows is bound by how much a compute unit has on its way: with blocks up to 512, segments of 1024, two loads per lane, are the
-    // faster ones where a row has more than three of them (512 against 1024: 4096 x 2304 in blocks of 256 11.35 us / 11.31, x 1280 7.2
-    // / 8.0; 4096 x 3584 in blocks of 512 13.3 / 12.0, 8192 x 5632 40.5 / 32.1; 4096 x 5696 in blocks of 64 20.7 / 17.6).  The
-    // un-rotations have 4-byte inputs, the MXFP6 quantiser more to do with a value, and 512 is the faster one for both throughout.
+    // faster ones where a row has more than three of them and there are rows for all compute units (512 against 1024: 4096 x 2304 in
+    // blocks of 256 11.35 us / 11.31, x 1280 7.2 / 8.0; 4096 x 3584 in blocks of 512 13.3 / 12.0, 8192 x 5632 40.5 / 32.1; 4096 x 5696 in
+    // blocks of 64 20.7 / 17.6).  With few rows a wavefront's time counts, and that is longer: 16 x 5632 3.4 / 4.2, 256 x 5632 3.6 / 4.4,
+    // 1024 x 3136 5.4 / 5.6, 768 x 4608 5.3 / 5.6, 512 x 5632 4.9 / 5.2, 256 x 7168 4.0 / 4.2; beyond the line 2048 x 3136 8.2 / 8.2, 1536 x
+    // 3584 7.1 / 6.6, 1024 x 4608 6.2 / 6.0 (1536 x 4608 is an exception, 7.4 / 8.1), 768 x 5120 6.4 / 5.7, 640 x 5632 6.0 / 5.8, 512 x 7168
+    // 5.7 / 5.2.  The un-rotations have 4-byte inputs, the MXFP6 quantiser more to do with a value, and 512 is the faster one for both
+    // throughout.
     int logseg = a.log_block < 9 ? 9 : a.log_block;
-    if (IN == IN_BF16 && OUT == OUT_Q8 && logseg == 9 && a.cols > 3072) logseg = 10;
+    if (IN == IN_BF16 && OUT == OUT_Q8 && logseg == 9 && a.cols > 3072 && (a.rows + a.rows2) * (a.cols - 2048) >= 1 << 21) logseg = 10;
     if (a.log_block == 0) {
         // no rotation: any segmentation is valid; 1024-element segments keep register use low
         logseg = a.cols <= 512 ? 9 : 10;

@@ -57,11 +57,12 @@ def test_row_quant_bf16_bit_exact(rows, cols, hb, frac):
         assert torch.all(out_q[:, cols:] == 55), "padding columns were overwritten"
 
 
-# Blocks of up to 512 in segments of 1024 (more than 3072 columns): the first width beyond the line and the last one on it, a last segment of
-# one block, of half a segment and of all but one block; as many segments as a workgroup takes, and one more.  One scale per tensor
-# goes the same way.
+# Blocks of up to 512 in rows of more than 3072 columns, few of them and, in segments of 1024, many: the first width beyond the line and
+# the last one on it, a last segment of one block, of half a segment and of all but one block; as many segments as a workgroup takes, and
+# one more; the last number of rows on the line and the first beyond it.  One scale per tensor goes the same way.
 @pytest.mark.parametrize("rows,cols,hb", [(6, 3072, 512), (7, 3080, 8), (9, 3136, 64), (5, 3584, 512), (3, 4032, 64), (5, 5632, 512), (4, 15872, 512),
-                                          (3, 16384, 256), (2, 16896, 512)])
+                                          (3, 16384, 256), (2, 16896, 512),
+                                          (1927, 3136, 64), (1928, 3136, 64), (1366, 3584, 512), (1058, 4032, 64), (586, 5632, 512), (342, 8192, 256)])
 def test_row_quant_short_blocks_of_long_rows(rows, cols, hb):
     bits = inputs.make_activations(rows, cols, 0.002, seed=rows + cols)
     rotated = orc.fwht(orc.bf16_bits_to_real(bits), hb, 1)
