@@ -162,12 +162,13 @@ __device__ __forceinline__ float row_phase1(const RowArgs& a, const RowCtx& x, f
     if (log_block > 0) {
         FwhtStages<VPL, LOGE, 0, LOGSEG>::run(v, log_block, x.lane, x.bperm_addr);
         if constexpr (XS > 0) {
-            // Strides 2^LOGSEG .. 2^(LOGSEG+XS-1) pair up whole segments, i.e. wavefronts of this workgroup: each wavefront
-            // publishes its registers in LDS, once, and combines them with its partner's, the lower segment taking a+b and the
-            // upper one a-b (the lane signs carried so far are the same in both).  Two strides: it also works out what its
-            // partner of the second one has after the first, one more add per value for one barrier instead of three and 16-byte
-            // LDS accesses.  Blocks of 4096, quantising 2048 x 4096 9.5 -> 8.7 us, 1024 x 8192 9.7 -> 9.1; un-rotating 2048 x 4096 to
-            // bf16 11.1 -> 10.4, 16384 x 4096 71.5 -> 71.2.
+            // Strides 2^LOGSEG .. 2^(LOGSEG+XS-1) pair up whole segments, i.e. wavefronts of this workgroup: each wavefront publishes its
+            // registers in LDS and combines them with its partner's, the lower segment taking a+b and the upper one a-b (the lane
+            // signs carried so far are the same in both), 16 bytes a lane at a time.  bf16 inputs, two strides: it publishes once
+            // and also works out what its partner of the second one has after the first, one more add per value for one barrier
+            // instead of three; blocks of 4096, quantising 2048 x 4096 9.5 -> 8.7 us, 1024 x 8192 9.7 -> 9.1.  32-bit inputs go a
+            // round per stride: the un-rotations of 2048 x 4096 and 4096 x 4096 take 28.9 us in one launch so, and 28.9 with the
+            // 4-byte accesses of before.
             static_assert(XS <= 2 && VPL % 4 == 0, "wavefronts of a block");
             float4* xb = reinterpret_cast<float4*>(x.xbuf) + x.lane;
             const float sg0 = x.seg & 1 ? -1.0f : 1.0f, sg1 = x.seg & 2 ? -1.0f : 1.0f;
