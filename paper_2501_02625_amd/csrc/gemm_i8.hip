@@ -816,8 +816,12 @@ __device__ __forceinline__ void one_tile(const GemmArgs& a, int bid, int tiles_m
 // LR: this instance also carries the low-rank side product (lowrank_prepare).
 // RAGGED: N (of either product) is not a multiple of 16.
 // TN2: the second product of the launch has tiles of that width.
+// The alignment: how fast these kernels run depends by up to 2 % on where in memory their instructions lie, whatever they are.  Steps of
+// 2048 x 4096 x 4096, the pair of products, the same instructions: 63.8 us where the kernel began on a multiple of 32 KB, 65.2 and 65.6
+// elsewhere; on another card 65.8 there, 67.1 in front of other kernels, and beginning on a multiple of 4 KB 66.7, 8 KB 65.9, 16 KB 66.9,
+// 32 KB 67.0, 64 KB 66.3.
 template <int TM, int TN, bool TRANSB, bool LEFT, bool LR, bool RAGGED, int TN2 = TN>
-__global__ void __launch_bounds__(256, 1)
+__global__ void __launch_bounds__(256, 1) __attribute__((aligned(8192)))
 gemm_i8_kernel(GemmArgs a, int tiles_m, int tiles_n, GemmArgs a2, int tiles_m2, int tiles_n2, unsigned blocks1) {
     extern __shared__ __align__(16) unsigned char smem[];
     // A second, independent product may ride in the same launch (workgroups from blocks1 on): the tail and the
